@@ -62,11 +62,24 @@ constexpr int BB = 16;
 constexpr int WG = 256;                 // threads per workgroup (4 wavefronts of 64)
 constexpr int ROWS_PER_WG = WG / BS;    // one quad of 4 lanes per block row
 
-// vector kernels: elements per thread and workgroup tile
-constexpr int VEC_E = 8;
-constexpr int VEC_TILE = WG * VEC_E;    // 2048 doubles per workgroup
-
 __host__ __device__ inline int div_up(int64_t a, int64_t b) { return (int)((a + b - 1) / b); }
+
+// vector kernels of FGMRES: elements of a workgroup's tile. Below VEC_SMALL elements tiles of 4 per
+// thread, from there on 8: the 720,000 elements of 180,000 cells fill 256 compute units with 704
+// tiles in three rounds, 352 tiles of twice the size in two of which the second is mostly empty
+// (a vector update 13.1 against 9 us); the longest vectors want fewer partial sums instead.
+constexpr int64_t VEC_SMALL = (int64_t)1 << 21;
+__host__ __device__ inline int vec_e(int64_t len) { return len < VEC_SMALL ? 4 : 8; }
+__host__ __device__ inline int vec_tile(int64_t len) { return WG * vec_e(len); }
+
+// diagnostics: rows per workgroup
+constexpr int DIAG_ROWS = 512;
+
+// completion counts of the reductions (ints, a cache line apart): the root, then one per group of
+// workgroups (last_workgroup)
+constexpr int DONE_GROUPS = 16, DONE_STRIDE = 32;
+constexpr int DONE_INTS = (1 + DONE_GROUPS) * DONE_STRIDE;
+
 
 // ------------------------------------------------------------------ workspace layout
 struct Workspace {
@@ -77,10 +90,12 @@ struct Workspace {
     size_t partials;   // double[(restart+2) * nb_vec]
     size_t hess;       // double[(restart+1) * restart], column-major, ld = restart+1
     size_t cs, sn, g, coef, misc;  // double[restart+2] each; misc double[16]
+    size_t done;       // int[DONE_INTS]
     size_t red;        // double[restart+4]: outputs of column reductions
     size_t V, Z;       // double[(restart+1) * 4N], double[restart * 4N]
     size_t total;
     int nb_vec;        // workgroups of the vector kernels
+    int nb_diag;       // workgroups of the diagnostics (DIAG_ROWS rows each)
     int restart;
 };
 

@@ -17,7 +17,8 @@ Workspace layout(const abilu_pattern *p, abilu_prec prec, int restart) {
     const size_t n = (size_t)p->n, Z = (size_t)p->nnzb, nv = 4 * n;
     const int m = restart > 0 ? restart : 0;
     W.restart = m;
-    W.nb_vec = div_up((int64_t)(nv > 0 ? nv : 1), VEC_TILE);
+    W.nb_vec = div_up((int64_t)(nv > 0 ? nv : 1), vec_tile((int64_t)nv));
+    W.nb_diag = div_up((int64_t)(n > 0 ? n : 1), DIAG_ROWS);
     size_t o = 0;
     W.flags = 0;
     W.status = 64;                      // 8 doubles at byte 64..127
@@ -35,6 +36,7 @@ Workspace layout(const abilu_pattern *p, abilu_prec prec, int restart) {
     W.g = o; o = align256(o + sizeof(double) * (m + 2));
     W.coef = o; o = align256(o + sizeof(double) * (m + 2));
     W.misc = o; o = align256(o + sizeof(double) * 16);
+    W.done = o; o = align256(o + sizeof(int) * DONE_INTS);
     W.red = o; o = align256(o + sizeof(double) * (m + 4));
     if (m > 0) {
         W.V = o; o = align256(o + sizeof(double) * (size_t)(m + 1) * nv);

@@ -122,9 +122,9 @@ struct DiagScratch {
 bool diag_scratch(const abilu_pattern *p, void *work, size_t work_bytes, DiagScratch *out) {
     const Workspace W = layout(p, ABILU_F32, 0);    // the smaller of the two precisions' layouts
     if (work_bytes < W.total) return false;
-    const size_t part = ((size_t)16 * W.nb_vec + 255) & ~(size_t)255;
+    const size_t part = ((size_t)16 * W.nb_diag + 255) & ~(size_t)255;
     if (256 + part + 256 > W.total) return false;
-    out->nb = W.nb_vec;
+    out->nb = W.nb_diag;
     out->partial = (double *)((char *)work + 256);
     out->red = (double *)((char *)work + 256 + part);
     return true;

@@ -64,6 +64,49 @@ __device__ __forceinline__ double wave_sum(double v) {
 
 __device__ __forceinline__ bool skipped(const int *guard) { return guard && *guard == 0; }
 
+// Values handed from one workgroup to another inside a launch (partial sums, counts): agent-scope
+// accesses go past the L2 of the XCD to the memory all XCDs share, so no L2 write-back or
+// invalidation is needed around them.
+__device__ __forceinline__ void store_agent(double *p, double v) {
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ double load_agent(const double *p) {
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// True in the last of `total` workgroups to get here; what the others stored with store_agent
+// before is then visible to its load_agent. Each wave waits for its own stores, which have then
+// reached the shared memory, before its workgroup counts itself done; the counts are cleared for
+// the next launch. A __threadfence in every thread, which writes the whole L2 back, took 10 us over
+// 64 workgroups against 2.4 us this way (a grid-wide count and wait, timed alone). GROUPED: more
+// than DONE_GROUPS^2 / 8 workgroups count in DONE_GROUPS groups and the last of each counts at the
+// root, since additions to one address follow each other at about 15 ns (704 in a row: 10 us).
+template <bool GROUPED>
+__device__ __forceinline__ bool last_workgroup(int *done, int total, int id) {
+    __shared__ int last;
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        auto count = [](int *c, int of) {
+            if (of <= 1) return true;
+            if (__hip_atomic_fetch_add(c, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != of - 1) return false;
+            __hip_atomic_store(c, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            return true;
+        };
+        bool is_last;
+        if (GROUPED && total > DONE_GROUPS * DONE_GROUPS / 8) {
+            const int g = id % DONE_GROUPS;
+            is_last = count(done + (1 + g) * DONE_STRIDE, (total - g + DONE_GROUPS - 1) / DONE_GROUPS) &&
+                      count(done, DONE_GROUPS);
+        } else {
+            is_last = count(done, total);
+        }
+        last = is_last ? 1 : 0;
+    }
+    __syncthreads();
+    return last != 0;
+}
+
 // Forward sweep on rows ib, ib + stride, ... (rpq<T>() rows per quad; rows >= n are skipped).
 template <typename T, typename YI, bool EMIT_Z>
 __device__ __forceinline__ void fwd_rows(int ib, int stride, int n, const int32_t *__restrict__ lrow,
@@ -242,12 +285,17 @@ __device__ __forceinline__ void spmv_body(int blk, int n, const int32_t *__restr
     if (h == 0) y[(int64_t)i * 4 + rr] = RESID ? b[(int64_t)i * 4 + rr] - acc : acc;
 }
 
+// partial[k nb + blk] = sum over the tile of V_k w for k < q, partial[q nb + blk] = that of w^2.
+// The vectors are taken four at a time (16 or 32 loads in flight per lane): a system of a few hundred
+// tiles leaves each compute unit one workgroup or two, which would otherwise wait for each vector
+// in turn.
+// VEC_E elements per lane (vec_e); sh: MAX_RESTART + 2 columns of LDS.
+typedef double WaveSums[WG / 64];
+template <int VEC_E>
 __device__ __forceinline__ void mdot_body(int blk, int64_t len, const double *__restrict__ V, int64_t ldv, int q,
-                                             const double *__restrict__ w, double *__restrict__ partial, int nb,
-                                             const int *guard) {
-    if (skipped(guard)) return;
-    __shared__ double sh[MAX_RESTART + 2][WG / 64];
-    const int64_t base = (int64_t)blk * VEC_TILE + threadIdx.x;
+                                          const double *__restrict__ w, double *__restrict__ partial, int nb,
+                                          WaveSums *sh) {
+    const int64_t base = (int64_t)blk * (WG * VEC_E) + threadIdx.x;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     double wv[VEC_E];
     const bool full = base + (int64_t)(VEC_E - 1) * WG < len;
@@ -256,33 +304,49 @@ __device__ __forceinline__ void mdot_body(int blk, int64_t len, const double *__
         const int64_t t = base + (int64_t)e * WG;
         wv[e] = (full || t < len) ? w[t] : 0.0;
     }
-    for (int k = 0; k < q; ++k) {
-        const double *vk = V + (int64_t)k * ldv;
-        double s = 0.0;
+    auto dots = [&](int k, auto count) {
+        constexpr int C = decltype(count)::value;
+        double v[C][VEC_E], s[C];
 #pragma unroll
-        for (int e = 0; e < VEC_E; ++e) {
-            const int64_t t = base + (int64_t)e * WG;
-            s += ((full || t < len) ? vk[t] : 0.0) * wv[e];
+        for (int c = 0; c < C; ++c)
+#pragma unroll
+            for (int e = 0; e < VEC_E; ++e) {
+                const int64_t t = base + (int64_t)e * WG;
+                v[c][e] = (full || t < len) ? V[(int64_t)(k + c) * ldv + t] : 0.0;
+            }
+#pragma unroll
+        for (int c = 0; c < C; ++c) {
+            s[c] = 0.0;
+#pragma unroll
+            for (int e = 0; e < VEC_E; ++e) s[c] += v[c][e] * wv[e];
         }
-        s = wave_sum(s);
-        if (lane == 0) sh[k][wave] = s;
-    }
+#pragma unroll
+        for (int c = 0; c < C; ++c) {
+            s[c] = wave_sum(s[c]);
+            if (lane == 0) sh[k + c][wave] = s[c];
+        }
+    };
+    int k = 0;
+    for (; k + 4 <= q; k += 4) dots(k, std::integral_constant<int, 4>{});
+    for (; k < q; ++k) dots(k, std::integral_constant<int, 1>{});
     double s = 0.0;
 #pragma unroll
     for (int e = 0; e < VEC_E; ++e) s += wv[e] * wv[e];
     s = wave_sum(s);
     if (lane == 0) sh[q][wave] = s;
     __syncthreads();
-    for (int k = threadIdx.x; k <= q; k += WG)
-        partial[(int64_t)k * nb + blk] = ((sh[k][0] + sh[k][1]) + (sh[k][2] + sh[k][3]));
+    for (int c = threadIdx.x; c <= q; c += WG)
+        store_agent(partial + (int64_t)c * nb + blk, ((sh[c][0] + sh[c][1]) + (sh[c][2] + sh[c][3])));
 }
 
+// w += alpha sum_k c[k] V_k over the tile; if partial: partial[blk] = sum of the new w^2
+template <int VEC_E>
 __device__ __forceinline__ void update_body(int blk, int64_t len, const double *__restrict__ V, int64_t ldv, int q,
                                                const double *__restrict__ c, double alpha, double *__restrict__ w,
                                                double *__restrict__ partial, const int *guard) {
     if (skipped(guard)) return;
     __shared__ double sh[WG / 64];
-    const int64_t base = (int64_t)blk * VEC_TILE + threadIdx.x;
+    const int64_t base = (int64_t)blk * (WG * VEC_E) + threadIdx.x;
     const bool full = base + (int64_t)(VEC_E - 1) * WG < len;
     double acc[VEC_E];
 #pragma unroll
@@ -290,15 +354,26 @@ __device__ __forceinline__ void update_body(int blk, int64_t len, const double *
         const int64_t t = base + (int64_t)e * WG;
         acc[e] = (full || t < len) ? w[t] : 0.0;
     }
-    for (int k = 0; k < q; ++k) {
-        const double ck = alpha * c[k];
-        const double *vk = V + (int64_t)k * ldv;
+    auto add = [&](int k, auto count) {
+        constexpr int C = decltype(count)::value;
+        double v[C][VEC_E];
 #pragma unroll
-        for (int e = 0; e < VEC_E; ++e) {
-            const int64_t t = base + (int64_t)e * WG;
-            acc[e] += ck * ((full || t < len) ? vk[t] : 0.0);
+        for (int u = 0; u < C; ++u)
+#pragma unroll
+            for (int e = 0; e < VEC_E; ++e) {
+                const int64_t t = base + (int64_t)e * WG;
+                v[u][e] = (full || t < len) ? V[(int64_t)(k + u) * ldv + t] : 0.0;
+            }
+#pragma unroll
+        for (int u = 0; u < C; ++u) {
+            const double ck = alpha * c[k + u];
+#pragma unroll
+            for (int e = 0; e < VEC_E; ++e) acc[e] += ck * v[u][e];
         }
-    }
+    };
+    int k = 0;
+    for (; k + 4 <= q; k += 4) add(k, std::integral_constant<int, 4>{});
+    for (; k < q; ++k) add(k, std::integral_constant<int, 1>{});
     double s = 0.0;
 #pragma unroll
     for (int e = 0; e < VEC_E; ++e) {
@@ -310,15 +385,118 @@ __device__ __forceinline__ void update_body(int blk, int64_t len, const double *
         s = wave_sum(s);
         if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = s;
         __syncthreads();
-        if (threadIdx.x == 0) partial[blk] = (sh[0] + sh[1]) + (sh[2] + sh[3]);
+        if (threadIdx.x == 0) store_agent(partial + blk, (sh[0] + sh[1]) + (sh[2] + sh[3]));
     }
 }
 
-__device__ __forceinline__ void reduce_cols_body(int blk, const double *__restrict__ partial, int nb,
-                                                    double *__restrict__ out, const int *guard) {
-    if (skipped(guard)) return;
+// The first Gram-Schmidt update and the second pass's dots in one pass over the basis:
+// w -= sum_k c[k] V_k, then partial[k nb + blk] = sum over the tile of V_k w (new w), and that of
+// w^2 at k = q. Bound by reading the basis once, where update and dots apart read it twice.
+// QM >= q vectors of EB elements per lane stay in registers between the two uses (QM EB = 32
+// doubles, 64 registers); QM = 0 takes any q and reads each vector again for its dot (the tile's
+// second read mostly hits a cache). The sums run in the same order for every QM, so the choice
+// does not change a bit. On 4 million cells, FGMRES(50), 8 vectors: update + dots apart 141 + 100 us.
+template <int QM, int VEC_E>
+__device__ __forceinline__ void update_dot_body(int blk, int64_t len, const double *__restrict__ V, int64_t ldv, int q,
+                                                const double *__restrict__ c, double *__restrict__ w,
+                                                double *__restrict__ partial, int nb, WaveSums *sh) {
+    const int64_t base = (int64_t)blk * (WG * VEC_E) + threadIdx.x;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const bool full = base + (int64_t)(VEC_E - 1) * WG < len;
+    double sn = 0.0;
+    if constexpr (QM > 0) {
+        constexpr int EB = 32 / QM < VEC_E ? 32 / QM : VEC_E;
+        double s[QM];
+#pragma unroll
+        for (int k = 0; k < QM; ++k) s[k] = 0.0;
+#pragma unroll
+        for (int e0 = 0; e0 < VEC_E; e0 += EB) {
+            double v[QM][EB], acc[EB];
+#pragma unroll
+            for (int e = 0; e < EB; ++e) {
+                const int64_t t = base + (int64_t)(e0 + e) * WG;
+                acc[e] = (full || t < len) ? w[t] : 0.0;
+            }
+#pragma unroll
+            for (int k = 0; k < QM; ++k)
+                if (k < q) {
+#pragma unroll
+                    for (int e = 0; e < EB; ++e) {
+                        const int64_t t = base + (int64_t)(e0 + e) * WG;
+                        v[k][e] = (full || t < len) ? V[(int64_t)k * ldv + t] : 0.0;
+                    }
+                }
+#pragma unroll
+            for (int k = 0; k < QM; ++k)
+                if (k < q) {
+                    const double ck = -c[k];
+#pragma unroll
+                    for (int e = 0; e < EB; ++e) acc[e] += ck * v[k][e];
+                }
+#pragma unroll
+            for (int e = 0; e < EB; ++e) {
+                const int64_t t = base + (int64_t)(e0 + e) * WG;
+                if (full || t < len) w[t] = acc[e];
+                sn += acc[e] * acc[e];
+            }
+#pragma unroll
+            for (int k = 0; k < QM; ++k)
+                if (k < q) {
+#pragma unroll
+                    for (int e = 0; e < EB; ++e) s[k] += v[k][e] * acc[e];
+                }
+        }
+#pragma unroll
+        for (int k = 0; k < QM; ++k)
+            if (k < q) {
+                s[k] = wave_sum(s[k]);
+                if (lane == 0) sh[k][wave] = s[k];
+            }
+    } else {
+        double acc[VEC_E];
+#pragma unroll
+        for (int e = 0; e < VEC_E; ++e) {
+            const int64_t t = base + (int64_t)e * WG;
+            acc[e] = (full || t < len) ? w[t] : 0.0;
+        }
+        for (int k = 0; k < q; ++k) {
+            const double ck = -c[k];
+#pragma unroll
+            for (int e = 0; e < VEC_E; ++e) {
+                const int64_t t = base + (int64_t)e * WG;
+                acc[e] += ck * ((full || t < len) ? V[(int64_t)k * ldv + t] : 0.0);
+            }
+        }
+#pragma unroll
+        for (int e = 0; e < VEC_E; ++e) {
+            const int64_t t = base + (int64_t)e * WG;
+            if (full || t < len) w[t] = acc[e];
+            sn += acc[e] * acc[e];
+        }
+        for (int k = 0; k < q; ++k) {
+            double s = 0.0;
+#pragma unroll
+            for (int e = 0; e < VEC_E; ++e) {
+                const int64_t t = base + (int64_t)e * WG;
+                s += ((full || t < len) ? V[(int64_t)k * ldv + t] : 0.0) * acc[e];
+            }
+            s = wave_sum(s);
+            if (lane == 0) sh[k][wave] = s;
+        }
+    }
+    sn = wave_sum(sn);
+    if (lane == 0) sh[q][wave] = sn;
+    __syncthreads();
+    for (int k = threadIdx.x; k <= q; k += WG)
+        store_agent(partial + (int64_t)k * nb + blk, ((sh[k][0] + sh[k][1]) + (sh[k][2] + sh[k][3])));
+}
+
+// The register form for q vectors (0: any number).
+inline int update_dot_form(int q) { return q <= 4 ? 4 : q <= 8 ? 8 : q <= 16 ? 16 : q <= 32 ? 32 : 0; }
+
+// One column's sum by a whole workgroup; valid in lane 0 of the workgroup.
+__device__ __forceinline__ double reduce_col(const double *__restrict__ pc, int nb) {
     __shared__ double sh[WG / 64];
-    const double *pc = partial + (int64_t)blk * nb;
     // eight independent partial sums keep eight loads in flight per lane (fixed order: entry b
     // goes to sum (b / WG) mod 8 while whole groups of 8 WG entries remain, the rest to sum 0)
     double a0 = 0.0, a1 = 0.0, a2 = 0.0, a3 = 0.0, a4 = 0.0, a5 = 0.0, a6 = 0.0, a7 = 0.0;
@@ -338,90 +516,190 @@ __device__ __forceinline__ void reduce_cols_body(int blk, const double *__restri
     s = wave_sum(s);
     if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = s;
     __syncthreads();
-    if (threadIdx.x == 0) out[blk] = (sh[0] + sh[1]) + (sh[2] + sh[3]);
+    return (sh[0] + sh[1]) + (sh[2] + sh[3]);
+}
+
+__device__ __forceinline__ void reduce_cols_body(int blk, const double *__restrict__ partial, int nb,
+                                                    double *__restrict__ out, const int *guard) {
+    if (skipped(guard)) return;
+    const double s = reduce_col(partial + (int64_t)blk * nb, nb);
+    if (threadIdx.x == 0) store_agent(out + blk, s);
+}
+
+// All `cols` column sums (nb <= FOLD_NB entries each, stored by other workgroups of this launch)
+// by one workgroup, a wave per column: lane l of the wave adds the entries that lanes l, l + 64,
+// l + 128 and l + 192 of reduce_col's workgroup would add, in the same order, so the sums have the
+// same bits. out: LDS, valid for the whole workgroup on return.
+constexpr int FOLD_NB = 512;
+__device__ __forceinline__ void reduce_cols_fold(const double *partial, int nb, int cols, double *out) {
+    constexpr int PER = FOLD_NB / WG;   // rounds of WG entries
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    for (int c = wave; c < cols; c += WG / 64) {
+        double v[PER][WG / 64];
+#pragma unroll
+        for (int r = 0; r < PER; ++r)
+#pragma unroll
+            for (int p = 0; p < WG / 64; ++p) {
+                const int b = r * WG + p * 64 + lane;
+                v[r][p] = b < nb ? load_agent(partial + (int64_t)c * nb + b) : 0.0;
+            }
+        double s[WG / 64];
+#pragma unroll
+        for (int p = 0; p < WG / 64; ++p) {
+            s[p] = 0.0;
+#pragma unroll
+            for (int r = 0; r < PER; ++r) s[p] += v[r][p];
+        }
+#pragma unroll
+        for (int p = 0; p < WG / 64; ++p) s[p] = wave_sum(s[p]);
+        if (lane == 0) out[c] = (s[0] + s[1]) + (s[2] + s[3]);
+    }
+    __syncthreads();
 }
 
 __device__ __forceinline__ void scale_body(int blk, int64_t len, const double *w, double *v, const double *h) {
     const double hv = *h;
-    const int64_t base = (int64_t)blk * VEC_TILE + threadIdx.x;
-#pragma unroll
-    for (int e = 0; e < VEC_E; ++e) {
-        const int64_t t = base + (int64_t)e * WG;
-        if (t < len) v[t] = (hv != 0.0) ? w[t] / hv : w[t];
+    const int64_t tile = vec_tile(len), t0 = blk * tile, t1 = min(len, t0 + tile);
+    for (int64_t t = t0 + threadIdx.x; t < t1; t += WG) v[t] = (hv != 0.0) ? w[t] / hv : w[t];
+}
+
+// ---- steps on the small dense Hessenberg problem (column-major, ld = m + 1), run by one workgroup
+// on the column sums `red` of the reduction before them (LDS or registers of the caller's choice:
+// red(c) is column c's sum). Columns and rotations are taken one per lane; only the chain of
+// rotations and the substitution are serial, and those run in LDS. (One lane taking everything from
+// memory spent 8-12 us on six Arnoldi vectors, a load at a time.)
+enum { RS_BETA_START_ZERO = 0, RS_BETA_START_X, RS_BETA, RS_GS1, RS_GS2, RS_GIVENS, RS_NONE };
+
+struct KPtrs {
+    double *partials, *red, *H, *cs, *sn, *g, *coef, *misc, *status;
+    int *guard, *done;
+    bool grouped;   // done has the counts of the groups too
+};
+
+__device__ __forceinline__ void beta_step(const KPtrs &P, int m, double r0, bool num, bool beta_slot, bool init_g) {
+    const double beta = sqrt(r0);
+    if (threadIdx.x == 0) {
+        if (num) P.status[ST_NUM] = beta;
+        if (beta_slot) P.status[ST_BETA] = beta;
+        P.misc[MI_BETA] = beta;
+    }
+    if (init_g)
+        for (int q = threadIdx.x; q <= m + 1; q += blockDim.x) P.g[q] = q == 0 ? beta : 0.0;
+}
+
+// H(0:k,k) = dots, coef = dots, nrm0 = ||w|| before the first pass
+__device__ __forceinline__ void gs1_step(const KPtrs &P, int k, int m, const double *red) {
+    for (int q = threadIdx.x; q <= k; q += blockDim.x) {
+        P.H[(int64_t)k * (m + 1) + q] = red[q];
+        P.coef[q] = red[q];
+    }
+    if (threadIdx.x == 0) P.misc[MI_NRM0] = sqrt(red[k + 1]);
+}
+
+// after the first update (red: the second pass's dots and ||w'||^2): a second pass if
+// ||w'|| < ||w|| / sqrt(2); then H(0:k,k) += dots, coef = dots
+__device__ __forceinline__ void gs2_step(const KPtrs &P, int k, int m, const double *red) {
+    const double n1 = sqrt(red[k + 1]);
+    const int again = n1 < 0.70710678118654752440 * P.misc[MI_NRM0] ? 1 : 0;
+    if (threadIdx.x == 0) {
+        P.misc[MI_NRM1] = n1;
+        *P.guard = again;
+    }
+    if (!again) return;
+    for (int q = threadIdx.x; q <= k; q += blockDim.x) {
+        P.H[(int64_t)k * (m + 1) + q] += red[q];
+        P.coef[q] = red[q];
     }
 }
 
-__device__ __forceinline__ void gs1_body(int blk, int k, int m, const double *__restrict__ red, double *H, double *coef, double *misc) {
-    for (int q = 0; q <= k; ++q) {
-        H[(int64_t)k * (m + 1) + q] = red[q];
-        coef[q] = red[q];
+// final norm, Givens rotations, residual estimate
+__device__ __forceinline__ void givens_step(const KPtrs &P, int k, int m, const double *red) {
+    __shared__ double lh[MAX_RESTART + 1], lc[MAX_RESTART], ls[MAX_RESTART];
+    double *h = P.H + (int64_t)k * (m + 1);
+    for (int q = threadIdx.x; q <= k; q += blockDim.x) {
+        lh[q] = h[q];
+        if (q < k) {
+            lc[q] = P.cs[q];
+            ls[q] = P.sn[q];
+        }
     }
-    misc[MI_NRM0] = sqrt(red[k + 1]);
-}
-
-__device__ __forceinline__ void gs1_done_body(int blk, const double *__restrict__ nrm2, double *misc, int *guard) {
-    const double n1 = sqrt(nrm2[0]);
-    misc[MI_NRM1] = n1;
-    *guard = (n1 < 0.70710678118654752440 * misc[MI_NRM0]) ? 1 : 0;
-}
-
-__device__ __forceinline__ void gs2_body(int blk, int k, int m, const double *__restrict__ red, double *H, double *coef, const int *guard) {
-    if (*guard == 0) return;
-    for (int q = 0; q <= k; ++q) {
-        H[(int64_t)k * (m + 1) + q] += red[q];
-        coef[q] = red[q];
+    const int guard = *P.guard;
+    const double gk = P.g[k], n1 = P.misc[MI_NRM1];
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        const double hn = guard ? sqrt(red[0]) : n1;
+        double a = lh[0];
+        for (int q = 0; q < k; ++q) {
+            const double b = lh[q + 1];
+            lh[q] = lc[q] * a + ls[q] * b;
+            a = -ls[q] * a + lc[q] * b;
+        }
+        const double rho = sqrt(a * a + hn * hn);
+        const double c = rho > 0 ? a / rho : 1.0, sn = rho > 0 ? hn / rho : 0.0;
+        lh[k] = rho;
+        P.cs[k] = c;
+        P.sn[k] = sn;
+        P.g[k + 1] = -sn * gk;
+        P.g[k] = c * gk;
+        P.misc[MI_HN] = hn;
+        P.status[ST_EST] = fabs(-sn * gk);
+        P.status[ST_HN] = hn;
+        P.status[ST_GUARD] = (double)guard;
     }
+    __syncthreads();
+    for (int q = threadIdx.x; q <= k; q += blockDim.x) h[q] = lh[q];
+    if (threadIdx.x == 0) h[k + 1] = 0.0;
 }
 
-__device__ __forceinline__ void givens_body(int blk, int k, int m, const double *__restrict__ nrm2_pass2, const int *guard, double *H,
-                         double *cs, double *sn, double *g, double *misc, double *status) {
-    const double hn = (*guard) ? sqrt(nrm2_pass2[0]) : misc[MI_NRM1];
-    double *h = H + (int64_t)k * (m + 1);
-    h[k + 1] = hn;
-    for (int q = 0; q < k; ++q) {
-        const double a = h[q], b = h[q + 1];
-        h[q] = cs[q] * a + sn[q] * b;
-        h[q + 1] = -sn[q] * a + cs[q] * b;
+// The step OP on the column sums red (whole workgroup; red readable by every lane).
+template <int OP>
+__device__ __forceinline__ void step_tail(const KPtrs &P, int k, int m, const double *red) {
+    if constexpr (OP == RS_BETA_START_ZERO || OP == RS_BETA_START_X) {
+        // the solve's first reduction (one column, so it counts nothing): also clears the count
+        beta_step(P, m, red[0], true, OP == RS_BETA_START_ZERO, OP == RS_BETA_START_ZERO);
+        if (P.grouped && threadIdx.x <= DONE_GROUPS) P.done[threadIdx.x * DONE_STRIDE] = 0;
+        else if (threadIdx.x == 0) *P.done = 0;
     }
-    const double a = h[k], b = h[k + 1];
-    const double rho = sqrt(a * a + b * b);
-    cs[k] = rho > 0 ? a / rho : 1.0;
-    sn[k] = rho > 0 ? b / rho : 0.0;
-    h[k] = rho;
-    h[k + 1] = 0.0;
-    g[k + 1] = -sn[k] * g[k];
-    g[k] = cs[k] * g[k];
-    misc[MI_HN] = hn;
-    status[ST_EST] = fabs(g[k + 1]);
-    status[ST_HN] = hn;
-    status[ST_GUARD] = (double)(*guard);
+    else if constexpr (OP == RS_BETA) beta_step(P, m, red[0], false, true, true);
+    else if constexpr (OP == RS_GS1) gs1_step(P, k, m, red);
+    else if constexpr (OP == RS_GS2) gs2_step(P, k, m, red);
+    else if constexpr (OP == RS_GIVENS) givens_step(P, k, m, red);
 }
 
-__device__ __forceinline__ void solve_body(int blk, int k, int m, const double *__restrict__ H, const double *__restrict__ g, double *coef) {
+// Column blk's sum, then step OP in the last of the `cols` workgroups to finish. The step runs also
+// when the guard skipped the reduction (the Givens step needs it either way).
+template <int OP>
+__device__ __forceinline__ void reduce_step_body(int blk, int cols, const KPtrs &P, int nb, const int *guard, int k,
+                                                 int m) {
+    __shared__ double sred[MAX_RESTART + 2];
+    reduce_cols_body(blk, P.partials, nb, P.red, guard);
+    if (!last_workgroup<false>(P.done, cols, blk)) return;
+    for (int c = threadIdx.x; c < cols; c += WG) sred[c] = load_agent(P.red + c);
+    __syncthreads();
+    step_tail<OP>(P, k, m, sred);
+}
+
+// Back substitution on the k x k upper triangle: coef = y, by columns (one workgroup).
+__device__ __forceinline__ void solve_body(int k, int m, const double *__restrict__ H, const double *__restrict__ g,
+                                           double *coef) {
+    __shared__ double y[MAX_RESTART];
+    for (int t = threadIdx.x; t < k; t += blockDim.x) y[t] = g[t];
+    __syncthreads();
     for (int q = k - 1; q >= 0; --q) {
-        double s = g[q];
-        for (int t = q + 1; t < k; ++t) s -= H[(int64_t)t * (m + 1) + q] * coef[t];
-        coef[q] = s / H[(int64_t)q * (m + 1) + q];
-    }
-}
-
-__device__ __forceinline__ void beta_body(int blk, int m, const double *__restrict__ red, double *g, double *misc, double *status, int slot) {
-    const double beta = sqrt(red[0]);
-    status[slot] = beta;
-    misc[MI_BETA] = beta;
-    if (g) {
-        g[0] = beta;
-        for (int q = 1; q <= m + 1; ++q) g[q] = 0.0;
+        const double *h = H + (int64_t)q * (m + 1);
+        const double yq = y[q] / h[q];
+        __syncthreads();
+        for (int t = threadIdx.x; t <= q; t += blockDim.x) {
+            if (t < q) y[t] -= h[t] * yq;
+            else coef[q] = yq;
+        }
+        __syncthreads();
     }
 }
 
 __device__ __forceinline__ void zero_body(int blk, int64_t len, double *v) {
-    const int64_t base = (int64_t)blk * VEC_TILE + threadIdx.x;
-#pragma unroll
-    for (int e = 0; e < VEC_E; ++e) {
-        const int64_t t = base + (int64_t)e * WG;
-        if (t < len) v[t] = 0.0;
-    }
+    const int64_t tile = vec_tile(len), t0 = blk * tile, t1 = min(len, t0 + tile);
+    for (int64_t t = t0 + threadIdx.x; t < t1; t += WG) v[t] = 0.0;
 }
 
 template <typename T, typename S, bool SRC_CSR, bool COPY>

@@ -2,7 +2,7 @@
 // sweep apply, entirely in double precision on the device: Arnoldi basis V and preconditioned
 // basis Z in the workspace, classical Gram-Schmidt with a second pass when the norm falls below
 // 1/sqrt(2) of its value before orthogonalisation ("twice is enough"), Givens rotations on the
-// Hessenberg matrix by one lane of the reduction before them, x update and true residual at each
+// Hessenberg matrix by the last workgroup of the reduction before them, x update and true residual at each
 // cycle end. The host loop reads back a few scalars per iteration to decide when to stop.
 //
 // All reductions are fixed-order (per-workgroup partials, then one workgroup per column in
@@ -18,20 +18,28 @@ using namespace abilu_k;
 
 namespace {
 
-// partial[k*nb + b] = sum_{t in tile b} V_k[t] w[t] for k < q;  partial[q*nb + b] = sum w[t]^2
+template <int VE>
 __global__ __launch_bounds__(WG) void k_mdot(int64_t len, const double *__restrict__ V, int64_t ldv, int q,
-                                             const double *__restrict__ w, double *__restrict__ partial, int nb,
-                                             const int *guard) {
-    mdot_body(blockIdx.x, len, V, ldv, q, w, partial, nb, guard);
+                                             const double *__restrict__ w, double *__restrict__ partial, int nb) {
+    __shared__ WaveSums sh[MAX_RESTART + 2];
+    mdot_body<VE>(blockIdx.x, len, V, ldv, q, w, partial, nb, sh);
 }
 
-// w[t] += alpha * sum_k c[k] V_k[t]; if partial: partial[b] = sum over tile of new w[t]^2. The
-// workgroups take the tiles in descending order: the dot products before it run ascending, so it
-// starts on the tiles they read last (the partials stay indexed by tile, so sums are unchanged).
+// The updates take the tiles in descending order: the kernel before them runs ascending, so they
+// start on the tiles it read last (the partials stay indexed by tile, so sums are unchanged).
+template <int VE>
 __global__ __launch_bounds__(WG) void k_update(int64_t len, const double *__restrict__ V, int64_t ldv, int q,
                                                const double *__restrict__ c, double alpha, double *__restrict__ w,
                                                double *__restrict__ partial, const int *guard) {
-    update_body(gridDim.x - 1 - blockIdx.x, len, V, ldv, q, c, alpha, w, partial, guard);
+    update_body<VE>(gridDim.x - 1 - blockIdx.x, len, V, ldv, q, c, alpha, w, partial, guard);
+}
+
+template <int QM, int VE>
+__global__ __launch_bounds__(WG) void k_update_dot(int64_t len, const double *__restrict__ V, int64_t ldv, int q,
+                                                   const double *__restrict__ c, double *__restrict__ w,
+                                                   double *__restrict__ partial, int nb) {
+    __shared__ WaveSums sh[MAX_RESTART + 2];
+    update_dot_body<QM, VE>(gridDim.x - 1 - blockIdx.x, len, V, ldv, q, c, w, partial, nb, sh);
 }
 
 // out[col] = sum_b partial[col*nb + b], one workgroup per column, fixed order
@@ -40,111 +48,49 @@ __global__ __launch_bounds__(WG) void k_reduce_cols(const double *__restrict__ p
     reduce_cols_body(blockIdx.x, partial, nb, out, guard);
 }
 
-// The single-lane steps that follow a column reduction, run by its last workgroup.
-enum { RS_BETA_START_ZERO = 0, RS_BETA_START_X, RS_BETA, RS_GS1, RS_GS1_DONE, RS_GS2, RS_GIVENS };
-
-struct KPtrs {
-    double *partials, *red, *H, *cs, *sn, *g, *coef, *misc, *status;
-    int *guard, *done;
-};
-
-// The single-lane step OP on the column sums in P.red (run by one lane of the last workgroup).
-template <int OP>
-__device__ __forceinline__ void step_tail(const KPtrs &P, int k, int m) {
-    if constexpr (OP == RS_BETA_START_ZERO) {   // the solve's first reduction (one column): also
-        beta_body(0, m, P.red, P.g, P.misc, P.status, ST_NUM);   // clears the completion count
-        beta_body(0, m, P.red, nullptr, P.misc, P.status, ST_BETA);
-        *P.done = 0;
-    } else if constexpr (OP == RS_BETA_START_X) {
-        beta_body(0, m, P.red, nullptr, P.misc, P.status, ST_NUM);
-        *P.done = 0;
-    } else if constexpr (OP == RS_BETA) {
-        beta_body(0, m, P.red, P.g, P.misc, P.status, ST_BETA);
-    } else if constexpr (OP == RS_GS1) {
-        gs1_body(0, k, m, P.red, P.H, P.coef, P.misc);
-    } else if constexpr (OP == RS_GS1_DONE) {
-        gs1_done_body(0, P.red, P.misc, P.guard);
-    } else if constexpr (OP == RS_GS2) {
-        gs2_body(0, k, m, P.red, P.H, P.coef, P.guard);
-    } else {
-        givens_body(0, k, m, P.red, P.guard, P.H, P.cs, P.sn, P.g, P.misc, P.status);
-    }
-}
-
-// k_reduce_cols followed by single-lane step OP on the column sums, in one launch: each
-// workgroup reduces its column (or nothing when the guard says skip), then counts itself done;
-// the last one (agent-scope fences on both sides of the count, so the other columns' sums are
-// visible to it) runs the step and clears the count for the next launch. The step runs even when
-// the reduction was skipped (the Givens step needs it either way; the guarded steps check the
-// guard themselves).
+// k_reduce_cols followed by step OP on the column sums in the last workgroup, in one launch.
 template <int OP>
 __global__ __launch_bounds__(WG) void k_reduce_step(KPtrs P, int nb, const int *guard, int k, int m) {
-    reduce_cols_body(blockIdx.x, P.partials, nb, P.red, guard);
-    __shared__ int last;
-    if (threadIdx.x == 0) {
-        int is_last = 1;
-        if (gridDim.x > 1) {
-            __threadfence();
-            is_last = atomicAdd(P.done, 1) == (int)gridDim.x - 1;
-            if (is_last) {
-                __threadfence();
-                *P.done = 0;
-            }
-        }
-        last = is_last;
-    }
-    __syncthreads();
-    if (!last || threadIdx.x != 0) return;
-    step_tail<OP>(P, k, m);
+    reduce_step_body<OP>(blockIdx.x, gridDim.x, P, nb, guard, k, m);
 }
 
-// ---- small systems (at most FOLD_NB vector workgroups): the dot and update kernels reduce their
-// own partials in their last workgroup and run the step there, one launch instead of two. The
-// columns are summed by reduce_cols_body, in the same order, so the results are those of the
-// two-launch form bit for bit.
-constexpr int FOLD_NB = 64;
+// ---- systems of at most FOLD_NB vector workgroups (all of the smaller tile): the dot and update
+// kernels reduce their own partials in their last workgroup and run the step there, one launch
+// instead of two, with the sums of the two-launch form bit for bit. Beyond FOLD_NB one workgroup
+// would add more than four entries per lane and column (at 4 million cells, 31).
+constexpr int FOLD_VE = 4;
+static_assert((int64_t)FOLD_NB * WG * FOLD_VE < VEC_SMALL, "folded systems have the smaller tile");
 
-// true in the last workgroup to finish (every workgroup's partials then visible to all its
-// lanes); clears the count for the next launch
-__device__ __forceinline__ bool last_workgroup(int *done) {
-    __shared__ int last;
-    __threadfence();
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        int is_last = 1;
-        if (gridDim.x > 1) {
-            is_last = atomicAdd(done, 1) == (int)gridDim.x - 1;
-            if (is_last) *done = 0;
-        }
-        last = is_last;
-    }
-    __syncthreads();
-    if (last) __threadfence();
-    return last;
+template <int OP>
+__device__ __forceinline__ void fold_tail(const KPtrs &P, int nb, int cols, const int *guard, int k, int m) {
+    __shared__ double sred[MAX_RESTART + 2];
+    if (!last_workgroup<true>(P.done, gridDim.x, blockIdx.x)) return;
+    if (!skipped(guard)) reduce_cols_fold(P.partials, nb, cols, sred);
+    step_tail<OP>(P, k, m, sred);
 }
 
 template <int OP>
 __global__ __launch_bounds__(WG) void k_mdot_step(int64_t len, const double *__restrict__ V, int64_t ldv, int q,
-                                                  const double *__restrict__ w, KPtrs P, int nb, const int *guard,
-                                                  int k, int m) {
-    mdot_body(blockIdx.x, len, V, ldv, q, w, P.partials, nb, guard);
-    if (!last_workgroup(P.done)) return;
-    for (int c = 0; c <= q; ++c) {
-        reduce_cols_body(c, P.partials, nb, P.red, guard);
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) step_tail<OP>(P, k, m);
+                                                  const double *__restrict__ w, KPtrs P, int nb, int k, int m) {
+    __shared__ WaveSums sh[MAX_RESTART + 2];
+    mdot_body<FOLD_VE>(blockIdx.x, len, V, ldv, q, w, P.partials, nb, sh);
+    fold_tail<OP>(P, nb, q + 1, nullptr, k, m);
 }
 
-template <int OP>
+template <int QM>
+__global__ __launch_bounds__(WG) void k_update_dot_step(int64_t len, const double *__restrict__ V, int64_t ldv, int q,
+                                                        const double *__restrict__ c, double *__restrict__ w, KPtrs P,
+                                                        int nb, int k, int m) {
+    __shared__ WaveSums sh[MAX_RESTART + 2];
+    update_dot_body<QM, FOLD_VE>(gridDim.x - 1 - blockIdx.x, len, V, ldv, q, c, w, P.partials, nb, sh);
+    fold_tail<RS_GS2>(P, nb, q + 1, nullptr, k, m);
+}
+
 __global__ __launch_bounds__(WG) void k_update_step(int64_t len, const double *__restrict__ V, int64_t ldv, int q,
                                                     const double *__restrict__ c, double alpha, double *__restrict__ w,
                                                     KPtrs P, int nb, const int *guard, int k, int m) {
-    update_body(gridDim.x - 1 - blockIdx.x, len, V, ldv, q, c, alpha, w, P.partials, guard);
-    if (!last_workgroup(P.done)) return;
-    reduce_cols_body(0, P.partials, nb, P.red, guard);
-    __syncthreads();
-    if (threadIdx.x == 0) step_tail<OP>(P, k, m);
+    update_body<FOLD_VE>(gridDim.x - 1 - blockIdx.x, len, V, ldv, q, c, alpha, w, P.partials, guard);
+    fold_tail<RS_GIVENS>(P, nb, 1, guard, k, m);
 }
 
 // v = w / h (h read from device memory; left unchanged if h == 0)
@@ -152,15 +98,10 @@ __global__ __launch_bounds__(WG) void k_scale(int64_t len, const double *w, doub
     scale_body(blockIdx.x, len, w, v, h);
 }
 
-// ---- single-lane steps on the small dense Hessenberg problem (column-major, ld = m+1). After the
-// first Gram-Schmidt pass: H(0:k,k) = dots, coef = dots, nrm0 = ||w|| before (gs1). After the
-// first update: a second pass (guard = 1) if ||w'|| < ||w|| / sqrt(2) (gs1_done). After the second
-// dot pass, only if guard: H(0:k,k) += dots2, coef = dots2 (gs2). Final norm, Givens rotations,
-// residual estimate (givens). All run fused into the reduction before them (k_reduce_step).
-
 // Back substitution on the k x k upper triangle: coef = y.
-__global__ void k_solve(int k, int m, const double *__restrict__ H, const double *__restrict__ g, double *coef) {
-    solve_body(blockIdx.x, k, m, H, g, coef);
+__global__ __launch_bounds__(64) void k_solve(int k, int m, const double *__restrict__ H, const double *__restrict__ g,
+                                              double *coef) {
+    solve_body(k, m, H, g, coef);
 }
 
 __global__ __launch_bounds__(WG) void k_zero(int64_t len, double *v) {
@@ -180,8 +121,8 @@ __global__ __launch_bounds__(WG) void k_ilu_residual(int n, int ZL, const int32_
     __shared__ double shn[WG / 64], shd[WG / 64];
     const int r = threadIdx.x & 3;
     double num = 0.0, den = 0.0;
-    for (int pass = 0; pass < VEC_TILE / 4 / ROWS_PER_WG; ++pass) {
-        const int i = (blockIdx.x * (VEC_TILE / 4 / ROWS_PER_WG) + pass) * ROWS_PER_WG + (threadIdx.x >> 2);
+    for (int pass = 0; pass < DIAG_ROWS / ROWS_PER_WG; ++pass) {
+        const int i = blockIdx.x * DIAG_ROWS + pass * ROWS_PER_WG + (threadIdx.x >> 2);
         if (i < n) {
             const int b0 = rowptr[i], b1 = rowptr[i + 1], d = diag_pos[i];
             for (int e = b0; e < b1; ++e) {
@@ -236,7 +177,7 @@ struct Ctx {
     double *partials, *H, *cs, *sn, *g, *coef, *misc, *status, *red, *V, *Zb;
     int *guard, *done;
     int m;
-    KPtrs ptrs() const { return KPtrs{partials, red, H, cs, sn, g, coef, misc, status, guard, done}; }
+    KPtrs ptrs() const { return KPtrs{partials, red, H, cs, sn, g, coef, misc, status, guard, done, true}; }
 };
 
 #define CKL()                                                     \
@@ -244,7 +185,7 @@ struct Ctx {
         if (launch_status() != ABILU_OK) return ABILU_EDEVICE;    \
     } while (0)
 
-// Column sums of the partials into c.red (ncols columns), then single-lane step op.
+// Column sums of the partials into c.red (ncols columns), then step op.
 abilu_status reduce_step(Ctx &c, int ncols, const int *guard, int op, int k) {
     const int nb = c.W.nb_vec;
     ProfScope ps("fgmres_reduce", c.s, 8.0 * ncols * nb);
@@ -254,7 +195,6 @@ abilu_status reduce_step(Ctx &c, int ncols, const int *guard, int op, int k) {
         case RS_BETA_START_X: k_reduce_step<RS_BETA_START_X><<<ncols, WG, 0, c.s>>>(P, nb, guard, k, c.m); break;
         case RS_BETA: k_reduce_step<RS_BETA><<<ncols, WG, 0, c.s>>>(P, nb, guard, k, c.m); break;
         case RS_GS1: k_reduce_step<RS_GS1><<<ncols, WG, 0, c.s>>>(P, nb, guard, k, c.m); break;
-        case RS_GS1_DONE: k_reduce_step<RS_GS1_DONE><<<ncols, WG, 0, c.s>>>(P, nb, guard, k, c.m); break;
         case RS_GS2: k_reduce_step<RS_GS2><<<ncols, WG, 0, c.s>>>(P, nb, guard, k, c.m); break;
         default: k_reduce_step<RS_GIVENS><<<ncols, WG, 0, c.s>>>(P, nb, guard, k, c.m); break;
     }
@@ -262,57 +202,77 @@ abilu_status reduce_step(Ctx &c, int ncols, const int *guard, int op, int k) {
     return ABILU_OK;
 }
 
-// one launch of kernel template K<OP> for a runtime op (the steps after a dot or update kernel)
-#define ABILU_STEP_SWITCH(K, ARGS)                                                  \
-    switch (op) {                                                                   \
-        case RS_BETA: K<RS_BETA><<<nb, WG, 0, c.s>>> ARGS; break;                   \
-        case RS_GS1: K<RS_GS1><<<nb, WG, 0, c.s>>> ARGS; break;                     \
-        case RS_GS1_DONE: K<RS_GS1_DONE><<<nb, WG, 0, c.s>>> ARGS; break;           \
-        case RS_GS2: K<RS_GS2><<<nb, WG, 0, c.s>>> ARGS; break;                     \
-        default: K<RS_GIVENS><<<nb, WG, 0, c.s>>> ARGS; break;                      \
-    }
-
 // c.red[0..q] <- dots of w with V_0..V_{q-1}, then ||w||^2; then step op
-abilu_status mdot_reduce(Ctx &c, const double *Vb, int q, const double *w, const int *guard, int op, int k) {
+abilu_status mdot_reduce(Ctx &c, const double *Vb, int q, const double *w, int op, int k) {
     const int nb = c.W.nb_vec;
     const double n8 = 8.0 * (double)c.nv;
     if (nb <= FOLD_NB && op != RS_BETA_START_ZERO && op != RS_BETA_START_X) {
-        {
-            ProfScope ps("fgmres_mdot", c.s, (q + 1) * n8 + 8.0 * (q + 1) * nb);
-            const KPtrs P = c.ptrs();
-            ABILU_STEP_SWITCH(k_mdot_step, (c.nv, Vb, c.nv, q, w, P, nb, guard, k, c.m))
-        }
+        ProfScope ps("fgmres_mdot", c.s, (q + 1) * n8 + 8.0 * (q + 1) * nb);
+        const KPtrs P = c.ptrs();
+        if (op == RS_BETA) k_mdot_step<RS_BETA><<<nb, WG, 0, c.s>>>(c.nv, Vb, c.nv, q, w, P, nb, k, c.m);
+        else k_mdot_step<RS_GS1><<<nb, WG, 0, c.s>>>(c.nv, Vb, c.nv, q, w, P, nb, k, c.m);
         CKL();
         return ABILU_OK;
     }
     {
         ProfScope ps("fgmres_mdot", c.s, (q + 1) * n8);
-        k_mdot<<<nb, WG, 0, c.s>>>(c.nv, Vb, c.nv, q, w, c.partials, nb, guard);
+        if (vec_e(c.nv) == 4) k_mdot<4><<<nb, WG, 0, c.s>>>(c.nv, Vb, c.nv, q, w, c.partials, nb);
+        else k_mdot<8><<<nb, WG, 0, c.s>>>(c.nv, Vb, c.nv, q, w, c.partials, nb);
     }
     CKL();
-    return reduce_step(c, q + 1, guard, op, k);
+    return reduce_step(c, q + 1, nullptr, op, k);
 }
 
-// w += alpha * sum_k coef[k] Vb_k; with a step op (>= 0): c.red[0] <- ||w||^2 afterwards, then the step
-abilu_status update_reduce(Ctx &c, const double *Vb, int q, double alpha, double *w, const int *guard, int op, int k) {
+// first Gram-Schmidt update of w against V_0..V_{q-1} with the second pass's dots, then the
+// decision on that pass
+abilu_status update_dot_reduce(Ctx &c, int q, double *w, int k) {
+    const int nb = c.W.nb_vec;
+    const bool fold = nb <= FOLD_NB;
+    const double n8 = 8.0 * (double)c.nv;
+    {
+        ProfScope ps("fgmres_update_dot", c.s, (q + 2) * n8 + (fold ? 8.0 * (q + 1) * nb : 0.0));
+        const KPtrs P = c.ptrs();
+#define ABILU_UPDATE_DOT(QM)                                                                                          \
+    do {                                                                                                              \
+        if (fold) k_update_dot_step<QM><<<nb, WG, 0, c.s>>>(c.nv, c.V, c.nv, q, c.coef, w, P, nb, k, c.m);            \
+        else if (vec_e(c.nv) == 4)                                                                                    \
+            k_update_dot<QM, 4><<<nb, WG, 0, c.s>>>(c.nv, c.V, c.nv, q, c.coef, w, c.partials, nb);                   \
+        else k_update_dot<QM, 8><<<nb, WG, 0, c.s>>>(c.nv, c.V, c.nv, q, c.coef, w, c.partials, nb);                  \
+    } while (0)
+        switch (update_dot_form(q)) {
+            case 4: ABILU_UPDATE_DOT(4); break;
+            case 8: ABILU_UPDATE_DOT(8); break;
+            case 16: ABILU_UPDATE_DOT(16); break;
+            case 32: ABILU_UPDATE_DOT(32); break;
+            default: ABILU_UPDATE_DOT(0); break;
+        }
+#undef ABILU_UPDATE_DOT
+    }
+    CKL();
+    return fold ? ABILU_OK : reduce_step(c, q + 1, nullptr, RS_GS2, k);
+}
+
+// w += alpha * sum_k coef[k] Vb_k; with givens: c.red[0] <- ||w||^2 afterwards, then the Givens step
+abilu_status update_reduce(Ctx &c, const double *Vb, int q, double alpha, double *w, const int *guard, bool givens,
+                           int k) {
     const int nb = c.W.nb_vec;
     const double n8 = 8.0 * (double)c.nv;
-    const bool with_norm = op >= 0;
-    if (with_norm && nb <= FOLD_NB) {
+    if (givens && nb <= FOLD_NB) {
         {
             ProfScope ps("fgmres_update", c.s, (q + 2) * n8 + 8.0 * nb);
-            const KPtrs P = c.ptrs();
-            ABILU_STEP_SWITCH(k_update_step, (c.nv, Vb, c.nv, q, c.coef, alpha, w, P, nb, guard, k, c.m))
+            k_update_step<<<nb, WG, 0, c.s>>>(c.nv, Vb, c.nv, q, c.coef, alpha, w, c.ptrs(), nb, guard, k, c.m);
         }
         CKL();
         return ABILU_OK;
     }
     {
         ProfScope ps("fgmres_update", c.s, (q + 2) * n8);
-        k_update<<<nb, WG, 0, c.s>>>(c.nv, Vb, c.nv, q, c.coef, alpha, w, with_norm ? c.partials : nullptr, guard);
+        double *part = givens ? c.partials : nullptr;
+        if (vec_e(c.nv) == 4) k_update<4><<<nb, WG, 0, c.s>>>(c.nv, Vb, c.nv, q, c.coef, alpha, w, part, guard);
+        else k_update<8><<<nb, WG, 0, c.s>>>(c.nv, Vb, c.nv, q, c.coef, alpha, w, part, guard);
     }
     CKL();
-    return with_norm ? reduce_step(c, 1, guard, op, k) : ABILU_OK;
+    return givens ? reduce_step(c, 1, guard, RS_GIVENS, k) : ABILU_OK;
 }
 
 // copies the flag word and the status scalars to the host
@@ -330,7 +290,7 @@ abilu_status readback(Ctx &c, double *h, uint32_t *flags) {
 abilu_status true_residual(Ctx &c, const double *A, const double *b, const double *x) {
     abilu_status st = spmv_impl(c.p, A, x, c.V, b, true, c.s);
     if (st != ABILU_OK) return st;
-    return mdot_reduce(c, c.V, 0, c.V, nullptr, RS_BETA, 0);
+    return mdot_reduce(c, c.V, 0, c.V, RS_BETA, 0);
 }
 
 }  // namespace
@@ -371,7 +331,7 @@ extern "C" abilu_status fgmres_solve(const abilu_pattern *p, const double *d_A, 
     c.V = (double *)(c.work + c.W.V);
     c.Zb = (double *)(c.work + c.W.Z);
     c.guard = (int *)(c.misc + MI_GUARD);
-    c.done = (int *)(c.misc + MI_DONE);
+    c.done = (int *)(c.work + c.W.done);
     c.m = m;
     double h[8];
     uint32_t flags = 0;
@@ -379,9 +339,7 @@ extern "C" abilu_status fgmres_solve(const abilu_pattern *p, const double *d_A, 
 
     // ||b|| and the initial residual (b itself for a zero initial guess)
     const bool zero_guess = (options & ABILU_FGMRES_ZERO_GUESS) != 0;
-    if ((st = mdot_reduce(c, c.V, 0, d_b, nullptr, zero_guess ? RS_BETA_START_ZERO : RS_BETA_START_X, 0)) !=
-        ABILU_OK)
-        return st;
+    if ((st = mdot_reduce(c, c.V, 0, d_b, zero_guess ? RS_BETA_START_ZERO : RS_BETA_START_X, 0)) != ABILU_OK) return st;
     const double *first_v0 = c.V;   // the vector the first cycle normalises into V_0
     if (zero_guess) {
         {
@@ -419,15 +377,14 @@ extern "C" abilu_status fgmres_solve(const abilu_pattern *p, const double *d_A, 
             if ((st = spmv_impl(p, d_A, zk, w, nullptr, !apply_ends_descending(apply_sweeps, mode), c.s)) !=
                 ABILU_OK)
                 return st;
-            // Gram-Schmidt pass 1
-            // pass 1: dots, H(0:k,k); update, then the decision on a second pass
-            if ((st = mdot_reduce(c, c.V, k + 1, w, nullptr, RS_GS1, k)) != ABILU_OK) return st;
-            if ((st = update_reduce(c, c.V, k + 1, -1.0, w, nullptr, RS_GS1_DONE, k)) != ABILU_OK) return st;
-            // pass 2, executed by the device only when the guard is set; the Givens step after its
-            // update runs either way
+            // Gram-Schmidt pass 1: dots, H(0:k,k); the update, with the second pass's dots and the
+            // decision on that pass
+            if ((st = mdot_reduce(c, c.V, k + 1, w, RS_GS1, k)) != ABILU_OK) return st;
+            if ((st = update_dot_reduce(c, k + 1, w, k)) != ABILU_OK) return st;
+            // pass 2's update, executed by the device only when the guard is set; the Givens step
+            // after it runs either way
             const int pass2_begin = prof_mark();
-            if ((st = mdot_reduce(c, c.V, k + 1, w, c.guard, RS_GS2, k)) != ABILU_OK) return st;
-            if ((st = update_reduce(c, c.V, k + 1, -1.0, w, c.guard, RS_GIVENS, k)) != ABILU_OK) return st;
+            if ((st = update_reduce(c, c.V, k + 1, -1.0, w, c.guard, true, k)) != ABILU_OK) return st;
             const int pass2_end = prof_mark();
             {
                 ProfScope ps("fgmres_scale", c.s, 16.0 * (double)c.nv);
@@ -452,10 +409,10 @@ extern "C" abilu_status fgmres_solve(const abilu_pattern *p, const double *d_A, 
         // least squares and x += Z y
         {
             ProfScope ps("fgmres_small", c.s);
-            k_solve<<<1, 1, 0, c.s>>>(k, m, c.H, c.g, c.coef);
+            k_solve<<<1, 64, 0, c.s>>>(k, m, c.H, c.g, c.coef);
         }
         CKL();
-        if ((st = update_reduce(c, c.Zb, k, 1.0, d_x, nullptr, -1, 0)) != ABILU_OK) return st;
+        if ((st = update_reduce(c, c.Zb, k, 1.0, d_x, nullptr, false, 0)) != ABILU_OK) return st;
         if ((st = true_residual(c, d_A, d_b, d_x)) != ABILU_OK) return st;
         if ((st = readback(c, h, &flags)) != ABILU_OK) return st;
         ++restarts;
@@ -479,7 +436,7 @@ extern "C" abilu_status fgmres_solve(const abilu_pattern *p, const double *d_A, 
 template <typename T>
 static abilu_status ilu_residual_t(const abilu_pattern *p, const double *A, const T *X, char *work,
                                    const Workspace &W, double *h_rel, hipStream_t s) {
-    const int nb = W.nb_vec;
+    const int nb = W.nb_diag;
     double *partial = (double *)(work + W.partials);
     double *red = (double *)(work + W.red);
     {

@@ -37,7 +37,7 @@ namespace {
 
 constexpr int HDR = 128;        // per-slot status header: flags word at 0, status doubles at 64
 constexpr int MAX_SLOTS = 4096;
-constexpr int ONE_WG = 64;      // threads per workgroup of the single-lane kernels
+constexpr int ONE_WG = 64;      // threads per workgroup of the back substitution
 constexpr int64_t ADMIT_MIN_CELLS = 1 << 20;   // admission budget per step when few cells are active
 
 size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
@@ -148,12 +148,8 @@ __global__ __launch_bounds__(WG) void kb_copy(const Slot *slots, const Member *m
     MEMBER();
     const double *s = (const double *)role(S, M.k, src);
     double *d = (double *)role(S, M.k, dst);
-    const int64_t base = (int64_t)blk * VEC_TILE + threadIdx.x;
-#pragma unroll
-    for (int e = 0; e < VEC_E; ++e) {
-        const int64_t t = base + (int64_t)e * WG;
-        if (t < S.nv) d[t] = s[t];
-    }
+    const int64_t tile = vec_tile(S.nv), t0 = blk * tile, t1 = min(S.nv, t0 + tile);
+    for (int64_t t = t0 + threadIdx.x; t < t1; t += WG) d[t] = s[t];
 }
 
 template <bool RESID>
@@ -165,25 +161,51 @@ __global__ __launch_bounds__(WG) void kb_spmv(const Slot *slots, const Member *m
 }
 
 // q_plus: q = k + q_plus (Arnoldi: k + 1 basis vectors), or q = 0 when q_plus < 0
-__global__ __launch_bounds__(WG) void kb_mdot(const Slot *slots, const Member *mem, int nmem, int w, int q_plus,
-                                              int use_guard) {
+__global__ __launch_bounds__(WG) void kb_mdot(const Slot *slots, const Member *mem, int nmem, int w, int q_plus) {
     MEMBER();
     const int q = q_plus < 0 ? 0 : M.k + q_plus;
-    mdot_body(blk, S.nv, S.V, S.nv, q, (const double *)role(S, M.k, w), S.partials, S.nb_vec,
-              use_guard ? (const int *)(S.misc + MI_GUARD) : nullptr);
+    const double *wv = (const double *)role(S, M.k, w);
+    __shared__ WaveSums sh[MAX_RESTART + 2];
+    if (vec_e(S.nv) == 4) mdot_body<4>(blk, S.nv, S.V, S.nv, q, wv, S.partials, S.nb_vec, sh);
+    else mdot_body<8>(blk, S.nv, S.V, S.nv, q, wv, S.partials, S.nb_vec, sh);
 }
 
 __global__ __launch_bounds__(WG) void kb_update(const Slot *slots, const Member *mem, int nmem, int base, int q_plus,
                                                 double alpha, int w, int with_norm, int use_guard) {
     MEMBER_DIR(true);
-    update_body(blk, S.nv, (const double *)role(S, M.k, base), S.nv, M.k + q_plus, S.coef, alpha,
-                (double *)role(S, M.k, w), with_norm ? S.partials : nullptr,
-                use_guard ? (const int *)(S.misc + MI_GUARD) : nullptr);
+    const double *bv = (const double *)role(S, M.k, base);
+    double *wv = (double *)role(S, M.k, w), *part = with_norm ? S.partials : nullptr;
+    const int *guard = use_guard ? (const int *)(S.misc + MI_GUARD) : nullptr;
+    if (vec_e(S.nv) == 4) update_body<4>(blk, S.nv, bv, S.nv, M.k + q_plus, S.coef, alpha, wv, part, guard);
+    else update_body<8>(blk, S.nv, bv, S.nv, M.k + q_plus, S.coef, alpha, wv, part, guard);
 }
 
-__global__ __launch_bounds__(WG) void kb_reduce(const Slot *slots, const Member *mem, int nmem, int use_guard) {
+// QM: the register form of the member with the most vectors (every form gives the same bits)
+template <int QM>
+__global__ __launch_bounds__(WG) void kb_update_dot(const Slot *slots, const Member *mem, int nmem) {
+    MEMBER_DIR(true);
+    double *w = S.V + (int64_t)(M.k + 1) * S.nv;
+    __shared__ WaveSums sh[MAX_RESTART + 2];
+    if (vec_e(S.nv) == 4) update_dot_body<QM, 4>(blk, S.nv, S.V, S.nv, M.k + 1, S.coef, w, S.partials, S.nb_vec, sh);
+    else update_dot_body<QM, 8>(blk, S.nv, S.V, S.nv, M.k + 1, S.coef, w, S.partials, S.nb_vec, sh);
+}
+
+// Column sums of each member (k + 2 columns for the Gram-Schmidt steps, else one), then step OP in
+// the member's last workgroup.
+template <int OP>
+__global__ __launch_bounds__(WG) void kb_reduce_step(const Slot *slots, const Member *mem, int nmem, int m) {
     MEMBER();
-    reduce_cols_body(blk, S.partials, S.nb_vec, S.red, use_guard ? (const int *)(S.misc + MI_GUARD) : nullptr);
+    const int cols = OP == RS_GS1 || OP == RS_GS2 ? M.k + 2 : 1;
+    const KPtrs P{S.partials, S.red, S.H, S.cs, S.sn, S.g, S.coef, S.misc, S.status, (int *)(S.misc + MI_GUARD),
+                  (int *)(S.misc + MI_DONE), false};
+    reduce_step_body<OP>(blk, cols, P, S.nb_vec, OP == RS_GIVENS ? P.guard : nullptr, M.k, m);
+}
+
+// back substitution, one workgroup per member
+__global__ __launch_bounds__(64) void kb_solve(const Slot *slots, const Member *mem, int nmem, int m) {
+    MEMBER();
+    (void)blk;
+    solve_body(M.k, m, S.H, S.g, S.coef);
 }
 
 // hv = misc[slot]: MI_BETA or MI_HN
@@ -195,30 +217,6 @@ __global__ __launch_bounds__(WG) void kb_scale(const Slot *slots, const Member *
 __global__ __launch_bounds__(WG) void kb_zero(const Slot *slots, const Member *mem, int nmem, int v) {
     MEMBER();
     zero_body(blk, S.nv, (double *)role(S, M.k, v));
-}
-
-enum { OP_BETA0 = 0, OP_GS1, OP_GS1_DONE, OP_GS2, OP_GIVENS, OP_SOLVE, OP_BETA_CE };
-
-// single-lane steps on the small dense problem, one lane per member
-__global__ void kb_small(const Slot *slots, const Member *mem, int nmem, int op, int m) {
-    const int t = blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= nmem) return;
-    const Member M = mem[t];
-    const Slot &S = slots[M.slot];
-    const int k = M.k;
-    int *guard = (int *)(S.misc + MI_GUARD);
-    switch (op) {
-        case OP_BETA0:
-            beta_body(0, m, S.red, S.g, S.misc, S.status, ST_NUM);
-            beta_body(0, m, S.red, nullptr, S.misc, S.status, ST_BETA);
-            break;
-        case OP_GS1: gs1_body(0, k, m, S.red, S.H, S.coef, S.misc); break;
-        case OP_GS1_DONE: gs1_done_body(0, S.red, S.misc, guard); break;
-        case OP_GS2: gs2_body(0, k, m, S.red, S.H, S.coef, guard); break;
-        case OP_GIVENS: givens_body(0, k, m, S.red, guard, S.H, S.cs, S.sn, S.g, S.misc, S.status); break;
-        case OP_SOLVE: solve_body(0, k, m, S.H, S.g, S.coef); break;
-        default: beta_body(0, m, S.red, S.g, S.misc, S.status, ST_BETA); break;
-    }
 }
 
 // ------------------------------------------------------------------ batched admission kernels
@@ -419,7 +417,7 @@ ReqLayout req_layout(const abilu_serve_config &c, int32_t n, int64_t Z, size_t g
     // of a generated pattern lies in one triangle; its update sets are the diagonal ones)
     L.zcap = Z - n;
     L.pcap = Z - n;
-    L.nb_vec = div_up((int64_t)(nv > 0 ? nv : 1), VEC_TILE);
+    L.nb_vec = div_up((int64_t)(nv > 0 ? nv : 1), vec_tile((int64_t)nv));
     L.rowptr = take(4 * (size_t)(n + 1));
     L.colidx = take(4 * (size_t)Z);
     L.diag_pos = take(4 * (size_t)(n + 1));
@@ -824,48 +822,47 @@ abilu_status run_group(abilu_server *s, Group &G, hipStream_t st) {
     auto nv8 = [](const Sizes &z) { return 32.0 * z.N; };   // bytes of one FP64 Krylov vector
 #define L_(shape) dim3(G.t[shape].tiles), dim3(WG), 0, st
 #define A_(shape) sl, G.t[shape].d, G.t[shape].count
-#define ONE_() dim3(div_up(G.t[SH_ONE].count, ONE_WG)), dim3(ONE_WG), 0, st
 #define CKL()                                                  \
     do {                                                       \
         if (launch_status() != ABILU_OK) return ABILU_EDEVICE; \
     } while (0)
-    // dots of w with V_0..V_{q-1} and ||w||^2; q = k + q_plus, or 0 when q_plus < 0
-    auto mdot = [&](int w, int q_plus, int guard) -> abilu_status {
-        auto qof = [&](const Req &r) { return q_plus < 0 ? 0 : r.k + q_plus; };
-        {
-            ProfScope ps("serve_mdot", st, B([&](const Sizes &z, const Req &r) { return (qof(r) + 1) * nv8(z); }));
-            kb_mdot<<<L_(SH_VEC)>>>(A_(SH_VEC), w, q_plus, guard);
-        }
+    // column sums of the partials (GS1, GS2: k + 2 columns, else one), then step OP
+    auto reduce = [&](auto op) -> abilu_status {
+        constexpr int OP = decltype(op)::value;
+        constexpr bool many = OP == RS_GS1 || OP == RS_GS2;
+        ProfScope ps("serve_reduce", st,
+                     B([&](const Sizes &, const Req &r) { return 8.0 * (many ? r.k + 2 : 1) * r.L.nb_vec; }));
+        kb_reduce_step<OP><<<L_(many ? SH_COLSQ : SH_ONE)>>>(A_(many ? SH_COLSQ : SH_ONE), m);
         CKL();
-        {
-            ProfScope ps("serve_reduce", st,
-                         B([&](const Sizes &, const Req &r) { return 8.0 * (qof(r) + 1) * r.L.nb_vec; }));
-            if (q_plus < 0)
-                kb_reduce<<<L_(SH_ONE)>>>(A_(SH_ONE), guard);
-            else
-                kb_reduce<<<L_(SH_COLSQ)>>>(A_(SH_COLSQ), guard);
-        }
+        return ABILU_OK;
+    };
+    // dots of w with V_0..V_{q-1} and ||w||^2; q = k + q_plus, or 0 when q_plus < 0
+    auto mdot = [&](int w, int q_plus) -> abilu_status {
+        auto qof = [&](const Req &r) { return q_plus < 0 ? 0 : r.k + q_plus; };
+        ProfScope ps("serve_mdot", st, B([&](const Sizes &z, const Req &r) { return (qof(r) + 1) * nv8(z); }));
+        kb_mdot<<<L_(SH_VEC)>>>(A_(SH_VEC), w, q_plus);
         CKL();
         return ABILU_OK;
     };
     // w += alpha sum_k coef_k base_k over q = k + q_plus vectors (+ ||w||^2 partials)
     auto update = [&](int base, int q_plus, double alpha, int w, int norm, int guard) -> abilu_status {
-        {
-            ProfScope ps("serve_update", st,
-                         B([&](const Sizes &z, const Req &r) { return (r.k + q_plus + 2) * nv8(z); }));
-            kb_update<<<L_(SH_VEC)>>>(A_(SH_VEC), base, q_plus, alpha, w, norm, guard);
-        }
+        ProfScope ps("serve_update", st, B([&](const Sizes &z, const Req &r) { return (r.k + q_plus + 2) * nv8(z); }));
+        kb_update<<<L_(SH_VEC)>>>(A_(SH_VEC), base, q_plus, alpha, w, norm, guard);
         CKL();
-        if (norm) {
-            ProfScope ps("serve_reduce", st, B([&](const Sizes &, const Req &r) { return 8.0 * r.L.nb_vec; }));
-            kb_reduce<<<L_(SH_ONE)>>>(A_(SH_ONE), guard);
-            CKL();
-        }
         return ABILU_OK;
     };
-    auto small = [&](int op) -> abilu_status {
-        ProfScope ps("serve_small", st, B([](const Sizes &, const Req &) { return 0.0; }));
-        kb_small<<<ONE_()>>>(A_(SH_ONE), op, m);
+    // the first update of V_{k+1} with the second pass's dots
+    auto update_dot = [&]() -> abilu_status {
+        ProfScope ps("serve_update_dot", st, B([&](const Sizes &z, const Req &r) { return (r.k + 3) * nv8(z); }));
+        int q = 0;
+        for (int64_t id : G.ids) q = std::max(q, s->reqs[id].k + 1);
+        switch (update_dot_form(q)) {
+            case 4: kb_update_dot<4><<<L_(SH_VEC)>>>(A_(SH_VEC)); break;
+            case 8: kb_update_dot<8><<<L_(SH_VEC)>>>(A_(SH_VEC)); break;
+            case 16: kb_update_dot<16><<<L_(SH_VEC)>>>(A_(SH_VEC)); break;
+            case 32: kb_update_dot<32><<<L_(SH_VEC)>>>(A_(SH_VEC)); break;
+            default: kb_update_dot<0><<<L_(SH_VEC)>>>(A_(SH_VEC)); break;
+        }
         CKL();
         return ABILU_OK;
     };
@@ -947,8 +944,8 @@ abilu_status run_group(abilu_server *s, Group &G, hipStream_t st) {
             }
         }
         // ||b||; zero initial guess: beta = ||b||, V_0 = b / beta
-        if ((e = mdot(R_B, -1, 0)) != ABILU_OK) return e;
-        if ((e = small(OP_BETA0)) != ABILU_OK) return e;
+        if ((e = mdot(R_B, -1)) != ABILU_OK) return e;
+        if ((e = reduce(std::integral_constant<int, RS_BETA_START_ZERO>{})) != ABILU_OK) return e;
         {
             ProfScope ps("serve_zero", st, B([&](const Sizes &z, const Req &) { return nv8(z); }));
             kb_zero<<<L_(SH_VEC)>>>(A_(SH_VEC), R_X);
@@ -998,30 +995,32 @@ abilu_status run_group(abilu_server *s, Group &G, hipStream_t st) {
             }
         }
         if ((e = spmv(false, R_ZK, R_VK1)) != ABILU_OK) return e;
-        // Gram-Schmidt pass 1, then pass 2 only where the device set the guard
-        if ((e = mdot(R_VK1, 1, 0)) != ABILU_OK) return e;
-        if ((e = small(OP_GS1)) != ABILU_OK) return e;
-        if ((e = update(R_VBASE, 1, -1.0, R_VK1, 1, 0)) != ABILU_OK) return e;
-        if ((e = small(OP_GS1_DONE)) != ABILU_OK) return e;
-        // launches pass2 .. pass2 + 4: mdot, reduce, gs2, update, reduce (bytes corrected after
-        // the tick for members whose guard stayed clear)
+        // Gram-Schmidt pass 1 with the second pass's dots, then its update only where the device set
+        // the guard
+        if ((e = mdot(R_VK1, 1)) != ABILU_OK) return e;
+        if ((e = reduce(std::integral_constant<int, RS_GS1>{})) != ABILU_OK) return e;
+        if ((e = update_dot()) != ABILU_OK) return e;
+        if ((e = reduce(std::integral_constant<int, RS_GS2>{})) != ABILU_OK) return e;
+        // launches pass2, pass2 + 1: update, reduce (bytes corrected after the tick for members
+        // whose guard stayed clear)
         G.pass2 = prof_mark();
-        if ((e = mdot(R_VK1, 1, 1)) != ABILU_OK) return e;
-        if ((e = small(OP_GS2)) != ABILU_OK) return e;
         if ((e = update(R_VBASE, 1, -1.0, R_VK1, 1, 1)) != ABILU_OK) return e;
-        if ((e = small(OP_GIVENS)) != ABILU_OK) return e;
+        if ((e = reduce(std::integral_constant<int, RS_GIVENS>{})) != ABILU_OK) return e;
         return scale(R_VK1, R_VK1, MI_HN);
     }
     // end of a restart cycle over k Arnoldi steps: x += Z y, true residual, next V_0
-    if ((e = small(OP_SOLVE)) != ABILU_OK) return e;
+    {
+        ProfScope ps("serve_small", st, B([](const Sizes &, const Req &) { return 0.0; }));
+        kb_solve<<<dim3(G.t[SH_ONE].tiles), dim3(ONE_WG), 0, st>>>(A_(SH_ONE), m);
+        CKL();
+    }
     if ((e = update(R_ZBASE, 0, 1.0, R_X, 0, 0)) != ABILU_OK) return e;
     if ((e = spmv(true, R_X, R_V0)) != ABILU_OK) return e;
-    if ((e = mdot(R_V0, -1, 0)) != ABILU_OK) return e;
-    if ((e = small(OP_BETA_CE)) != ABILU_OK) return e;
+    if ((e = mdot(R_V0, -1)) != ABILU_OK) return e;
+    if ((e = reduce(std::integral_constant<int, RS_BETA>{})) != ABILU_OK) return e;
     return scale(R_V0, R_V0, MI_BETA);
 #undef L_
 #undef A_
-#undef ONE_
 #undef CKL
 }
 
@@ -1142,23 +1141,18 @@ abilu_status step_impl(abilu_server *s, hipStream_t st) {
     // the second Gram-Schmidt pass exited at once where the guard stayed clear: remove its bytes
     {
         Group &G = groups[1];
-        double dm = 0, dr = 0, du = 0, dr2 = 0;
+        double du = 0, dr = 0;
         for (int64_t id : G.ids) {
             const Req &r = s->reqs[id];
             const double *stv = (const double *)(s->h_hdr + (size_t)r.slot * HDR + 64);
             if (stv[ST_GUARD] != 0.0) continue;
-            const double nv8 = 32.0 * r.n, q = r.k + 1;
-            dm += (q + 1) * nv8;
-            dr += 8.0 * (q + 1) * r.L.nb_vec;
-            du += (q + 2) * nv8;
-            dr2 += 8.0 * r.L.nb_vec;
+            du += (r.k + 3) * 32.0 * r.n;
+            dr += 8.0 * r.L.nb_vec;
         }
-        s->stat_bytes -= dm + dr + du + dr2;
+        s->stat_bytes -= du + dr;
         if (!G.ids.empty()) {
-            prof_add_bytes(G.pass2, -dm);
+            prof_add_bytes(G.pass2, -du);
             prof_add_bytes(G.pass2 + 1, -dr);
-            prof_add_bytes(G.pass2 + 3, -du);
-            prof_add_bytes(G.pass2 + 4, -dr2);
         }
     }
     // advance, retire finished requests (copy x out first)
