@@ -90,6 +90,7 @@ struct Workspace {
     size_t partials;   // double[(restart+2) * nb_vec]
     size_t hess;       // double[(restart+1) * restart], column-major, ld = restart+1
     size_t cs, sn, g, coef, misc;  // double[restart+2] each; misc double[16]
+    size_t vscale;     // double[restart+2]: V_k holds v_k / vscale[k] (krylov.hip)
     size_t done;       // int[DONE_INTS]
     size_t red;        // double[restart+4]: outputs of column reductions
     size_t V, Z;       // double[(restart+1) * 4N], double[restart * 4N]
@@ -241,8 +242,9 @@ constexpr int REC_CAP = 4;
 enum : int { REC_PREV = 0, REC_CHUNK = 1, REC_OUT = 2 };
 
 // ------------------------------------------------------------------ entry points used across files
+// rscale (device, may be null): the right-hand side is *rscale times r.
 abilu_status apply_impl(const abilu_pattern *p, const void *LU, const void *Dinv, abilu_prec prec,
-                        const double *r, double *z, int nsweeps, abilu_mode mode, char *work,
+                        const double *r, const double *rscale, double *z, int nsweeps, abilu_mode mode, char *work,
                         const Workspace &W, hipStream_t s);
 // Whether the last kernel of apply_impl(nsweeps, mode) ran its workgroups in descending row order.
 bool apply_ends_descending(int nsweeps, abilu_mode mode);
@@ -299,6 +301,12 @@ __device__ __forceinline__ T sub_prod(T a, T b, T c) {
     } else {
         return a - b * c;
     }
+}
+
+// a s, rounded before it is used (no fused multiply-add with what follows); s = 1 leaves a.
+__device__ __forceinline__ double scaled(double a, double s) {
+#pragma clang fp contract(off)
+    return a * s;
 }
 
 // Row r (this lane's row) of a 4x4 block at `blk` (row-major), converted to T.

@@ -36,6 +36,7 @@ Workspace layout(const abilu_pattern *p, abilu_prec prec, int restart) {
     W.g = o; o = align256(o + sizeof(double) * (m + 2));
     W.coef = o; o = align256(o + sizeof(double) * (m + 2));
     W.misc = o; o = align256(o + sizeof(double) * 16);
+    W.vscale = o; o = align256(o + sizeof(double) * (m + 2));
     W.done = o; o = align256(o + sizeof(int) * DONE_INTS);
     W.red = o; o = align256(o + sizeof(double) * (m + 4));
     if (m > 0) {

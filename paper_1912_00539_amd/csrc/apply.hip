@@ -27,26 +27,34 @@ using namespace abilu_k;
 namespace {
 
 
-// Forward sweep over the strictly lower part of the factor layout (lrow/lcol/Lb).
+// The factor on the right-hand side (1 without one).
+__device__ __forceinline__ double rhs_scale(const double *rscale) { return rscale ? *rscale : 1.0; }
+
+// Forward sweep over the strictly lower part of the factor layout (lrow/lcol/Lb). first: yin is the
+// right-hand side itself.
 // Each quad owns rpq<T>() rows (ib, ib + 64) and loads two blocks of each per step (clamped, so
 // the loads are branch-free); a row with fewer blocks reads index 0 of the part, which exists
 // whenever the loop runs, and discards the product.
 template <typename T, typename YI, bool EMIT_Z>
 __global__ __launch_bounds__(WG) void k_fwd(int n, const int32_t *__restrict__ lrow, const int32_t *__restrict__ lcol,
                                             const T *__restrict__ Lb, const double *__restrict__ rhs, const YI *yin,
-                                            T *yout, const T *__restrict__ Dinv, T *__restrict__ zout) {
-    fwd_body<T, YI, EMIT_Z>(blockIdx.x, n, lrow, lcol, Lb, rhs, yin, yout, Dinv, zout);
+                                            T *yout, const T *__restrict__ Dinv, T *__restrict__ zout,
+                                            const double *__restrict__ rscale, int first) {
+    const double rs = rhs_scale(rscale);
+    fwd_body<T, YI, EMIT_Z>(blockIdx.x, n, lrow, lcol, Lb, rhs, yin, yout, Dinv, zout, rs, first ? rs : 1.0);
 }
 
 // Backward sweep over the strictly upper part (urow/ucol/Ub), then z_i = Dinv_i (y_i - sum).
-// OFFDIAG = false: z = Dinv y only. DUAL: also store z (precision T) into zout2. desc: workgroups
+// OFFDIAG = false: z = Dinv y only, y the right-hand side. DUAL: also store z (precision T) into zout2. desc: workgroups
 // take the rows in descending order.
 template <typename T, typename YI, typename ZO, bool OFFDIAG, bool DUAL>
 __global__ __launch_bounds__(WG) void k_bwd(int n, const int32_t *__restrict__ urow, const int32_t *__restrict__ ucol,
                                             const T *__restrict__ Ub, const T *__restrict__ Dinv,
-                                            const YI *__restrict__ y, const T *zin, ZO *zout, T *zout2, int desc) {
+                                            const YI *__restrict__ y, const T *zin, ZO *zout, T *zout2, int desc,
+                                            const double *__restrict__ rscale) {
     const int blk = desc ? (int)(gridDim.x - 1 - blockIdx.x) : (int)blockIdx.x;
-    bwd_body<T, YI, ZO, OFFDIAG, DUAL>(blk, n, urow, ucol, Ub, Dinv, y, zin, zout, zout2);
+    bwd_body<T, YI, ZO, OFFDIAG, DUAL>(blk, n, urow, ucol, Ub, Dinv, y, zin, zout, zout2,
+                                       OFFDIAG ? 1.0 : rhs_scale(rscale));
 }
 
 // Single-worker sweeps (ABILU_ASYNC_SERIAL): one quad, in place; forward rows ascending,
@@ -54,9 +62,11 @@ __global__ __launch_bounds__(WG) void k_bwd(int n, const int32_t *__restrict__ u
 template <typename T>
 __global__ __launch_bounds__(64) void k_fwd_serial(int n, const int32_t *__restrict__ lrow,
                                                    const int32_t *__restrict__ lcol, const T *__restrict__ Lb,
-                                                   const double *__restrict__ rhs, T *y) {
+                                                   const double *__restrict__ rhs, T *y,
+                                                   const double *__restrict__ rscale) {
+    const double rs = rhs_scale(rscale);
     for (int i = 0; i < n; ++i) {
-        fwd_rows<T, T, false>(i, n, n, lrow, lcol, Lb, rhs, y, y, (const T *)nullptr, (T *)nullptr);
+        fwd_rows<T, T, false>(i, n, n, lrow, lcol, Lb, rhs, y, y, (const T *)nullptr, (T *)nullptr, rs, 1.0);
         __threadfence();
     }
 }
@@ -80,6 +90,12 @@ __global__ __launch_bounds__(WG) void k_zero2(int64_t len, T *a, T *b) {
     }
 }
 
+__global__ __launch_bounds__(WG) void k_scaled_copy(int64_t len, const double *__restrict__ r,
+                                                    const double *__restrict__ rscale, double *__restrict__ z) {
+    const int64_t t = (int64_t)blockIdx.x * WG + threadIdx.x;
+    if (t < len) z[t] = scaled(r[t], rhs_scale(rscale));
+}
+
 // Chunked sweeps: workgroup c runs chunk c = rows [c0, c0 + R) level by level, one quad per row,
 // with a barrier after each level. Forward: y_i = r_i - sum_{j<i} L_ij y_j, where y_j comes from
 // this sweep (yn) for rows of the chunk and from the previous sweep (yo) for earlier rows; in the
@@ -87,10 +103,10 @@ __global__ __launch_bounds__(WG) void k_zero2(int64_t len, T *a, T *b) {
 template <typename T, bool ZERO_OUT>
 __device__ __forceinline__ void fwd_chunk_row(int i, int c0, const int32_t *__restrict__ lrow,
                                               const int32_t *__restrict__ lcol, const T *__restrict__ Lb,
-                                              const double *__restrict__ rhs, const T *yo, T *yn) {
+                                              const double *__restrict__ rhs, double rs, const T *yo, T *yn) {
     const int r = threadIdx.x & 3;
     const int b0 = lrow[i], b1 = lrow[i + 1];
-    T acc = (T)rhs[(int64_t)i * 4 + r];
+    T acc = (T)scaled(rhs[(int64_t)i * 4 + r], rs);
     for (int e0 = b0; e0 < b1; e0 += 2) {
         int j[2];
         T l[2][4], yv[2];
@@ -162,14 +178,15 @@ __global__ __launch_bounds__(WG) void k_fwd_chunk(int n, int R, const int32_t *_
                                                   const int32_t *__restrict__ lvstart,
                                                   const int32_t *__restrict__ lrow, const int32_t *__restrict__ lcol,
                                                   const T *__restrict__ Lb, const double *__restrict__ rhs,
-                                                  const T *yo, T *yn) {
+                                                  const double *__restrict__ rscale, const T *yo, T *yn) {
+    const double rs = rhs_scale(rscale);
     const int c = blockIdx.x, c0 = c * R;
     const int b = lvptr[c], nl = lvptr[c + 1] - b - 1;
     const int quad = threadIdx.x >> 2;
     for (int l = 0; l < nl; ++l) {
         const int p1 = lvstart[b + l + 1];
         for (int q = lvstart[b + l] + quad; q < p1; q += ROWS_PER_WG)
-            fwd_chunk_row<T, ZERO_OUT>(order[q], c0, lrow, lcol, Lb, rhs, yo, yn);
+            fwd_chunk_row<T, ZERO_OUT>(order[q], c0, lrow, lcol, Lb, rhs, rs, yo, yn);
         __syncthreads();
     }
 }
@@ -201,7 +218,9 @@ template <typename T, bool ZERO_OUT>
 __global__ __launch_bounds__(WG) void k_fwd_chunk_rows(int n, int R, int nch, const int32_t *__restrict__ rec,
                                                        const int32_t *__restrict__ lrow,
                                                        const int32_t *__restrict__ lcol, const T *__restrict__ Lb,
-                                                       const double *__restrict__ rhs, const T *yo, T *yn) {
+                                                       const double *__restrict__ rhs,
+                                                       const double *__restrict__ rscale, const T *yo, T *yn) {
+    const double rs = rhs_scale(rscale);
     const int c = blockIdx.x * ROWS_PER_WG + (threadIdx.x >> 2);
     if (c >= nch) return;
     const int r = threadIdx.x & 3;
@@ -218,11 +237,11 @@ __global__ __launch_bounds__(WG) void k_fwd_chunk_rows(int n, int R, int nch, co
                 h = rec_quad(rec, R, c, nch, t + 1, 0);
                 cols = rec_quad(rec, R, c, nch, t + 1, 1);
             }
-            fwd_chunk_row<T, ZERO_OUT>(i, c0, lrow, lcol, Lb, rhs, yo, yn);
+            fwd_chunk_row<T, ZERO_OUT>(i, c0, lrow, lcol, Lb, rhs, rs, yo, yn);
             have_prev = false;
             continue;
         }
-        T acc = (T)rhs[(int64_t)i * 4 + r];
+        T acc = (T)scaled(rhs[(int64_t)i * 4 + r], rs);
         T l[REC_CAP][4], yv[REC_CAP];
 #pragma unroll
         for (int u = 0; u < REC_CAP; ++u)
@@ -359,7 +378,8 @@ __device__ __forceinline__ void load_chunk_records(const int32_t *__restrict__ r
 template <typename T, bool ZERO_OUT>
 __global__ __launch_bounds__(WG) void k_fwd_chunk_short(int n, int R, int nch, const int32_t *__restrict__ rec,
                                                         const T *__restrict__ Lb, const double *__restrict__ rhs,
-                                                        const T *yo, T *yn) {
+                                                        const double *__restrict__ rscale, const T *yo, T *yn) {
+    const double rs = rhs_scale(rscale);
     const int c = blockIdx.x * ROWS_PER_WG + (threadIdx.x >> 2);
     if (c >= nch) return;
     const int r = threadIdx.x & 3;
@@ -399,7 +419,7 @@ __global__ __launch_bounds__(WG) void k_fwd_chunk_short(int n, int R, int nch, c
         if (S < m) {
             const Ops &o = ring[S % (LOOKAHEAD + 1)];
             const int nl = o.meta & 15;
-            T acc = (T)o.b;
+            T acc = (T)scaled(o.b, rs);
 #pragma unroll
             for (int u = 0; u < REC_CAP; ++u) {
                 if (u < nl) {
@@ -505,7 +525,7 @@ template <>
 const char *tname<double>() { return "f64"; }
 
 template <typename T>
-abilu_status apply_t(const abilu_pattern *p, const T *LU, const T *Dinv, const double *r, double *z, int nsw,
+abilu_status apply_t(const abilu_pattern *p, const T *LU, const T *Dinv, const double *r, const double *rs, double *z, int nsw,
                      abilu_mode mode, char *work, const Workspace &W, hipStream_t s) {
     const int n = p->n;
     const int grid = div_up(n, rows_per_wg2<T>());
@@ -540,7 +560,7 @@ abilu_status apply_t(const abilu_pattern *p, const T *LU, const T *Dinv, const d
         LAUNCHED();
         for (int q = 1; q <= nsw; ++q) {
             ProfScope ps(NAME("apply_fwd"), s, bytes_fwd(zz, sF, sF, false));
-            k_fwd_serial<T><<<1, 4, 0, s>>>(n, lrow, lcol, Lb, r, ya);
+            k_fwd_serial<T><<<1, 4, 0, s>>>(n, lrow, lcol, Lb, r, ya, rs);
             LAUNCHED();
         }
         for (int q = 1; q <= nsw; ++q) {
@@ -571,14 +591,14 @@ abilu_status apply_t(const abilu_pattern *p, const T *LU, const T *Dinv, const d
         const bool short_bwd = by_rows && R <= SHORT_CHUNK && p->rec_max[1] <= REC_CAP;
         auto fwd = [&](const T *yo, T *yn) {
             if (short_fwd) {
-                if (!yo) k_fwd_chunk_short<T, true><<<g, WG, 0, s>>>(n, R, nch, p->rec, Lb, r, yo, yn);
-                else k_fwd_chunk_short<T, false><<<g, WG, 0, s>>>(n, R, nch, p->rec, Lb, r, yo, yn);
+                if (!yo) k_fwd_chunk_short<T, true><<<g, WG, 0, s>>>(n, R, nch, p->rec, Lb, r, rs, yo, yn);
+                else k_fwd_chunk_short<T, false><<<g, WG, 0, s>>>(n, R, nch, p->rec, Lb, r, rs, yo, yn);
             } else if (by_rows) {
-                if (!yo) k_fwd_chunk_rows<T, true><<<g, WG, 0, s>>>(n, R, nch, p->rec, lrow, lcol, Lb, r, yo, yn);
-                else k_fwd_chunk_rows<T, false><<<g, WG, 0, s>>>(n, R, nch, p->rec, lrow, lcol, Lb, r, yo, yn);
+                if (!yo) k_fwd_chunk_rows<T, true><<<g, WG, 0, s>>>(n, R, nch, p->rec, lrow, lcol, Lb, r, rs, yo, yn);
+                else k_fwd_chunk_rows<T, false><<<g, WG, 0, s>>>(n, R, nch, p->rec, lrow, lcol, Lb, r, rs, yo, yn);
             } else {
-                if (!yo) k_fwd_chunk<T, true><<<g, WG, 0, s>>>(n, R, O[0], LP[0], LS[0], lrow, lcol, Lb, r, yo, yn);
-                else k_fwd_chunk<T, false><<<g, WG, 0, s>>>(n, R, O[0], LP[0], LS[0], lrow, lcol, Lb, r, yo, yn);
+                if (!yo) k_fwd_chunk<T, true><<<g, WG, 0, s>>>(n, R, O[0], LP[0], LS[0], lrow, lcol, Lb, r, rs, yo, yn);
+                else k_fwd_chunk<T, false><<<g, WG, 0, s>>>(n, R, O[0], LP[0], LS[0], lrow, lcol, Lb, r, rs, yo, yn);
             }
         };
         auto bwd = [&](const T *y, const T *zo, auto *zn) {
@@ -625,7 +645,7 @@ abilu_status apply_t(const abilu_pattern *p, const T *LU, const T *Dinv, const d
     if (nsw == 1) {
         ProfScope ps(NAME("apply_diag"), s, 32 * zz.N + 16 * sF * zz.N + 32 * zz.N);
         k_bwd<T, double, double, false, false><<<grid, WG, 0, s>>>(n, urow, ucol, Ub, Dinv, r, (const T *)nullptr, z,
-                                                                   (T *)nullptr, 0);
+                                                                   (T *)nullptr, 0, rs);
         LAUNCHED();
         return ABILU_OK;
     }
@@ -637,14 +657,14 @@ abilu_status apply_t(const abilu_pattern *p, const T *LU, const T *Dinv, const d
         ProfScope ps(NAME(last ? "apply_fwd_emitz" : "apply_fwd"), s, bytes_fwd(zz, sF, q == 2 ? 8 : sF, last));
         if (q == 2) {
             if (last)
-                k_fwd<T, double, true><<<grid, WG, 0, s>>>(n, lrow, lcol, Lb, r, r, ycur, Dinv, za);
+                k_fwd<T, double, true><<<grid, WG, 0, s>>>(n, lrow, lcol, Lb, r, r, ycur, Dinv, za, rs, 1);
             else
-                k_fwd<T, double, false><<<grid, WG, 0, s>>>(n, lrow, lcol, Lb, r, r, ycur, Dinv, (T *)nullptr);
+                k_fwd<T, double, false><<<grid, WG, 0, s>>>(n, lrow, lcol, Lb, r, r, ycur, Dinv, (T *)nullptr, rs, 1);
         } else {
             if (last)
-                k_fwd<T, T, true><<<grid, WG, 0, s>>>(n, lrow, lcol, Lb, r, yprev, ycur, Dinv, za);
+                k_fwd<T, T, true><<<grid, WG, 0, s>>>(n, lrow, lcol, Lb, r, yprev, ycur, Dinv, za, rs, 0);
             else
-                k_fwd<T, T, false><<<grid, WG, 0, s>>>(n, lrow, lcol, Lb, r, yprev, ycur, Dinv, (T *)nullptr);
+                k_fwd<T, T, false><<<grid, WG, 0, s>>>(n, lrow, lcol, Lb, r, yprev, ycur, Dinv, (T *)nullptr, rs, 0);
         }
         LAUNCHED();
         yprev = ycur;
@@ -667,12 +687,12 @@ abilu_status apply_t(const abilu_pattern *p, const T *LU, const T *Dinv, const d
         if (last) {
             if (!dual)
                 k_bwd<T, T, double, true, false><<<grid, WG, 0, s>>>(n, urow, ucol, Ub, Dinv, yfin, zprev, z, (T *)nullptr,
-                                                                     desc);
+                                                                     desc, (const double *)nullptr);
             else
-                k_bwd<T, T, double, true, true><<<grid, WG, 0, s>>>(n, urow, ucol, Ub, Dinv, yfin, zprev, z, zprev, desc);
+                k_bwd<T, T, double, true, true><<<grid, WG, 0, s>>>(n, urow, ucol, Ub, Dinv, yfin, zprev, z, zprev, desc, (const double *)nullptr);
         } else {
             T *zcur = sync ? ((zprev == za) ? zb : za) : za;
-            k_bwd<T, T, T, true, false><<<grid, WG, 0, s>>>(n, urow, ucol, Ub, Dinv, yfin, zprev, zcur, (T *)nullptr, desc);
+            k_bwd<T, T, T, true, false><<<grid, WG, 0, s>>>(n, urow, ucol, Ub, Dinv, yfin, zprev, zcur, (T *)nullptr, desc, (const double *)nullptr);
             zprev = zcur;
         }
         LAUNCHED();
@@ -686,8 +706,14 @@ abilu_status apply_t(const abilu_pattern *p, const T *LU, const T *Dinv, const d
 namespace abilu {
 
 abilu_status apply_impl(const abilu_pattern *p, const void *LU, const void *Dinv, abilu_prec prec, const double *r,
-                        double *z, int nsweeps, abilu_mode mode, char *work, const Workspace &W, hipStream_t s) {
+                        const double *rscale, double *z, int nsweeps, abilu_mode mode, char *work, const Workspace &W,
+                        hipStream_t s) {
     if (p->n == 0) return ABILU_OK;
+    if (nsweeps == 0 && rscale) {
+        const int64_t len = 4 * (int64_t)p->n;
+        k_scaled_copy<<<div_up(len, WG), WG, 0, s>>>(len, r, rscale, z);
+        return launch_status();
+    }
     if (nsweeps == 0) {
         return hip_ok(hipMemcpyAsync(z, r, sizeof(double) * 4 * (size_t)p->n, hipMemcpyDeviceToDevice, s),
                       "apply identity copy")
@@ -695,8 +721,8 @@ abilu_status apply_impl(const abilu_pattern *p, const void *LU, const void *Dinv
                    : ABILU_EDEVICE;
     }
     if (prec == ABILU_F32)
-        return apply_t<float>(p, (const float *)LU, (const float *)Dinv, r, z, nsweeps, mode, work, W, s);
-    return apply_t<double>(p, (const double *)LU, (const double *)Dinv, r, z, nsweeps, mode, work, W, s);
+        return apply_t<float>(p, (const float *)LU, (const float *)Dinv, r, rscale, z, nsweeps, mode, work, W, s);
+    return apply_t<double>(p, (const double *)LU, (const double *)Dinv, r, rscale, z, nsweeps, mode, work, W, s);
 }
 
 bool apply_ends_descending(int nsweeps, abilu_mode mode) {
@@ -733,7 +759,7 @@ extern "C" abilu_status abilu_apply(const abilu_pattern *p, const void *d_LU, co
     if (p->n == 0) return ABILU_OK;
     if (!d_r || !d_z || d_r == d_z) return ABILU_EINVAL;
     if (nsweeps > 0 && (!d_LU || !d_Dinv)) return ABILU_EINVAL;
-    return apply_impl(p, d_LU, d_Dinv, prec, d_r, d_z, nsweeps, mode, (char *)d_work, W, (hipStream_t)stream);
+    return apply_impl(p, d_LU, d_Dinv, prec, d_r, nullptr, d_z, nsweeps, mode, (char *)d_work, W, (hipStream_t)stream);
 }
 
 // ------------------------------------------------------------------ allocation-free application
@@ -798,7 +824,7 @@ extern "C" abilu_status abilu_apply_noalloc(const abilu_pattern *p, const void *
     char *work = nullptr;
     const abilu_status st = scratch_ptr(dev, &work);
     if (st != ABILU_OK) return st;
-    return apply_impl(p, d_LU, d_Dinv, prec, d_r, d_z, nsweeps, mode, work, W, (hipStream_t)stream);
+    return apply_impl(p, d_LU, d_Dinv, prec, d_r, nullptr, d_z, nsweeps, mode, work, W, (hipStream_t)stream);
 }
 
 extern "C" abilu_status abilu_spmv(const abilu_pattern *p, const double *d_A, const double *d_x, double *d_y,

@@ -31,7 +31,7 @@ constexpr int SPMV_ROWS = WG / 8;            // SpMV: eight lanes per block row
 // status slots (double[8] in the workspace header, copied to the host)
 enum { ST_EST = 0, ST_HN = 1, ST_BETA = 2, ST_NUM = 3, ST_GUARD = 4 };
 // misc slots (double[16])
-enum { MI_NRM0 = 0, MI_NRM1 = 1, MI_HN = 2, MI_BETA = 3, MI_DONE = 14, MI_GUARD = 15 };
+enum { MI_NRM0 = 0, MI_NRM1 = 1, MI_DONE = 14, MI_GUARD = 15 };
 
 template <typename T, typename S>
 __device__ __forceinline__ void load_block_row(const S *base, int64_t pos, int r, T (&v)[4]) {
@@ -107,12 +107,14 @@ __device__ __forceinline__ bool last_workgroup(int *done, int total, int id) {
     return last != 0;
 }
 
-// Forward sweep on rows ib, ib + stride, ... (rpq<T>() rows per quad; rows >= n are skipped).
+// Forward sweep on rows ib, ib + stride, ... (rpq<T>() rows per quad; rows >= n are skipped). The
+// right-hand side is rs rhs, and the input vector ys yin where it is double (ys = rs when the input
+// is the right-hand side itself, else 1): FGMRES hands over its basis vectors unnormalised.
 template <typename T, typename YI, bool EMIT_Z>
 __device__ __forceinline__ void fwd_rows(int ib, int stride, int n, const int32_t *__restrict__ lrow,
                                          const int32_t *__restrict__ lcol, const T *__restrict__ Lb,
                                          const double *__restrict__ rhs, const YI *yin, T *yout,
-                                         const T *__restrict__ Dinv, T *__restrict__ zout) {
+                                         const T *__restrict__ Dinv, T *__restrict__ zout, double rs, double ys) {
     constexpr int RPQ = rpq<T>();
     const int r = threadIdx.x & 3;
     if (ib >= n) return;
@@ -124,7 +126,7 @@ __device__ __forceinline__ void fwd_rows(int ib, int stride, int n, const int32_
         const int i = min(ii[h], n - 1);
         b0[h] = lrow[i];
         b1[h] = (ii[h] < n) ? lrow[i + 1] : b0[h];
-        acc[h] = (T)rhs[(int64_t)i * 4 + r];
+        acc[h] = (T)scaled(rhs[(int64_t)i * 4 + r], rs);
     }
     int cnt = 0;
 #pragma unroll
@@ -143,7 +145,10 @@ __device__ __forceinline__ void fwd_rows(int ib, int stride, int n, const int32_
 #pragma unroll
         for (int h = 0; h < RPQ; ++h)
 #pragma unroll
-            for (int u = 0; u < 2; ++u) yv[h][u] = (T)yin[(int64_t)j[h][u] * 4 + r];
+            for (int u = 0; u < 2; ++u) {
+                if constexpr (sizeof(YI) == 8) yv[h][u] = (T)scaled(yin[(int64_t)j[h][u] * 4 + r], ys);
+                else yv[h][u] = (T)yin[(int64_t)j[h][u] * 4 + r];
+            }
 #pragma unroll
         for (int h = 0; h < RPQ; ++h)
 #pragma unroll
@@ -171,17 +176,19 @@ __device__ __forceinline__ void fwd_rows(int ib, int stride, int n, const int32_
 template <typename T, typename YI, bool EMIT_Z>
 __device__ __forceinline__ void fwd_body(int blk, int n, const int32_t *__restrict__ lrow, const int32_t *__restrict__ lcol,
                                             const T *__restrict__ Lb, const double *__restrict__ rhs, const YI *yin,
-                                            T *yout, const T *__restrict__ Dinv, T *__restrict__ zout) {
+                                            T *yout, const T *__restrict__ Dinv, T *__restrict__ zout, double rs,
+                                            double ys) {
     fwd_rows<T, YI, EMIT_Z>(blk * rows_per_wg2<T>() + (threadIdx.x >> 2), ROWS_PER_WG, n, lrow, lcol, Lb, rhs, yin, yout,
-                            Dinv, zout);
+                            Dinv, zout, rs, ys);
 }
 
-// Backward sweep on rows ib, ib + stride, ... (rpq<T>() rows per quad).
+// Backward sweep on rows ib, ib + stride, ... (rpq<T>() rows per quad). Without OFFDIAG, y is the
+// right-hand side, taken times rs.
 template <typename T, typename YI, typename ZO, bool OFFDIAG, bool DUAL>
 __device__ __forceinline__ void bwd_rows(int ib, int stride, int n, const int32_t *__restrict__ urow,
                                          const int32_t *__restrict__ ucol, const T *__restrict__ Ub,
                                          const T *__restrict__ Dinv, const YI *__restrict__ y, const T *zin, ZO *zout,
-                                         T *zout2) {
+                                         T *zout2, double rs = 1.0) {
     constexpr int RPQ = rpq<T>();
     const int r = threadIdx.x & 3;
     if (ib >= n) return;
@@ -191,7 +198,8 @@ __device__ __forceinline__ void bwd_rows(int ib, int stride, int n, const int32_
     for (int h = 0; h < RPQ; ++h) {
         ii[h] = ib + h * stride;
         const int i = min(ii[h], n - 1);
-        acc[h] = (T)y[(int64_t)i * 4 + r];
+        if constexpr (OFFDIAG) acc[h] = (T)y[(int64_t)i * 4 + r];
+        else acc[h] = (T)scaled(y[(int64_t)i * 4 + r], rs);
         if constexpr (OFFDIAG) {
             b0[h] = urow[i];
             b1[h] = (ii[h] < n) ? urow[i + 1] : b0[h];
@@ -243,9 +251,10 @@ __device__ __forceinline__ void bwd_rows(int ib, int stride, int n, const int32_
 template <typename T, typename YI, typename ZO, bool OFFDIAG, bool DUAL>
 __device__ __forceinline__ void bwd_body(int blk, int n, const int32_t *__restrict__ urow, const int32_t *__restrict__ ucol,
                                             const T *__restrict__ Ub, const T *__restrict__ Dinv,
-                                            const YI *__restrict__ y, const T *zin, ZO *zout, T *zout2) {
+                                            const YI *__restrict__ y, const T *zin, ZO *zout, T *zout2,
+                                            double rs = 1.0) {
     bwd_rows<T, YI, ZO, OFFDIAG, DUAL>(blk * rows_per_wg2<T>() + (threadIdx.x >> 2), ROWS_PER_WG, n, urow, ucol, Ub, Dinv, y,
-                                       zin, zout, zout2);
+                                       zin, zout, zout2, rs);
 }
 
 template <bool RESID>
@@ -290,9 +299,15 @@ __device__ __forceinline__ void spmv_body(int blk, int n, const int32_t *__restr
 // tiles leaves each compute unit one workgroup or two, which would otherwise wait for each vector
 // in turn.
 // VEC_E elements per lane (vec_e); sh: MAX_RESTART + 2 columns of LDS.
+// Basis vector k lies at Basis{V0, V, ldv}(k): the first one may lie elsewhere (the right-hand side).
+struct Basis {
+    const double *V0, *V;
+    int64_t ldv;
+    __device__ __forceinline__ const double *operator()(int k) const { return k == 0 ? V0 : V + (int64_t)k * ldv; }
+};
 typedef double WaveSums[WG / 64];
 template <int VEC_E>
-__device__ __forceinline__ void mdot_body(int blk, int64_t len, const double *__restrict__ V, int64_t ldv, int q,
+__device__ __forceinline__ void mdot_body(int blk, int64_t len, const Basis &V, int q,
                                           const double *__restrict__ w, double *__restrict__ partial, int nb,
                                           WaveSums *sh) {
     const int64_t base = (int64_t)blk * (WG * VEC_E) + threadIdx.x;
@@ -312,7 +327,7 @@ __device__ __forceinline__ void mdot_body(int blk, int64_t len, const double *__
 #pragma unroll
             for (int e = 0; e < VEC_E; ++e) {
                 const int64_t t = base + (int64_t)e * WG;
-                v[c][e] = (full || t < len) ? V[(int64_t)(k + c) * ldv + t] : 0.0;
+                v[c][e] = (full || t < len) ? V(k + c)[t] : 0.0;
             }
 #pragma unroll
         for (int c = 0; c < C; ++c) {
@@ -339,11 +354,12 @@ __device__ __forceinline__ void mdot_body(int blk, int64_t len, const double *__
         store_agent(partial + (int64_t)c * nb + blk, ((sh[c][0] + sh[c][1]) + (sh[c][2] + sh[c][3])));
 }
 
-// w += alpha sum_k c[k] V_k over the tile; if partial: partial[blk] = sum of the new w^2
+// w += alpha sum_k c[k] V_k over the tile (fresh: w was 0 and is not read); if partial:
+// partial[blk] = sum of the new w^2
 template <int VEC_E>
-__device__ __forceinline__ void update_body(int blk, int64_t len, const double *__restrict__ V, int64_t ldv, int q,
+__device__ __forceinline__ void update_body(int blk, int64_t len, const Basis &V, int q,
                                                const double *__restrict__ c, double alpha, double *__restrict__ w,
-                                               double *__restrict__ partial, const int *guard) {
+                                               double *__restrict__ partial, const int *guard, bool fresh = false) {
     if (skipped(guard)) return;
     __shared__ double sh[WG / 64];
     const int64_t base = (int64_t)blk * (WG * VEC_E) + threadIdx.x;
@@ -352,7 +368,7 @@ __device__ __forceinline__ void update_body(int blk, int64_t len, const double *
 #pragma unroll
     for (int e = 0; e < VEC_E; ++e) {
         const int64_t t = base + (int64_t)e * WG;
-        acc[e] = (full || t < len) ? w[t] : 0.0;
+        acc[e] = (!fresh && (full || t < len)) ? w[t] : 0.0;
     }
     auto add = [&](int k, auto count) {
         constexpr int C = decltype(count)::value;
@@ -362,7 +378,7 @@ __device__ __forceinline__ void update_body(int blk, int64_t len, const double *
 #pragma unroll
             for (int e = 0; e < VEC_E; ++e) {
                 const int64_t t = base + (int64_t)e * WG;
-                v[u][e] = (full || t < len) ? V[(int64_t)(k + u) * ldv + t] : 0.0;
+                v[u][e] = (full || t < len) ? V(k + u)[t] : 0.0;
             }
 #pragma unroll
         for (int u = 0; u < C; ++u) {
@@ -397,7 +413,7 @@ __device__ __forceinline__ void update_body(int blk, int64_t len, const double *
 // second read mostly hits a cache). The sums run in the same order for every QM, so the choice
 // does not change a bit. On 4 million cells, FGMRES(50), 8 vectors: update + dots apart 141 + 100 us.
 template <int QM, int VEC_E>
-__device__ __forceinline__ void update_dot_body(int blk, int64_t len, const double *__restrict__ V, int64_t ldv, int q,
+__device__ __forceinline__ void update_dot_body(int blk, int64_t len, const Basis &V, int q,
                                                 const double *__restrict__ c, double *__restrict__ w,
                                                 double *__restrict__ partial, int nb, WaveSums *sh) {
     const int64_t base = (int64_t)blk * (WG * VEC_E) + threadIdx.x;
@@ -423,7 +439,7 @@ __device__ __forceinline__ void update_dot_body(int blk, int64_t len, const doub
 #pragma unroll
                     for (int e = 0; e < EB; ++e) {
                         const int64_t t = base + (int64_t)(e0 + e) * WG;
-                        v[k][e] = (full || t < len) ? V[(int64_t)k * ldv + t] : 0.0;
+                        v[k][e] = (full || t < len) ? V(k)[t] : 0.0;
                     }
                 }
 #pragma unroll
@@ -464,7 +480,7 @@ __device__ __forceinline__ void update_dot_body(int blk, int64_t len, const doub
 #pragma unroll
             for (int e = 0; e < VEC_E; ++e) {
                 const int64_t t = base + (int64_t)e * WG;
-                acc[e] += ck * ((full || t < len) ? V[(int64_t)k * ldv + t] : 0.0);
+                acc[e] += ck * ((full || t < len) ? V(k)[t] : 0.0);
             }
         }
 #pragma unroll
@@ -478,7 +494,7 @@ __device__ __forceinline__ void update_dot_body(int blk, int64_t len, const doub
 #pragma unroll
             for (int e = 0; e < VEC_E; ++e) {
                 const int64_t t = base + (int64_t)e * WG;
-                s += ((full || t < len) ? V[(int64_t)k * ldv + t] : 0.0) * acc[e];
+                s += ((full || t < len) ? V(k)[t] : 0.0) * acc[e];
             }
             s = wave_sum(s);
             if (lane == 0) sh[k][wave] = s;
@@ -557,11 +573,11 @@ __device__ __forceinline__ void reduce_cols_fold(const double *partial, int nb, 
     __syncthreads();
 }
 
-__device__ __forceinline__ void scale_body(int blk, int64_t len, const double *w, double *v, const double *h) {
-    const double hv = *h;
-    const int64_t tile = vec_tile(len), t0 = blk * tile, t1 = min(len, t0 + tile);
-    for (int64_t t = t0 + threadIdx.x; t < t1; t += WG) v[t] = (hv != 0.0) ? w[t] / hv : w[t];
-}
+// Normalisation. The basis vectors stay as the Gram-Schmidt passes leave them, u_k; v_k = s_k u_k
+// with s_k = 1 / ||u_k|| in vscale[k] (norms are at least 1e-162, a square root of a sum of squares,
+// so s_k is finite; a zero norm leaves s_k = 1). The dots come as u_k . w and the coefficients are
+// taken on u_k, each times s_k, and the preconditioner multiplies its input by s_k where it reads
+// it. A pass that read u_k and wrote v_k took 40 us of 1,690 per iteration at 4 million cells.
 
 // ---- steps on the small dense Hessenberg problem (column-major, ld = m + 1), run by one workgroup
 // on the column sums `red` of the reduction before them (LDS or registers of the caller's choice:
@@ -571,7 +587,7 @@ __device__ __forceinline__ void scale_body(int blk, int64_t len, const double *w
 enum { RS_BETA_START_ZERO = 0, RS_BETA_START_X, RS_BETA, RS_GS1, RS_GS2, RS_GIVENS, RS_NONE };
 
 struct KPtrs {
-    double *partials, *red, *H, *cs, *sn, *g, *coef, *misc, *status;
+    double *partials, *red, *H, *cs, *sn, *g, *coef, *misc, *status, *vscale;
     int *guard, *done;
     bool grouped;   // done has the counts of the groups too
 };
@@ -581,23 +597,24 @@ __device__ __forceinline__ void beta_step(const KPtrs &P, int m, double r0, bool
     if (threadIdx.x == 0) {
         if (num) P.status[ST_NUM] = beta;
         if (beta_slot) P.status[ST_BETA] = beta;
-        P.misc[MI_BETA] = beta;
+        P.vscale[0] = beta != 0.0 ? 1.0 / beta : 1.0;
     }
     if (init_g)
         for (int q = threadIdx.x; q <= m + 1; q += blockDim.x) P.g[q] = q == 0 ? beta : 0.0;
 }
 
-// H(0:k,k) = dots, coef = dots, nrm0 = ||w|| before the first pass
+// H(0:k,k) = v_k . w, coef those on u_k, nrm0 = ||w|| before the first pass
 __device__ __forceinline__ void gs1_step(const KPtrs &P, int k, int m, const double *red) {
     for (int q = threadIdx.x; q <= k; q += blockDim.x) {
-        P.H[(int64_t)k * (m + 1) + q] = red[q];
-        P.coef[q] = red[q];
+        const double sq = P.vscale[q], h = sq * red[q];
+        P.H[(int64_t)k * (m + 1) + q] = h;
+        P.coef[q] = sq * h;
     }
     if (threadIdx.x == 0) P.misc[MI_NRM0] = sqrt(red[k + 1]);
 }
 
 // after the first update (red: the second pass's dots and ||w'||^2): a second pass if
-// ||w'|| < ||w|| / sqrt(2); then H(0:k,k) += dots, coef = dots
+// ||w'|| < ||w|| / sqrt(2); then H(0:k,k) += dots, coef likewise
 __device__ __forceinline__ void gs2_step(const KPtrs &P, int k, int m, const double *red) {
     const double n1 = sqrt(red[k + 1]);
     const int again = n1 < 0.70710678118654752440 * P.misc[MI_NRM0] ? 1 : 0;
@@ -607,8 +624,9 @@ __device__ __forceinline__ void gs2_step(const KPtrs &P, int k, int m, const dou
     }
     if (!again) return;
     for (int q = threadIdx.x; q <= k; q += blockDim.x) {
-        P.H[(int64_t)k * (m + 1) + q] += red[q];
-        P.coef[q] = red[q];
+        const double sq = P.vscale[q], h = sq * red[q];
+        P.H[(int64_t)k * (m + 1) + q] += h;
+        P.coef[q] = sq * h;
     }
 }
 
@@ -641,7 +659,7 @@ __device__ __forceinline__ void givens_step(const KPtrs &P, int k, int m, const 
         P.sn[k] = sn;
         P.g[k + 1] = -sn * gk;
         P.g[k] = c * gk;
-        P.misc[MI_HN] = hn;
+        P.vscale[k + 1] = hn != 0.0 ? 1.0 / hn : 1.0;
         P.status[ST_EST] = fabs(-sn * gk);
         P.status[ST_HN] = hn;
         P.status[ST_GUARD] = (double)guard;

@@ -19,27 +19,27 @@ using namespace abilu_k;
 namespace {
 
 template <int VE>
-__global__ __launch_bounds__(WG) void k_mdot(int64_t len, const double *__restrict__ V, int64_t ldv, int q,
+__global__ __launch_bounds__(WG) void k_mdot(int64_t len, Basis V, int q,
                                              const double *__restrict__ w, double *__restrict__ partial, int nb) {
     __shared__ WaveSums sh[MAX_RESTART + 2];
-    mdot_body<VE>(blockIdx.x, len, V, ldv, q, w, partial, nb, sh);
+    mdot_body<VE>(blockIdx.x, len, V, q, w, partial, nb, sh);
 }
 
 // The updates take the tiles in descending order: the kernel before them runs ascending, so they
 // start on the tiles it read last (the partials stay indexed by tile, so sums are unchanged).
 template <int VE>
-__global__ __launch_bounds__(WG) void k_update(int64_t len, const double *__restrict__ V, int64_t ldv, int q,
+__global__ __launch_bounds__(WG) void k_update(int64_t len, Basis V, int q,
                                                const double *__restrict__ c, double alpha, double *__restrict__ w,
-                                               double *__restrict__ partial, const int *guard) {
-    update_body<VE>(gridDim.x - 1 - blockIdx.x, len, V, ldv, q, c, alpha, w, partial, guard);
+                                               double *__restrict__ partial, const int *guard, bool fresh) {
+    update_body<VE>(gridDim.x - 1 - blockIdx.x, len, V, q, c, alpha, w, partial, guard, fresh);
 }
 
 template <int QM, int VE>
-__global__ __launch_bounds__(WG) void k_update_dot(int64_t len, const double *__restrict__ V, int64_t ldv, int q,
+__global__ __launch_bounds__(WG) void k_update_dot(int64_t len, Basis V, int q,
                                                    const double *__restrict__ c, double *__restrict__ w,
                                                    double *__restrict__ partial, int nb) {
     __shared__ WaveSums sh[MAX_RESTART + 2];
-    update_dot_body<QM, VE>(gridDim.x - 1 - blockIdx.x, len, V, ldv, q, c, w, partial, nb, sh);
+    update_dot_body<QM, VE>(gridDim.x - 1 - blockIdx.x, len, V, q, c, w, partial, nb, sh);
 }
 
 // out[col] = sum_b partial[col*nb + b], one workgroup per column, fixed order
@@ -70,32 +70,27 @@ __device__ __forceinline__ void fold_tail(const KPtrs &P, int nb, int cols, cons
 }
 
 template <int OP>
-__global__ __launch_bounds__(WG) void k_mdot_step(int64_t len, const double *__restrict__ V, int64_t ldv, int q,
+__global__ __launch_bounds__(WG) void k_mdot_step(int64_t len, Basis V, int q,
                                                   const double *__restrict__ w, KPtrs P, int nb, int k, int m) {
     __shared__ WaveSums sh[MAX_RESTART + 2];
-    mdot_body<FOLD_VE>(blockIdx.x, len, V, ldv, q, w, P.partials, nb, sh);
+    mdot_body<FOLD_VE>(blockIdx.x, len, V, q, w, P.partials, nb, sh);
     fold_tail<OP>(P, nb, q + 1, nullptr, k, m);
 }
 
 template <int QM>
-__global__ __launch_bounds__(WG) void k_update_dot_step(int64_t len, const double *__restrict__ V, int64_t ldv, int q,
+__global__ __launch_bounds__(WG) void k_update_dot_step(int64_t len, Basis V, int q,
                                                         const double *__restrict__ c, double *__restrict__ w, KPtrs P,
                                                         int nb, int k, int m) {
     __shared__ WaveSums sh[MAX_RESTART + 2];
-    update_dot_body<QM, FOLD_VE>(gridDim.x - 1 - blockIdx.x, len, V, ldv, q, c, w, P.partials, nb, sh);
+    update_dot_body<QM, FOLD_VE>(gridDim.x - 1 - blockIdx.x, len, V, q, c, w, P.partials, nb, sh);
     fold_tail<RS_GS2>(P, nb, q + 1, nullptr, k, m);
 }
 
-__global__ __launch_bounds__(WG) void k_update_step(int64_t len, const double *__restrict__ V, int64_t ldv, int q,
+__global__ __launch_bounds__(WG) void k_update_step(int64_t len, Basis V, int q,
                                                     const double *__restrict__ c, double alpha, double *__restrict__ w,
                                                     KPtrs P, int nb, const int *guard, int k, int m) {
-    update_body<FOLD_VE>(gridDim.x - 1 - blockIdx.x, len, V, ldv, q, c, alpha, w, P.partials, guard);
+    update_body<FOLD_VE>(gridDim.x - 1 - blockIdx.x, len, V, q, c, alpha, w, P.partials, guard);
     fold_tail<RS_GIVENS>(P, nb, 1, guard, k, m);
-}
-
-// v = w / h (h read from device memory; left unchanged if h == 0)
-__global__ __launch_bounds__(WG) void k_scale(int64_t len, const double *w, double *v, const double *h) {
-    scale_body(blockIdx.x, len, w, v, h);
 }
 
 // Back substitution on the k x k upper triangle: coef = y.
@@ -174,10 +169,12 @@ struct Ctx {
     char *work;
     hipStream_t s;
     int64_t nv;
-    double *partials, *H, *cs, *sn, *g, *coef, *misc, *status, *red, *V, *Zb;
+    double *partials, *H, *cs, *sn, *g, *coef, *misc, *status, *vscale, *red, *V, *Zb;
+    const double *v0;   // the first basis vector: the right-hand side or V
     int *guard, *done;
     int m;
-    KPtrs ptrs() const { return KPtrs{partials, red, H, cs, sn, g, coef, misc, status, guard, done, true}; }
+    Basis basis() const { return Basis{v0, V, nv}; }
+    KPtrs ptrs() const { return KPtrs{partials, red, H, cs, sn, g, coef, misc, status, vscale, guard, done, true}; }
 };
 
 #define CKL()                                                     \
@@ -203,21 +200,21 @@ abilu_status reduce_step(Ctx &c, int ncols, const int *guard, int op, int k) {
 }
 
 // c.red[0..q] <- dots of w with V_0..V_{q-1}, then ||w||^2; then step op
-abilu_status mdot_reduce(Ctx &c, const double *Vb, int q, const double *w, int op, int k) {
+abilu_status mdot_reduce(Ctx &c, int q, const double *w, int op, int k) {
     const int nb = c.W.nb_vec;
     const double n8 = 8.0 * (double)c.nv;
     if (nb <= FOLD_NB && op != RS_BETA_START_ZERO && op != RS_BETA_START_X) {
         ProfScope ps("fgmres_mdot", c.s, (q + 1) * n8 + 8.0 * (q + 1) * nb);
         const KPtrs P = c.ptrs();
-        if (op == RS_BETA) k_mdot_step<RS_BETA><<<nb, WG, 0, c.s>>>(c.nv, Vb, c.nv, q, w, P, nb, k, c.m);
-        else k_mdot_step<RS_GS1><<<nb, WG, 0, c.s>>>(c.nv, Vb, c.nv, q, w, P, nb, k, c.m);
+        if (op == RS_BETA) k_mdot_step<RS_BETA><<<nb, WG, 0, c.s>>>(c.nv, c.basis(), q, w, P, nb, k, c.m);
+        else k_mdot_step<RS_GS1><<<nb, WG, 0, c.s>>>(c.nv, c.basis(), q, w, P, nb, k, c.m);
         CKL();
         return ABILU_OK;
     }
     {
         ProfScope ps("fgmres_mdot", c.s, (q + 1) * n8);
-        if (vec_e(c.nv) == 4) k_mdot<4><<<nb, WG, 0, c.s>>>(c.nv, Vb, c.nv, q, w, c.partials, nb);
-        else k_mdot<8><<<nb, WG, 0, c.s>>>(c.nv, Vb, c.nv, q, w, c.partials, nb);
+        if (vec_e(c.nv) == 4) k_mdot<4><<<nb, WG, 0, c.s>>>(c.nv, c.basis(), q, w, c.partials, nb);
+        else k_mdot<8><<<nb, WG, 0, c.s>>>(c.nv, c.basis(), q, w, c.partials, nb);
     }
     CKL();
     return reduce_step(c, q + 1, nullptr, op, k);
@@ -234,10 +231,10 @@ abilu_status update_dot_reduce(Ctx &c, int q, double *w, int k) {
         const KPtrs P = c.ptrs();
 #define ABILU_UPDATE_DOT(QM)                                                                                          \
     do {                                                                                                              \
-        if (fold) k_update_dot_step<QM><<<nb, WG, 0, c.s>>>(c.nv, c.V, c.nv, q, c.coef, w, P, nb, k, c.m);            \
+        if (fold) k_update_dot_step<QM><<<nb, WG, 0, c.s>>>(c.nv, c.basis(), q, c.coef, w, P, nb, k, c.m);            \
         else if (vec_e(c.nv) == 4)                                                                                    \
-            k_update_dot<QM, 4><<<nb, WG, 0, c.s>>>(c.nv, c.V, c.nv, q, c.coef, w, c.partials, nb);                   \
-        else k_update_dot<QM, 8><<<nb, WG, 0, c.s>>>(c.nv, c.V, c.nv, q, c.coef, w, c.partials, nb);                  \
+            k_update_dot<QM, 4><<<nb, WG, 0, c.s>>>(c.nv, c.basis(), q, c.coef, w, c.partials, nb);                   \
+        else k_update_dot<QM, 8><<<nb, WG, 0, c.s>>>(c.nv, c.basis(), q, c.coef, w, c.partials, nb);                  \
     } while (0)
         switch (update_dot_form(q)) {
             case 4: ABILU_UPDATE_DOT(4); break;
@@ -253,23 +250,23 @@ abilu_status update_dot_reduce(Ctx &c, int q, double *w, int k) {
 }
 
 // w += alpha * sum_k coef[k] Vb_k; with givens: c.red[0] <- ||w||^2 afterwards, then the Givens step
-abilu_status update_reduce(Ctx &c, const double *Vb, int q, double alpha, double *w, const int *guard, bool givens,
-                           int k) {
+abilu_status update_reduce(Ctx &c, const Basis &Vb, int q, double alpha, double *w, const int *guard, bool givens,
+                           int k, bool fresh = false) {
     const int nb = c.W.nb_vec;
     const double n8 = 8.0 * (double)c.nv;
     if (givens && nb <= FOLD_NB) {
         {
             ProfScope ps("fgmres_update", c.s, (q + 2) * n8 + 8.0 * nb);
-            k_update_step<<<nb, WG, 0, c.s>>>(c.nv, Vb, c.nv, q, c.coef, alpha, w, c.ptrs(), nb, guard, k, c.m);
+            k_update_step<<<nb, WG, 0, c.s>>>(c.nv, Vb, q, c.coef, alpha, w, c.ptrs(), nb, guard, k, c.m);
         }
         CKL();
         return ABILU_OK;
     }
     {
-        ProfScope ps("fgmres_update", c.s, (q + 2) * n8);
+        ProfScope ps("fgmres_update", c.s, (q + (fresh ? 1 : 2)) * n8);
         double *part = givens ? c.partials : nullptr;
-        if (vec_e(c.nv) == 4) k_update<4><<<nb, WG, 0, c.s>>>(c.nv, Vb, c.nv, q, c.coef, alpha, w, part, guard);
-        else k_update<8><<<nb, WG, 0, c.s>>>(c.nv, Vb, c.nv, q, c.coef, alpha, w, part, guard);
+        if (vec_e(c.nv) == 4) k_update<4><<<nb, WG, 0, c.s>>>(c.nv, Vb, q, c.coef, alpha, w, part, guard, fresh);
+        else k_update<8><<<nb, WG, 0, c.s>>>(c.nv, Vb, q, c.coef, alpha, w, part, guard, fresh);
     }
     CKL();
     return givens ? reduce_step(c, 1, guard, RS_GIVENS, k) : ABILU_OK;
@@ -285,12 +282,13 @@ abilu_status readback(Ctx &c, double *h, uint32_t *flags) {
     return ABILU_OK;
 }
 
-// r = b - A x into V_0, beta = ||r|| into g[0], misc[MI_BETA] and status[ST_BETA]. The SpMV runs
+// r = b - A x into V_0, beta = ||r|| into g[0] and status[ST_BETA], 1 / beta into vscale[0]. The SpMV runs
 // its workgroups descending (measured slightly faster than ascending after either predecessor).
 abilu_status true_residual(Ctx &c, const double *A, const double *b, const double *x) {
     abilu_status st = spmv_impl(c.p, A, x, c.V, b, true, c.s);
     if (st != ABILU_OK) return st;
-    return mdot_reduce(c, c.V, 0, c.V, RS_BETA, 0);
+    c.v0 = c.V;
+    return mdot_reduce(c, 0, c.V, RS_BETA, 0);
 }
 
 }  // namespace
@@ -327,6 +325,7 @@ extern "C" abilu_status fgmres_solve(const abilu_pattern *p, const double *d_A, 
     c.coef = (double *)(c.work + c.W.coef);
     c.misc = (double *)(c.work + c.W.misc);
     c.status = (double *)(c.work + c.W.status);
+    c.vscale = (double *)(c.work + c.W.vscale);
     c.red = (double *)(c.work + c.W.red);
     c.V = (double *)(c.work + c.W.V);
     c.Zb = (double *)(c.work + c.W.Z);
@@ -337,20 +336,12 @@ extern "C" abilu_status fgmres_solve(const abilu_pattern *p, const double *d_A, 
     uint32_t flags = 0;
     abilu_status st;
 
-    // ||b|| and the initial residual (b itself for a zero initial guess)
+    // ||b|| and the initial residual: b itself for a zero initial guess, which then also is the
+    // first basis vector, and whose x is first written by the first cycle's update
     const bool zero_guess = (options & ABILU_FGMRES_ZERO_GUESS) != 0;
-    if ((st = mdot_reduce(c, c.V, 0, d_b, zero_guess ? RS_BETA_START_ZERO : RS_BETA_START_X, 0)) != ABILU_OK) return st;
-    const double *first_v0 = c.V;   // the vector the first cycle normalises into V_0
-    if (zero_guess) {
-        {
-            ProfScope ps("fgmres_scale", c.s, 8.0 * (double)c.nv);
-            k_zero<<<c.W.nb_vec, WG, 0, c.s>>>(c.nv, d_x);
-        }
-        CKL();
-        first_v0 = d_b;
-    } else if ((st = true_residual(c, d_A, d_b, d_x)) != ABILU_OK) {
-        return st;
-    }
+    c.v0 = d_b;
+    if ((st = mdot_reduce(c, 0, d_b, zero_guess ? RS_BETA_START_ZERO : RS_BETA_START_X, 0)) != ABILU_OK) return st;
+    if (!zero_guess && (st = true_residual(c, d_A, d_b, d_x)) != ABILU_OK) return st;
     if ((st = readback(c, h, &flags)) != ABILU_OK) return st;
     const double bnorm = h[ST_NUM];
     const double bn = bnorm > 0 ? bnorm : 1.0;
@@ -361,36 +352,26 @@ extern "C" abilu_status fgmres_solve(const abilu_pattern *p, const double *d_A, 
     bool nonfinite = !std::isfinite(beta) || !std::isfinite(bnorm);
 
     while (!converged && !nonfinite && iters < maxit && beta > 0.0) {
-        {
-            ProfScope ps("fgmres_scale", c.s, 16.0 * (double)c.nv);
-            k_scale<<<c.W.nb_vec, WG, 0, c.s>>>(c.nv, first_v0, c.V, c.misc + MI_BETA);
-        }
-        CKL();
-        first_v0 = c.V;
         int k = 0;
         while (k < m && iters < maxit) {
-            const double *vk = c.V + (int64_t)k * c.nv;
+            const double *vk = k == 0 ? c.v0 : c.V + (int64_t)k * c.nv;
             double *zk = c.Zb + (int64_t)k * c.nv;
             double *w = c.V + (int64_t)(k + 1) * c.nv;
-            if ((st = apply_impl(p, d_LU, d_Dinv, prec, vk, zk, apply_sweeps, mode, c.work, c.W, c.s)) != ABILU_OK)
+            if ((st = apply_impl(p, d_LU, d_Dinv, prec, vk, c.vscale + k, zk, apply_sweeps, mode, c.work, c.W,
+                                 c.s)) != ABILU_OK)
                 return st;
             if ((st = spmv_impl(p, d_A, zk, w, nullptr, !apply_ends_descending(apply_sweeps, mode), c.s)) !=
                 ABILU_OK)
                 return st;
             // Gram-Schmidt pass 1: dots, H(0:k,k); the update, with the second pass's dots and the
             // decision on that pass
-            if ((st = mdot_reduce(c, c.V, k + 1, w, RS_GS1, k)) != ABILU_OK) return st;
+            if ((st = mdot_reduce(c, k + 1, w, RS_GS1, k)) != ABILU_OK) return st;
             if ((st = update_dot_reduce(c, k + 1, w, k)) != ABILU_OK) return st;
             // pass 2's update, executed by the device only when the guard is set; the Givens step
             // after it runs either way
             const int pass2_begin = prof_mark();
-            if ((st = update_reduce(c, c.V, k + 1, -1.0, w, c.guard, true, k)) != ABILU_OK) return st;
+            if ((st = update_reduce(c, c.basis(), k + 1, -1.0, w, c.guard, true, k)) != ABILU_OK) return st;
             const int pass2_end = prof_mark();
-            {
-                ProfScope ps("fgmres_scale", c.s, 16.0 * (double)c.nv);
-                k_scale<<<c.W.nb_vec, WG, 0, c.s>>>(c.nv, w, w, c.misc + MI_HN);
-            }
-            CKL();
             if ((st = readback(c, h, &flags)) != ABILU_OK) return st;
             if (h[ST_GUARD] != 0.0)
                 ++reorth;
@@ -412,13 +393,21 @@ extern "C" abilu_status fgmres_solve(const abilu_pattern *p, const double *d_A, 
             k_solve<<<1, 64, 0, c.s>>>(k, m, c.H, c.g, c.coef);
         }
         CKL();
-        if ((st = update_reduce(c, c.Zb, k, 1.0, d_x, nullptr, false, 0)) != ABILU_OK) return st;
+        if ((st = update_reduce(c, Basis{c.Zb, c.Zb, c.nv}, k, 1.0, d_x, nullptr, false, 0, zero_guess && restarts == 0)) !=
+            ABILU_OK)
+            return st;
         if ((st = true_residual(c, d_A, d_b, d_x)) != ABILU_OK) return st;
         if ((st = readback(c, h, &flags)) != ABILU_OK) return st;
         ++restarts;
         beta = h[ST_BETA];
         if (!std::isfinite(beta)) nonfinite = true;
         converged = beta <= tol;
+    }
+    if (zero_guess && restarts == 0) {   // no cycle wrote x
+        ProfScope ps("fgmres_zero", c.s, 8.0 * (double)c.nv);
+        k_zero<<<c.W.nb_vec, WG, 0, c.s>>>(c.nv, d_x);
+        CKL();
+        if (!hip_ok(hipStreamSynchronize(c.s), "fgmres x sync")) return ABILU_EDEVICE;
     }
     out->iters = iters;
     out->restarts = restarts;

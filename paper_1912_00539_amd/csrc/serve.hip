@@ -50,13 +50,14 @@ struct Slot {
     const double *A, *b;
     double *x;
     void *LU, *Dinv, *X1, *D1, *ya, *yb, *za, *zb;
-    double *partials, *H, *cs, *sn, *g, *coef, *misc, *red, *V, *Z;
+    double *partials, *H, *cs, *sn, *g, *coef, *misc, *vscale, *red, *V, *Z;
     double *status;
     unsigned *flags;
 };
 
+// bv0: the request's first basis vector is its right-hand side (first cycle), else V_0
 struct Member {
-    int32_t slot, tile0, k, pad;
+    int32_t slot, tile0, k, bv0;
 };
 
 // ------------------------------------------------------------------ device side
@@ -74,9 +75,12 @@ __device__ __forceinline__ int find_member(const Member *mem, int nmem, int b) {
 // vector roles, resolved per member
 enum { R_VK = 0, R_YA, R_YB, R_ZA, R_ZB, R_ZK, R_VK1, R_V0, R_B, R_X, R_VBASE, R_ZBASE };
 
-__device__ __forceinline__ void *role(const Slot &S, int k, int code) {
+__device__ __forceinline__ Basis basis_of(const Slot &S, const Member &M) { return Basis{M.bv0 ? S.b : S.V, S.V, S.nv}; }
+
+__device__ __forceinline__ void *role(const Slot &S, const Member &M, int code) {
+    const int k = M.k;
     switch (code) {
-        case R_VK: return S.V + (int64_t)k * S.nv;
+        case R_VK: return k == 0 && M.bv0 ? (void *)S.b : S.V + (int64_t)k * S.nv;
         case R_YA: return S.ya;
         case R_YB: return S.yb;
         case R_ZA: return S.za;
@@ -131,8 +135,10 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(sweep_waves<
 template <typename T, typename YI, bool EMIT_Z>
 __global__ __launch_bounds__(WG) void kb_fwd(const Slot *slots, const Member *mem, int nmem, int yin, int yout) {
     MEMBER();
-    fwd_body<T, YI, EMIT_Z>(blk, S.n, S.lrow, S.lcol, (const T *)S.LU, S.V + (int64_t)M.k * S.nv,
-                            (const YI *)role(S, M.k, yin), (T *)role(S, M.k, yout), (const T *)S.Dinv, (T *)S.za);
+    const double rs = S.vscale[M.k];
+    fwd_body<T, YI, EMIT_Z>(blk, S.n, S.lrow, S.lcol, (const T *)S.LU, (const double *)role(S, M, R_VK),
+                            (const YI *)role(S, M, yin), (T *)role(S, M, yout), (const T *)S.Dinv, (T *)S.za, rs,
+                            yin == R_VK ? rs : 1.0);
 }
 
 template <typename T, typename YI, typename ZO, bool OFFDIAG, bool DUAL>
@@ -140,44 +146,47 @@ __global__ __launch_bounds__(WG) void kb_bwd(const Slot *slots, const Member *me
                                              int desc) {
     MEMBER_DIR(desc);
     const T *Ub = (const T *)S.LU + ((int64_t)S.ZL + S.n) * BB;
-    bwd_body<T, YI, ZO, OFFDIAG, DUAL>(blk, S.n, S.urow, S.ucol, Ub, (const T *)S.Dinv, (const YI *)role(S, M.k, y),
-                                       (const T *)role(S, M.k, zin), (ZO *)role(S, M.k, zout), (T *)S.za);
+    bwd_body<T, YI, ZO, OFFDIAG, DUAL>(blk, S.n, S.urow, S.ucol, Ub, (const T *)S.Dinv, (const YI *)role(S, M, y),
+                                       (const T *)role(S, M, zin), (ZO *)role(S, M, zout), (T *)S.za,
+                                       OFFDIAG ? 1.0 : S.vscale[M.k]);
 }
 
+// no preconditioner: z_k = v_k
 __global__ __launch_bounds__(WG) void kb_copy(const Slot *slots, const Member *mem, int nmem, int src, int dst) {
     MEMBER();
-    const double *s = (const double *)role(S, M.k, src);
-    double *d = (double *)role(S, M.k, dst);
+    const double rs = S.vscale[M.k];
+    const double *s = (const double *)role(S, M, src);
+    double *d = (double *)role(S, M, dst);
     const int64_t tile = vec_tile(S.nv), t0 = blk * tile, t1 = min(S.nv, t0 + tile);
-    for (int64_t t = t0 + threadIdx.x; t < t1; t += WG) d[t] = s[t];
+    for (int64_t t = t0 + threadIdx.x; t < t1; t += WG) d[t] = scaled(s[t], rs);
 }
 
 template <bool RESID>
 __global__ __launch_bounds__(WG) void kb_spmv(const Slot *slots, const Member *mem, int nmem, int xin, int yout,
                                               int desc) {
     MEMBER_DIR(desc);
-    spmv_body<RESID>(blk, S.n, S.rowptr, S.colidx, S.A, (const double *)role(S, M.k, xin),
-                     (double *)role(S, M.k, yout), S.b);
+    spmv_body<RESID>(blk, S.n, S.rowptr, S.colidx, S.A, (const double *)role(S, M, xin),
+                     (double *)role(S, M, yout), S.b);
 }
 
 // q_plus: q = k + q_plus (Arnoldi: k + 1 basis vectors), or q = 0 when q_plus < 0
 __global__ __launch_bounds__(WG) void kb_mdot(const Slot *slots, const Member *mem, int nmem, int w, int q_plus) {
     MEMBER();
     const int q = q_plus < 0 ? 0 : M.k + q_plus;
-    const double *wv = (const double *)role(S, M.k, w);
+    const double *wv = (const double *)role(S, M, w);
     __shared__ WaveSums sh[MAX_RESTART + 2];
-    if (vec_e(S.nv) == 4) mdot_body<4>(blk, S.nv, S.V, S.nv, q, wv, S.partials, S.nb_vec, sh);
-    else mdot_body<8>(blk, S.nv, S.V, S.nv, q, wv, S.partials, S.nb_vec, sh);
+    if (vec_e(S.nv) == 4) mdot_body<4>(blk, S.nv, basis_of(S, M), q, wv, S.partials, S.nb_vec, sh);
+    else mdot_body<8>(blk, S.nv, basis_of(S, M), q, wv, S.partials, S.nb_vec, sh);
 }
 
 __global__ __launch_bounds__(WG) void kb_update(const Slot *slots, const Member *mem, int nmem, int base, int q_plus,
                                                 double alpha, int w, int with_norm, int use_guard) {
     MEMBER_DIR(true);
-    const double *bv = (const double *)role(S, M.k, base);
-    double *wv = (double *)role(S, M.k, w), *part = with_norm ? S.partials : nullptr;
+    const Basis bv = base == R_ZBASE ? Basis{S.Z, S.Z, S.nv} : basis_of(S, M);
+    double *wv = (double *)role(S, M, w), *part = with_norm ? S.partials : nullptr;
     const int *guard = use_guard ? (const int *)(S.misc + MI_GUARD) : nullptr;
-    if (vec_e(S.nv) == 4) update_body<4>(blk, S.nv, bv, S.nv, M.k + q_plus, S.coef, alpha, wv, part, guard);
-    else update_body<8>(blk, S.nv, bv, S.nv, M.k + q_plus, S.coef, alpha, wv, part, guard);
+    if (vec_e(S.nv) == 4) update_body<4>(blk, S.nv, bv, M.k + q_plus, S.coef, alpha, wv, part, guard);
+    else update_body<8>(blk, S.nv, bv, M.k + q_plus, S.coef, alpha, wv, part, guard);
 }
 
 // QM: the register form of the member with the most vectors (every form gives the same bits)
@@ -186,8 +195,8 @@ __global__ __launch_bounds__(WG) void kb_update_dot(const Slot *slots, const Mem
     MEMBER_DIR(true);
     double *w = S.V + (int64_t)(M.k + 1) * S.nv;
     __shared__ WaveSums sh[MAX_RESTART + 2];
-    if (vec_e(S.nv) == 4) update_dot_body<QM, 4>(blk, S.nv, S.V, S.nv, M.k + 1, S.coef, w, S.partials, S.nb_vec, sh);
-    else update_dot_body<QM, 8>(blk, S.nv, S.V, S.nv, M.k + 1, S.coef, w, S.partials, S.nb_vec, sh);
+    if (vec_e(S.nv) == 4) update_dot_body<QM, 4>(blk, S.nv, basis_of(S, M), M.k + 1, S.coef, w, S.partials, S.nb_vec, sh);
+    else update_dot_body<QM, 8>(blk, S.nv, basis_of(S, M), M.k + 1, S.coef, w, S.partials, S.nb_vec, sh);
 }
 
 // Column sums of each member (k + 2 columns for the Gram-Schmidt steps, else one), then step OP in
@@ -196,7 +205,7 @@ template <int OP>
 __global__ __launch_bounds__(WG) void kb_reduce_step(const Slot *slots, const Member *mem, int nmem, int m) {
     MEMBER();
     const int cols = OP == RS_GS1 || OP == RS_GS2 ? M.k + 2 : 1;
-    const KPtrs P{S.partials, S.red, S.H, S.cs, S.sn, S.g, S.coef, S.misc, S.status, (int *)(S.misc + MI_GUARD),
+    const KPtrs P{S.partials, S.red, S.H, S.cs, S.sn, S.g, S.coef, S.misc, S.status, S.vscale, (int *)(S.misc + MI_GUARD),
                   (int *)(S.misc + MI_DONE), false};
     reduce_step_body<OP>(blk, cols, P, S.nb_vec, OP == RS_GIVENS ? P.guard : nullptr, M.k, m);
 }
@@ -208,15 +217,9 @@ __global__ __launch_bounds__(64) void kb_solve(const Slot *slots, const Member *
     solve_body(M.k, m, S.H, S.g, S.coef);
 }
 
-// hv = misc[slot]: MI_BETA or MI_HN
-__global__ __launch_bounds__(WG) void kb_scale(const Slot *slots, const Member *mem, int nmem, int w, int v, int hslot) {
-    MEMBER();
-    scale_body(blk, S.nv, (const double *)role(S, M.k, w), (double *)role(S, M.k, v), S.misc + hslot);
-}
-
 __global__ __launch_bounds__(WG) void kb_zero(const Slot *slots, const Member *mem, int nmem, int v) {
     MEMBER();
-    zero_body(blk, S.nv, (double *)role(S, M.k, v));
+    zero_body(blk, S.nv, (double *)role(S, M, v));
 }
 
 // ------------------------------------------------------------------ batched admission kernels
@@ -391,7 +394,7 @@ constexpr size_t NONE = ~(size_t)0;
 struct ReqLayout {
     size_t rowptr, colidx, diag_pos, pair_ptr, lrow, urow, lcol, ucol, pik, pkj, sik, skj;
     size_t A, b, x, LU, Dinv, X1, D1, ya, yb, za, zb;
-    size_t partials, H, cs, sn, g, coef, misc, red, V, Z, scratch;
+    size_t partials, H, cs, sn, g, coef, misc, vscale, red, V, Z, scratch;
     size_t total;
     int64_t zcap, pcap;
     int nb_vec;
@@ -448,6 +451,7 @@ ReqLayout req_layout(const abilu_serve_config &c, int32_t n, int64_t Z, size_t g
     L.g = take(8 * (m + 2));
     L.coef = take(8 * (m + 2));
     L.misc = take(8 * 16);
+    L.vscale = take(8 * (m + 2));
     L.red = take(8 * (m + 4));
     L.V = take(8 * (m + 1) * nv);
     L.Z = take(8 * m * nv);
@@ -651,6 +655,7 @@ void stage_request(abilu_server *s, Req &r, int m) {
     d.g = (double *)P(L.g);
     d.coef = (double *)P(L.coef);
     d.misc = (double *)P(L.misc);
+    d.vscale = (double *)P(L.vscale);
     d.red = (double *)P(L.red);
     d.V = (double *)P(L.V);
     d.Z = (double *)P(L.Z);
@@ -866,12 +871,6 @@ abilu_status run_group(abilu_server *s, Group &G, hipStream_t st) {
         CKL();
         return ABILU_OK;
     };
-    auto scale = [&](int w, int v, int hslot) -> abilu_status {
-        ProfScope ps("serve_scale", st, B([&](const Sizes &z, const Req &) { return 2 * nv8(z); }));
-        kb_scale<<<L_(SH_VEC)>>>(A_(SH_VEC), w, v, hslot);
-        CKL();
-        return ABILU_OK;
-    };
     auto init = [&](bool copy, int sel) -> abilu_status {
         ProfScope ps("serve_factor_init", st, B([&](const Sizes &z, const Req &) { return bytes_init(z, 8, sF, copy); }));
         if (copy)
@@ -943,7 +942,7 @@ abilu_status run_group(abilu_server *s, Group &G, hipStream_t st) {
                 CKL();
             }
         }
-        // ||b||; zero initial guess: beta = ||b||, V_0 = b / beta
+        // ||b||; zero initial guess: beta = ||b||, and b is the first basis vector
         if ((e = mdot(R_B, -1)) != ABILU_OK) return e;
         if ((e = reduce(std::integral_constant<int, RS_BETA_START_ZERO>{})) != ABILU_OK) return e;
         {
@@ -951,7 +950,7 @@ abilu_status run_group(abilu_server *s, Group &G, hipStream_t st) {
             kb_zero<<<L_(SH_VEC)>>>(A_(SH_VEC), R_X);
         }
         CKL();
-        return scale(R_B, R_V0, MI_BETA);
+        return ABILU_OK;
     }
     if (G.st == Q_ITER) {
         // z_k = M^{-1} v_k
@@ -1006,7 +1005,7 @@ abilu_status run_group(abilu_server *s, Group &G, hipStream_t st) {
         G.pass2 = prof_mark();
         if ((e = update(R_VBASE, 1, -1.0, R_VK1, 1, 1)) != ABILU_OK) return e;
         if ((e = reduce(std::integral_constant<int, RS_GIVENS>{})) != ABILU_OK) return e;
-        return scale(R_VK1, R_VK1, MI_HN);
+        return ABILU_OK;
     }
     // end of a restart cycle over k Arnoldi steps: x += Z y, true residual, next V_0
     {
@@ -1018,7 +1017,7 @@ abilu_status run_group(abilu_server *s, Group &G, hipStream_t st) {
     if ((e = spmv(true, R_X, R_V0)) != ABILU_OK) return e;
     if ((e = mdot(R_V0, -1)) != ABILU_OK) return e;
     if ((e = reduce(std::integral_constant<int, RS_BETA>{})) != ABILU_OK) return e;
-    return scale(R_V0, R_V0, MI_BETA);
+    return ABILU_OK;
 #undef L_
 #undef A_
 #undef CKL
@@ -1112,7 +1111,7 @@ abilu_status step_impl(abilu_server *s, hipStream_t st) {
             int tile = 0;
             for (size_t q = 0; q < G.ids.size(); ++q) {
                 const Req &r = s->reqs[G.ids[q]];
-                s->h_tab[used + q] = Member{r.slot, tile, r.k, 0};
+                s->h_tab[used + q] = Member{r.slot, tile, r.k, r.restarts == 0 ? 1 : 0};
                 tile += tiles_of(r, sh, G.st, (abilu_prec)s->cfg.prec);
             }
             T.tiles = tile;
