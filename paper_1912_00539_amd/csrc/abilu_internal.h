@@ -29,6 +29,9 @@ struct abilu_pattern {
     int32_t *lcol = nullptr;      // device [ZL+1] columns of the lower part (one padding entry)
     int32_t *ucol = nullptr;      // device [ZU+1] columns of the upper part
     double *pinned = nullptr;     // host pinned, 64 doubles, for blocking scalar reads
+    double *pinned_dev = nullptr; // the same memory as kernels address it
+    int32_t *done = nullptr;      // device [DONE_INTS] completion counts of FGMRES's reductions, zero
+                                  // between launches (behind lrow in its allocation)
     bool symmetric = false;       // (i,j) in S_B implies (j,i) in S_B
     int device = 0;
     // chunk schedule (abilu_pattern_set_chunks): chunks of chunk_rows consecutive rows; per chunk,
@@ -91,7 +94,6 @@ struct Workspace {
     size_t hess;       // double[(restart+1) * restart], column-major, ld = restart+1
     size_t cs, sn, g, coef, misc;  // double[restart+2] each; misc double[16]
     size_t vscale;     // double[restart+2]: V_k holds v_k / vscale[k] (krylov.hip)
-    size_t done;       // int[DONE_INTS]
     size_t red;        // double[restart+4]: outputs of column reductions
     size_t V, Z;       // double[(restart+1) * 4N], double[restart * 4N]
     size_t total;
@@ -242,10 +244,17 @@ constexpr int REC_CAP = 4;
 enum : int { REC_PREV = 0, REC_CHUNK = 1, REC_OUT = 2 };
 
 // ------------------------------------------------------------------ entry points used across files
-// rscale (device, may be null): the right-hand side is *rscale times r.
+// Asked after each launch of an application that was started before it was certain to be needed:
+// false ends the application there (its vectors are scratch, z_k is not yet written).
+struct Gate {
+    virtual bool go() = 0;
+};
+
+// rscale (device, may be null): the right-hand side is *rscale times r. gate (may be null): asked by
+// the SYNC and ASYNC modes with two or more sweeps; the others run whole.
 abilu_status apply_impl(const abilu_pattern *p, const void *LU, const void *Dinv, abilu_prec prec,
                         const double *r, const double *rscale, double *z, int nsweeps, abilu_mode mode, char *work,
-                        const Workspace &W, hipStream_t s);
+                        const Workspace &W, hipStream_t s, Gate *gate = nullptr);
 // Whether the last kernel of apply_impl(nsweeps, mode) ran its workgroups in descending row order.
 bool apply_ends_descending(int nsweeps, abilu_mode mode);
 // desc: run the workgroups in descending row order (the result does not depend on it; a kernel

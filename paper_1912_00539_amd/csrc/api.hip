@@ -37,7 +37,6 @@ Workspace layout(const abilu_pattern *p, abilu_prec prec, int restart) {
     W.coef = o; o = align256(o + sizeof(double) * (m + 2));
     W.misc = o; o = align256(o + sizeof(double) * 16);
     W.vscale = o; o = align256(o + sizeof(double) * (m + 2));
-    W.done = o; o = align256(o + sizeof(int) * DONE_INTS);
     W.red = o; o = align256(o + sizeof(double) * (m + 4));
     if (m > 0) {
         W.V = o; o = align256(o + sizeof(double) * (size_t)(m + 1) * nv);

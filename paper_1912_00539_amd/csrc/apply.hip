@@ -526,7 +526,7 @@ const char *tname<double>() { return "f64"; }
 
 template <typename T>
 abilu_status apply_t(const abilu_pattern *p, const T *LU, const T *Dinv, const double *r, const double *rs, double *z, int nsw,
-                     abilu_mode mode, char *work, const Workspace &W, hipStream_t s) {
+                     abilu_mode mode, char *work, const Workspace &W, hipStream_t s, Gate *gate) {
     const int n = p->n;
     const int grid = div_up(n, rows_per_wg2<T>());
     const T *Lb = LU;                                              // strictly lower part
@@ -667,6 +667,7 @@ abilu_status apply_t(const abilu_pattern *p, const T *LU, const T *Dinv, const d
                 k_fwd<T, T, false><<<grid, WG, 0, s>>>(n, lrow, lcol, Lb, r, yprev, ycur, Dinv, (T *)nullptr, rs, 0);
         }
         LAUNCHED();
+        if (gate && !gate->go()) return ABILU_OK;
         yprev = ycur;
     }
     const T *yfin = ycur;
@@ -696,6 +697,7 @@ abilu_status apply_t(const abilu_pattern *p, const T *LU, const T *Dinv, const d
             zprev = zcur;
         }
         LAUNCHED();
+        if (gate && !gate->go()) return ABILU_OK;
     }
     return ABILU_OK;
 #undef LAUNCHED
@@ -707,7 +709,7 @@ namespace abilu {
 
 abilu_status apply_impl(const abilu_pattern *p, const void *LU, const void *Dinv, abilu_prec prec, const double *r,
                         const double *rscale, double *z, int nsweeps, abilu_mode mode, char *work, const Workspace &W,
-                        hipStream_t s) {
+                        hipStream_t s, Gate *gate) {
     if (p->n == 0) return ABILU_OK;
     if (nsweeps == 0 && rscale) {
         const int64_t len = 4 * (int64_t)p->n;
@@ -721,8 +723,8 @@ abilu_status apply_impl(const abilu_pattern *p, const void *LU, const void *Dinv
                    : ABILU_EDEVICE;
     }
     if (prec == ABILU_F32)
-        return apply_t<float>(p, (const float *)LU, (const float *)Dinv, r, rscale, z, nsweeps, mode, work, W, s);
-    return apply_t<double>(p, (const double *)LU, (const double *)Dinv, r, rscale, z, nsweeps, mode, work, W, s);
+        return apply_t<float>(p, (const float *)LU, (const float *)Dinv, r, rscale, z, nsweeps, mode, work, W, s, gate);
+    return apply_t<double>(p, (const double *)LU, (const double *)Dinv, r, rscale, z, nsweeps, mode, work, W, s, gate);
 }
 
 bool apply_ends_descending(int nsweeps, abilu_mode mode) {

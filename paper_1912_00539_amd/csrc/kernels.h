@@ -28,10 +28,18 @@ constexpr int rows_per_wg2() { return rpq<T>() * ROWS_PER_WG; }
 constexpr int MAX_RESTART = 256;
 constexpr int SPMV_ROWS = WG / 8;            // SpMV: eight lanes per block row
 
-// status slots (double[8] in the workspace header, copied to the host)
+// status slots (double[8] in the workspace header; the server copies them to the host)
 enum { ST_EST = 0, ST_HN = 1, ST_BETA = 2, ST_NUM = 3, ST_GUARD = 4 };
+// A single solve's status reaches the host through the pattern's pinned buffer: PIN_SLOTS slots of
+// PIN_WORDS 8-byte words from word PIN_BASE on, taken in turn. The host fills a slot with
+// PIN_EMPTY before it launches the kernel that will write it, and has the status when no word it
+// needs is empty any more: no order between the words matters. Word 0 holds est (Arnoldi step) or
+// beta, word 1 hn or ||b||, word 2 the flag word with bit 32 the second pass's guard. (PIN_EMPTY is a
+// NaN whose payload no arithmetic gives; the kernel writes other NaNs as the default one.)
+enum { PIN_BASE = 32, PIN_WORDS = 4, PIN_SLOTS = 4 };
+constexpr unsigned long long PIN_EMPTY = 0x7ff4dead0badf00dull;
 // misc slots (double[16])
-enum { MI_NRM0 = 0, MI_NRM1 = 1, MI_DONE = 14, MI_GUARD = 15 };
+enum { MI_NRM0 = 0, MI_NRM1 = 1, MI_TOL = 2, MI_DONE = 14, MI_GUARD = 15 };
 
 template <typename T, typename S>
 __device__ __forceinline__ void load_block_row(const S *base, int64_t pos, int r, T (&v)[4]) {
@@ -590,12 +598,52 @@ struct KPtrs {
     double *partials, *red, *H, *cs, *sn, *g, *coef, *misc, *status, *vscale;
     int *guard, *done;
     bool grouped;   // done has the counts of the groups too
+    // a single solve only (host null in the server)
+    unsigned long long *host = nullptr;   // the slot that this launch's status goes to
+    const unsigned *flags = nullptr;
+    double rtol = 0.0;
+    bool single = false, last = false;    // last: no Arnoldi step follows this one
 };
+
+// Hand the status to the host (one lane): three writes through to its pinned memory.
+__device__ __forceinline__ void publish(const KPtrs &P, double v0, double v1, int guard) {
+    if (!P.host) return;
+    auto put = [&](int w, unsigned long long v) {
+        __hip_atomic_store(P.host + w, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    };
+    auto bits = [](double v) {
+        return v == v ? (unsigned long long)__double_as_longlong(v) : 0x7ff8000000000000ull;
+    };
+    put(2, (unsigned long long)*P.flags | (guard ? 1ull << 32 : 0ull));
+    put(0, bits(v0));
+    put(1, bits(v1));
+}
+
+// Back substitution on the k x k upper triangle: coef = y, by columns (one workgroup).
+__device__ __forceinline__ void solve_body(int k, int m, const double *H, const double *g, double *coef) {
+    __shared__ double y[MAX_RESTART];
+    for (int t = threadIdx.x; t < k; t += blockDim.x) y[t] = g[t];
+    __syncthreads();
+    for (int q = k - 1; q >= 0; --q) {
+        const double *h = H + (int64_t)q * (m + 1);
+        const double yq = y[q] / h[q];
+        __syncthreads();
+        for (int t = threadIdx.x; t <= q; t += blockDim.x) {
+            if (t < q) y[t] -= h[t] * yq;
+            else coef[q] = yq;
+        }
+        __syncthreads();
+    }
+}
 
 __device__ __forceinline__ void beta_step(const KPtrs &P, int m, double r0, bool num, bool beta_slot, bool init_g) {
     const double beta = sqrt(r0);
     if (threadIdx.x == 0) {
-        if (num) P.status[ST_NUM] = beta;
+        if (num) {
+            P.status[ST_NUM] = beta;
+            P.misc[MI_TOL] = P.rtol * (beta > 0 ? beta : 1.0);
+        }
+        if (beta_slot) publish(P, beta, num ? beta : P.status[ST_NUM], 0);
         if (beta_slot) P.status[ST_BETA] = beta;
         P.vscale[0] = beta != 0.0 ? 1.0 / beta : 1.0;
     }
@@ -663,20 +711,23 @@ __device__ __forceinline__ void givens_step(const KPtrs &P, int k, int m, const 
         P.status[ST_EST] = fabs(-sn * gk);
         P.status[ST_HN] = hn;
         P.status[ST_GUARD] = (double)guard;
+        publish(P, fabs(-sn * gk), hn, guard);
     }
     __syncthreads();
     for (int q = threadIdx.x; q <= k; q += blockDim.x) h[q] = lh[q];
     if (threadIdx.x == 0) h[k + 1] = 0.0;
+    // where the cycle ends, its least-squares solution (the host takes the same decision)
+    if (P.single) {
+        __syncthreads();
+        if (P.last || P.status[ST_EST] <= P.misc[MI_TOL] || P.status[ST_HN] == 0.0) solve_body(k + 1, m, P.H, P.g, P.coef);
+    }
 }
 
 // The step OP on the column sums red (whole workgroup; red readable by every lane).
 template <int OP>
 __device__ __forceinline__ void step_tail(const KPtrs &P, int k, int m, const double *red) {
     if constexpr (OP == RS_BETA_START_ZERO || OP == RS_BETA_START_X) {
-        // the solve's first reduction (one column, so it counts nothing): also clears the count
         beta_step(P, m, red[0], true, OP == RS_BETA_START_ZERO, OP == RS_BETA_START_ZERO);
-        if (P.grouped && threadIdx.x <= DONE_GROUPS) P.done[threadIdx.x * DONE_STRIDE] = 0;
-        else if (threadIdx.x == 0) *P.done = 0;
     }
     else if constexpr (OP == RS_BETA) beta_step(P, m, red[0], false, true, true);
     else if constexpr (OP == RS_GS1) gs1_step(P, k, m, red);
@@ -695,24 +746,6 @@ __device__ __forceinline__ void reduce_step_body(int blk, int cols, const KPtrs 
     for (int c = threadIdx.x; c < cols; c += WG) sred[c] = load_agent(P.red + c);
     __syncthreads();
     step_tail<OP>(P, k, m, sred);
-}
-
-// Back substitution on the k x k upper triangle: coef = y, by columns (one workgroup).
-__device__ __forceinline__ void solve_body(int k, int m, const double *__restrict__ H, const double *__restrict__ g,
-                                           double *coef) {
-    __shared__ double y[MAX_RESTART];
-    for (int t = threadIdx.x; t < k; t += blockDim.x) y[t] = g[t];
-    __syncthreads();
-    for (int q = k - 1; q >= 0; --q) {
-        const double *h = H + (int64_t)q * (m + 1);
-        const double yq = y[q] / h[q];
-        __syncthreads();
-        for (int t = threadIdx.x; t <= q; t += blockDim.x) {
-            if (t < q) y[t] -= h[t] * yq;
-            else coef[q] = yq;
-        }
-        __syncthreads();
-    }
 }
 
 __device__ __forceinline__ void zero_body(int blk, int64_t len, double *v) {

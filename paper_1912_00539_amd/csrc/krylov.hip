@@ -8,7 +8,10 @@
 // All reductions are fixed-order (per-workgroup partials, then one workgroup per column in
 // index order), so results do not depend on scheduling. The only atomic is the completion count
 // that picks the last workgroup of a reduction; it orders work, not values.
+#include <chrono>
 #include <cmath>
+#include <cstring>
+#include <functional>
 
 #include "kernels.h"
 
@@ -93,12 +96,6 @@ __global__ __launch_bounds__(WG) void k_update_step(int64_t len, Basis V, int q,
     fold_tail<RS_GIVENS>(P, nb, 1, guard, k, m);
 }
 
-// Back substitution on the k x k upper triangle: coef = y.
-__global__ __launch_bounds__(64) void k_solve(int k, int m, const double *__restrict__ H, const double *__restrict__ g,
-                                              double *coef) {
-    solve_body(k, m, H, g, coef);
-}
-
 __global__ __launch_bounds__(WG) void k_zero(int64_t len, double *v) {
     zero_body(blockIdx.x, len, v);
 }
@@ -173,8 +170,20 @@ struct Ctx {
     const double *v0;   // the first basis vector: the right-hand side or V
     int *guard, *done;
     int m;
+    double rtol;
+    unsigned long long *slot = nullptr, *slot_dev = nullptr;   // where the next status goes, host and device
+    unsigned turn = 0;
+    bool last = false;
+    void ask() {   // the launch that follows publishes a status
+        const unsigned at = PIN_BASE + PIN_WORDS * (turn++ % PIN_SLOTS);
+        slot = (unsigned long long *)p->pinned + at;
+        slot_dev = (unsigned long long *)p->pinned_dev + at;
+        for (int w = 0; w < PIN_WORDS; ++w) __atomic_store_n(slot + w, PIN_EMPTY, __ATOMIC_RELAXED);
+        __atomic_thread_fence(__ATOMIC_RELEASE);
+    }
     Basis basis() const { return Basis{v0, V, nv}; }
-    KPtrs ptrs() const { return KPtrs{partials, red, H, cs, sn, g, coef, misc, status, vscale, guard, done, true}; }
+    KPtrs ptrs() const { return KPtrs{partials, red, H, cs, sn, g, coef, misc, status, vscale, guard, done, true, slot_dev,
+                     (const unsigned *)work, rtol, true, last}; }
 };
 
 #define CKL()                                                     \
@@ -203,11 +212,18 @@ abilu_status reduce_step(Ctx &c, int ncols, const int *guard, int op, int k) {
 abilu_status mdot_reduce(Ctx &c, int q, const double *w, int op, int k) {
     const int nb = c.W.nb_vec;
     const double n8 = 8.0 * (double)c.nv;
-    if (nb <= FOLD_NB && op != RS_BETA_START_ZERO && op != RS_BETA_START_X) {
+    if (nb <= FOLD_NB) {
         ProfScope ps("fgmres_mdot", c.s, (q + 1) * n8 + 8.0 * (q + 1) * nb);
         const KPtrs P = c.ptrs();
-        if (op == RS_BETA) k_mdot_step<RS_BETA><<<nb, WG, 0, c.s>>>(c.nv, c.basis(), q, w, P, nb, k, c.m);
-        else k_mdot_step<RS_GS1><<<nb, WG, 0, c.s>>>(c.nv, c.basis(), q, w, P, nb, k, c.m);
+#define ABILU_MDOT_STEP(OP) \
+    case OP: k_mdot_step<OP><<<nb, WG, 0, c.s>>>(c.nv, c.basis(), q, w, P, nb, k, c.m); break
+        switch (op) {
+            ABILU_MDOT_STEP(RS_BETA_START_ZERO);
+            ABILU_MDOT_STEP(RS_BETA_START_X);
+            ABILU_MDOT_STEP(RS_BETA);
+            ABILU_MDOT_STEP(RS_GS1);
+        }
+#undef ABILU_MDOT_STEP
         CKL();
         return ABILU_OK;
     }
@@ -272,13 +288,43 @@ abilu_status update_reduce(Ctx &c, const Basis &Vb, int q, double alpha, double 
     return givens ? reduce_step(c, 1, guard, RS_GIVENS, k) : ABILU_OK;
 }
 
-// copies the flag word and the status scalars to the host
-abilu_status readback(Ctx &c, double *h, uint32_t *flags) {
-    if (!hip_ok(hipMemcpyAsync(c.p->pinned, c.work, 128, hipMemcpyDeviceToHost, c.s), "fgmres readback"))
+struct Status {
+    double v0, v1;   // est and hn, or beta and ||b||
+    uint32_t flags;
+    bool guard;
+};
+
+// Whether the status asked for in `slot` has arrived.
+bool status_here(const unsigned long long *slot) {
+    for (int w = 0; w < 3; ++w)
+        if (__atomic_load_n(slot + w, __ATOMIC_ACQUIRE) == PIN_EMPTY) return false;
+    return true;
+}
+
+// Waits for the status asked for in `slot` and reads it. The wait polls the pinned buffer, where the
+// status is some 10 us before a stream synchronisation behind a copy would return; every
+// millisecond it asks the stream whether it has failed, or has run dry without the status.
+abilu_status read_status(Ctx &c, const unsigned long long *slot, Status *out) {
+    using clock = std::chrono::steady_clock;
+    auto next = clock::now() + std::chrono::milliseconds(1);
+    for (unsigned spins = 1; !status_here(slot); ++spins) {
+        __builtin_ia32_pause();
+        if (spins % 256 != 0 || clock::now() < next) continue;
+        const hipError_t e = hipStreamQuery(c.s);
+        if (e == hipErrorNotReady) {
+            (void)hipGetLastError();
+            next = clock::now() + std::chrono::milliseconds(1);
+            continue;
+        }
+        if (!hip_ok(e, "fgmres stream")) return ABILU_EDEVICE;
+        if (status_here(slot)) break;
+        note_error("fgmres_solve: the stream ended without a status");
         return ABILU_EDEVICE;
-    if (!hip_ok(hipStreamSynchronize(c.s), "fgmres readback sync")) return ABILU_EDEVICE;
-    *flags = *(const uint32_t *)c.p->pinned;
-    for (int q = 0; q < 8; ++q) h[q] = c.p->pinned[8 + q];
+    }
+    memcpy(&out->v0, slot, sizeof(double));
+    memcpy(&out->v1, slot + 1, sizeof(double));
+    out->flags = (uint32_t)slot[2];
+    out->guard = ((slot[2] >> 32) & 1) != 0;
     return ABILU_OK;
 }
 
@@ -288,6 +334,7 @@ abilu_status true_residual(Ctx &c, const double *A, const double *b, const doubl
     abilu_status st = spmv_impl(c.p, A, x, c.V, b, true, c.s);
     if (st != ABILU_OK) return st;
     c.v0 = c.V;
+    c.ask();
     return mdot_reduce(c, 0, c.V, RS_BETA, 0);
 }
 
@@ -330,36 +377,108 @@ extern "C" abilu_status fgmres_solve(const abilu_pattern *p, const double *d_A, 
     c.V = (double *)(c.work + c.W.V);
     c.Zb = (double *)(c.work + c.W.Z);
     c.guard = (int *)(c.misc + MI_GUARD);
-    c.done = (int *)(c.work + c.W.done);
+    c.done = p->done;
     c.m = m;
-    double h[8];
-    uint32_t flags = 0;
+    c.rtol = rtol;
+    // the solve waits for its own launches: it cannot be recorded into a graph
+    hipStreamCaptureStatus capturing = hipStreamCaptureStatusNone;
+    if (!hip_ok(hipStreamIsCapturing(c.s, &capturing), "fgmres capture status")) return ABILU_EDEVICE;
+    if (capturing != hipStreamCaptureStatusNone) {
+        note_error("fgmres_solve: the stream is being captured");
+        return ABILU_EDEVICE;
+    }
     abilu_status st;
 
     // ||b|| and the initial residual: b itself for a zero initial guess, which then also is the
     // first basis vector, and whose x is first written by the first cycle's update
     const bool zero_guess = (options & ABILU_FGMRES_ZERO_GUESS) != 0;
     c.v0 = d_b;
+    if (zero_guess) c.ask();
     if ((st = mdot_reduce(c, 0, d_b, zero_guess ? RS_BETA_START_ZERO : RS_BETA_START_X, 0)) != ABILU_OK) return st;
     if (!zero_guess && (st = true_residual(c, d_A, d_b, d_x)) != ABILU_OK) return st;
-    if ((st = readback(c, h, &flags)) != ABILU_OK) return st;
-    const double bnorm = h[ST_NUM];
-    const double bn = bnorm > 0 ? bnorm : 1.0;
-    const double tol = rtol * bn;
-    double beta = h[ST_BETA], est = beta;
-    int iters = 0, restarts = 0, reorth = 0;
-    bool converged = beta <= tol;
-    bool nonfinite = !std::isfinite(beta) || !std::isfinite(bnorm);
 
-    while (!converged && !nonfinite && iters < maxit && beta > 0.0) {
-        int k = 0;
-        while (k < m && iters < maxit) {
+    double bn = 1.0, tol = 0.0, beta = 0.0, est = 0.0;
+    int iters = 0, restarts = 0, reorth = 0;
+    bool converged = false, nonfinite = false;
+    // The status of the launches so far (the start's, a cycle's or an Arnoldi step's), not yet read.
+    // An Arnoldi step's application may begin before: it stops at the first launch after which the
+    // status says that it is not needed, and has then written scratch vectors only. Ahead of the
+    // status at most `ahead` sweeps are launched: enough to cover the 6-8 us between the status
+    // being written and the next launch arriving, and none where a needless sweep costs more.
+    enum { START, CYCLE, STEP };
+    struct Pending : Gate {
+        Ctx &c;
+        Status now{};
+        const unsigned long long *slot = nullptr;
+        bool open = false, stop = false;
+        int kind = START, launched = 0, limit = 0;
+        abilu_status st = ABILU_OK;
+        std::function<bool(int)> decide;   // takes the status in; true: stop
+        explicit Pending(Ctx &ctx) : c(ctx) {}
+        void expect(int k) {
+            open = true;
+            kind = k;
+            slot = c.slot;
+            launched = 0;
+        }
+        void read() {
+            if (!open) return;
+            open = false;
+            st = read_status(c, slot, &now);
+            stop = st != ABILU_OK || decide(kind);
+        }
+        bool go() override {
+            if (open && (status_here(slot) || ++launched >= limit)) read();
+            return !stop;
+        }
+    } pending(c);
+    const bool gated = (mode == ABILU_SYNC || mode == ABILU_ASYNC) && apply_sweeps >= 2;   // modes that ask the gate
+    pending.limit = !gated ? 0 : p->n <= 60000 ? 2 : p->n <= 400000 ? 1 : 0;
+    int pass2_begin = 0, pass2_end = 0;
+    pending.decide = [&](int kind) {
+        if (kind == STEP) {
+            if (pending.now.guard)
+                ++reorth;
+            else
+                prof_cancel_bytes(pass2_begin, pass2_end);   // the second pass exited at once
+            ++iters;
+            est = pending.now.v0;
+            nonfinite = !std::isfinite(est) || !std::isfinite(pending.now.v1);
+            return nonfinite || est <= tol || pending.now.v1 == 0.0;
+        }
+        beta = pending.now.v0;
+        if (kind == START) {
+            const double bnorm = pending.now.v1;
+            bn = bnorm > 0 ? bnorm : 1.0;
+            tol = rtol * bn;
+            est = beta;
+            nonfinite = !std::isfinite(bnorm);
+        } else {
+            ++restarts;
+        }
+        nonfinite = nonfinite || !std::isfinite(beta);
+        converged = beta <= tol;
+        return converged || nonfinite || iters >= maxit || !(beta > 0.0);
+    };
+    pending.expect(START);
+    if (pending.limit == 0 || maxit == 0) pending.read();
+
+    while (!pending.stop) {
+        int k = 0;   // Arnoldi steps launched in this cycle
+        while (true) {
             const double *vk = k == 0 ? c.v0 : c.V + (int64_t)k * c.nv;
             double *zk = c.Zb + (int64_t)k * c.nv;
             double *w = c.V + (int64_t)(k + 1) * c.nv;
-            if ((st = apply_impl(p, d_LU, d_Dinv, prec, vk, c.vscale + k, zk, apply_sweeps, mode, c.work, c.W,
-                                 c.s)) != ABILU_OK)
+            const int apply_begin = prof_mark();
+            if ((st = apply_impl(p, d_LU, d_Dinv, prec, vk, c.vscale + k, zk, apply_sweeps, mode, c.work, c.W, c.s,
+                                 pending.open ? &pending : nullptr)) != ABILU_OK)
                 return st;
+            pending.read();
+            if (pending.st != ABILU_OK) return pending.st;
+            if (pending.stop) {
+                prof_cancel_bytes(apply_begin, prof_mark());   // begun for nothing
+                break;
+            }
             if ((st = spmv_impl(p, d_A, zk, w, nullptr, !apply_ends_descending(apply_sweeps, mode), c.s)) !=
                 ABILU_OK)
                 return st;
@@ -368,57 +487,47 @@ extern "C" abilu_status fgmres_solve(const abilu_pattern *p, const double *d_A, 
             if ((st = mdot_reduce(c, k + 1, w, RS_GS1, k)) != ABILU_OK) return st;
             if ((st = update_dot_reduce(c, k + 1, w, k)) != ABILU_OK) return st;
             // pass 2's update, executed by the device only when the guard is set; the Givens step
-            // after it runs either way
-            const int pass2_begin = prof_mark();
+            // after it runs either way and, at the cycle's end, the least-squares solution
+            c.ask();
+            c.last = k + 1 == m || iters + 1 >= maxit;
+            pass2_begin = prof_mark();
             if ((st = update_reduce(c, c.basis(), k + 1, -1.0, w, c.guard, true, k)) != ABILU_OK) return st;
-            const int pass2_end = prof_mark();
-            if ((st = readback(c, h, &flags)) != ABILU_OK) return st;
-            if (h[ST_GUARD] != 0.0)
-                ++reorth;
-            else
-                prof_cancel_bytes(pass2_begin, pass2_end);   // the second pass exited at once
-            ++iters;
+            pass2_end = prof_mark();
+            pending.expect(STEP);
             ++k;
-            est = h[ST_EST];
-            if (!std::isfinite(est) || !std::isfinite(h[ST_HN])) {
-                nonfinite = true;
-                break;
+            if (c.last || pending.limit == 0) {
+                pending.read();
+                if (pending.st != ABILU_OK) return pending.st;
+                if (pending.stop || c.last) break;
             }
-            if (est <= tol || h[ST_HN] == 0.0) break;
         }
-        if (nonfinite) break;
-        // least squares and x += Z y
-        {
-            ProfScope ps("fgmres_small", c.s);
-            k_solve<<<1, 64, 0, c.s>>>(k, m, c.H, c.g, c.coef);
-        }
-        CKL();
+        if (nonfinite || k == 0) break;
+        // x += Z y
         if ((st = update_reduce(c, Basis{c.Zb, c.Zb, c.nv}, k, 1.0, d_x, nullptr, false, 0, zero_guess && restarts == 0)) !=
             ABILU_OK)
             return st;
         if ((st = true_residual(c, d_A, d_b, d_x)) != ABILU_OK) return st;
-        if ((st = readback(c, h, &flags)) != ABILU_OK) return st;
-        ++restarts;
-        beta = h[ST_BETA];
-        if (!std::isfinite(beta)) nonfinite = true;
-        converged = beta <= tol;
+        pending.expect(CYCLE);
+        pending.read();
+        if (pending.st != ABILU_OK) return pending.st;
     }
     if (zero_guess && restarts == 0) {   // no cycle wrote x
         ProfScope ps("fgmres_zero", c.s, 8.0 * (double)c.nv);
         k_zero<<<c.W.nb_vec, WG, 0, c.s>>>(c.nv, d_x);
         CKL();
-        if (!hip_ok(hipStreamSynchronize(c.s), "fgmres x sync")) return ABILU_EDEVICE;
     }
+    // the last kernel is past its status but may still be ending
+    if (!hip_ok(hipStreamSynchronize(c.s), "fgmres end sync")) return ABILU_EDEVICE;
     out->iters = iters;
     out->restarts = restarts;
     out->converged = converged ? 1 : 0;
-    out->flags = flags;
+    out->flags = pending.now.flags;
     out->reorth = reorth;
     out->rel_true_residual = beta / bn;
     out->rel_estimate = est / bn;
     if (nonfinite) return ABILU_ENONFINITE;
     if (!converged) return ABILU_WARN_NOCONV;
-    if (flags & ABILU_FLAG_MODIFIED) return ABILU_WARN_MODIFIED;
+    if (pending.now.flags & ABILU_FLAG_MODIFIED) return ABILU_WARN_MODIFIED;
     return ABILU_OK;
 }
 

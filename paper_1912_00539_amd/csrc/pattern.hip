@@ -206,11 +206,16 @@ extern "C" abilu_status abilu_build_pattern(int32_t nbrows, const int32_t *d_row
         if (Z > 0 && !d_colidx) { st = ABILU_EINVAL; goto fail; }
         p->nnzb = Z;
         CKA(hipHostMalloc((void **)&p->pinned, 64 * sizeof(double), hipHostMallocDefault));
+        CK(hipHostGetDevicePointer((void **)&p->pinned_dev, p->pinned, 0));
+        for (int q = 0; q < 64; ++q) p->pinned[q] = 0.0;
         CKA(hipMalloc(&p->rowptr, sizeof(int32_t) * (n + 1)));
         CKA(hipMalloc(&p->colidx, sizeof(int32_t) * (Z + 1)));
         CKA(hipMalloc(&p->diag_pos, sizeof(int32_t) * (n + 1)));
         CKA(hipMalloc(&p->pair_ptr, sizeof(int32_t) * (Z + 1)));
-        CKA(hipMalloc(&p->lrow, sizeof(int32_t) * (n + 1)));
+        const size_t lrow_ints = ((size_t)n + 1 + DONE_STRIDE - 1) / DONE_STRIDE * DONE_STRIDE;
+        CKA(hipMalloc(&p->lrow, sizeof(int32_t) * (lrow_ints + DONE_INTS)));
+        p->done = p->lrow + lrow_ints;
+        CK(hipMemsetAsync(p->done, 0, sizeof(int32_t) * DONE_INTS, s));
         CKA(hipMalloc(&p->urow, sizeof(int32_t) * (n + 1)));
         CKA(hipMalloc(&scratch, pattern_scratch_bytes(n, Z)));
         CK(hipMemcpyAsync(p->rowptr, d_rowptr, sizeof(int32_t) * (n + 1), hipMemcpyDeviceToDevice, s));
