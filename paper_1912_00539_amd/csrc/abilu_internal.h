@@ -28,11 +28,17 @@ struct abilu_pattern {
     int32_t *urow = nullptr;      // device [n+1]
     int32_t *lcol = nullptr;      // device [ZL+1] columns of the lower part (one padding entry)
     int32_t *ucol = nullptr;      // device [ZU+1] columns of the upper part
+    int32_t *ldiag = nullptr;     // device [ZL+1] CSR position of the diagonal block of each lower column
+                                  // (behind lcol in its allocation)
     double *pinned = nullptr;     // host pinned, 64 doubles, for blocking scalar reads
     double *pinned_dev = nullptr; // the same memory as kernels address it
     int32_t *done = nullptr;      // device [DONE_INTS] completion counts of FGMRES's reductions, zero
                                   // between launches (behind lrow in its allocation)
     bool symmetric = false;       // (i,j) in S_B implies (j,i) in S_B
+    int32_t max_lower = 0, max_upper = 0;   // most strictly lower / upper blocks of a row
+    // update sets of the diagonal blocks only, and rows that the factor sweeps' row-at-once form holds
+    // (FV_CAP lower and upper blocks): finite-volume meshes of triangles and quads
+    bool fv() const { return symmetric && npairs == nnzb_lower && max_lower <= 3 && max_upper <= 3; }
     int device = 0;
     // chunk schedule (abilu_pattern_set_chunks): chunks of chunk_rows consecutive rows; per chunk,
     // the rows grouped by level in the chunk's lower (forward, factor) and upper (backward)
@@ -61,6 +67,7 @@ struct abilu_pattern {
 namespace abilu {
 
 constexpr int BS = 4;
+constexpr int FV_CAP = 3;               // abilu_pattern::fv
 constexpr int BB = 16;
 constexpr int WG = 256;                 // threads per workgroup (4 wavefronts of 64)
 constexpr int ROWS_PER_WG = WG / BS;    // one quad of 4 lanes per block row
@@ -208,7 +215,7 @@ abilu_status pattern_count(int32_t n, int64_t Z, const int32_t *rowptr, const in
                            hipStream_t s, int64_t *ZL, int64_t *ZU, int64_t *npairs);
 abilu_status pattern_fill(int32_t n, int64_t Z, int64_t ZL, int64_t ZU, int64_t npairs, const int32_t *rowptr,
                           const int32_t *colidx, const int32_t *diag_pos, const int32_t *lrow, const int32_t *urow,
-                          int32_t *lcol, int32_t *ucol, int32_t *pik, int32_t *pkj, int32_t *sik, int32_t *skj,
+                          int32_t *lcol, int32_t *ldiag, int32_t *ucol, int32_t *pik, int32_t *pkj, int32_t *sik, int32_t *skj,
                           const void *scratch, hipStream_t s);
 
 // A mode the single-system entry points accept for this pattern (the chunked modes need the
@@ -276,14 +283,14 @@ __device__ __forceinline__ int split_pos(int e, int i, int b0, int d, int lbase,
 // quad_perm move per 32-bit word. All four lanes of the quad must be active.
 template <int L>
 __device__ __forceinline__ float qb(float v) {
-    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), L * 0x55, 0xF, 0xF, false));
+    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), L * 0x55, 0xF, 0xF, true));
 }
 template <int L>
 __device__ __forceinline__ double qb(double v) {
     long long b = __double_as_longlong(v);
     int lo = (int)(b & 0xffffffffll), hi = (int)(b >> 32);
-    lo = __builtin_amdgcn_update_dpp(0, lo, L * 0x55, 0xF, 0xF, false);
-    hi = __builtin_amdgcn_update_dpp(0, hi, L * 0x55, 0xF, 0xF, false);
+    lo = __builtin_amdgcn_mov_dpp(lo, L * 0x55, 0xF, 0xF, true);
+    hi = __builtin_amdgcn_mov_dpp(hi, L * 0x55, 0xF, 0xF, true);
     return __longlong_as_double(((long long)hi << 32) | (unsigned long long)(unsigned)lo);
 }
 
@@ -382,16 +389,40 @@ __device__ __forceinline__ void gather_vec(T v, T (&x)[4]) {
     x[0] = qb<0>(v); x[1] = qb<1>(v); x[2] = qb<2>(v); x[3] = qb<3>(v);
 }
 
-// Row r (this lane's index in the quad) of the inverse of the 4x4 block M, which every lane of
-// the quad holds: Gaussian elimination with partial pivoting and back substitution, all indices
-// static (row exchanges are selects). Every lane eliminates on M but carries only column r of
-// the identity as right-hand side and back-substitutes only column r of the inverse; the quad
-// then exchanges columns for rows by DPP. Each element goes through the same operations, in the
-// same order, as in the elimination on the full [M | I] (10 instead of 22 divisions per lane).
+// True in all four lanes of the quad when it is in each.
+__device__ __forceinline__ bool quad_all(bool v) {
+    const int i = v ? 1 : 0;
+    return (__builtin_amdgcn_update_dpp(0, i, 0x00, 0xF, 0xF, false) &
+            __builtin_amdgcn_update_dpp(0, i, 0x55, 0xF, 0xF, false) &
+            __builtin_amdgcn_update_dpp(0, i, 0xAA, 0xF, 0xF, false) &
+            __builtin_amdgcn_update_dpp(0, i, 0xFF, 0xF, 0xF, false)) != 0;
+}
+
+// out[c] = inverse(r, c) = element r of lane c's column x.
+template <typename T>
+__device__ __forceinline__ void quad_transpose(const T (&x)[4], int r, T (&out)[4]) {
+    const bool b0 = (r & 1) != 0, b1 = (r & 2) != 0;
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+        T col[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) col[q] = c == 0 ? qb<0>(x[q]) : c == 1 ? qb<1>(x[q]) : c == 2 ? qb<2>(x[q]) : qb<3>(x[q]);
+        const T lo = b0 ? col[1] : col[0];
+        const T hi = b0 ? col[3] : col[2];
+        out[c] = b1 ? hi : lo;
+    }
+}
+
+// The general 4x4 inverse, row r (this lane's index in the quad) of the inverse of the block M that
+// every lane of the quad holds: Gaussian elimination with partial pivoting and back substitution,
+// all indices static (row exchanges are selects). Every lane eliminates on M but carries only
+// column r of the identity as right-hand side and back-substitutes only column r of the inverse;
+// the quad then exchanges columns for rows by DPP. Each element goes through the same operations,
+// in the same order, as in the elimination on the full [M | I].
 // Returns false for the whole quad, with the identity row, if a pivot is exactly zero or any
 // element of the inverse is not finite (the modified iteration's replacement).
 template <typename T>
-__device__ __forceinline__ bool inv4_row(T (&M)[16], int r, T (&out)[4]) {
+__device__ __forceinline__ bool inv4_row_pivoted(T (&M)[16], int r, T (&out)[4]) {
     T x[4];
 #pragma unroll
     for (int q = 0; q < 4; ++q) x[q] = (q == r) ? T(1) : T(0);
@@ -440,25 +471,110 @@ __device__ __forceinline__ bool inv4_row(T (&M)[16], int r, T (&out)[4]) {
 #pragma unroll
     for (int q = 0; q < 4; ++q) ok = ok && isfinite(x[q]);
     // the block is replaced if any lane's column failed
-    const int okl = ok ? 1 : 0;
-    const int okq = __builtin_amdgcn_update_dpp(0, okl, 0x00, 0xF, 0xF, false) &
-                    __builtin_amdgcn_update_dpp(0, okl, 0x55, 0xF, 0xF, false) &
-                    __builtin_amdgcn_update_dpp(0, okl, 0xAA, 0xF, 0xF, false) &
-                    __builtin_amdgcn_update_dpp(0, okl, 0xFF, 0xF, 0xF, false);
-    // out[c] = inverse(r, c) = element r of lane c's column
-    const bool b0 = (r & 1) != 0, b1 = (r & 2) != 0;
-    T col[4];
+    ok = quad_all(ok);
+    quad_transpose(x, r, out);
+    if (!ok) {
 #pragma unroll
-    for (int c = 0; c < 4; ++c) {
-        if (c == 0) { col[0] = qb<0>(x[0]); col[1] = qb<0>(x[1]); col[2] = qb<0>(x[2]); col[3] = qb<0>(x[3]); }
-        if (c == 1) { col[0] = qb<1>(x[0]); col[1] = qb<1>(x[1]); col[2] = qb<1>(x[2]); col[3] = qb<1>(x[3]); }
-        if (c == 2) { col[0] = qb<2>(x[0]); col[1] = qb<2>(x[1]); col[2] = qb<2>(x[2]); col[3] = qb<2>(x[3]); }
-        if (c == 3) { col[0] = qb<3>(x[0]); col[1] = qb<3>(x[1]); col[2] = qb<3>(x[2]); col[3] = qb<3>(x[3]); }
-        const T lo = b0 ? col[1] : col[0];
-        const T hi = b0 ? col[3] : col[2];
-        out[c] = okq ? (b1 ? hi : lo) : ((c == r) ? T(1) : T(0));
+        for (int c = 0; c < 4; ++c) out[c] = c == r ? T(1) : T(0);
     }
-    return okq != 0;
+    return ok;
+}
+
+// The general inverse of the block whose rows the quad's lanes hold. The chunked sweeps use it as it
+// is: a chunk's rows wait for each other's inverses, and the chain of dependent instructions is
+// shorter here than across the quad (128 against 137 us for the sweep of 500,000 cells in line order).
+template <typename T>
+__device__ __forceinline__ bool inv4_row_gathered(const T (&row)[4], int r, T (&out)[4]) {
+    T M[16];
+    gather_block(row, M);
+    return inv4_row_pivoted(M, r, out);
+}
+
+// Several quotients by one divisor. double: the division itself. float: the product with the
+// reciprocal in double, which is within 2^-51 of 1 / b after two Newton steps; a quotient of two
+// floats is either a float or at least 2^-49 (relative) away from the midpoint of two floats, so
+// rounding the product to float gives the correctly rounded quotient, in 3 instructions (and 6 per
+// divisor) where a float division takes about 12. (Quotients in the subnormal range may differ in
+// the last place from the division's; a zero or non-finite divisor gives a non-finite quotient.)
+template <typename T>
+struct Divisor {
+    double b;
+    __device__ __forceinline__ explicit Divisor(T v) : b((double)v) {
+        if constexpr (sizeof(T) == 4) {
+            double r = __builtin_amdgcn_rcp(b);
+            r = __builtin_fma(__builtin_fma(-b, r, 1.0), r, r);
+            b = __builtin_fma(__builtin_fma(-b, r, 1.0), r, r);
+        }
+    }
+    __device__ __forceinline__ T under(T a) const {
+        if constexpr (sizeof(T) == 4) return (T)((double)a * b);
+        else return a / b;
+    }
+};
+
+// Row r (this lane's index in the quad) of the inverse of the 4x4 block whose rows the quad's lanes
+// hold. Blocks whose natural pivots are the partial pivoting's (every multiplier at most 1, as for
+// the diagonally dominant blocks of a pseudo-time Jacobian) are eliminated across the quad: lane q
+// forms its own multiplier and updates its own row, the pivot row coming by DPP, then lane c solves
+// for column c of the inverse and the quad transposes: the operations of inv4_row_pivoted on each
+// element, in its order (the same bits), with 7 divisions per lane instead of 10, 18 product
+// subtractions instead of 42 and no row exchanges. A quad that finds a larger multiplier takes
+// inv4_row_pivoted.
+template <typename T>
+__device__ __forceinline__ bool inv4_row(const T (&row)[4], int r, T (&out)[4]) {
+    T m1 = row[1], m2 = row[2], m3 = row[3];
+    const T u00 = qb<0>(row[0]), u01 = qb<0>(m1), u02 = qb<0>(m2), u03 = qb<0>(m3);
+    // (lanes at or above the pivot row go on with values that nothing reads)
+    const Divisor<T> d0(u00);
+    const T f0 = d0.under(row[0]);
+    m1 = sub_prod(m1, f0, u01);
+    m2 = sub_prod(m2, f0, u02);
+    m3 = sub_prod(m3, f0, u03);
+    const T u11 = qb<1>(m1), u12 = qb<1>(m2), u13 = qb<1>(m3);
+    const Divisor<T> d1(u11);
+    const T f1 = d1.under(m1);
+    m2 = sub_prod(m2, f1, u12);
+    m3 = sub_prod(m3, f1, u13);
+    const T u22 = qb<2>(m2), u23 = qb<2>(m3);
+    const Divisor<T> d2(u22);
+    const T f2 = d2.under(m2);
+    m3 = sub_prod(m3, f2, u23);
+    const T u33 = qb<3>(m3);
+    const bool natural = (r < 1 || fabs(f0) <= T(1)) && (r < 2 || fabs(f1) <= T(1)) && (r < 3 || fabs(f2) <= T(1));
+    T x[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) x[q] = q == r ? T(1) : T(0);
+    const T l10 = qb<1>(f0), l20 = qb<2>(f0), l30 = qb<3>(f0);
+    x[1] = sub_prod(x[1], l10, x[0]);
+    x[2] = sub_prod(x[2], l20, x[0]);
+    x[3] = sub_prod(x[3], l30, x[0]);
+    const T l21 = qb<2>(f1), l31 = qb<3>(f1);
+    x[2] = sub_prod(x[2], l21, x[1]);
+    x[3] = sub_prod(x[3], l31, x[1]);
+    const T l32 = qb<3>(f2);
+    x[3] = sub_prod(x[3], l32, x[2]);
+    x[3] = Divisor<T>(u33).under(x[3]);
+    x[2] = d2.under(sub_prod(x[2], u23, x[3]));
+    x[1] = d1.under(sub_prod(sub_prod(x[1], u12, x[2]), u13, x[3]));
+    x[0] = d0.under(sub_prod(sub_prod(sub_prod(x[0], u01, x[1]), u02, x[2]), u03, x[3]));
+    if (!quad_all(natural)) return inv4_row_gathered(row, r, out);
+    const bool ok =
+        quad_all(u33 != T(0) && isfinite(x[0]) && isfinite(x[1]) && isfinite(x[2]) && isfinite(x[3]));
+    quad_transpose(x, r, out);
+    if (!ok) {
+#pragma unroll
+        for (int c = 0; c < 4; ++c) out[c] = c == r ? T(1) : T(0);
+    }
+    return ok;
+}
+
+// Whether a 4x4 block (this lane's row) certainly has a finite inverse by elimination: entries of
+// ordinary size and each row's diagonal entry 1.1 times the sum of the others. False says nothing.
+template <typename T>
+__device__ __forceinline__ bool surely_invertible(const T (&row)[4], int r) {
+    const T d = fabs(r == 0 ? row[0] : r == 1 ? row[1] : r == 2 ? row[2] : row[3]);
+    const T sum = (fabs(row[0]) + fabs(row[1])) + (fabs(row[2]) + fabs(row[3]));
+    return quad_all(d > T(1e-15) && d < T(1e15) && d >= T(1.1) * (sum - d));
 }
 
 template <typename T>

@@ -61,6 +61,15 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(sweep_waves<
     factor_sweep_body<T, L_FROM_A, U_FROM_A, D_FROM_A>(blockIdx.x, n, ZL, rowptr, colidx, diag_pos, lrow, urow, pair_ptr, pik, pkj, sik, skj, A, XL, XU, Dp, Xn, Dn, flags, sym != 0);
 }
 
+// The same on a pattern whose update sets are the diagonal ones, with at most CL lower and CU upper
+// blocks a row.
+template <typename T, int LSRC, bool FROM_A, int CL, int CU>
+__global__ __launch_bounds__(WG) void k_factor_sweep_fv(FvPattern P, const double *__restrict__ A, const T *XP,
+                                                        const T *Dp, T *Xn, T *Dn, unsigned *flags) {
+    factor_sweep_fv_row<T, LSRC, FROM_A, CL, CU>(blockIdx.x * ROWS_PER_WG + (threadIdx.x >> 2), P, A, XP, Dp, Xn, Dn,
+                                                 flags);
+}
+
 // The asynchronous sweep with a single worker: one quad over the rows in ascending order, in
 // place (a Gauss-Seidel sweep). Launched with one workgroup of 4 lanes.
 template <typename T>
@@ -201,9 +210,7 @@ __global__ __launch_bounds__(WG) void k_factor_sweep_chunk_rows(
             }
             fl |= nonfinite4(aD);
             store_row(Xn + ((int64_t)ZL + i) * BB, r, aD);
-            T M[16];
-            gather_block(aD, M);
-            if (!inv4_row(M, r, pD)) fl |= ABILU_FLAG_MODIFIED;
+            if (!inv4_row_gathered(aD, r, pD)) fl |= ABILU_FLAG_MODIFIED;
             store_row(Dn + (int64_t)i * BB, r, pD);
         }
         // strictly upper blocks
@@ -369,9 +376,7 @@ __device__ __forceinline__ unsigned compute_row(const RecRow<CL, CP> &f, int i, 
         }
         fl |= nonfinite4(td);
         store_row(Xn + ((int64_t)ZL + i) * BB, r, td);
-        T M[16];
-        gather_block(td, M);
-        if (!inv4_row(M, r, pD)) fl |= ABILU_FLAG_MODIFIED;
+        if (!inv4_row_gathered(td, r, pD)) fl |= ABILU_FLAG_MODIFIED;
         store_row(Dn + (int64_t)i * BB, r, pD);
     }
     // strictly upper blocks
@@ -457,9 +462,24 @@ const char *tname<float>() { return "f32"; }
 template <>
 const char *tname<double>() { return "f64"; }
 
+// One sweep over all rows at once. XL, XU: the previous iterate (null where A takes its place); Xn ==
+// XL: in place.
 template <typename T, bool LA, bool UA, bool DA = false>
 void launch_sweep(const abilu_pattern *p, int grid, hipStream_t s, const double *A, const T *XL, const T *XU,
                   const T *Dp, T *Xn, T *Dn, unsigned *flags) {
+    if (p->fv()) {
+        const FvPattern P{p->n, (int)p->nnzb_lower, p->rowptr, p->lrow, p->urow, p->lcol, p->ldiag, p->pkj, p->skj};
+        const bool two = p->max_lower <= 2 && p->max_upper <= 2;
+        auto go = [&](auto lsrc) {
+            constexpr int LSRC = decltype(lsrc)::value;
+            if (two) k_factor_sweep_fv<T, LSRC, UA, 2, 2><<<grid, WG, 0, s>>>(P, A, XU, Dp, Xn, Dn, flags);
+            else k_factor_sweep_fv<T, LSRC, UA, FV_CAP, FV_CAP><<<grid, WG, 0, s>>>(P, A, XU, Dp, Xn, Dn, flags);
+        };
+        if constexpr (LA) go(std::integral_constant<int, L_FROM_A0>{});
+        else if (XL == Xn) go(std::integral_constant<int, L_FROM_NEW>{});
+        else if constexpr (!UA) go(std::integral_constant<int, L_FROM_PREV>{});
+        return;
+    }
     k_factor_sweep<T, LA, UA, DA><<<grid, WG, 0, s>>>(p->n, (int)p->nnzb_lower, p->rowptr, p->colidx, p->diag_pos,
                                                        p->lrow, p->urow, p->pair_ptr, p->pik, p->pkj, p->sik, p->skj,
                                                        A, XL, XU, Dp, Xn, Dn, flags, p->symmetric ? 1 : 0);

@@ -773,10 +773,9 @@ __device__ __forceinline__ void factor_init_body(int blk, int n, int ZL, const i
         }
     }
     const int64_t dpos = SRC_CSR ? (int64_t)diag_pos[i] : (int64_t)ZL + i;
-    T u[4], M[16], out[4];
+    T u[4], out[4];
     load_row(X0 + dpos * BB, r, u);
-    gather_block(u, M);
-    bool ok = inv4_row(M, r, out);
+    bool ok = inv4_row(u, r, out);
     store_row(D0 + (int64_t)i * BB, r, out);
     if (!ok && r == 0) atomicOr(flags, ABILU_FLAG_MODIFIED);
 }
@@ -823,10 +822,9 @@ __device__ __forceinline__ void factor_sweep_row(int i,
         if constexpr (D_FROM_A) {
 #pragma unroll
             for (int u = 0; u < CHL; ++u) {
-                T a[4], M[16];
+                T a[4];
                 load_row(A + (int64_t)diag_pos[j[u]] * BB, r, a);
-                gather_block(a, M);
-                if (!inv4_row(M, r, dr[u])) fl |= ABILU_FLAG_MODIFIED;
+                if (!inv4_row(a, r, dr[u])) fl |= ABILU_FLAG_MODIFIED;
             }
         } else {
 #pragma unroll
@@ -850,18 +848,16 @@ __device__ __forceinline__ void factor_sweep_row(int i,
         T t[4];
         load_row(A + (int64_t)d * BB, r, t);
         if constexpr (D_FROM_A) {
-            if (!sym || d + 1 == b1) {
-                T M[16], unused[4];
-                gather_block(t, M);
-                if (!inv4_row(M, r, unused)) fl |= ABILU_FLAG_MODIFIED;
+            if ((!sym || d + 1 == b1) && !surely_invertible(t, r)) {
+                T unused[4];
+                if (!inv4_row(t, r, unused)) fl |= ABILU_FLAG_MODIFIED;
             }
         }
         update_terms<T, L_FROM_A, U_FROM_A>(pd, pd1, r, pik, pkj, sik, skj, A, XL, XU, t);
         fl |= nonfinite4(t);
         store_row(Xn + ((int64_t)ZL + i) * BB, r, t);
-        T M[16], out[4];
-        gather_block(t, M);
-        if (!inv4_row(M, r, out)) fl |= ABILU_FLAG_MODIFIED;
+        T out[4];
+        if (!inv4_row(t, r, out)) fl |= ABILU_FLAG_MODIFIED;
         store_row(Dn + (int64_t)i * BB, r, out);
     }
     // strictly upper blocks: U_ij = A_ij - sum
@@ -882,6 +878,121 @@ __device__ __forceinline__ void factor_sweep_row(int i,
                 fl |= nonfinite4(t[u]);
                 store_row(XnU + (int64_t)(e0 + u - d - 1) * BB, r, t[u]);
             }
+        }
+    }
+    if (fl) atomicOr(flags, fl);
+}
+
+// One sweep over block row i of a pattern whose update sets are those of the diagonal blocks alone:
+// structurally symmetric and free of triples of mutual neighbours (P = ZL: a mesh of triangles or
+// quads without corner links), with at most CL strictly lower and CU strictly upper blocks a row.
+// Then pair u of the row is its lower block u with the block (k, i) of column k, entry lrow[i] + u of
+// the pair lists, and U_ij = A_ij above the diagonal.
+// Bound by latency in factor_sweep_row, whose chain of dependent loads is about twelve long (row
+// pointers, columns, diagonal positions, pairs, blocks, the row's own L_ik read back, one block or
+// pair after the other). Here the loads form three levels: row pointers; the row's blocks and index
+// entries; the gathered blocks. The arithmetic on every block, and its order, is that of
+// factor_sweep_row.
+//   LSRC  where L_ik of the diagonal update comes from: A (first synchronous sweep), the previous
+//         iterate XP, or this sweep (in place)
+//   FROM_A  first sweep from X0 = A: U_kj and the inverses U_jj^{-1} come from A
+enum { L_FROM_A0 = 0, L_FROM_PREV = 1, L_FROM_NEW = 2 };
+struct FvPattern {
+    int n, ZL;
+    const int32_t *rowptr, *lrow, *urow, *lcol, *ldiag, *pkj, *skj;
+};
+template <typename T, int LSRC, bool FROM_A, int CL, int CU>
+__device__ __forceinline__ void factor_sweep_fv_row(int i, const FvPattern &P, const double *__restrict__ A,
+                                                    const T *XP, const T *Dp, T *Xn, T *Dn, unsigned *flags) {
+    const int r = threadIdx.x & 3;
+    if (i >= P.n) return;
+    const int b0 = P.rowptr[i], b1 = P.rowptr[i + 1], lb = P.lrow[i], nl = P.lrow[i + 1] - lb, ub = P.urow[i];
+    const int d = b0 + nl, nu = b1 - d - 1;
+    // the row's blocks and index entries (unused slots read the diagonal block's)
+    int jd[CL], jc[CL], pk[CL];
+    using LV = typename std::conditional<FROM_A, double, T>::type;
+    double aL[CL][4], aD[4], aU[CU][4];
+    T xl[LSRC == L_FROM_PREV ? CL : 1][4];
+#pragma unroll
+    for (int u = 0; u < CL; ++u) {
+        const int e = lb + min(u, max(nl - 1, 0));
+        if constexpr (FROM_A) {
+            const int q = P.ldiag[e], k = P.pkj[e];
+            jd[u] = u < nl ? q : d;
+            pk[u] = u < nl ? k : d;
+        } else {
+            const int q = P.lcol[e], k = P.skj[e];
+            jc[u] = u < nl ? q : i;
+            pk[u] = u < nl ? k : P.ZL + i;
+        }
+    }
+#pragma unroll
+    for (int u = 0; u < CL; ++u) load_row(A + (int64_t)(b0 + min(u, nl)) * BB, r, aL[u]);
+    load_row(A + (int64_t)d * BB, r, aD);
+    if constexpr (LSRC == L_FROM_PREV) {
+#pragma unroll
+        for (int u = 0; u < CL; ++u) load_row(XP + (int64_t)(u < nl ? lb + u : P.ZL + i) * BB, r, xl[u]);
+    }
+    // the gathered blocks: U_kk^{-1} (or A_kk, to be inverted) and U_ki
+    LV dj[CL][4], uk[CL][4];
+#pragma unroll
+    for (int u = 0; u < CL; ++u) {
+        if constexpr (FROM_A) {
+            load_row(A + (int64_t)jd[u] * BB, r, dj[u]);
+            load_row(A + (int64_t)pk[u] * BB, r, uk[u]);
+        } else {
+            load_row(Dp + (int64_t)jc[u] * BB, r, dj[u]);
+            load_row(XP + (int64_t)pk[u] * BB, r, uk[u]);
+        }
+    }
+#pragma unroll
+    for (int w = 0; w < CU; ++w) load_row(A + (int64_t)(d + min(w + 1, nu)) * BB, r, aU[w]);
+    unsigned fl = 0;
+    T t[4];
+#pragma unroll
+    for (int c = 0; c < 4; ++c) t[c] = (T)aD[c];
+    // a row without upper blocks has its A_ii inverted by no other row: raise the flag here
+    if (FROM_A && nu == 0 && !surely_invertible(t, r)) {
+        T unused[4];
+        if (!inv4_row(t, r, unused)) fl |= ABILU_FLAG_MODIFIED;
+    }
+#pragma unroll
+    for (int u = 0; u < CL; ++u) {
+        if (u < nl) {
+            T a[4], D[4], v[4], x[4];
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                a[c] = (T)aL[u][c];
+                D[c] = (T)dj[u][c];
+                v[c] = (T)uk[u][c];
+            }
+            if constexpr (FROM_A) {
+                T Di[4];
+                if (!inv4_row(D, r, Di)) fl |= ABILU_FLAG_MODIFIED;
+                row_times_block(a, Di, x);
+            } else {
+                row_times_block(a, D, x);
+            }
+            fl |= nonfinite4(x);
+            store_row(Xn + (int64_t)(lb + u) * BB, r, x);
+            if constexpr (LSRC == L_FROM_A0) row_times_block_sub(a, v, t);
+            else if constexpr (LSRC == L_FROM_PREV) row_times_block_sub(xl[u], v, t);
+            else row_times_block_sub(x, v, t);
+        }
+    }
+    fl |= nonfinite4(t);
+    store_row(Xn + ((int64_t)P.ZL + i) * BB, r, t);
+    T out[4];
+    if (!inv4_row(t, r, out)) fl |= ABILU_FLAG_MODIFIED;
+    store_row(Dn + (int64_t)i * BB, r, out);
+#pragma unroll
+    for (int w = 0; w < CU; ++w) {
+        if (w < nu) {
+            T v[4];
+#pragma unroll
+            for (int c = 0; c < 4; ++c) v[c] = (T)aU[w][c];
+            fl |= nonfinite4(v);
+            store_row(Xn + ((int64_t)P.ZL + P.n + ub + w) * BB, r, v);
         }
     }
     if (fl) atomicOr(flags, fl);
@@ -987,9 +1098,8 @@ __device__ __forceinline__ void factor_chunk_row(int i, int c0, int ubound,
         update_terms_chunk<T, OUT_FROM_A, PAIR2>(pair_ptr[d], pair_ptr[d + 1], r, ubound, pkj, sik, skj, A, Xn, XO, t);
         fl |= nonfinite4(t);
         store_row(Xn + ((int64_t)ZL + i) * BB, r, t);
-        T M[16], out[4];
-        gather_block(t, M);
-        if (!inv4_row(M, r, out)) fl |= ABILU_FLAG_MODIFIED;
+        T out[4];
+        if (!inv4_row_gathered(t, r, out)) fl |= ABILU_FLAG_MODIFIED;
         store_row(Dn + (int64_t)i * BB, r, out);
     }
     // strictly upper blocks: U_ij = A_ij - sum (independent of each other)

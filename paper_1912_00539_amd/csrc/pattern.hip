@@ -38,13 +38,13 @@ __global__ void k_pat_tri_counts(int n, const int32_t *__restrict__ rowptr, cons
 __global__ void k_pat_tri_cols(int n, const int32_t *__restrict__ rowptr, const int32_t *__restrict__ colidx,
                                const int32_t *__restrict__ diag_pos, const int32_t *__restrict__ lrow,
                                const int32_t *__restrict__ urow, int32_t *__restrict__ lcol,
-                               int32_t *__restrict__ ucol) {
-    pat_tri_cols_body(blockIdx.x, n, rowptr, colidx, diag_pos, lrow, urow, lcol, ucol);
+                               int32_t *__restrict__ ldiag, int32_t *__restrict__ ucol) {
+    pat_tri_cols_body(blockIdx.x, n, rowptr, colidx, diag_pos, lrow, urow, lcol, ldiag, ucol);
 }
 
 __global__ void k_pat_sym(int n, const int32_t *__restrict__ rowptr, const int32_t *__restrict__ colidx,
-                          unsigned *__restrict__ asym) {
-    pat_sym_body(blockIdx.x, n, rowptr, colidx, asym);
+                          const int32_t *__restrict__ diag_pos, unsigned *__restrict__ shape) {
+    pat_sym_body(blockIdx.x, n, rowptr, colidx, diag_pos, shape);
 }
 
 void free_pattern(abilu_pattern *p) {
@@ -146,14 +146,15 @@ abilu_status pattern_count(int32_t n, int64_t Z, const int32_t *rowptr, const in
 // still hold what pattern_count left there).
 abilu_status pattern_fill(int32_t n, int64_t Z, int64_t ZL, int64_t ZU, int64_t npairs, const int32_t *rowptr,
                           const int32_t *colidx, const int32_t *diag_pos, const int32_t *lrow, const int32_t *urow,
-                          int32_t *lcol, int32_t *ucol, int32_t *pik, int32_t *pkj, int32_t *sik, int32_t *skj,
-                          const void *scratch, hipStream_t s) {
+                          int32_t *lcol, int32_t *ldiag, int32_t *ucol, int32_t *pik, int32_t *pkj, int32_t *sik,
+                          int32_t *skj, const void *scratch, hipStream_t s) {
     const int64_t *ptr64 = pat_scratch(const_cast<void *>(scratch), n, Z).ptr64;
-    if (!hip_ok(hipMemsetAsync(lcol, 0, sizeof(int32_t) * (ZL + 1), s), "lcol clear") ||
+    // ldiag follows lcol
+    if (!hip_ok(hipMemsetAsync(lcol, 0, sizeof(int32_t) * 2 * (ZL + 1), s), "lcol clear") ||
         !hip_ok(hipMemsetAsync(ucol, 0, sizeof(int32_t) * (ZU + 1), s), "ucol clear"))
         return ABILU_EDEVICE;
     if (n > 0) {
-        k_pat_tri_cols<<<div_up(n, 256), 256, 0, s>>>(n, rowptr, colidx, diag_pos, lrow, urow, lcol, ucol);
+        k_pat_tri_cols<<<div_up(n, 256), 256, 0, s>>>(n, rowptr, colidx, diag_pos, lrow, urow, lcol, ldiag, ucol);
         if (launch_status() != ABILU_OK) return ABILU_EDEVICE;
     }
     if (n > 0 && npairs > 0) {
@@ -226,27 +227,30 @@ extern "C" abilu_status abilu_build_pattern(int32_t nbrows, const int32_t *d_row
         p->nnzb_lower = ZL;
         p->nnzb_upper = ZU;
         p->npairs = npairs;
-        CKA(hipMalloc(&p->lcol, sizeof(int32_t) * (ZL + 1)));
+        CKA(hipMalloc(&p->lcol, sizeof(int32_t) * 2 * (ZL + 1)));
+        p->ldiag = p->lcol + (ZL + 1);
         CKA(hipMalloc(&p->ucol, sizeof(int32_t) * (ZU + 1)));
         CKA(hipMalloc(&p->pik, sizeof(int32_t) * (npairs + 1)));
         CKA(hipMalloc(&p->pkj, sizeof(int32_t) * (npairs + 1)));
         CKA(hipMalloc(&p->sik, sizeof(int32_t) * (npairs + 1)));
         CKA(hipMalloc(&p->skj, sizeof(int32_t) * (npairs + 1)));
         st = pattern_fill(n, Z, ZL, ZU, npairs, p->rowptr, p->colidx, p->diag_pos, p->lrow, p->urow, p->lcol,
-                          p->ucol, p->pik, p->pkj, p->sik, p->skj, scratch, s);
+                          p->ldiag, p->ucol, p->pik, p->pkj, p->sik, p->skj, scratch, s);
         if (st != ABILU_OK) goto fail;
-        // structural symmetry (the first factor sweep from A uses it to find the rows whose initial
-        // inverse no other row forms)
+        // structural symmetry and the longest rows (the factor sweeps choose their form by them)
         {
-            unsigned *asym = (unsigned *)scratch;
-            CK(hipMemsetAsync(asym, 0, sizeof(unsigned), s));
+            unsigned *shape = (unsigned *)scratch;
+            CK(hipMemsetAsync(shape, 0, 3 * sizeof(unsigned), s));
             if (n > 0) {
-                k_pat_sym<<<div_up(n, 256), 256, 0, s>>>(n, p->rowptr, p->colidx, asym);
+                k_pat_sym<<<div_up(n, 256), 256, 0, s>>>(n, p->rowptr, p->colidx, p->diag_pos, shape);
                 CK(hipGetLastError());
             }
-            CK(hipMemcpyAsync(p->pinned, asym, sizeof(unsigned), hipMemcpyDeviceToHost, s));
+            CK(hipMemcpyAsync(p->pinned, shape, 3 * sizeof(unsigned), hipMemcpyDeviceToHost, s));
             CK(hipStreamSynchronize(s));
-            p->symmetric = *(const unsigned *)p->pinned == 0;
+            const unsigned *h = (const unsigned *)p->pinned;
+            p->symmetric = h[0] == 0;
+            p->max_lower = (int32_t)h[1];
+            p->max_upper = (int32_t)h[2];
         }
     }
     (void)hipFree(scratch);

@@ -46,7 +46,7 @@ size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 struct Slot {
     int32_t n, ZL, nb_vec, pad;
     int64_t nv;
-    const int32_t *rowptr, *colidx, *diag_pos, *pair_ptr, *pik, *pkj, *sik, *skj, *lrow, *urow, *lcol, *ucol;
+    const int32_t *rowptr, *colidx, *diag_pos, *pair_ptr, *pik, *pkj, *sik, *skj, *lrow, *urow, *lcol, *ldiag, *ucol;
     const double *A, *b;
     double *x;
     void *LU, *Dinv, *X1, *D1, *ya, *yb, *za, *zb;
@@ -130,6 +130,17 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(sweep_waves<
     factor_sweep_body<T, LA, UA, DA>(blk, S.n, S.ZL, S.rowptr, S.colidx, S.diag_pos, S.lrow, S.urow, S.pair_ptr, S.pik,
                                  S.pkj, S.sik, S.skj, S.A, Xin, UA ? (const T *)nullptr : Xin,
                                  fbuf_d<T>(S, sel & 2), fbuf_x<T>(S, sel & 4), fbuf_d<T>(S, sel & 8), S.flags);
+}
+
+// The row-at-once form, where every member of the group has diagonal update sets only (the generated
+// meshes are structurally symmetric and have at most three neighbours of lower and of higher index).
+template <typename T, int LSRC, bool FROM_A>
+__global__ __launch_bounds__(WG) void kb_factor_sweep_fv(const Slot *slots, const Member *mem, int nmem, int sel) {
+    MEMBER();
+    const FvPattern P{S.n, S.ZL, S.rowptr, S.lrow, S.urow, S.lcol, S.ldiag, S.pkj, S.skj};
+    factor_sweep_fv_row<T, LSRC, FROM_A, FV_CAP, FV_CAP>(
+        blk * ROWS_PER_WG + (threadIdx.x >> 2), P, S.A, FROM_A ? (const T *)nullptr : fbuf_x<T>(S, sel & 1),
+        fbuf_d<T>(S, sel & 2), fbuf_x<T>(S, sel & 4), fbuf_d<T>(S, sel & 8), S.flags);
 }
 
 template <typename T, typename YI, bool EMIT_Z>
@@ -231,7 +242,7 @@ struct SetupDesc {
     int64_t Z;
     double cfl;
     uint64_t seed;
-    int32_t *rowptr, *colidx, *diag_pos, *lrow, *urow, *lcol, *ucol, *pair_ptr, *pik, *pkj, *sik, *skj;
+    int32_t *rowptr, *colidx, *diag_pos, *lrow, *urow, *lcol, *ldiag, *ucol, *pair_ptr, *pik, *pkj, *sik, *skj;
     double *A, *b;
     int64_t *cnt, *ptr64, *tot;   // scratch: 2 x (Z + n + 2) + tiles + 1 int64
     int32_t slot, pad;
@@ -313,7 +324,7 @@ __global__ void kbs_pat_count(const SetupDesc *sd, const Member *mem, int nmem) 
 
 __global__ void kbs_pat_tri_cols(const SetupDesc *sd, const Member *mem, int nmem, const int64_t *adm) {
     SMEMBER();
-    abilu_setup::pat_tri_cols_body(blk, D.n, D.rowptr, D.colidx, D.diag_pos, D.lrow, D.urow, D.lcol, D.ucol);
+    abilu_setup::pat_tri_cols_body(blk, D.n, D.rowptr, D.colidx, D.diag_pos, D.lrow, D.urow, D.lcol, D.ldiag, D.ucol);
     if (blk == 0 && threadIdx.x == 0) {   // the padding entry after each part
         D.lcol[adm[4 * m_ + SC_LROW]] = 0;
         D.ucol[adm[4 * m_ + SC_UROW]] = 0;
@@ -392,7 +403,7 @@ struct Pool {
 // byte offsets of one request's arrays inside its pool block (NONE: not allocated)
 constexpr size_t NONE = ~(size_t)0;
 struct ReqLayout {
-    size_t rowptr, colidx, diag_pos, pair_ptr, lrow, urow, lcol, ucol, pik, pkj, sik, skj;
+    size_t rowptr, colidx, diag_pos, pair_ptr, lrow, urow, lcol, ldiag, ucol, pik, pkj, sik, skj;
     size_t A, b, x, LU, Dinv, X1, D1, ya, yb, za, zb;
     size_t partials, H, cs, sn, g, coef, misc, vscale, red, V, Z, scratch;
     size_t total;
@@ -428,6 +439,7 @@ ReqLayout req_layout(const abilu_serve_config &c, int32_t n, int64_t Z, size_t g
     L.lrow = take(4 * (size_t)(n + 1));
     L.urow = take(4 * (size_t)(n + 1));
     L.lcol = take(4 * (size_t)(L.zcap + 1));
+    L.ldiag = take(4 * (size_t)(L.zcap + 1));
     L.ucol = take(4 * (size_t)(L.zcap + 1));
     L.pik = take(4 * (size_t)(L.pcap + 1));
     L.pkj = take(4 * (size_t)(L.pcap + 1));
@@ -606,6 +618,7 @@ void stage_request(abilu_server *s, Req &r, int m) {
     D.lrow = (int32_t *)P(L.lrow);
     D.urow = (int32_t *)P(L.urow);
     D.lcol = (int32_t *)P(L.lcol);
+    D.ldiag = (int32_t *)P(L.ldiag);
     D.ucol = (int32_t *)P(L.ucol);
     D.pair_ptr = (int32_t *)P(L.pair_ptr);
     D.pik = (int32_t *)P(L.pik);
@@ -636,6 +649,7 @@ void stage_request(abilu_server *s, Req &r, int m) {
     d.lrow = D.lrow;
     d.urow = D.urow;
     d.lcol = D.lcol;
+    d.ldiag = D.ldiag;
     d.ucol = D.ucol;
     d.A = D.A;
     d.b = D.b;
@@ -907,6 +921,15 @@ abilu_status run_group(abilu_server *s, Group &G, hipStream_t st) {
     };
     abilu_status e;
     if (G.st == Q_FACTOR) {
+        bool fv = true;
+        for (int64_t id : G.ids) fv = fv && s->reqs[id].P == s->reqs[id].ZL;
+        auto sweep = [&](auto la, auto ua, int sel) {
+            constexpr bool LA = decltype(la)::value, UA = decltype(ua)::value;
+            constexpr int LSRC = LA ? L_FROM_A0 : L_FROM_NEW;
+            if (!fv) kb_factor_sweep<T, LA, UA, UA><<<L_(SH_ROW64)>>>(A_(SH_ROW64), sel);
+            else if (LA || !sync) kb_factor_sweep_fv<T, LSRC, UA><<<L_(SH_ROW64)>>>(A_(SH_ROW64), sel);
+            else if constexpr (!UA) kb_factor_sweep_fv<T, L_FROM_PREV, UA><<<L_(SH_ROW64)>>>(A_(SH_ROW64), sel);
+        };
         if (fsw == 0) {
             if ((e = init(true, 0)) != ABILU_OK) return e;
         } else if (!sync) {
@@ -914,13 +937,13 @@ abilu_status run_group(abilu_server *s, Group &G, hipStream_t st) {
             {
                 ProfScope ps("serve_factor_sweep_fromA", st,
                              B([&](const Sizes &z, const Req &) { return bytes_sweep_from_a(z, sF, false); }));
-                kb_factor_sweep<T, false, true, true><<<L_(SH_ROW64)>>>(A_(SH_ROW64), 0);
+                sweep(std::false_type{}, std::true_type{}, 0);
             }
             CKL();
             for (int q = 1; q < fsw; ++q) {
                 ProfScope ps("serve_factor_sweep", st,
                              B([&](const Sizes &z, const Req &) { return bytes_sweep(z, sF, false, false); }));
-                kb_factor_sweep<T, false, false><<<L_(SH_ROW64)>>>(A_(SH_ROW64), 0);
+                sweep(std::false_type{}, std::false_type{}, 0);
                 CKL();
             }
         } else {
@@ -930,15 +953,14 @@ abilu_status run_group(abilu_server *s, Group &G, hipStream_t st) {
             {
                 ProfScope ps("serve_factor_sweep_fromA", st,
                              B([&](const Sizes &z, const Req &) { return bytes_sweep_from_a(z, sF, true); }));
-                kb_factor_sweep<T, true, true, true>
-                    <<<L_(SH_ROW64)>>>(A_(SH_ROW64), (one(0) ? 2 : 0) | (one(1) ? 4 : 0) | (one(1) ? 8 : 0));
+                sweep(std::true_type{}, std::true_type{}, (one(0) ? 2 : 0) | (one(1) ? 4 : 0) | (one(1) ? 8 : 0));
             }
             CKL();
             for (int q = 2; q <= fsw; ++q) {
                 const int sel = (one(q - 1) ? 3 : 0) | (one(q) ? 12 : 0);
                 ProfScope ps("serve_factor_sweep", st,
                              B([&](const Sizes &z, const Req &) { return bytes_sweep(z, sF, false, false); }));
-                kb_factor_sweep<T, false, false><<<L_(SH_ROW64)>>>(A_(SH_ROW64), sel);
+                sweep(std::false_type{}, std::false_type{}, sel);
                 CKL();
             }
         }

@@ -244,15 +244,27 @@ __device__ __forceinline__ void pat_fill_body(int blk, int n, int ZL, const int3
     }
 }
 
-// structural symmetry: one thread per block row; sets *asym when some (i,j) in S_B has no (j,i)
+// structural symmetry: one thread per block row; sets shape[0] when some (i,j) in S_B has no (j,i).
+// shape[1], shape[2]: the most strictly lower and upper blocks of a row.
 __device__ __forceinline__ void pat_sym_body(int blk, int n, const int32_t *__restrict__ rowptr,
-                                             const int32_t *__restrict__ colidx, unsigned *__restrict__ asym) {
+                                             const int32_t *__restrict__ colidx, const int32_t *__restrict__ diag_pos,
+                                             unsigned *__restrict__ shape) {
     int i = blk * blockDim.x + threadIdx.x;
+    int nl = i < n ? diag_pos[i] - rowptr[i] : 0, nu = i < n ? rowptr[i + 1] - diag_pos[i] - 1 : 0;
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+        nl = max(nl, __shfl_xor(nl, o, 64));
+        nu = max(nu, __shfl_xor(nu, o, 64));
+    }
+    if ((threadIdx.x & 63) == 0) {   // a read first: after the first few wavefronts it holds the maximum
+        if ((unsigned)nl > shape[1]) atomicMax(shape + 1, (unsigned)nl);
+        if ((unsigned)nu > shape[2]) atomicMax(shape + 2, (unsigned)nu);
+    }
     if (i >= n) return;
     for (int e = rowptr[i]; e < rowptr[i + 1]; ++e) {
         const int j = colidx[e];
         if (j != i && find_col(rowptr, colidx, j, i) < 0) {
-            atomicOr(asym, 1u);
+            atomicOr(shape, 1u);
             return;
         }
     }
@@ -267,15 +279,20 @@ __device__ __forceinline__ void pat_tri_counts_body(int blk, int n, const int32_
     nu[i] = rowptr[i + 1] - diag_pos[i] - 1;
 }
 
-// columns of the lower and upper parts in factor-layout order
+// columns of the lower and upper parts in factor-layout order, and where the diagonal blocks of the
+// lower columns lie
 __device__ __forceinline__ void pat_tri_cols_body(int blk, int n, const int32_t *__restrict__ rowptr, const int32_t *__restrict__ colidx,
                                const int32_t *__restrict__ diag_pos, const int32_t *__restrict__ lrow,
                                const int32_t *__restrict__ urow, int32_t *__restrict__ lcol,
-                               int32_t *__restrict__ ucol) {
+                               int32_t *__restrict__ ldiag, int32_t *__restrict__ ucol) {
     int i = blk * blockDim.x + threadIdx.x;
     if (i >= n) return;
     const int b0 = rowptr[i], d = diag_pos[i], b1 = rowptr[i + 1];
-    for (int e = b0; e < d; ++e) lcol[lrow[i] + (e - b0)] = colidx[e];
+    for (int e = b0; e < d; ++e) {
+        const int j = colidx[e];
+        lcol[lrow[i] + (e - b0)] = j;
+        ldiag[lrow[i] + (e - b0)] = diag_pos[j];
+    }
     for (int e = d + 1; e < b1; ++e) ucol[urow[i] + (e - d - 1)] = colidx[e];
 }
 
