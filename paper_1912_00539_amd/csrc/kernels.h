@@ -265,6 +265,154 @@ __device__ __forceinline__ void bwd_body(int blk, int n, const int32_t *__restri
                                        zin, zout, zout2, rs);
 }
 
+// The tile of workgroup b of g (a multiple of 8) when each XCD takes one contiguous eighth of the
+// tiles: workgroup b runs on XCD b mod 8.
+__device__ __forceinline__ int xcd_tile(int b, int g) { return (b & 7) * (g >> 3) + (b >> 3); }
+inline int xcd_grid(int tiles) { return (tiles + 7) / 8 * 8; }
+
+// Two forward sweeps in one, for rows of at most CL strictly lower blocks: row i of the second sweep
+// needs y_j of the first for its lower neighbours j, and forms each again from its own row,
+// y_j = r_j - sum_k L_jk yin_k. Same operations on each element, so the bits of two synchronous
+// sweeps; as an asynchronous iteration it is the schedule in which no read of the second sweep sees
+// a value written in it.
+// A small mesh spends a launch and a chain of three loads on a sweep (here five loads and one launch
+// for both); a large one reads L once instead of twice, if the neighbours' rows are still in the L2
+// of the same XCD, hence xcd_tile. Forward and backward together, three sweeps, us: 2,000 triangles
+// 19 -> 11.5 (two launches for four); 61,952 FP64 21.2 -> 16.1; 180,000 FP32 29.8 -> 24.0; 500,000
+// line-ordered quads FP32 87.6 -> 73.9 (94.3 without xcd_tile); 2 million FP64 628 -> 471.
+template <typename T, typename YI, bool EMIT_Z, int CL>
+__device__ __forceinline__ void fwd_pair_row(int i, int n, const int32_t *__restrict__ lrow,
+                                             const int32_t *__restrict__ lcol, const T *__restrict__ Lb,
+                                             const double *__restrict__ rhs, const YI *__restrict__ yin,
+                                             T *__restrict__ yout, const T *__restrict__ Dinv, T *__restrict__ zout,
+                                             double rs, double ys) {
+    const int r = threadIdx.x & 3;
+    if (i >= n) return;
+    const int b0 = lrow[i], nl = lrow[i + 1] - b0;
+    T acc = (T)scaled(rhs[(int64_t)i * 4 + r], rs);
+    int j[CL], c0[CL], nj[CL];
+    T l[CL][4], yj[CL], m[CL][CL][4], yk[CL][CL];
+#pragma unroll
+    for (int u = 0; u < CL; ++u) {
+        if (u < nl) {
+            j[u] = lcol[b0 + u];
+            load_row(Lb + (int64_t)(b0 + u) * BB, r, l[u]);
+        }
+    }
+#pragma unroll
+    for (int u = 0; u < CL; ++u) {
+        if (u < nl) {
+            c0[u] = lrow[j[u]];
+            nj[u] = lrow[j[u] + 1] - c0[u];
+            yj[u] = (T)scaled(rhs[(int64_t)j[u] * 4 + r], rs);
+        }
+    }
+    T dr[4];
+    if constexpr (EMIT_Z) load_row(Dinv + (int64_t)i * BB, r, dr);
+#pragma unroll
+    for (int u = 0; u < CL; ++u) {
+        if (u < nl) {
+#pragma unroll
+            for (int v = 0; v < CL; ++v) {
+                if (v < nj[u]) {
+                    const int k = lcol[c0[u] + v];
+                    load_row(Lb + (int64_t)(c0[u] + v) * BB, r, m[u][v]);
+                    if constexpr (sizeof(YI) == 8) yk[u][v] = (T)scaled(yin[(int64_t)k * 4 + r], ys);
+                    else yk[u][v] = (T)yin[(int64_t)k * 4 + r];
+                }
+            }
+        }
+    }
+#pragma unroll
+    for (int u = 0; u < CL; ++u) {
+        if (u < nl) {
+#pragma unroll
+            for (int v = 0; v < CL; ++v) {
+                if (v < nj[u]) {
+                    T y[4];
+                    gather_vec(yk[u][v], y);
+                    yj[u] -= dot4(m[u][v][0], y[0], m[u][v][1], y[1], m[u][v][2], y[2], m[u][v][3], y[3]);
+                }
+            }
+            T y[4];
+            gather_vec(yj[u], y);
+            acc -= dot4(l[u][0], y[0], l[u][1], y[1], l[u][2], y[2], l[u][3], y[3]);
+        }
+    }
+    yout[(int64_t)i * 4 + r] = acc;
+    if constexpr (EMIT_Z) {
+        T y[4];
+        gather_vec(acc, y);
+        zout[(int64_t)i * 4 + r] = dot4(dr[0], y[0], dr[1], y[1], dr[2], y[2], dr[3], y[3]);
+    }
+}
+
+// Two backward sweeps in one, likewise (rows of at most CU strictly upper blocks):
+// z_j = D_j (y_j - sum_k U_jk zin_k) for the upper neighbours j, then z_i from them.
+template <typename T, typename ZO, int CU>
+__device__ __forceinline__ void bwd_pair_row(int i, int n, const int32_t *__restrict__ urow,
+                                             const int32_t *__restrict__ ucol, const T *__restrict__ Ub,
+                                             const T *__restrict__ Dinv, const T *__restrict__ y,
+                                             const T *__restrict__ zin, ZO *__restrict__ zout) {
+    const int r = threadIdx.x & 3;
+    if (i >= n) return;
+    const int b0 = urow[i], nu = urow[i + 1] - b0;
+    T acc = y[(int64_t)i * 4 + r];
+    int j[CU], c0[CU], nj[CU];
+    T l[CU][4], yj[CU], dj[CU][4], m[CU][CU][4], zk[CU][CU], dr[4];
+#pragma unroll
+    for (int u = 0; u < CU; ++u) {
+        if (u < nu) {
+            j[u] = ucol[b0 + u];
+            load_row(Ub + (int64_t)(b0 + u) * BB, r, l[u]);
+        }
+    }
+    load_row(Dinv + (int64_t)i * BB, r, dr);
+#pragma unroll
+    for (int u = 0; u < CU; ++u) {
+        if (u < nu) {
+            c0[u] = urow[j[u]];
+            nj[u] = urow[j[u] + 1] - c0[u];
+            yj[u] = y[(int64_t)j[u] * 4 + r];
+            load_row(Dinv + (int64_t)j[u] * BB, r, dj[u]);
+        }
+    }
+#pragma unroll
+    for (int u = 0; u < CU; ++u) {
+        if (u < nu) {
+#pragma unroll
+            for (int v = 0; v < CU; ++v) {
+                if (v < nj[u]) {
+                    const int k = ucol[c0[u] + v];
+                    load_row(Ub + (int64_t)(c0[u] + v) * BB, r, m[u][v]);
+                    zk[u][v] = zin[(int64_t)k * 4 + r];
+                }
+            }
+        }
+    }
+#pragma unroll
+    for (int u = 0; u < CU; ++u) {
+        if (u < nu) {
+#pragma unroll
+            for (int v = 0; v < CU; ++v) {
+                if (v < nj[u]) {
+                    T z[4];
+                    gather_vec(zk[u][v], z);
+                    yj[u] -= dot4(m[u][v][0], z[0], m[u][v][1], z[1], m[u][v][2], z[2], m[u][v][3], z[3]);
+                }
+            }
+            T a[4], z[4];
+            gather_vec(yj[u], a);
+            const T zj = dot4(dj[u][0], a[0], dj[u][1], a[1], dj[u][2], a[2], dj[u][3], a[3]);
+            gather_vec(zj, z);
+            acc -= dot4(l[u][0], z[0], l[u][1], z[1], l[u][2], z[2], l[u][3], z[3]);
+        }
+    }
+    T a[4];
+    gather_vec(acc, a);
+    zout[(int64_t)i * 4 + r] = (ZO)dot4(dr[0], a[0], dr[1], a[1], dr[2], a[2], dr[3], a[3]);
+}
+
 template <bool RESID>
 __device__ __forceinline__ void spmv_body(int blk, int n, const int32_t *__restrict__ rowptr,
                                              const int32_t *__restrict__ colidx, const double *__restrict__ A,

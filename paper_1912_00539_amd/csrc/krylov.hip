@@ -402,9 +402,10 @@ extern "C" abilu_status fgmres_solve(const abilu_pattern *p, const double *d_A, 
     bool converged = false, nonfinite = false;
     // The status of the launches so far (the start's, a cycle's or an Arnoldi step's), not yet read.
     // An Arnoldi step's application may begin before: it stops at the first launch after which the
-    // status says that it is not needed, and has then written scratch vectors only. Ahead of the
-    // status at most `ahead` sweeps are launched: enough to cover the 6-8 us between the status
-    // being written and the next launch arriving, and none where a needless sweep costs more.
+    // status says that it is not needed, and has then written scratch vectors only (or a z_k that
+    // nothing reads). Ahead of the status at most `limit` kernels are launched: enough to cover the
+    // 6-8 us between the status being written and the next launch arriving, and none where a needless
+    // sweep costs more.
     enum { START, CYCLE, STEP };
     struct Pending : Gate {
         Ctx &c;

@@ -152,6 +152,36 @@ __global__ __launch_bounds__(WG) void kb_fwd(const Slot *slots, const Member *me
                             yin == R_VK ? rs : 1.0);
 }
 
+// Two sweeps in one launch (fwd_pair_row, bwd_pair_row; three blocks a side hold every generated
+// mesh's rows). The launch's tiles are dealt to the XCDs in contiguous eighths; its grid is a multiple
+// of 8, and the workgroups past the last of `tiles` end at once.
+template <typename T, typename YI, bool EMIT_Z>
+__global__ __launch_bounds__(WG) void kb_fwd_pair(const Slot *slots, const Member *mem, int nmem, int tiles, int yin,
+                                                  int yout) {
+    const int b = xcd_tile(blockIdx.x, gridDim.x);
+    if (b >= tiles) return;
+    const Member M = mem[find_member(mem, nmem, b)];
+    const Slot &S = slots[M.slot];
+    const double rs = S.vscale[M.k];
+    fwd_pair_row<T, YI, EMIT_Z, FV_CAP>((b - M.tile0) * ROWS_PER_WG + (threadIdx.x >> 2), S.n, S.lrow, S.lcol,
+                                        (const T *)S.LU, (const double *)role(S, M, R_VK),
+                                        (const YI *)role(S, M, yin), (T *)role(S, M, yout), (const T *)S.Dinv,
+                                        (T *)S.za, rs, yin == R_VK ? rs : 1.0);
+}
+
+template <typename T, typename ZO>
+__global__ __launch_bounds__(WG) void kb_bwd_pair(const Slot *slots, const Member *mem, int nmem, int tiles, int y,
+                                                  int zin, int zout, int desc) {
+    const int b = xcd_tile(desc ? (int)(gridDim.x - 1 - blockIdx.x) : (int)blockIdx.x, gridDim.x);
+    if (b >= tiles) return;
+    const Member M = mem[find_member(mem, nmem, b)];
+    const Slot &S = slots[M.slot];
+    const T *Ub = (const T *)S.LU + ((int64_t)S.ZL + S.n) * BB;
+    bwd_pair_row<T, ZO, FV_CAP>((b - M.tile0) * ROWS_PER_WG + (threadIdx.x >> 2), S.n, S.urow, S.ucol, Ub,
+                                (const T *)S.Dinv, (const T *)role(S, M, y), (const T *)role(S, M, zin),
+                                (ZO *)role(S, M, zout));
+}
+
 template <typename T, typename YI, typename ZO, bool OFFDIAG, bool DUAL>
 __global__ __launch_bounds__(WG) void kb_bwd(const Slot *slots, const Member *mem, int nmem, int y, int zin, int zout,
                                              int desc) {
@@ -454,8 +484,9 @@ ReqLayout req_layout(const abilu_serve_config &c, int32_t n, int64_t Z, size_t g
     L.D1 = (sync && c.factor_sweeps >= 1) ? take(16 * sF * (size_t)n) : NONE;
     L.ya = take(sF * nv);
     L.za = take(sF * nv);
-    L.yb = sync ? take(sF * nv) : NONE;
-    L.zb = sync ? take(sF * nv) : NONE;
+    const bool two = sync || c.apply_sweeps >= 4;   // a second vector: synchronous sweeps, and pairs of sweeps after the first
+    L.yb = two ? take(sF * nv) : NONE;
+    L.zb = two ? take(sF * nv) : NONE;
     L.partials = take(8 * (m + 2) * (size_t)L.nb_vec);
     L.H = take(8 * (m + 1) * m);
     L.cs = take(8 * (m + 2));
@@ -894,9 +925,19 @@ abilu_status run_group(abilu_server *s, Group &G, hipStream_t st) {
         CKL();
         return ABILU_OK;
     };
-    auto fwd = [&](const char *name, bool yin_f64, bool emit, int yin, int yout) -> abilu_status {
+    bool fv = true;   // diagonal update sets only, as the generated meshes have
+    for (int64_t id : G.ids) fv = fv && s->reqs[id].P == s->reqs[id].ZL;
+#define P_() dim3(xcd_grid(G.t[SH_ROW64].tiles)), dim3(WG), 0, st
+    auto fwd = [&](const char *name, bool pair, bool yin_f64, bool emit, int yin, int yout) -> abilu_status {
         ProfScope ps(name, st, B([&](const Sizes &z, const Req &) { return bytes_fwd(z, sF, yin_f64 ? 8 : sF, emit); }));
-        if (yin_f64) {
+        const int tiles = G.t[SH_ROW64].tiles;
+        if (pair && yin_f64) {
+            if (emit) kb_fwd_pair<T, double, true><<<P_()>>>(A_(SH_ROW64), tiles, yin, yout);
+            else kb_fwd_pair<T, double, false><<<P_()>>>(A_(SH_ROW64), tiles, yin, yout);
+        } else if (pair) {
+            if (emit) kb_fwd_pair<T, T, true><<<P_()>>>(A_(SH_ROW64), tiles, yin, yout);
+            else kb_fwd_pair<T, T, false><<<P_()>>>(A_(SH_ROW64), tiles, yin, yout);
+        } else if (yin_f64) {
             if (emit) kb_fwd<T, double, true><<<L_(SH_APPLY)>>>(A_(SH_APPLY), yin, yout);
             else kb_fwd<T, double, false><<<L_(SH_APPLY)>>>(A_(SH_APPLY), yin, yout);
         } else {
@@ -921,8 +962,6 @@ abilu_status run_group(abilu_server *s, Group &G, hipStream_t st) {
     };
     abilu_status e;
     if (G.st == Q_FACTOR) {
-        bool fv = true;
-        for (int64_t id : G.ids) fv = fv && s->reqs[id].P == s->reqs[id].ZL;
         auto sweep = [&](auto la, auto ua, int sel) {
             constexpr bool LA = decltype(la)::value, UA = decltype(ua)::value;
             constexpr int LSRC = LA ? L_FROM_A0 : L_FROM_NEW;
@@ -987,31 +1026,39 @@ abilu_status run_group(abilu_server *s, Group &G, hipStream_t st) {
             CKL();
         } else {
             // sweep 1 forward is y = v_k and sweep 1 backward z = Dinv y (emitted by the last forward
-            // sweep); ASYNC sweeps 2.. update in place, SYNC sweeps ping-pong
+            // sweep); ASYNC sweeps 2.. update in place, SYNC sweeps and pairs of sweeps ping-pong
+            const bool pairs = fv && nsw >= 3;
             int yprev = R_VK, ycur = R_YA;
             for (int q = 2; q <= nsw; ++q) {
-                ycur = (!sync || q % 2 == 0) ? R_YA : R_YB;
+                const bool from_r = q == 2, pair = pairs && q + 1 <= nsw;
+                ycur = pairs ? (yprev == R_YA ? R_YB : R_YA) : (!sync || q % 2 == 0) ? R_YA : R_YB;
+                if (pair) ++q;
                 const bool last = q == nsw;
-                if ((e = fwd(last ? "serve_apply_fwd_emitz" : "serve_apply_fwd", q == 2, last, yprev, ycur)) != ABILU_OK)
+                if ((e = fwd(last ? "serve_apply_fwd_emitz" : "serve_apply_fwd", pair, from_r, last, yprev, ycur)) != ABILU_OK)
                     return e;
                 yprev = ycur;
             }
             int zprev = R_ZA;
             for (int q = 2; q <= nsw; ++q) {
+                const bool pair = pairs && q + 1 <= nsw;
+                const int desc = q % 2 == 0;
+                if (pair) ++q;
                 const bool last = q == nsw;
-                const bool dual = last && !sync && q % 2 == 0;   // the in-place copy serves only a descending sweep
+                const bool dual = last && !sync && desc && !pairs;   // the in-place copy serves only a descending sweep
                 ProfScope ps(last ? "serve_apply_bwd_last" : "serve_apply_bwd", st,
                              B([&](const Sizes &z, const Req &) { return bytes_bwd(z, sF, last ? 8 : sF, dual); }));
-                if (last) {
-                    if (dual)
-                        kb_bwd<T, T, double, true, true><<<L_(SH_APPLY)>>>(A_(SH_APPLY), ycur, zprev, R_ZK, q % 2 == 0);
-                    else
-                        kb_bwd<T, T, double, true, false><<<L_(SH_APPLY)>>>(A_(SH_APPLY), ycur, zprev, R_ZK, q % 2 == 0);
-                } else {
-                    const int zcur = sync ? ((zprev == R_ZA) ? R_ZB : R_ZA) : R_ZA;
-                    kb_bwd<T, T, T, true, false><<<L_(SH_APPLY)>>>(A_(SH_APPLY), ycur, zprev, zcur, q % 2 == 0);
-                    zprev = zcur;
-                }
+                const int zcur = (sync || pairs) ? ((zprev == R_ZA) ? R_ZB : R_ZA) : R_ZA, tiles = G.t[SH_ROW64].tiles;
+                if (pair && last)
+                    kb_bwd_pair<T, double><<<P_()>>>(A_(SH_ROW64), tiles, ycur, zprev, R_ZK, desc);
+                else if (pair)
+                    kb_bwd_pair<T, T><<<P_()>>>(A_(SH_ROW64), tiles, ycur, zprev, zcur, desc);
+                else if (last && dual)
+                    kb_bwd<T, T, double, true, true><<<L_(SH_APPLY)>>>(A_(SH_APPLY), ycur, zprev, R_ZK, desc);
+                else if (last)
+                    kb_bwd<T, T, double, true, false><<<L_(SH_APPLY)>>>(A_(SH_APPLY), ycur, zprev, R_ZK, desc);
+                else
+                    kb_bwd<T, T, T, true, false><<<L_(SH_APPLY)>>>(A_(SH_APPLY), ycur, zprev, zcur, desc);
+                zprev = zcur;
                 CKL();
             }
         }
@@ -1041,6 +1088,7 @@ abilu_status run_group(abilu_server *s, Group &G, hipStream_t st) {
     if ((e = reduce(std::integral_constant<int, RS_BETA>{})) != ABILU_OK) return e;
     return ABILU_OK;
 #undef L_
+#undef P_
 #undef A_
 #undef CKL
 }
