@@ -871,11 +871,12 @@ TRAFFIC_KERNELS = {
     "k_spmv<false>": "spmv", "k_spmv<true>": "spmv_resid",
     "k_factor_sweep_fv<float, 2, true, 2, 2>": "factor_sweep_f32_async_fromA",
     "k_factor_sweep_fv<float, 2, true, 3, 3>": "factor_sweep_f32_async_fromA",
-    "k_fwd<float, double, false>": "apply_fwd_f32_async", "k_fwd<float, float, true>": "apply_fwd_emitz_f32_async",
+    "k_fwd<float, double, false, true>": "apply_fwd_f32_async",
+    "k_fwd<float, float, true, true>": "apply_fwd_emitz_f32_async",
     "k_bwd<float, float, float, true, false>": "apply_bwd_f32_async",
     "k_bwd<float, float, double, true, false>": "apply_bwd_last_f32_async",
-    "k_fwd_pair<float, double, true, 2>": "apply_fwd_emitz_f32_async",
-    "k_fwd_pair<float, double, true, 3>": "apply_fwd_emitz_f32_async",
+    "k_fwd_pair<float, double, true, 2, true>": "apply_fwd_emitz_f32_async",
+    "k_fwd_pair<float, double, true, 3, true>": "apply_fwd_emitz_f32_async",
     "k_bwd_pair<float, double, 2>": "apply_bwd_last_f32_async", "k_bwd_pair<float, double, 3>": "apply_bwd_last_f32_async",
     "k_update<8>": "fgmres_update", "k_update_dot<4, 8>": "fgmres_update_dot", "k_mdot<8>": "fgmres_mdot",
     "k_stream_copy": "stream_copy",

@@ -35,10 +35,10 @@ struct abilu_pattern {
     int32_t *done = nullptr;      // device [DONE_INTS] completion counts of FGMRES's reductions, zero
                                   // between launches (behind lrow in its allocation)
     bool symmetric = false;       // (i,j) in S_B implies (j,i) in S_B
-    int32_t max_lower = 0, max_upper = 0;   // most strictly lower / upper blocks of a row
+    int32_t side = 4;             // most blocks of a row on one side of the diagonal: 2 (at most), 3, 4 (or more)
     // update sets of the diagonal blocks only, and rows that the factor sweeps' row-at-once form holds
     // (FV_CAP lower and upper blocks): finite-volume meshes of triangles and quads
-    bool fv() const { return symmetric && npairs == nnzb_lower && max_lower <= 3 && max_upper <= 3; }
+    bool fv() const { return symmetric && npairs == nnzb_lower && side <= 3; }
     int device = 0;
     // chunk schedule (abilu_pattern_set_chunks): chunks of chunk_rows consecutive rows; per chunk,
     // the rows grouped by level in the chunk's lower (forward, factor) and upper (backward)
@@ -88,6 +88,7 @@ constexpr int DIAG_ROWS = 512;
 // completion counts of the reductions (ints, a cache line apart): the root, then one per group of
 // workgroups (last_workgroup)
 constexpr int DONE_GROUPS = 16, DONE_STRIDE = 32;
+constexpr int DONE_SINGLE = 64;   // up to this many workgroups all count at the root
 constexpr int DONE_INTS = (1 + DONE_GROUPS) * DONE_STRIDE;
 
 

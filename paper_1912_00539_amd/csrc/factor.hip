@@ -469,7 +469,7 @@ void launch_sweep(const abilu_pattern *p, int grid, hipStream_t s, const double 
                   const T *Dp, T *Xn, T *Dn, unsigned *flags) {
     if (p->fv()) {
         const FvPattern P{p->n, (int)p->nnzb_lower, p->rowptr, p->lrow, p->urow, p->lcol, p->ldiag, p->pkj, p->skj};
-        const bool two = p->max_lower <= 2 && p->max_upper <= 2;
+        const bool two = p->side <= 2;
         auto go = [&](auto lsrc) {
             constexpr int LSRC = decltype(lsrc)::value;
             if (two) k_factor_sweep_fv<T, LSRC, UA, 2, 2><<<grid, WG, 0, s>>>(P, A, XU, Dp, Xn, Dn, flags);

@@ -64,10 +64,28 @@ __device__ __forceinline__ void update_terms(int p0, int p1, int r, const int32_
     }
 }
 
+// Sum over the 64 lanes, in every lane: within rows of 16 lanes by DPP (neighbour, pair, half row,
+// row mirrored), then the four rows' sums by readlane. No LDS crossbar: six shuffles of a double
+// through it take about four times as long, and a dot product kernel does one per vector and wave.
+template <int CTRL>
+__device__ __forceinline__ double add_dpp(double v) {
+    const long long b = __double_as_longlong(v);
+    const int lo = __builtin_amdgcn_mov_dpp((int)(b & 0xffffffffll), CTRL, 0xF, 0xF, true);
+    const int hi = __builtin_amdgcn_mov_dpp((int)(b >> 32), CTRL, 0xF, 0xF, true);
+    return v + __longlong_as_double(((long long)hi << 32) | (unsigned long long)(unsigned)lo);
+}
 __device__ __forceinline__ double wave_sum(double v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-    return v;
+    v = add_dpp<0xB1>(v);    // quad_perm [1,0,3,2]
+    v = add_dpp<0x4E>(v);    // quad_perm [2,3,0,1]
+    v = add_dpp<0x141>(v);   // row_half_mirror
+    v = add_dpp<0x140>(v);   // row_mirror
+    const long long b = __double_as_longlong(v);
+    const int lo = (int)(b & 0xffffffffll), hi = (int)(b >> 32);
+    auto row = [&](int lane) {
+        return __longlong_as_double(((long long)__builtin_amdgcn_readlane(hi, lane) << 32) |
+                                    (unsigned long long)(unsigned)__builtin_amdgcn_readlane(lo, lane));
+    };
+    return (row(0) + row(16)) + (row(32) + row(48));
 }
 
 __device__ __forceinline__ bool skipped(const int *guard) { return guard && *guard == 0; }
@@ -87,7 +105,7 @@ __device__ __forceinline__ double load_agent(const double *p) {
 // reached the shared memory, before its workgroup counts itself done; the counts are cleared for
 // the next launch. A __threadfence in every thread, which writes the whole L2 back, took 10 us over
 // 64 workgroups against 2.4 us this way (a grid-wide count and wait, timed alone). GROUPED: more
-// than DONE_GROUPS^2 / 8 workgroups count in DONE_GROUPS groups and the last of each counts at the
+// than DONE_SINGLE workgroups count in DONE_GROUPS groups and the last of each counts at the
 // root, since additions to one address follow each other at about 15 ns (704 in a row: 10 us).
 template <bool GROUPED>
 __device__ __forceinline__ bool last_workgroup(int *done, int total, int id) {
@@ -102,7 +120,7 @@ __device__ __forceinline__ bool last_workgroup(int *done, int total, int id) {
             return true;
         };
         bool is_last;
-        if (GROUPED && total > DONE_GROUPS * DONE_GROUPS / 8) {
+        if (GROUPED && total > DONE_SINGLE) {
             const int g = id % DONE_GROUPS;
             is_last = count(done + (1 + g) * DONE_STRIDE, (total - g + DONE_GROUPS - 1) / DONE_GROUPS) &&
                       count(done, DONE_GROUPS);

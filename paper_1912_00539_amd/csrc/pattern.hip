@@ -249,8 +249,7 @@ extern "C" abilu_status abilu_build_pattern(int32_t nbrows, const int32_t *d_row
             CK(hipStreamSynchronize(s));
             const unsigned *h = (const unsigned *)p->pinned;
             p->symmetric = h[0] == 0;
-            p->max_lower = (int32_t)h[1];
-            p->max_upper = (int32_t)h[2];
+            p->side = side_class(h + 1);
         }
     }
     (void)hipFree(scratch);

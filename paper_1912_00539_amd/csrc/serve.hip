@@ -133,12 +133,12 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(sweep_waves<
 }
 
 // The row-at-once form, where every member of the group has diagonal update sets only (the generated
-// meshes are structurally symmetric and have at most three neighbours of lower and of higher index).
-template <typename T, int LSRC, bool FROM_A>
+// meshes are structurally symmetric) and at most CL blocks a side of a row.
+template <typename T, int LSRC, bool FROM_A, int CL>
 __global__ __launch_bounds__(WG) void kb_factor_sweep_fv(const Slot *slots, const Member *mem, int nmem, int sel) {
     MEMBER();
     const FvPattern P{S.n, S.ZL, S.rowptr, S.lrow, S.urow, S.lcol, S.ldiag, S.pkj, S.skj};
-    factor_sweep_fv_row<T, LSRC, FROM_A, FV_CAP, FV_CAP>(
+    factor_sweep_fv_row<T, LSRC, FROM_A, CL, CL>(
         blk * ROWS_PER_WG + (threadIdx.x >> 2), P, S.A, FROM_A ? (const T *)nullptr : fbuf_x<T>(S, sel & 1),
         fbuf_d<T>(S, sel & 2), fbuf_x<T>(S, sel & 4), fbuf_d<T>(S, sel & 8), S.flags);
 }
@@ -152,10 +152,9 @@ __global__ __launch_bounds__(WG) void kb_fwd(const Slot *slots, const Member *me
                             yin == R_VK ? rs : 1.0);
 }
 
-// Two sweeps in one launch (fwd_pair_row, bwd_pair_row; three blocks a side hold every generated
-// mesh's rows). The launch's tiles are dealt to the XCDs in contiguous eighths; its grid is a multiple
+// Two sweeps in one launch (fwd_pair_row, bwd_pair_row). The launch's tiles are dealt to the XCDs in contiguous eighths; its grid is a multiple
 // of 8, and the workgroups past the last of `tiles` end at once.
-template <typename T, typename YI, bool EMIT_Z>
+template <typename T, typename YI, bool EMIT_Z, int CL>
 __global__ __launch_bounds__(WG) void kb_fwd_pair(const Slot *slots, const Member *mem, int nmem, int tiles, int yin,
                                                   int yout) {
     const int b = xcd_tile(blockIdx.x, gridDim.x);
@@ -163,13 +162,13 @@ __global__ __launch_bounds__(WG) void kb_fwd_pair(const Slot *slots, const Membe
     const Member M = mem[find_member(mem, nmem, b)];
     const Slot &S = slots[M.slot];
     const double rs = S.vscale[M.k];
-    fwd_pair_row<T, YI, EMIT_Z, FV_CAP>((b - M.tile0) * ROWS_PER_WG + (threadIdx.x >> 2), S.n, S.lrow, S.lcol,
+    fwd_pair_row<T, YI, EMIT_Z, CL>((b - M.tile0) * ROWS_PER_WG + (threadIdx.x >> 2), S.n, S.lrow, S.lcol,
                                         (const T *)S.LU, (const double *)role(S, M, R_VK),
                                         (const YI *)role(S, M, yin), (T *)role(S, M, yout), (const T *)S.Dinv,
                                         (T *)S.za, rs, yin == R_VK ? rs : 1.0);
 }
 
-template <typename T, typename ZO>
+template <typename T, typename ZO, int CL>
 __global__ __launch_bounds__(WG) void kb_bwd_pair(const Slot *slots, const Member *mem, int nmem, int tiles, int y,
                                                   int zin, int zout, int desc) {
     const int b = xcd_tile(desc ? (int)(gridDim.x - 1 - blockIdx.x) : (int)blockIdx.x, gridDim.x);
@@ -177,7 +176,7 @@ __global__ __launch_bounds__(WG) void kb_bwd_pair(const Slot *slots, const Membe
     const Member M = mem[find_member(mem, nmem, b)];
     const Slot &S = slots[M.slot];
     const T *Ub = (const T *)S.LU + ((int64_t)S.ZL + S.n) * BB;
-    bwd_pair_row<T, ZO, FV_CAP>((b - M.tile0) * ROWS_PER_WG + (threadIdx.x >> 2), S.n, S.urow, S.ucol, Ub,
+    bwd_pair_row<T, ZO, CL>((b - M.tile0) * ROWS_PER_WG + (threadIdx.x >> 2), S.n, S.urow, S.ucol, Ub,
                                 (const T *)S.Dinv, (const T *)role(S, M, y), (const T *)role(S, M, zin),
                                 (ZO *)role(S, M, zout));
 }
@@ -342,9 +341,11 @@ __global__ void kbs_pat_rows(const SetupDesc *sd, const Member *mem, int nmem, i
     abilu_setup::pat_rows_body(blk, D.n, D.Z, D.rowptr, D.colidx, D.diag_pos, (unsigned *)(adm + 4 * m_));
 }
 
-__global__ void kbs_pat_tri_counts(const SetupDesc *sd, const Member *mem, int nmem) {
+// also the length of the rows, into pshape (two words a member)
+__global__ void kbs_pat_tri_counts(const SetupDesc *sd, const Member *mem, int nmem, unsigned *pshape) {
     SMEMBER();
     abilu_setup::pat_tri_counts_body(blk, D.n, D.rowptr, D.diag_pos, D.cnt, D.cnt + (D.n + 1));
+    abilu_setup::pat_side_body(blk * blockDim.x + threadIdx.x, D.n, D.rowptr, D.diag_pos, pshape + 2 * m_);
 }
 
 __global__ void kbs_pat_count(const SetupDesc *sd, const Member *mem, int nmem) {
@@ -518,6 +519,7 @@ struct Req {
     ReqLayout L{};
     int32_t n = 0;
     int64_t Z = 0, ZL = 0, ZU = 0, P = 0;   // pattern sizes (after admission)
+    int side = 0;                           // most strictly lower or strictly upper blocks of a row
     int k = 0, iters = 0, restarts = 0, reorth = 0;
     double bnorm = 0, tol = 0, beta = 0, est = 0;
     uint32_t flags = 0;
@@ -541,7 +543,7 @@ struct abilu_server {
     SetupDesc *d_sdesc = nullptr, *h_sdesc = nullptr;
     Slot *d_sslot = nullptr;
     Member *d_stab = nullptr, *h_stab = nullptr;
-    int64_t *d_adm = nullptr, *h_adm = nullptr;    // per member: error word, ZL, ZU, npairs
+    int64_t *d_adm = nullptr, *h_adm = nullptr;    // per member: error word, ZL, ZU, npairs; then two words of row shape each
     std::vector<hipEvent_t> ev;                    // per slot: setup finished
     std::vector<Req> reqs;
     std::deque<int64_t> queue;                     // released, not yet admitted (FIFO)
@@ -748,7 +750,7 @@ abilu_status admit_queued(abilu_server *s, int64_t cell_budget) {
     } while (0)
     CKS(hipMemcpyAsync(s->d_sdesc, s->h_sdesc, sizeof(SetupDesc) * B, hipMemcpyHostToDevice, st));
     CKS(hipMemcpyAsync(s->d_sslot, s->h_slots, sizeof(Slot) * B, hipMemcpyHostToDevice, st));
-    CKS(hipMemsetAsync(s->d_adm, 0, sizeof(int64_t) * 4 * B, st));
+    CKS(hipMemsetAsync(s->d_adm, 0, sizeof(int64_t) * 5 * B, st));
     if (upload_setup_tables(s, ids, members, T) != ABILU_OK) return ABILU_EDEVICE;
     // pass 1: generation (row lengths, row pointers, blocks and right-hand side) and validation
     kbs_gen_rowlen<<<T.tiles[SS_ROW256], 256, 0, st>>>(s->d_sdesc, T.d[SS_ROW256], T.count);
@@ -776,13 +778,14 @@ abilu_status admit_queued(abilu_server *s, int64_t cell_budget) {
         if (upload_setup_tables(s, ids, members, T) != ABILU_OK) return ABILU_EDEVICE;
     }
     // pass 2: lower / upper part offsets and update-set offsets, with their totals
-    kbs_pat_tri_counts<<<T.tiles[SS_ROW256], 256, 0, st>>>(s->d_sdesc, T.d[SS_ROW256], T.count);
+    kbs_pat_tri_counts<<<T.tiles[SS_ROW256], 256, 0, st>>>(s->d_sdesc, T.d[SS_ROW256], T.count,
+                                                                (unsigned *)(s->d_adm + 4 * B));
     CKL();
     if (launch_scan(s, T, SC_LROW) != ABILU_OK || launch_scan(s, T, SC_UROW) != ABILU_OK) return ABILU_EDEVICE;
     kbs_pat_count<<<T.tiles[SS_ROW128], abilu_setup::PAT_ROWS, 0, st>>>(s->d_sdesc, T.d[SS_ROW128], T.count);
     CKL();
     if (launch_scan(s, T, SC_PAIR) != ABILU_OK) return ABILU_EDEVICE;
-    CKS(hipMemcpyAsync(s->h_adm, s->d_adm, sizeof(int64_t) * 4 * B, hipMemcpyDeviceToHost, st));
+    CKS(hipMemcpyAsync(s->h_adm, s->d_adm, sizeof(int64_t) * 5 * B, hipMemcpyDeviceToHost, st));
     CKS(hipStreamSynchronize(st));
     if (keep(
             [&](int m, const Req &r) {
@@ -806,6 +809,7 @@ abilu_status admit_queued(abilu_server *s, int64_t cell_budget) {
     for (int m : members) {
         Req &r = s->reqs[ids[m]];
         const int64_t *sz = s->h_adm + 4 * m + 1;
+        r.side = abilu_setup::side_class((const unsigned *)(s->h_adm + 4 * B + m));
         r.ZL = sz[0];
         r.ZU = sz[1];
         r.P = sz[2];
@@ -925,18 +929,30 @@ abilu_status run_group(abilu_server *s, Group &G, hipStream_t st) {
         CKL();
         return ABILU_OK;
     };
-    bool fv = true;   // diagonal update sets only, as the generated meshes have
-    for (int64_t id : G.ids) fv = fv && s->reqs[id].P == s->reqs[id].ZL;
+    // the forms for short rows (and diagonal update sets only), by the group's longest row
+    int side = 0;
+    bool fv = true;
+    for (int64_t id : G.ids) {
+        fv = fv && s->reqs[id].P == s->reqs[id].ZL;
+        side = std::max(side, s->reqs[id].side);
+    }
+    fv = fv && side <= FV_CAP;
+    auto with_cap = [&](auto f) {   // f(CL) with the smallest form that holds the rows
+        if (side <= 2) f(std::integral_constant<int, 2>{});
+        else f(std::integral_constant<int, FV_CAP>{});
+    };
 #define P_() dim3(xcd_grid(G.t[SH_ROW64].tiles)), dim3(WG), 0, st
     auto fwd = [&](const char *name, bool pair, bool yin_f64, bool emit, int yin, int yout) -> abilu_status {
         ProfScope ps(name, st, B([&](const Sizes &z, const Req &) { return bytes_fwd(z, sF, yin_f64 ? 8 : sF, emit); }));
         const int tiles = G.t[SH_ROW64].tiles;
-        if (pair && yin_f64) {
-            if (emit) kb_fwd_pair<T, double, true><<<P_()>>>(A_(SH_ROW64), tiles, yin, yout);
-            else kb_fwd_pair<T, double, false><<<P_()>>>(A_(SH_ROW64), tiles, yin, yout);
-        } else if (pair) {
-            if (emit) kb_fwd_pair<T, T, true><<<P_()>>>(A_(SH_ROW64), tiles, yin, yout);
-            else kb_fwd_pair<T, T, false><<<P_()>>>(A_(SH_ROW64), tiles, yin, yout);
+        if (pair) {
+            with_cap([&](auto cl) {
+                constexpr int CL = decltype(cl)::value;
+                if (yin_f64 && emit) kb_fwd_pair<T, double, true, CL><<<P_()>>>(A_(SH_ROW64), tiles, yin, yout);
+                else if (yin_f64) kb_fwd_pair<T, double, false, CL><<<P_()>>>(A_(SH_ROW64), tiles, yin, yout);
+                else if (emit) kb_fwd_pair<T, T, true, CL><<<P_()>>>(A_(SH_ROW64), tiles, yin, yout);
+                else kb_fwd_pair<T, T, false, CL><<<P_()>>>(A_(SH_ROW64), tiles, yin, yout);
+            });
         } else if (yin_f64) {
             if (emit) kb_fwd<T, double, true><<<L_(SH_APPLY)>>>(A_(SH_APPLY), yin, yout);
             else kb_fwd<T, double, false><<<L_(SH_APPLY)>>>(A_(SH_APPLY), yin, yout);
@@ -966,8 +982,12 @@ abilu_status run_group(abilu_server *s, Group &G, hipStream_t st) {
             constexpr bool LA = decltype(la)::value, UA = decltype(ua)::value;
             constexpr int LSRC = LA ? L_FROM_A0 : L_FROM_NEW;
             if (!fv) kb_factor_sweep<T, LA, UA, UA><<<L_(SH_ROW64)>>>(A_(SH_ROW64), sel);
-            else if (LA || !sync) kb_factor_sweep_fv<T, LSRC, UA><<<L_(SH_ROW64)>>>(A_(SH_ROW64), sel);
-            else if constexpr (!UA) kb_factor_sweep_fv<T, L_FROM_PREV, UA><<<L_(SH_ROW64)>>>(A_(SH_ROW64), sel);
+            else
+                with_cap([&](auto cl) {
+                    constexpr int CL = decltype(cl)::value;
+                    if (LA || !sync) kb_factor_sweep_fv<T, LSRC, UA, CL><<<L_(SH_ROW64)>>>(A_(SH_ROW64), sel);
+                    else if constexpr (!UA) kb_factor_sweep_fv<T, L_FROM_PREV, UA, CL><<<L_(SH_ROW64)>>>(A_(SH_ROW64), sel);
+                });
         };
         if (fsw == 0) {
             if ((e = init(true, 0)) != ABILU_OK) return e;
@@ -1048,10 +1068,12 @@ abilu_status run_group(abilu_server *s, Group &G, hipStream_t st) {
                 ProfScope ps(last ? "serve_apply_bwd_last" : "serve_apply_bwd", st,
                              B([&](const Sizes &z, const Req &) { return bytes_bwd(z, sF, last ? 8 : sF, dual); }));
                 const int zcur = (sync || pairs) ? ((zprev == R_ZA) ? R_ZB : R_ZA) : R_ZA, tiles = G.t[SH_ROW64].tiles;
-                if (pair && last)
-                    kb_bwd_pair<T, double><<<P_()>>>(A_(SH_ROW64), tiles, ycur, zprev, R_ZK, desc);
-                else if (pair)
-                    kb_bwd_pair<T, T><<<P_()>>>(A_(SH_ROW64), tiles, ycur, zprev, zcur, desc);
+                if (pair)
+                    with_cap([&](auto cl) {
+                        constexpr int CL = decltype(cl)::value;
+                        if (last) kb_bwd_pair<T, double, CL><<<P_()>>>(A_(SH_ROW64), tiles, ycur, zprev, R_ZK, desc);
+                        else kb_bwd_pair<T, T, CL><<<P_()>>>(A_(SH_ROW64), tiles, ycur, zprev, zcur, desc);
+                    });
                 else if (last && dual)
                     kb_bwd<T, T, double, true, true><<<L_(SH_APPLY)>>>(A_(SH_APPLY), ycur, zprev, R_ZK, desc);
                 else if (last)
@@ -1352,11 +1374,11 @@ extern "C" abilu_status abilu_serve_create(const abilu_serve_config *cfg, void *
               hip_ok(hipMalloc(&s->d_sdesc, sizeof(SetupDesc) * S), "serve setup descriptors") &&
               hip_ok(hipMalloc(&s->d_sslot, sizeof(Slot) * S), "serve staged slots") &&
               hip_ok(hipMalloc(&s->d_stab, sizeof(Member) * SS_COUNT * S), "serve setup tables") &&
-              hip_ok(hipMalloc(&s->d_adm, sizeof(int64_t) * 4 * S), "serve admission words") &&
+              hip_ok(hipMalloc(&s->d_adm, sizeof(int64_t) * 5 * S), "serve admission words") &&
               hip_ok(hipHostMalloc((void **)&s->h_sdesc, sizeof(SetupDesc) * S, hipHostMallocDefault), "serve pinned") &&
               hip_ok(hipHostMalloc((void **)&s->h_stab, sizeof(Member) * SS_COUNT * S, hipHostMallocDefault),
                      "serve pinned") &&
-              hip_ok(hipHostMalloc((void **)&s->h_adm, sizeof(int64_t) * 4 * S, hipHostMallocDefault), "serve pinned");
+              hip_ok(hipHostMalloc((void **)&s->h_adm, sizeof(int64_t) * 5 * S, hipHostMallocDefault), "serve pinned");
     for (int q = 0; ok && q < S; ++q)
         ok = hip_ok(hipEventCreateWithFlags(&s->ev[q], hipEventDisableTiming), "serve events");
     if (ok) ok = hip_ok(hipMemset(s->d_hdr, 0, (size_t)HDR * S), "serve header init");

@@ -244,22 +244,27 @@ __device__ __forceinline__ void pat_fill_body(int blk, int n, int ZL, const int3
     }
 }
 
+// Whether some row has more than two, more than three blocks on one side of the diagonal (strictly
+// lower or strictly upper): more[0], more[1]. Plain stores of ones from the wavefronts that have such
+// a row; a maximum by atomics cost 29 us over 700,000 rows.
+__device__ __forceinline__ void pat_side_body(int i, int n, const int32_t *__restrict__ rowptr,
+                                              const int32_t *__restrict__ diag_pos, unsigned *more) {
+    const int side = i < n ? max(diag_pos[i] - rowptr[i], rowptr[i + 1] - diag_pos[i] - 1) : 0;
+    const bool over2 = __any(side > 2), over3 = __any(side > 3);
+    if ((threadIdx.x & 63) == 0) {
+        if (over2) more[0] = 1u;
+        if (over3) more[1] = 1u;
+    }
+}
+inline int side_class(const unsigned *more) { return more[1] ? 4 : more[0] ? 3 : 2; }
+
 // structural symmetry: one thread per block row; sets shape[0] when some (i,j) in S_B has no (j,i).
-// shape[1], shape[2]: the most strictly lower and upper blocks of a row.
+// shape[1], shape[2]: pat_side_body.
 __device__ __forceinline__ void pat_sym_body(int blk, int n, const int32_t *__restrict__ rowptr,
                                              const int32_t *__restrict__ colidx, const int32_t *__restrict__ diag_pos,
                                              unsigned *__restrict__ shape) {
     int i = blk * blockDim.x + threadIdx.x;
-    int nl = i < n ? diag_pos[i] - rowptr[i] : 0, nu = i < n ? rowptr[i + 1] - diag_pos[i] - 1 : 0;
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-        nl = max(nl, __shfl_xor(nl, o, 64));
-        nu = max(nu, __shfl_xor(nu, o, 64));
-    }
-    if ((threadIdx.x & 63) == 0) {   // a read first: after the first few wavefronts it holds the maximum
-        if ((unsigned)nl > shape[1]) atomicMax(shape + 1, (unsigned)nl);
-        if ((unsigned)nu > shape[2]) atomicMax(shape + 2, (unsigned)nu);
-    }
+    pat_side_body(i, n, rowptr, diag_pos, shape + 1);
     if (i >= n) return;
     for (int e = rowptr[i]; e < rowptr[i + 1]; ++e) {
         const int j = colidx[e];
