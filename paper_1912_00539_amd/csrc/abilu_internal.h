@@ -58,6 +58,7 @@ struct abilu_pattern {
     // t * nchunks + c); then 4 ints of per-pattern maxima
     int32_t *rec = nullptr;
     int32_t rec_max[3] = {0, 0, 0};   // largest strictly lower / strictly upper / pair count of a row
+    bool chains = false;          // a row's only neighbours inside its chunk are the rows next to it
     // dependency analysis (abilu_pattern_depth): depth D and the lower/upper level counts, -1 until
     // computed
     int32_t depth_D = -1;

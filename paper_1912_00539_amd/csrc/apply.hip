@@ -533,6 +533,187 @@ __global__ __launch_bounds__(WG) void k_bwd_chunk_short(int n, int R, int nch, c
     });
 }
 
+// Chunks that are chains (a row's only neighbours inside its chunk are the rows next to it, as along
+// a line of cells), rows of at most CL blocks a side: sixteen lanes per chunk, quad q taking every
+// fourth row. A sweep is then bound by latency: a quad per chunk leaves two waves on a SIMD (31,250
+// chunks of 16 rows), each with a row or two in flight. Here four times as many lanes load the
+// operands of 16 rows at once and take off the other chunks' contributions row by row in parallel;
+// only the recurrence along the chain runs row after row, its value passing from quad to quad by a
+// rotation of the DPP row (quad 0 gets quad 3's). Same operations on each element, in the same order,
+// as fwd_chunk_row and bwd_chunk_row: a row's neighbour inside the chunk is the last of its lower
+// blocks and the first of its upper ones.
+template <typename T>
+__device__ __forceinline__ T from_quad_before(T v) {   // lane l of a DPP row of 16: the value of lane l - 4 (mod 16)
+    constexpr int ROR4 = 0x124;
+    if constexpr (sizeof(T) == 4) {
+        return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), ROR4, 0xF, 0xF, true));
+    } else {
+        const long long b = __double_as_longlong(v);
+        const int lo = __builtin_amdgcn_mov_dpp((int)(b & 0xffffffffll), ROR4, 0xF, 0xF, true);
+        const int hi = __builtin_amdgcn_mov_dpp((int)(b >> 32), ROR4, 0xF, 0xF, true);
+        return __longlong_as_double(((long long)hi << 32) | (unsigned long long)(unsigned)lo);
+    }
+}
+
+constexpr int CHAIN_LANES = 16, CHAIN_STEP = 16;   // lanes per chunk, rows taken at once
+
+template <typename T, bool ZERO_OUT, int CL>
+__global__ __launch_bounds__(WG) void k_fwd_chain(int n, int R, int nch, const int32_t *__restrict__ lrow,
+                                                  const int32_t *__restrict__ lcol, const T *__restrict__ Lb,
+                                                  const double *__restrict__ rhs, const double *__restrict__ rscale,
+                                                  const T *yo, T *yn) {
+    const int c = blockIdx.x * (WG / CHAIN_LANES) + threadIdx.x / CHAIN_LANES;
+    if (c >= nch) return;
+    const double rs = rhs_scale(rscale);
+    const int r = threadIdx.x & 3, quad = (threadIdx.x >> 2) & 3;
+    const int c0 = c * R, m = min(n, c0 + R) - c0;
+    constexpr int G = CHAIN_STEP / 4;
+    T y = T(0);   // this quad's latest row; quad 3 holds the row before each step's first
+    for (int s0 = 0; s0 < m; s0 += CHAIN_STEP) {
+        T acc[G], lp[G][4];
+        bool prev[G];
+        int nl[G], b0[G];
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
+            const int i = c0 + min(s0 + 4 * g + quad, m - 1);
+            b0[g] = lrow[i];
+            nl[g] = lrow[i + 1] - b0[g];
+        }
+        T l[G][CL][4], yv[G][CL];
+        int j[G][CL];
+        double b[G];
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
+            const int i = c0 + min(s0 + 4 * g + quad, m - 1);
+            b[g] = rhs[(int64_t)i * 4 + r];
+            prev[g] = false;
+#pragma unroll
+            for (int u = 0; u < CL; ++u) {
+                if (u < nl[g]) {
+                    j[g][u] = lcol[b0[g] + u];
+                    load_row(Lb + (int64_t)(b0[g] + u) * BB, r, l[g][u]);
+                }
+            }
+        }
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
+#pragma unroll
+            for (int u = 0; u < CL; ++u) {
+                yv[g][u] = T(0);
+                if (u < nl[g]) {
+                    if (j[g][u] >= c0) prev[g] = true;
+                    else if constexpr (!ZERO_OUT) yv[g][u] = yo[(int64_t)j[g][u] * 4 + r];
+                }
+            }
+        }
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
+            acc[g] = (T)scaled(b[g], rs);
+#pragma unroll
+            for (int q = 0; q < 4; ++q) lp[g][q] = T(0);
+#pragma unroll
+            for (int u = 0; u < CL; ++u) {
+                if (u < nl[g]) {
+                    if (prev[g] && u == nl[g] - 1) {
+#pragma unroll
+                        for (int q = 0; q < 4; ++q) lp[g][q] = l[g][u][q];
+                    } else {
+                        T v[4];
+                        gather_vec(yv[g][u], v);
+                        acc[g] -= dot4(l[g][u][0], v[0], l[g][u][1], v[1], l[g][u][2], v[2], l[g][u][3], v[3]);
+                    }
+                }
+            }
+        }
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                T v[4];
+                gather_vec(from_quad_before(y), v);
+                const T t = acc[g] - dot4(lp[g][0], v[0], lp[g][1], v[1], lp[g][2], v[2], lp[g][3], v[3]);
+                y = quad == q ? (prev[g] ? t : acc[g]) : y;
+            }
+            if (s0 + 4 * g + quad < m) yn[(int64_t)(c0 + s0 + 4 * g + quad) * 4 + r] = y;
+        }
+    }
+}
+
+template <typename T, typename ZN, bool ZERO_OUT, int CU>
+__global__ __launch_bounds__(WG) void k_bwd_chain(int n, int R, int nch, const int32_t *__restrict__ urow,
+                                                  const int32_t *__restrict__ ucol, const T *__restrict__ Ub,
+                                                  const T *__restrict__ Dinv, const T *__restrict__ y, const T *zo,
+                                                  ZN *zn) {
+    const int c = blockIdx.x * (WG / CHAIN_LANES) + threadIdx.x / CHAIN_LANES;
+    if (c >= nch) return;
+    const int r = threadIdx.x & 3, quad = (threadIdx.x >> 2) & 3;
+    const int c0 = c * R, c1 = min(n, c0 + R), m = c1 - c0;
+    constexpr int G = CHAIN_STEP / 4;
+    T z = T(0);   // this quad's latest row; quad 3 holds the row after each step's first
+    for (int s0 = 0; s0 < m; s0 += CHAIN_STEP) {
+        int nu[G], b0[G], j[G][CU];
+        T t0[G], u4[G][CU][4], zv[G][CU], dr[G][4];
+        bool next[G];
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
+            const int i = c1 - 1 - min(s0 + 4 * g + quad, m - 1);
+            b0[g] = urow[i];
+            nu[g] = urow[i + 1] - b0[g];
+        }
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
+            const int i = c1 - 1 - min(s0 + 4 * g + quad, m - 1);
+            t0[g] = y[(int64_t)i * 4 + r];
+            load_row(Dinv + (int64_t)i * BB, r, dr[g]);
+#pragma unroll
+            for (int u = 0; u < CU; ++u) {
+                if (u < nu[g]) {
+                    j[g][u] = ucol[b0[g] + u];
+                    load_row(Ub + (int64_t)(b0[g] + u) * BB, r, u4[g][u]);
+                }
+            }
+        }
+        T far[G][CU];   // the other chunks' terms
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
+            next[g] = nu[g] > 0 && j[g][0] < c1;
+#pragma unroll
+            for (int u = 0; u < CU; ++u) {
+                zv[g][u] = T(0);
+                if (u < nu[g] && !(u == 0 && next[g])) {
+                    if constexpr (!ZERO_OUT) zv[g][u] = zo[(int64_t)j[g][u] * 4 + r];
+                }
+            }
+        }
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
+#pragma unroll
+            for (int u = 0; u < CU; ++u) {
+                T v[4];
+                gather_vec(zv[g][u], v);
+                const T d = dot4(u4[g][u][0], v[0], u4[g][u][1], v[1], u4[g][u][2], v[2], u4[g][u][3], v[3]);
+                far[g][u] = u < nu[g] ? d : T(0);
+            }
+        }
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                T v[4], a[4];
+                gather_vec(from_quad_before(z), v);
+                const T d = dot4(u4[g][0][0], v[0], u4[g][0][1], v[1], u4[g][0][2], v[2], u4[g][0][3], v[3]);
+                T t = t0[g] - (next[g] ? d : far[g][0]);
+#pragma unroll
+                for (int u = 1; u < CU; ++u) t -= far[g][u];
+                gather_vec(t, a);
+                const T zi = dot4(dr[g][0], a[0], dr[g][1], a[1], dr[g][2], a[2], dr[g][3], a[3]);
+                z = quad == q ? zi : z;
+            }
+            if (s0 + 4 * g + quad < m) zn[(int64_t)(c1 - 1 - (s0 + 4 * g + quad)) * 4 + r] = (ZN)z;
+        }
+    }
+}
+
 // y = A x  (RESID: y = b - A x), double precision, CSR; eight lanes per block row, four blocks
 // loaded per step (clamped: rows always hold at least their diagonal block); desc: workgroups
 // take the rows in descending order
@@ -617,8 +798,19 @@ abilu_status apply_t(const abilu_pattern *p, const T *LU, const T *Dinv, const d
         // chunks of at most SHORT_CHUNK rows whose rows all fit a record: the unrolled runner
         const bool short_fwd = by_rows && R <= SHORT_CHUNK && p->rec_max[0] <= REC_CAP;
         const bool short_bwd = by_rows && R <= SHORT_CHUNK && p->rec_max[1] <= REC_CAP;
+        // chains of short rows: sixteen lanes per chunk
+        const bool chain = by_rows && p->chains && p->side <= FV_CAP;
+        const int cg = div_up(nch, WG / CHAIN_LANES);
         auto fwd = [&](const T *yo, T *yn) {
-            if (short_fwd) {
+            if (chain) {
+                auto go = [&](auto cl) {
+                    constexpr int CL = decltype(cl)::value;
+                    if (!yo) k_fwd_chain<T, true, CL><<<cg, WG, 0, s>>>(n, R, nch, lrow, lcol, Lb, r, rs, yo, yn);
+                    else k_fwd_chain<T, false, CL><<<cg, WG, 0, s>>>(n, R, nch, lrow, lcol, Lb, r, rs, yo, yn);
+                };
+                if (p->side <= 2) go(std::integral_constant<int, 2>{});
+                else go(std::integral_constant<int, FV_CAP>{});
+            } else if (short_fwd) {
                 if (!yo) k_fwd_chunk_short<T, true><<<g, WG, 0, s>>>(n, R, nch, p->rec, Lb, r, rs, yo, yn);
                 else k_fwd_chunk_short<T, false><<<g, WG, 0, s>>>(n, R, nch, p->rec, Lb, r, rs, yo, yn);
             } else if (by_rows) {
@@ -631,7 +823,15 @@ abilu_status apply_t(const abilu_pattern *p, const T *LU, const T *Dinv, const d
         };
         auto bwd = [&](const T *y, const T *zo, auto *zn) {
             using ZN = std::remove_pointer_t<decltype(zn)>;
-            if (short_bwd) {
+            if (chain) {
+                auto go = [&](auto cu) {
+                    constexpr int CU = decltype(cu)::value;
+                    if (!zo) k_bwd_chain<T, ZN, true, CU><<<cg, WG, 0, s>>>(n, R, nch, urow, ucol, Ub, Dinv, y, zo, zn);
+                    else k_bwd_chain<T, ZN, false, CU><<<cg, WG, 0, s>>>(n, R, nch, urow, ucol, Ub, Dinv, y, zo, zn);
+                };
+                if (p->side <= 2) go(std::integral_constant<int, 2>{});
+                else go(std::integral_constant<int, FV_CAP>{});
+            } else if (short_bwd) {
                 if (!zo) k_bwd_chunk_short<T, ZN, true><<<g, WG, 0, s>>>(n, R, nch, p->rec, Ub, Dinv, y, zo, zn);
                 else k_bwd_chunk_short<T, ZN, false><<<g, WG, 0, s>>>(n, R, nch, p->rec, Ub, Dinv, y, zo, zn);
             } else if (by_rows) {

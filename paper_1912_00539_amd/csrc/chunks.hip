@@ -76,13 +76,14 @@ __global__ __launch_bounds__(256) void k_chunk_order(int n, int R, const int32_t
 }
 
 // The record of row i (layout beside REC_INTS), written to `out`; returns the row's counts of
-// strictly lower and upper blocks and update pairs.
+// strictly lower and upper blocks and update pairs, and whether it has a neighbour inside the chunk
+// other than the rows next to it.
 __device__ void chunk_record(int i, int n, int R, int ZL, const int32_t *__restrict__ rowptr,
                              const int32_t *__restrict__ colidx, const int32_t *__restrict__ diag_pos,
                              const int32_t *__restrict__ lrow, const int32_t *__restrict__ urow,
                              const int32_t *__restrict__ pair_ptr, const int32_t *__restrict__ sik,
                              const int32_t *__restrict__ skj, const int32_t *__restrict__ pkj,
-                             int32_t *__restrict__ rec, int64_t idx, int64_t nr, int (&counts)[3]) {
+                             int32_t *__restrict__ rec, int64_t idx, int64_t nr, int (&counts)[4]) {
     // field k of this record: component k % 4 of entry idx of plane k / 4
     auto put = [&](int k, int v) { rec[((int64_t)(k >> 2) * nr + idx) * 4 + (k & 3)] = v; };
     const int c0 = (i / R) * R, c1 = min(n, c0 + R);
@@ -135,6 +136,11 @@ __device__ void chunk_record(int i, int n, int R, int ZL, const int32_t *__restr
     counts[0] = nl;
     counts[1] = nu;
     counts[2] = np;
+    counts[3] = 0;
+    for (int e2 = b0; e2 < b1; ++e2) {
+        const int j = colidx[e2];
+        if (j >= c0 && j < c1 && (j < i - 1 || j > i + 1)) counts[3] = 1;
+    }
 }
 
 // One thread per row: the records (planes of int4, each step-major: row c * R + t at index
@@ -146,18 +152,19 @@ __global__ void k_chunk_records(int n, int R, int nch, int ZL, const int32_t *__
                                 const int32_t *__restrict__ skj, const int32_t *__restrict__ pkj,
                                 int32_t *__restrict__ rec, int *__restrict__ maxima) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    int mx[3] = {0, 0, 0};
+    int mx[4] = {0, 0, 0, 0};
     if (i < n) {
         const int c = i / R, t = i - c * R;
         chunk_record(i, n, R, ZL, rowptr, colidx, diag_pos, lrow, urow, pair_ptr, sik, skj, pkj, rec,
                      (int64_t)t * nch + c, (int64_t)R * nch, mx);
     }
 #pragma unroll
-    for (int q = 0; q < 3; ++q)
+    for (int q = 0; q < 4; ++q)
 #pragma unroll
         for (int o = 32; o > 0; o >>= 1) mx[q] = max(mx[q], __shfl_xor(mx[q], o, 64));
     if ((threadIdx.x & 63) == 0)
-        for (int q = 0; q < 3; ++q) atomicMax(&maxima[q], mx[q]);
+        for (int q = 0; q < 4; ++q)
+            if (mx[q] > __hip_atomic_load(&maxima[q], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMax(&maxima[q], mx[q]);
 }
 
 }  // namespace
@@ -184,6 +191,7 @@ void free_chunks(abilu_pattern *p) {
     (void)hipFree(p->rec);
     p->rec = nullptr;
     p->rec_max[0] = p->rec_max[1] = p->rec_max[2] = 0;
+    p->chains = false;
     p->chunk_rows = 0;
     p->nchunks = 0;
     p->chunk_runner = 0;
@@ -274,8 +282,9 @@ extern "C" abilu_status abilu_pattern_set_chunks(abilu_pattern *p, int32_t rows_
                                                        p->diag_pos, p->lrow, p->urow, p->pair_ptr, p->sik, p->skj,
                                                        p->pkj, p->rec, maxima);
         CK(hipGetLastError());
-        CK(hipMemcpyAsync(h, maxima, 3 * sizeof(int), hipMemcpyDeviceToHost, s));
+        CK(hipMemcpyAsync(h, maxima, 4 * sizeof(int), hipMemcpyDeviceToHost, s));
         CK(hipStreamSynchronize(s));
+        p->chains = h[3] == 0;
         for (int q = 0; q < 3; ++q) p->rec_max[q] = h[q];
     }
     p->chunk_rows = R;
