@@ -28,6 +28,7 @@ struct abilu_pattern {
     int32_t *urow = nullptr;      // device [n+1]
     int32_t *lcol = nullptr;      // device [ZL+1] columns of the lower part (one padding entry)
     int32_t *ucol = nullptr;      // device [ZU+1] columns of the upper part
+    int4 *brec = nullptr;         // device [Z] by factor layout: CSR position, pair range, ldiag (not if fv())
     int32_t *ldiag = nullptr;     // device [ZL+1] CSR position of the diagonal block of each lower column
                                   // (behind lcol in its allocation)
     double *pinned = nullptr;     // host pinned, 64 doubles, for blocking scalar reads

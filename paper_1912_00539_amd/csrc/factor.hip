@@ -61,6 +61,14 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(sweep_waves<
     factor_sweep_body<T, L_FROM_A, U_FROM_A, D_FROM_A>(blockIdx.x, n, ZL, rowptr, colidx, diag_pos, lrow, urow, pair_ptr, pik, pkj, sik, skj, A, XL, XU, Dp, Xn, Dn, flags, sym != 0);
 }
 
+// The synchronous sweep with a quad per block of the factor layout.
+template <typename T, bool FROM_A>
+__global__ __launch_bounds__(WG) void k_factor_sweep_blocks(BlockPattern P, const double *__restrict__ A,
+                                                            const T *__restrict__ XP, const T *__restrict__ Dp,
+                                                            T *__restrict__ Xn, T *__restrict__ Dn, unsigned *flags) {
+    factor_sweep_block<T, FROM_A>(P.block(blockIdx.x, threadIdx.x >> 2), P, A, XP, Dp, Xn, Dn, flags);
+}
+
 // The same on a pattern whose update sets are the diagonal ones, with at most CL lower and CU upper
 // blocks a row.
 template <typename T, int LSRC, bool FROM_A, int CL, int CU>
@@ -480,9 +488,24 @@ void launch_sweep(const abilu_pattern *p, int grid, hipStream_t s, const double 
         else if constexpr (!UA) go(std::integral_constant<int, L_FROM_PREV>{});
         return;
     }
-    k_factor_sweep<T, LA, UA, DA><<<grid, WG, 0, s>>>(p->n, (int)p->nnzb_lower, p->rowptr, p->colidx, p->diag_pos,
-                                                       p->lrow, p->urow, p->pair_ptr, p->pik, p->pkj, p->sik, p->skj,
-                                                       A, XL, XU, Dp, Xn, Dn, flags, p->symmetric ? 1 : 0);
+    // Elsewhere, between two buffers: a quad per block; in place: a quad per row, since the asynchronous
+    // sweep takes its row's own lower blocks as this sweep has just made them.
+    if constexpr (LA == UA) {
+        if (XL != Xn) {
+            const auto eighth = [](int64_t blocks) { return div_up(div_up(blocks, ROWS_PER_WG), 8); };
+            const int64_t ZU = p->nnzb - p->nnzb_lower - p->n;
+            const int slabs = max(1, eighth(p->n) / 16);
+            const BlockPattern P{p->n, (int)p->nnzb_lower, (int)p->nnzb, p->brec, slabs,
+                                 div_up(eighth(p->nnzb_lower), slabs), div_up(eighth(p->n), slabs),
+                                 div_up(eighth(ZU), slabs), p->lcol, UA ? p->pik : p->sik, UA ? p->pkj : p->skj};
+            k_factor_sweep_blocks<T, UA><<<P.grid(), WG, 0, s>>>(P, A, XU, Dp, Xn, Dn, flags);
+            return;
+        }
+    }
+    if constexpr (!LA)
+        k_factor_sweep<T, LA, UA, DA><<<grid, WG, 0, s>>>(
+            p->n, (int)p->nnzb_lower, p->rowptr, p->colidx, p->diag_pos, p->lrow, p->urow, p->pair_ptr, p->pik, p->pkj,
+            p->sik, p->skj, A, XL, XU, Dp, Xn, Dn, flags, p->symmetric ? 1 : 0);
 }
 
 template <typename T>

@@ -47,16 +47,28 @@ __global__ void k_pat_sym(int n, const int32_t *__restrict__ rowptr, const int32
     pat_sym_body(blockIdx.x, n, rowptr, colidx, diag_pos, shape);
 }
 
+// What a synchronous factor sweep needs of each block, in one load.
+__global__ void k_pat_blocks(int n, int ZL, const int32_t *__restrict__ rowptr, const int32_t *__restrict__ diag_pos,
+                             const int32_t *__restrict__ lrow, const int32_t *__restrict__ urow,
+                             const int32_t *__restrict__ pair_ptr, const int32_t *__restrict__ ldiag,
+                             int4 *__restrict__ brec) {
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= n) return;
+    const int b0 = rowptr[i], d = diag_pos[i], b1 = rowptr[i + 1];
+    for (int e = b0; e < b1; ++e) {
+        const int g = (int)split_pos(e, i, b0, d, lrow[i], urow[i], ZL, n);
+        brec[g] = make_int4(e, pair_ptr[e], pair_ptr[e + 1], e < d ? ldiag[g] : 0);
+    }
+}
+
 void free_pattern(abilu_pattern *p) {
     if (!p) return;
     (void)hipFree(p->rowptr);
     (void)hipFree(p->colidx);
     (void)hipFree(p->diag_pos);
     (void)hipFree(p->pair_ptr);
-    (void)hipFree(p->pik);
-    (void)hipFree(p->pkj);
-    (void)hipFree(p->sik);
-    (void)hipFree(p->skj);
+    (void)hipFree(p->pik);   // with pkj, sik, skj
+    (void)hipFree(p->brec);
     (void)hipFree(p->lrow);
     (void)hipFree(p->urow);
     (void)hipFree(p->lcol);
@@ -230,10 +242,12 @@ extern "C" abilu_status abilu_build_pattern(int32_t nbrows, const int32_t *d_row
         CKA(hipMalloc(&p->lcol, sizeof(int32_t) * 2 * (ZL + 1)));
         p->ldiag = p->lcol + (ZL + 1);
         CKA(hipMalloc(&p->ucol, sizeof(int32_t) * (ZU + 1)));
-        CKA(hipMalloc(&p->pik, sizeof(int32_t) * (npairs + 1)));
-        CKA(hipMalloc(&p->pkj, sizeof(int32_t) * (npairs + 1)));
-        CKA(hipMalloc(&p->sik, sizeof(int32_t) * (npairs + 1)));
-        CKA(hipMalloc(&p->skj, sizeof(int32_t) * (npairs + 1)));
+        // one allocation for the four pair lists, each from a 256-byte boundary
+        const int64_t pl = (npairs + 1 + 63) / 64 * 64;
+        CKA(hipMalloc(&p->pik, sizeof(int32_t) * 4 * pl));
+        p->pkj = p->pik + pl;
+        p->sik = p->pkj + pl;
+        p->skj = p->sik + pl;
         st = pattern_fill(n, Z, ZL, ZU, npairs, p->rowptr, p->colidx, p->diag_pos, p->lrow, p->urow, p->lcol,
                           p->ldiag, p->ucol, p->pik, p->pkj, p->sik, p->skj, scratch, s);
         if (st != ABILU_OK) goto fail;
@@ -250,6 +264,13 @@ extern "C" abilu_status abilu_build_pattern(int32_t nbrows, const int32_t *d_row
             const unsigned *h = (const unsigned *)p->pinned;
             p->symmetric = h[0] == 0;
             p->side = side_class(h + 1);
+            if (n > 0 && !p->fv()) {
+                CKA(hipMalloc(&p->brec, sizeof(int4) * Z));
+                k_pat_blocks<<<div_up(n, 256), 256, 0, s>>>(n, (int)ZL, p->rowptr, p->diag_pos, p->lrow, p->urow,
+                                                            p->pair_ptr, p->ldiag, p->brec);
+                CK(hipGetLastError());
+                CK(hipStreamSynchronize(s));
+            }
         }
     }
     (void)hipFree(scratch);
