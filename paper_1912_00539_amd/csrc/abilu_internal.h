@@ -28,6 +28,8 @@ struct abilu_pattern {
     int32_t *urow = nullptr;      // device [n+1]
     int32_t *lcol = nullptr;      // device [ZL+1] columns of the lower part (one padding entry)
     int32_t *ucol = nullptr;      // device [ZU+1] columns of the upper part
+    int2 *lrec = nullptr;         // device [4n], [4n] indices of pairs of sweeps (side <= 2 only; PairIndex)
+    int2 *urec = nullptr;
     int4 *brec = nullptr;         // device [Z] by factor layout: CSR position, pair range, ldiag (not if fv())
     int32_t *ldiag = nullptr;     // device [ZL+1] CSR position of the diagonal block of each lower column
                                   // (behind lcol in its allocation)
@@ -284,6 +286,10 @@ __device__ __forceinline__ int split_pos(int e, int i, int b0, int d, int lbase,
 
 // Broadcast lane L of each quad (4 consecutive lanes) to the whole quad with one DPP
 // quad_perm move per 32-bit word. All four lanes of the quad must be active.
+template <int K>
+__device__ __forceinline__ int qb(int v) {
+    return __builtin_amdgcn_mov_dpp(v, K * 0x55, 0xF, 0xF, true);
+}
 template <int L>
 __device__ __forceinline__ float qb(float v) {
     return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), L * 0x55, 0xF, 0xF, true));

@@ -66,23 +66,26 @@ __global__ __launch_bounds__(WG) void k_bwd(int n, const int32_t *__restrict__ u
 // Two sweeps in one launch (see fwd_pair_row, bwd_pair_row).
 template <typename T, typename YI, bool EMIT_Z, int CL, bool SCALED>
 __global__ __launch_bounds__(WG) void k_fwd_pair(int n, const int32_t *__restrict__ lrow,
-                                                 const int32_t *__restrict__ lcol, const T *__restrict__ Lb,
-                                                 const double *__restrict__ rhs, const YI *__restrict__ yin,
-                                                 T *__restrict__ yout, const T *__restrict__ Dinv,
-                                                 T *__restrict__ zout, const double *__restrict__ rscale, int first) {
+                                                 const int32_t *__restrict__ lcol, const int2 *__restrict__ rec,
+                                                 const T *__restrict__ Lb, const double *__restrict__ rhs,
+                                                 const YI *__restrict__ yin, T *__restrict__ yout,
+                                                 const T *__restrict__ Dinv, T *__restrict__ zout,
+                                                 const double *__restrict__ rscale, int first) {
     const double rs = rhs_scale<SCALED>(rscale);
     const int blk = xcd_tile(blockIdx.x, gridDim.x);
-    fwd_pair_row<T, YI, EMIT_Z, CL>(blk * ROWS_PER_WG + (threadIdx.x >> 2), n, lrow, lcol, Lb, rhs, yin, yout,
+    fwd_pair_row<T, YI, EMIT_Z, CL, CL == 2>(blk * ROWS_PER_WG + (threadIdx.x >> 2), n, lrow, lcol, rec, Lb, rhs, yin, yout,
                                     Dinv, zout, rs, first ? rs : 1.0);
 }
 
 template <typename T, typename ZO, int CU>
 __global__ __launch_bounds__(WG) void k_bwd_pair(int n, const int32_t *__restrict__ urow,
-                                                 const int32_t *__restrict__ ucol, const T *__restrict__ Ub,
-                                                 const T *__restrict__ Dinv, const T *__restrict__ y,
-                                                 const T *__restrict__ zin, ZO *__restrict__ zout, int desc) {
+                                                 const int32_t *__restrict__ ucol, const int2 *__restrict__ rec,
+                                                 const T *__restrict__ Ub, const T *__restrict__ Dinv,
+                                                 const T *__restrict__ y, const T *__restrict__ zin,
+                                                 ZO *__restrict__ zout, int desc) {
     const int blk = xcd_tile(desc ? (int)(gridDim.x - 1 - blockIdx.x) : (int)blockIdx.x, gridDim.x);
-    bwd_pair_row<T, ZO, CU>(blk * ROWS_PER_WG + (threadIdx.x >> 2), n, urow, ucol, Ub, Dinv, y, zin, zout);
+    bwd_pair_row<T, ZO, CU, CU == 2>(blk * ROWS_PER_WG + (threadIdx.x >> 2), n, urow, ucol, rec, Ub, Dinv, y, zin,
+                            zout);
 }
 
 // Single-worker sweeps (ABILU_ASYNC_SERIAL): one quad, in place; forward rows ascending,
@@ -899,9 +902,9 @@ abilu_status apply_t(const abilu_pattern *p, const T *LU, const T *Dinv, const d
             T *zo = EMIT ? za : (T *)nullptr;
             const int first = from_r ? 1 : 0;
             if (pair && two)
-                k_fwd_pair<T, YI, EMIT, 2, SC><<<pgrid, WG, 0, s>>>(n, lrow, lcol, Lb, r, yin, ycur, Dinv, zo, rs, first);
+                k_fwd_pair<T, YI, EMIT, 2, SC><<<pgrid, WG, 0, s>>>(n, lrow, lcol, p->lrec, Lb, r, yin, ycur, Dinv, zo, rs, first);
             else if (pair)
-                k_fwd_pair<T, YI, EMIT, 3, SC><<<pgrid, WG, 0, s>>>(n, lrow, lcol, Lb, r, yin, ycur, Dinv, zo, rs, first);
+                k_fwd_pair<T, YI, EMIT, 3, SC><<<pgrid, WG, 0, s>>>(n, lrow, lcol, p->lrec, Lb, r, yin, ycur, Dinv, zo, rs, first);
             else
                 k_fwd<T, YI, EMIT, SC><<<grid, WG, 0, s>>>(n, lrow, lcol, Lb, r, yin, ycur, Dinv, zo, rs, first);
         };
@@ -938,11 +941,11 @@ abilu_status apply_t(const abilu_pattern *p, const T *LU, const T *Dinv, const d
         const double *none = nullptr;
         T *zcur = (sync || pairs) ? ((zprev == za) ? zb : za) : za;
         if (pair && last) {
-            if (two) k_bwd_pair<T, double, 2><<<pgrid, WG, 0, s>>>(n, urow, ucol, Ub, Dinv, yfin, zprev, z, desc);
-            else k_bwd_pair<T, double, 3><<<pgrid, WG, 0, s>>>(n, urow, ucol, Ub, Dinv, yfin, zprev, z, desc);
+            if (two) k_bwd_pair<T, double, 2><<<pgrid, WG, 0, s>>>(n, urow, ucol, p->urec, Ub, Dinv, yfin, zprev, z, desc);
+            else k_bwd_pair<T, double, 3><<<pgrid, WG, 0, s>>>(n, urow, ucol, p->urec, Ub, Dinv, yfin, zprev, z, desc);
         } else if (pair) {
-            if (two) k_bwd_pair<T, T, 2><<<pgrid, WG, 0, s>>>(n, urow, ucol, Ub, Dinv, yfin, zprev, zcur, desc);
-            else k_bwd_pair<T, T, 3><<<pgrid, WG, 0, s>>>(n, urow, ucol, Ub, Dinv, yfin, zprev, zcur, desc);
+            if (two) k_bwd_pair<T, T, 2><<<pgrid, WG, 0, s>>>(n, urow, ucol, p->urec, Ub, Dinv, yfin, zprev, zcur, desc);
+            else k_bwd_pair<T, T, 3><<<pgrid, WG, 0, s>>>(n, urow, ucol, p->urec, Ub, Dinv, yfin, zprev, zcur, desc);
         } else if (last && dual) {
             k_bwd<T, T, double, true, true><<<grid, WG, 0, s>>>(n, urow, ucol, Ub, Dinv, yfin, zprev, z, zprev, desc, none);
         } else if (last) {

@@ -288,40 +288,76 @@ __device__ __forceinline__ void bwd_body(int blk, int n, const int32_t *__restri
 __device__ __forceinline__ int xcd_tile(int b, int g) { return (b & 7) * (g >> 3) + (b >> 3); }
 inline int xcd_grid(int tiles) { return (tiles + 7) / 8 * 8; }
 
+// The indices of a row of a pair of sweeps: its first block b0 and its count, the columns j of its
+// blocks, the first block c0 and the count nj of each row j, and their columns. For rows of at most two
+// blocks the pattern keeps all but b0 in a record of 32 bytes, eight per lane of the quad, so that
+// every block and vector is asked for after one load, where the walk is two levels (four with the
+// columns) deeper.
+template <int CL, bool REC>
+struct PairIndex {
+    int b0, nl, j[CL], c0[CL], nj[CL], kk[CL][CL];
+    __device__ __forceinline__ void load(int i, int r, const int32_t *__restrict__ row,
+                                         const int32_t *__restrict__ col, const int2 *__restrict__ rec) {
+        b0 = row[i];
+        if constexpr (REC) {
+            const int2 w = rec[(int64_t)i * 4 + r];
+            const unsigned p0 = (unsigned)qb<1>(w.x), p1 = (unsigned)qb<1>(w.y);
+            j[0] = qb<0>(w.x);
+            j[1] = qb<0>(w.y);
+            nl = (j[0] >= 0) + (j[1] >= 0);
+            c0[0] = (int)(p0 >> 2);
+            nj[0] = (int)(p0 & 3);
+            c0[1] = (int)(p1 >> 2);
+            nj[1] = (int)(p1 & 3);
+            kk[0][0] = qb<2>(w.x);
+            kk[0][1] = qb<2>(w.y);
+            kk[1][0] = qb<3>(w.x);
+            kk[1][1] = qb<3>(w.y);
+        } else {
+            nl = row[i + 1] - b0;
+#pragma unroll
+            for (int u = 0; u < CL; ++u)
+                if (u < nl) j[u] = col[b0 + u];
+#pragma unroll
+            for (int u = 0; u < CL; ++u) {
+                if (u < nl) {
+                    c0[u] = row[j[u]];
+                    nj[u] = row[j[u] + 1] - c0[u];
+                }
+            }
+        }
+    }
+};
+
 // Two forward sweeps in one, for rows of at most CL strictly lower blocks: row i of the second sweep
 // needs y_j of the first for its lower neighbours j, and forms each again from its own row,
 // y_j = r_j - sum_k L_jk yin_k. Same operations on each element, so the bits of two synchronous
 // sweeps; as an asynchronous iteration it is the schedule in which no read of the second sweep sees
 // a value written in it.
-// A small mesh spends a launch and a chain of three loads on a sweep (here five loads and one launch
-// for both); a large one reads L once instead of twice, if the neighbours' rows are still in the L2
-// of the same XCD, hence xcd_tile. Forward and backward together, three sweeps, us: 2,000 triangles
-// 19 -> 11.5 (two launches for four); 61,952 FP64 21.2 -> 16.1; 180,000 FP32 29.8 -> 24.0; 500,000
-// line-ordered quads FP32 87.6 -> 73.9 (94.3 without xcd_tile); 2 million FP64 628 -> 471.
-template <typename T, typename YI, bool EMIT_Z, int CL>
+// A small mesh spends a launch and a chain of loads on a sweep, here one launch for both; a large one
+// reads L once instead of twice, if the neighbours' rows are still in the L2 of the same XCD, hence
+// xcd_tile. Forward and backward together, three sweeps, us: 2,000 triangles 19 -> 11.5 (two launches
+// for four); 61,952 FP64 21.2 -> 12.8; 180,000 FP32 29.8 -> 22.2; 500,000 line-ordered quads FP32
+// 87.6 -> 73.0 (94.3 without xcd_tile); 4 million triangles FP32 608 -> 477. Of this the records gave,
+// on kernels, 2,000 FP32 4 -> 3.1; 180,000 FP32 13.1 + 12.1 -> 12.1 + 10.1; 4 million 253 + 245 ->
+// 251 + 227. Two rows per quad at once (95 registers) lose: 180,000 14.7 + 11.1, 4 million 272 + 221.
+template <typename T, typename YI, bool EMIT_Z, int CL, bool REC>
 __device__ __forceinline__ void fwd_pair_row(int i, int n, const int32_t *__restrict__ lrow,
-                                             const int32_t *__restrict__ lcol, const T *__restrict__ Lb,
+                                             const int32_t *__restrict__ lcol, const int2 *__restrict__ rec, const T *__restrict__ Lb,
                                              const double *__restrict__ rhs, const YI *__restrict__ yin,
                                              T *__restrict__ yout, const T *__restrict__ Dinv, T *__restrict__ zout,
                                              double rs, double ys) {
     const int r = threadIdx.x & 3;
     if (i >= n) return;
-    const int b0 = lrow[i], nl = lrow[i + 1] - b0;
     T acc = (T)scaled(rhs[(int64_t)i * 4 + r], rs);
-    int j[CL], c0[CL], nj[CL];
+    PairIndex<CL, REC> X;
+    X.load(i, r, lrow, lcol, rec);
+    const auto &[b0, nl, j, c0, nj, kk] = X;
     T l[CL][4], yj[CL], m[CL][CL][4], yk[CL][CL];
 #pragma unroll
     for (int u = 0; u < CL; ++u) {
         if (u < nl) {
-            j[u] = lcol[b0 + u];
             load_row(Lb + (int64_t)(b0 + u) * BB, r, l[u]);
-        }
-    }
-#pragma unroll
-    for (int u = 0; u < CL; ++u) {
-        if (u < nl) {
-            c0[u] = lrow[j[u]];
-            nj[u] = lrow[j[u] + 1] - c0[u];
             yj[u] = (T)scaled(rhs[(int64_t)j[u] * 4 + r], rs);
         }
     }
@@ -333,7 +369,7 @@ __device__ __forceinline__ void fwd_pair_row(int i, int n, const int32_t *__rest
 #pragma unroll
             for (int v = 0; v < CL; ++v) {
                 if (v < nj[u]) {
-                    const int k = lcol[c0[u] + v];
+                    const int k = REC ? kk[u][v] : lcol[c0[u] + v];
                     load_row(Lb + (int64_t)(c0[u] + v) * BB, r, m[u][v]);
                     if constexpr (sizeof(YI) == 8) yk[u][v] = (T)scaled(yin[(int64_t)k * 4 + r], ys);
                     else yk[u][v] = (T)yin[(int64_t)k * 4 + r];
@@ -367,30 +403,24 @@ __device__ __forceinline__ void fwd_pair_row(int i, int n, const int32_t *__rest
 
 // Two backward sweeps in one, likewise (rows of at most CU strictly upper blocks):
 // z_j = D_j (y_j - sum_k U_jk zin_k) for the upper neighbours j, then z_i from them.
-template <typename T, typename ZO, int CU>
+template <typename T, typename ZO, int CU, bool REC>
 __device__ __forceinline__ void bwd_pair_row(int i, int n, const int32_t *__restrict__ urow,
-                                             const int32_t *__restrict__ ucol, const T *__restrict__ Ub,
-                                             const T *__restrict__ Dinv, const T *__restrict__ y,
-                                             const T *__restrict__ zin, ZO *__restrict__ zout) {
+                                             const int32_t *__restrict__ ucol, const int2 *__restrict__ rec,
+                                             const T *__restrict__ Ub, const T *__restrict__ Dinv,
+                                             const T *__restrict__ y, const T *__restrict__ zin,
+                                             ZO *__restrict__ zout) {
     const int r = threadIdx.x & 3;
     if (i >= n) return;
-    const int b0 = urow[i], nu = urow[i + 1] - b0;
     T acc = y[(int64_t)i * 4 + r];
-    int j[CU], c0[CU], nj[CU];
+    PairIndex<CU, REC> X;
+    X.load(i, r, urow, ucol, rec);
+    const auto &[b0, nu, j, c0, nj, kk] = X;
     T l[CU][4], yj[CU], dj[CU][4], m[CU][CU][4], zk[CU][CU], dr[4];
-#pragma unroll
-    for (int u = 0; u < CU; ++u) {
-        if (u < nu) {
-            j[u] = ucol[b0 + u];
-            load_row(Ub + (int64_t)(b0 + u) * BB, r, l[u]);
-        }
-    }
     load_row(Dinv + (int64_t)i * BB, r, dr);
 #pragma unroll
     for (int u = 0; u < CU; ++u) {
         if (u < nu) {
-            c0[u] = urow[j[u]];
-            nj[u] = urow[j[u] + 1] - c0[u];
+            load_row(Ub + (int64_t)(b0 + u) * BB, r, l[u]);
             yj[u] = y[(int64_t)j[u] * 4 + r];
             load_row(Dinv + (int64_t)j[u] * BB, r, dj[u]);
         }
@@ -401,7 +431,7 @@ __device__ __forceinline__ void bwd_pair_row(int i, int n, const int32_t *__rest
 #pragma unroll
             for (int v = 0; v < CU; ++v) {
                 if (v < nj[u]) {
-                    const int k = ucol[c0[u] + v];
+                    const int k = REC ? kk[u][v] : ucol[c0[u] + v];
                     load_row(Ub + (int64_t)(c0[u] + v) * BB, r, m[u][v]);
                     zk[u][v] = zin[(int64_t)k * 4 + r];
                 }

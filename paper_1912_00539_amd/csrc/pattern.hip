@@ -47,6 +47,32 @@ __global__ void k_pat_sym(int n, const int32_t *__restrict__ rowptr, const int32
     pat_sym_body(blockIdx.x, n, rowptr, colidx, diag_pos, shape);
 }
 
+// PairIndex's records of rows of at most two blocks a side: {j0, j1}, {c0, c1} with the counts in the
+// low two bits, {k00, k01}, {k10, k11}; -1 where there is none.
+__global__ void k_pat_pairs(int n, const int32_t *__restrict__ rowptr, const int32_t *__restrict__ colidx,
+                            const int32_t *__restrict__ diag_pos, const int32_t *__restrict__ lrow,
+                            const int32_t *__restrict__ urow, int2 *__restrict__ lrec, int2 *__restrict__ urec) {
+    const int t = blockIdx.x * blockDim.x + threadIdx.x;
+    const int i = t >> 1, upper = t & 1;
+    if (i >= n) return;
+    int j[2], k[2][2];
+    unsigned c[2];
+    const int d = diag_pos[i], e0 = upper ? d + 1 : rowptr[i], e1 = upper ? rowptr[i + 1] : d;
+    for (int u = 0; u < 2; ++u) {
+        j[u] = k[u][0] = k[u][1] = -1;
+        c[u] = 0;
+        if (e0 + u < e1) {
+            j[u] = colidx[e0 + u];
+            const int dj = diag_pos[j[u]], f0 = upper ? dj + 1 : rowptr[j[u]], f1 = upper ? rowptr[j[u] + 1] : dj;
+            c[u] = (unsigned)(upper ? urow[j[u]] : lrow[j[u]]) << 2 | (unsigned)(f1 - f0);
+            for (int v = 0; v < f1 - f0; ++v) k[u][v] = colidx[f0 + v];
+        }
+    }
+    int4 *out = (int4 *)((upper ? urec : lrec) + (int64_t)i * 4);
+    out[0] = make_int4(j[0], j[1], (int)c[0], (int)c[1]);
+    out[1] = make_int4(k[0][0], k[0][1], k[1][0], k[1][1]);
+}
+
 // What a synchronous factor sweep needs of each block, in one load.
 __global__ void k_pat_blocks(int n, int ZL, const int32_t *__restrict__ rowptr, const int32_t *__restrict__ diag_pos,
                              const int32_t *__restrict__ lrow, const int32_t *__restrict__ urow,
@@ -61,18 +87,15 @@ __global__ void k_pat_blocks(int n, int ZL, const int32_t *__restrict__ rowptr, 
     }
 }
 
+// a length in ints, up to a 256-byte boundary
+size_t ints(int64_t len) { return (size_t)((len + 63) / 64 * 64); }
+
 void free_pattern(abilu_pattern *p) {
     if (!p) return;
-    (void)hipFree(p->rowptr);
-    (void)hipFree(p->colidx);
-    (void)hipFree(p->diag_pos);
-    (void)hipFree(p->pair_ptr);
-    (void)hipFree(p->pik);   // with pkj, sik, skj
+    (void)hipFree(p->rowptr);   // with colidx, diag_pos, pair_ptr, lrow, done, urow
+    (void)hipFree(p->lcol);     // with ldiag, ucol, pik, pkj, sik, skj
+    (void)hipFree(p->lrec);     // with urec
     (void)hipFree(p->brec);
-    (void)hipFree(p->lrow);
-    (void)hipFree(p->urow);
-    (void)hipFree(p->lcol);
-    (void)hipFree(p->ucol);
     abilu::free_chunks(p);
     if (p->pinned) (void)hipHostFree(p->pinned);
     delete p;
@@ -161,9 +184,8 @@ abilu_status pattern_fill(int32_t n, int64_t Z, int64_t ZL, int64_t ZU, int64_t 
                           int32_t *lcol, int32_t *ldiag, int32_t *ucol, int32_t *pik, int32_t *pkj, int32_t *sik,
                           int32_t *skj, const void *scratch, hipStream_t s) {
     const int64_t *ptr64 = pat_scratch(const_cast<void *>(scratch), n, Z).ptr64;
-    // ldiag follows lcol
-    if (!hip_ok(hipMemsetAsync(lcol, 0, sizeof(int32_t) * 2 * (ZL + 1), s), "lcol clear") ||
-        !hip_ok(hipMemsetAsync(ucol, 0, sizeof(int32_t) * (ZU + 1), s), "ucol clear"))
+    // the arrays from lcol to ucol are one allocation
+    if (!hip_ok(hipMemsetAsync(lcol, 0, sizeof(int32_t) * (size_t)(ucol - lcol + ZU + 1), s), "column clear"))
         return ABILU_EDEVICE;
     if (n > 0) {
         k_pat_tri_cols<<<div_up(n, 256), 256, 0, s>>>(n, rowptr, colidx, diag_pos, lrow, urow, lcol, ldiag, ucol);
@@ -221,15 +243,17 @@ extern "C" abilu_status abilu_build_pattern(int32_t nbrows, const int32_t *d_row
         CKA(hipHostMalloc((void **)&p->pinned, 64 * sizeof(double), hipHostMallocDefault));
         CK(hipHostGetDevicePointer((void **)&p->pinned_dev, p->pinned, 0));
         for (int q = 0; q < 64; ++q) p->pinned[q] = 0.0;
-        CKA(hipMalloc(&p->rowptr, sizeof(int32_t) * (n + 1)));
-        CKA(hipMalloc(&p->colidx, sizeof(int32_t) * (Z + 1)));
-        CKA(hipMalloc(&p->diag_pos, sizeof(int32_t) * (n + 1)));
-        CKA(hipMalloc(&p->pair_ptr, sizeof(int32_t) * (Z + 1)));
-        const size_t lrow_ints = ((size_t)n + 1 + DONE_STRIDE - 1) / DONE_STRIDE * DONE_STRIDE;
-        CKA(hipMalloc(&p->lrow, sizeof(int32_t) * (lrow_ints + DONE_INTS)));
-        p->done = p->lrow + lrow_ints;
+        {
+            const size_t nr = ints(n + 1), nz = ints(Z + 1), nd = ints(DONE_INTS);
+            CKA(hipMalloc(&p->rowptr, sizeof(int32_t) * (4 * nr + 2 * nz + nd)));
+            p->diag_pos = p->rowptr + nr;
+            p->lrow = p->diag_pos + nr;
+            p->urow = p->lrow + nr;
+            p->done = p->urow + nr;
+            p->colidx = p->done + nd;
+            p->pair_ptr = p->colidx + nz;
+        }
         CK(hipMemsetAsync(p->done, 0, sizeof(int32_t) * DONE_INTS, s));
-        CKA(hipMalloc(&p->urow, sizeof(int32_t) * (n + 1)));
         CKA(hipMalloc(&scratch, pattern_scratch_bytes(n, Z)));
         CK(hipMemcpyAsync(p->rowptr, d_rowptr, sizeof(int32_t) * (n + 1), hipMemcpyDeviceToDevice, s));
         if (Z > 0) CK(hipMemcpyAsync(p->colidx, d_colidx, sizeof(int32_t) * Z, hipMemcpyDeviceToDevice, s));
@@ -239,15 +263,16 @@ extern "C" abilu_status abilu_build_pattern(int32_t nbrows, const int32_t *d_row
         p->nnzb_lower = ZL;
         p->nnzb_upper = ZU;
         p->npairs = npairs;
-        CKA(hipMalloc(&p->lcol, sizeof(int32_t) * 2 * (ZL + 1)));
-        p->ldiag = p->lcol + (ZL + 1);
-        CKA(hipMalloc(&p->ucol, sizeof(int32_t) * (ZU + 1)));
-        // one allocation for the four pair lists, each from a 256-byte boundary
-        const int64_t pl = (npairs + 1 + 63) / 64 * 64;
-        CKA(hipMalloc(&p->pik, sizeof(int32_t) * 4 * pl));
-        p->pkj = p->pik + pl;
-        p->sik = p->pkj + pl;
-        p->skj = p->sik + pl;
+        {
+            const size_t nl = ints(ZL + 1), nu = ints(ZU + 1), np = ints(npairs + 1);
+            CKA(hipMalloc(&p->lcol, sizeof(int32_t) * (2 * nl + nu + 4 * np)));
+            p->ldiag = p->lcol + nl;
+            p->ucol = p->ldiag + nl;
+            p->pik = p->ucol + nu;
+            p->pkj = p->pik + np;
+            p->sik = p->pkj + np;
+            p->skj = p->sik + np;
+        }
         st = pattern_fill(n, Z, ZL, ZU, npairs, p->rowptr, p->colidx, p->diag_pos, p->lrow, p->urow, p->lcol,
                           p->ldiag, p->ucol, p->pik, p->pkj, p->sik, p->skj, scratch, s);
         if (st != ABILU_OK) goto fail;
@@ -264,13 +289,20 @@ extern "C" abilu_status abilu_build_pattern(int32_t nbrows, const int32_t *d_row
             const unsigned *h = (const unsigned *)p->pinned;
             p->symmetric = h[0] == 0;
             p->side = side_class(h + 1);
+            if (n > 0 && p->side <= 2) {
+                CKA(hipMalloc(&p->lrec, sizeof(int2) * 8 * (size_t)n));
+                p->urec = p->lrec + 4 * (size_t)n;
+                k_pat_pairs<<<div_up(2 * (int64_t)n, 256), 256, 0, s>>>(n, p->rowptr, p->colidx, p->diag_pos, p->lrow,
+                                                                        p->urow, p->lrec, p->urec);
+                CK(hipGetLastError());
+            }
             if (n > 0 && !p->fv()) {
                 CKA(hipMalloc(&p->brec, sizeof(int4) * Z));
                 k_pat_blocks<<<div_up(n, 256), 256, 0, s>>>(n, (int)ZL, p->rowptr, p->diag_pos, p->lrow, p->urow,
                                                             p->pair_ptr, p->ldiag, p->brec);
                 CK(hipGetLastError());
-                CK(hipStreamSynchronize(s));
             }
+            CK(hipStreamSynchronize(s));
         }
     }
     (void)hipFree(scratch);

@@ -162,7 +162,7 @@ __global__ __launch_bounds__(WG) void kb_fwd_pair(const Slot *slots, const Membe
     const Member M = mem[find_member(mem, nmem, b)];
     const Slot &S = slots[M.slot];
     const double rs = S.vscale[M.k];
-    fwd_pair_row<T, YI, EMIT_Z, CL>((b - M.tile0) * ROWS_PER_WG + (threadIdx.x >> 2), S.n, S.lrow, S.lcol,
+    fwd_pair_row<T, YI, EMIT_Z, CL, false>((b - M.tile0) * ROWS_PER_WG + (threadIdx.x >> 2), S.n, S.lrow, S.lcol, nullptr,
                                         (const T *)S.LU, (const double *)role(S, M, R_VK),
                                         (const YI *)role(S, M, yin), (T *)role(S, M, yout), (const T *)S.Dinv,
                                         (T *)S.za, rs, yin == R_VK ? rs : 1.0);
@@ -176,7 +176,7 @@ __global__ __launch_bounds__(WG) void kb_bwd_pair(const Slot *slots, const Membe
     const Member M = mem[find_member(mem, nmem, b)];
     const Slot &S = slots[M.slot];
     const T *Ub = (const T *)S.LU + ((int64_t)S.ZL + S.n) * BB;
-    bwd_pair_row<T, ZO, CL>((b - M.tile0) * ROWS_PER_WG + (threadIdx.x >> 2), S.n, S.urow, S.ucol, Ub,
+    bwd_pair_row<T, ZO, CL, false>((b - M.tile0) * ROWS_PER_WG + (threadIdx.x >> 2), S.n, S.urow, S.ucol, nullptr, Ub,
                                 (const T *)S.Dinv, (const T *)role(S, M, y), (const T *)role(S, M, zin),
                                 (ZO *)role(S, M, zout));
 }
