@@ -292,12 +292,13 @@ inline int xcd_grid(int tiles) { return (tiles + 7) / 8 * 8; }
 // blocks, the first block c0 and the count nj of each row j, and their columns. For rows of at most two
 // blocks the pattern keeps all but b0 in a record of 32 bytes, eight per lane of the quad, so that
 // every block and vector is asked for after one load, where the walk is two levels (four with the
-// columns) deeper.
+// columns) deeper. The row's own blocks are asked for between first() and second(), so that the walk
+// does not hold them up (server, which keeps no records: 57 us a sweep behind it, 52 so).
 template <int CL, bool REC>
 struct PairIndex {
     int b0, nl, j[CL], c0[CL], nj[CL], kk[CL][CL];
-    __device__ __forceinline__ void load(int i, int r, const int32_t *__restrict__ row,
-                                         const int32_t *__restrict__ col, const int2 *__restrict__ rec) {
+    __device__ __forceinline__ void first(int i, int r, const int32_t *__restrict__ row,
+                                          const int32_t *__restrict__ col, const int2 *__restrict__ rec) {
         b0 = row[i];
         if constexpr (REC) {
             const int2 w = rec[(int64_t)i * 4 + r];
@@ -318,6 +319,10 @@ struct PairIndex {
 #pragma unroll
             for (int u = 0; u < CL; ++u)
                 if (u < nl) j[u] = col[b0 + u];
+        }
+    }
+    __device__ __forceinline__ void second(const int32_t *__restrict__ row) {
+        if constexpr (!REC) {
 #pragma unroll
             for (int u = 0; u < CL; ++u) {
                 if (u < nl) {
@@ -351,13 +356,16 @@ __device__ __forceinline__ void fwd_pair_row(int i, int n, const int32_t *__rest
     if (i >= n) return;
     T acc = (T)scaled(rhs[(int64_t)i * 4 + r], rs);
     PairIndex<CL, REC> X;
-    X.load(i, r, lrow, lcol, rec);
+    X.first(i, r, lrow, lcol, rec);
     const auto &[b0, nl, j, c0, nj, kk] = X;
     T l[CL][4], yj[CL], m[CL][CL][4], yk[CL][CL];
 #pragma unroll
+    for (int u = 0; u < CL; ++u)
+        if (u < nl) load_row(Lb + (int64_t)(b0 + u) * BB, r, l[u]);
+    X.second(lrow);
+#pragma unroll
     for (int u = 0; u < CL; ++u) {
         if (u < nl) {
-            load_row(Lb + (int64_t)(b0 + u) * BB, r, l[u]);
             yj[u] = (T)scaled(rhs[(int64_t)j[u] * 4 + r], rs);
         }
     }
@@ -413,14 +421,17 @@ __device__ __forceinline__ void bwd_pair_row(int i, int n, const int32_t *__rest
     if (i >= n) return;
     T acc = y[(int64_t)i * 4 + r];
     PairIndex<CU, REC> X;
-    X.load(i, r, urow, ucol, rec);
+    X.first(i, r, urow, ucol, rec);
     const auto &[b0, nu, j, c0, nj, kk] = X;
     T l[CU][4], yj[CU], dj[CU][4], m[CU][CU][4], zk[CU][CU], dr[4];
+#pragma unroll
+    for (int u = 0; u < CU; ++u)
+        if (u < nu) load_row(Ub + (int64_t)(b0 + u) * BB, r, l[u]);
     load_row(Dinv + (int64_t)i * BB, r, dr);
+    X.second(urow);
 #pragma unroll
     for (int u = 0; u < CU; ++u) {
         if (u < nu) {
-            load_row(Ub + (int64_t)(b0 + u) * BB, r, l[u]);
             yj[u] = y[(int64_t)j[u] * 4 + r];
             load_row(Dinv + (int64_t)j[u] * BB, r, dj[u]);
         }
@@ -753,26 +764,37 @@ __device__ __forceinline__ void reduce_cols_body(int blk, const double *__restri
 constexpr int FOLD_NB = 512;
 __device__ __forceinline__ void reduce_cols_fold(const double *partial, int nb, int cols, double *out) {
     constexpr int PER = FOLD_NB / WG;   // rounds of WG entries
+    constexpr int CC = 3;               // columns whose loads a wave has in flight together
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    for (int c = wave; c < cols; c += WG / 64) {
-        double v[PER][WG / 64];
+    for (int c0 = wave; c0 < cols; c0 += CC * (WG / 64)) {
+        double v[CC][PER][WG / 64];
 #pragma unroll
-        for (int r = 0; r < PER; ++r)
+        for (int h = 0; h < CC; ++h) {
+            const int c = c0 + h * (WG / 64);
 #pragma unroll
-            for (int p = 0; p < WG / 64; ++p) {
-                const int b = r * WG + p * 64 + lane;
-                v[r][p] = b < nb ? load_agent(partial + (int64_t)c * nb + b) : 0.0;
-            }
-        double s[WG / 64];
+            for (int r = 0; r < PER; ++r)
 #pragma unroll
-        for (int p = 0; p < WG / 64; ++p) {
-            s[p] = 0.0;
-#pragma unroll
-            for (int r = 0; r < PER; ++r) s[p] += v[r][p];
+                for (int p = 0; p < WG / 64; ++p) {
+                    const int b = r * WG + p * 64 + lane;
+                    v[h][r][p] = c < cols && b < nb ? load_agent(partial + (int64_t)c * nb + b) : 0.0;
+                }
         }
 #pragma unroll
-        for (int p = 0; p < WG / 64; ++p) s[p] = wave_sum(s[p]);
-        if (lane == 0) out[c] = (s[0] + s[1]) + (s[2] + s[3]);
+        for (int h = 0; h < CC; ++h) {
+            const int c = c0 + h * (WG / 64);
+            if (c < cols) {
+                double s[WG / 64];
+#pragma unroll
+                for (int p = 0; p < WG / 64; ++p) {
+                    s[p] = 0.0;
+#pragma unroll
+                    for (int r = 0; r < PER; ++r) s[p] += v[h][r][p];
+                }
+#pragma unroll
+                for (int p = 0; p < WG / 64; ++p) s[p] = wave_sum(s[p]);
+                if (lane == 0) out[c] = (s[0] + s[1]) + (s[2] + s[3]);
+            }
+        }
     }
     __syncthreads();
 }
@@ -784,10 +806,12 @@ __device__ __forceinline__ void reduce_cols_fold(const double *partial, int nb, 
 // it. A pass that read u_k and wrote v_k took 40 us of 1,690 per iteration at 4 million cells.
 
 // ---- steps on the small dense Hessenberg problem (column-major, ld = m + 1), run by one workgroup
-// on the column sums `red` of the reduction before them (LDS or registers of the caller's choice:
-// red(c) is column c's sum). Columns and rotations are taken one per lane; only the chain of
-// rotations and the substitution are serial, and those run in LDS. (One lane taking everything from
-// memory spent 8-12 us on six Arnoldi vectors, a load at a time.)
+// on the column sums `red` of the reduction before them (in LDS). Columns and rotations are taken one
+// per lane; only the chain of rotations and the substitution are serial. What a step reads of earlier
+// launches' results every workgroup loads before its reduction ends (StepIn): by the workgroup that
+// turns out to be the last, no load is waited for between the sums and the status. (One lane taking
+// everything from memory spent 8-12 us on six Arnoldi vectors. With the loads after the sums the
+// Givens step's launch took 8.8 us at 10,000 cells and 5.8 at 180,000, with them before 7.4 and 4.9.)
 enum { RS_BETA_START_ZERO = 0, RS_BETA_START_X, RS_BETA, RS_GS1, RS_GS2, RS_GIVENS, RS_NONE };
 
 struct KPtrs {
@@ -801,8 +825,34 @@ struct KPtrs {
     bool single = false, last = false;    // last: no Arnoldi step follows this one
 };
 
+// Lane q has entry q of the vectors (q <= k < MAX_RESTART = WG).
+static_assert(MAX_RESTART <= WG, "a lane per Arnoldi vector");
+struct StepIn {
+    double scale, h, cs, sn;      // of vector / rotation q
+    double gk, nrm, tol, num;
+    unsigned flags;
+    int guard;
+    template <int OP>
+    __device__ __forceinline__ void load(const KPtrs &P, int k, int m) {
+        const int q = threadIdx.x;
+        if (OP == RS_GS1 || OP == RS_GS2) scale = q <= k ? P.vscale[q] : 0.0;
+        if (OP == RS_GS2 || OP == RS_GIVENS) h = q <= k ? P.H[(int64_t)k * (m + 1) + q] : 0.0;
+        if (OP == RS_GS2) nrm = P.misc[MI_NRM0];
+        if (OP == RS_GIVENS) {
+            cs = q < k ? P.cs[q] : 0.0;
+            sn = q < k ? P.sn[q] : 0.0;
+            guard = *P.guard;
+            gk = P.g[k];
+            nrm = P.misc[MI_NRM1];
+            tol = P.misc[MI_TOL];
+        }
+        if (OP == RS_BETA) num = P.status[ST_NUM];
+        if (P.host) flags = *P.flags;
+    }
+};
+
 // Hand the status to the host (one lane): three writes through to its pinned memory.
-__device__ __forceinline__ void publish(const KPtrs &P, double v0, double v1, int guard) {
+__device__ __forceinline__ void publish(const KPtrs &P, double v0, double v1, unsigned flags, int guard) {
     if (!P.host) return;
     auto put = [&](int w, unsigned long long v) {
         __hip_atomic_store(P.host + w, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
@@ -810,13 +860,43 @@ __device__ __forceinline__ void publish(const KPtrs &P, double v0, double v1, in
     auto bits = [](double v) {
         return v == v ? (unsigned long long)__double_as_longlong(v) : 0x7ff8000000000000ull;
     };
-    put(2, (unsigned long long)*P.flags | (guard ? 1ull << 32 : 0ull));
+    put(2, (unsigned long long)flags | (guard ? 1ull << 32 : 0ull));
     put(0, bits(v0));
     put(1, bits(v1));
 }
 
-// Back substitution on the k x k upper triangle: coef = y, by columns (one workgroup).
+__device__ __forceinline__ double lane_value(double v, int lane) {
+    const long long b = __double_as_longlong(v);
+    const unsigned lo = (unsigned)__builtin_amdgcn_readlane((int)b, lane);
+    const unsigned hi = (unsigned)__builtin_amdgcn_readlane((int)(b >> 32), lane);
+    return __longlong_as_double((long long)((unsigned long long)hi << 32 | lo));
+}
+
+// Back substitution on the k x k upper triangle: coef = y, by columns (one workgroup). Up to 64
+// unknowns stay in the lanes of one wave, and eight columns are loaded at a time (of eight
+// unknowns: a launch of 4.2 us, and of 9.0 with a load and two barriers per column).
 __device__ __forceinline__ void solve_body(int k, int m, const double *H, const double *g, double *coef) {
+    if (k <= 64) {
+        const int t = threadIdx.x;
+        if (t >= 64) return;
+        constexpr int E = 8;
+        double y = t < k ? g[t] : 0.0;
+        for (int q0 = k - 1; q0 >= 0; q0 -= E) {
+            double h[E];
+#pragma unroll
+            for (int e = 0; e < E; ++e) h[e] = t <= q0 - e ? H[(int64_t)(q0 - e) * (m + 1) + t] : 0.0;
+#pragma unroll
+            for (int e = 0; e < E; ++e) {
+                const int q = q0 - e;
+                if (q < 0) break;
+                const double yq = lane_value(y, q) / lane_value(h[e], q);
+                if (t < q) y -= h[e] * yq;
+                else if (t == q) y = yq;
+            }
+        }
+        if (t < k) coef[t] = y;
+        return;
+    }
     __shared__ double y[MAX_RESTART];
     for (int t = threadIdx.x; t < k; t += blockDim.x) y[t] = g[t];
     __syncthreads();
@@ -832,14 +912,15 @@ __device__ __forceinline__ void solve_body(int k, int m, const double *H, const 
     }
 }
 
-__device__ __forceinline__ void beta_step(const KPtrs &P, int m, double r0, bool num, bool beta_slot, bool init_g) {
+__device__ __forceinline__ void beta_step(const KPtrs &P, const StepIn &I, int m, double r0, bool num, bool beta_slot,
+                                          bool init_g) {
     const double beta = sqrt(r0);
     if (threadIdx.x == 0) {
+        if (beta_slot) publish(P, beta, num ? beta : I.num, I.flags, 0);
         if (num) {
             P.status[ST_NUM] = beta;
             P.misc[MI_TOL] = P.rtol * (beta > 0 ? beta : 1.0);
         }
-        if (beta_slot) publish(P, beta, num ? beta : P.status[ST_NUM], 0);
         if (beta_slot) P.status[ST_BETA] = beta;
         P.vscale[0] = beta != 0.0 ? 1.0 / beta : 1.0;
     }
@@ -848,87 +929,87 @@ __device__ __forceinline__ void beta_step(const KPtrs &P, int m, double r0, bool
 }
 
 // H(0:k,k) = v_k . w, coef those on u_k, nrm0 = ||w|| before the first pass
-__device__ __forceinline__ void gs1_step(const KPtrs &P, int k, int m, const double *red) {
-    for (int q = threadIdx.x; q <= k; q += blockDim.x) {
-        const double sq = P.vscale[q], h = sq * red[q];
+__device__ __forceinline__ void gs1_step(const KPtrs &P, const StepIn &I, int k, int m, const double *red) {
+    const int q = threadIdx.x;
+    if (q <= k) {
+        const double h = I.scale * red[q];
         P.H[(int64_t)k * (m + 1) + q] = h;
-        P.coef[q] = sq * h;
+        P.coef[q] = I.scale * h;
     }
-    if (threadIdx.x == 0) P.misc[MI_NRM0] = sqrt(red[k + 1]);
+    if (q == 0) P.misc[MI_NRM0] = sqrt(red[k + 1]);
 }
 
 // after the first update (red: the second pass's dots and ||w'||^2): a second pass if
 // ||w'|| < ||w|| / sqrt(2); then H(0:k,k) += dots, coef likewise
-__device__ __forceinline__ void gs2_step(const KPtrs &P, int k, int m, const double *red) {
+__device__ __forceinline__ void gs2_step(const KPtrs &P, const StepIn &I, int k, int m, const double *red) {
+    const int q = threadIdx.x;
     const double n1 = sqrt(red[k + 1]);
-    const int again = n1 < 0.70710678118654752440 * P.misc[MI_NRM0] ? 1 : 0;
-    if (threadIdx.x == 0) {
+    const int again = n1 < 0.70710678118654752440 * I.nrm ? 1 : 0;
+    if (q == 0) {
         P.misc[MI_NRM1] = n1;
         *P.guard = again;
     }
-    if (!again) return;
-    for (int q = threadIdx.x; q <= k; q += blockDim.x) {
-        const double sq = P.vscale[q], h = sq * red[q];
-        P.H[(int64_t)k * (m + 1) + q] += h;
-        P.coef[q] = sq * h;
-    }
+    if (!again || q > k) return;
+    const double h = I.scale * red[q];
+    P.H[(int64_t)k * (m + 1) + q] = I.h + h;
+    P.coef[q] = I.scale * h;
 }
 
 // final norm, Givens rotations, residual estimate
-__device__ __forceinline__ void givens_step(const KPtrs &P, int k, int m, const double *red) {
-    __shared__ double lh[MAX_RESTART + 1], lc[MAX_RESTART], ls[MAX_RESTART];
+__device__ __forceinline__ void givens_step(const KPtrs &P, const StepIn &I, int k, int m, const double *red) {
+    __shared__ double lh[MAX_RESTART + 1], lc[MAX_RESTART], ls[MAX_RESTART], end[2];
     double *h = P.H + (int64_t)k * (m + 1);
-    for (int q = threadIdx.x; q <= k; q += blockDim.x) {
-        lh[q] = h[q];
-        if (q < k) {
-            lc[q] = P.cs[q];
-            ls[q] = P.sn[q];
-        }
+    const int q = threadIdx.x;
+    if (q <= k) lh[q] = I.h;
+    if (q < k) {
+        lc[q] = I.cs;
+        ls[q] = I.sn;
     }
-    const int guard = *P.guard;
-    const double gk = P.g[k], n1 = P.misc[MI_NRM1];
     __syncthreads();
-    if (threadIdx.x == 0) {
-        const double hn = guard ? sqrt(red[0]) : n1;
+    if (q == 0) {
+        const double hn = I.guard ? sqrt(red[0]) : I.nrm;
         double a = lh[0];
-        for (int q = 0; q < k; ++q) {
-            const double b = lh[q + 1];
-            lh[q] = lc[q] * a + ls[q] * b;
-            a = -ls[q] * a + lc[q] * b;
+        for (int e = 0; e < k; ++e) {
+            const double b = lh[e + 1];
+            lh[e] = lc[e] * a + ls[e] * b;
+            a = -ls[e] * a + lc[e] * b;
         }
         const double rho = sqrt(a * a + hn * hn);
         const double c = rho > 0 ? a / rho : 1.0, sn = rho > 0 ? hn / rho : 0.0;
+        const double est = fabs(-sn * I.gk);
+        publish(P, est, hn, I.flags, I.guard);
         lh[k] = rho;
         P.cs[k] = c;
         P.sn[k] = sn;
-        P.g[k + 1] = -sn * gk;
-        P.g[k] = c * gk;
+        P.g[k + 1] = -sn * I.gk;
+        P.g[k] = c * I.gk;
         P.vscale[k + 1] = hn != 0.0 ? 1.0 / hn : 1.0;
-        P.status[ST_EST] = fabs(-sn * gk);
+        P.status[ST_EST] = est;
         P.status[ST_HN] = hn;
-        P.status[ST_GUARD] = (double)guard;
-        publish(P, fabs(-sn * gk), hn, guard);
+        P.status[ST_GUARD] = (double)I.guard;
+        end[0] = est;
+        end[1] = hn;
     }
     __syncthreads();
-    for (int q = threadIdx.x; q <= k; q += blockDim.x) h[q] = lh[q];
-    if (threadIdx.x == 0) h[k + 1] = 0.0;
+    if (q <= k) h[q] = lh[q];
+    if (q == 0) h[k + 1] = 0.0;
     // where the cycle ends, its least-squares solution (the host takes the same decision)
-    if (P.single) {
+    if (P.single && (P.last || end[0] <= I.tol || end[1] == 0.0)) {
         __syncthreads();
-        if (P.last || P.status[ST_EST] <= P.misc[MI_TOL] || P.status[ST_HN] == 0.0) solve_body(k + 1, m, P.H, P.g, P.coef);
+        solve_body(k + 1, m, P.H, P.g, P.coef);
     }
 }
 
 // The step OP on the column sums red (whole workgroup; red readable by every lane).
 template <int OP>
-__device__ __forceinline__ void step_tail(const KPtrs &P, int k, int m, const double *red) {
+__device__ __forceinline__ void step_tail(const KPtrs &P, const StepIn &I, int k, int m, const double *red) {
     if constexpr (OP == RS_BETA_START_ZERO || OP == RS_BETA_START_X) {
-        beta_step(P, m, red[0], true, OP == RS_BETA_START_ZERO, OP == RS_BETA_START_ZERO);
+        beta_step(P, I, m, red[0], true, OP == RS_BETA_START_ZERO, OP == RS_BETA_START_ZERO);
     }
-    else if constexpr (OP == RS_BETA) beta_step(P, m, red[0], false, true, true);
-    else if constexpr (OP == RS_GS1) gs1_step(P, k, m, red);
-    else if constexpr (OP == RS_GS2) gs2_step(P, k, m, red);
-    else if constexpr (OP == RS_GIVENS) givens_step(P, k, m, red);
+    else if constexpr (OP == RS_BETA) beta_step(P, I, m, red[0], false, true, true);
+    else if constexpr (OP == RS_GS1) gs1_step(P, I, k, m, red);
+    else if constexpr (OP == RS_GS2) gs2_step(P, I, k, m, red);
+    else if constexpr (OP == RS_GIVENS) givens_step(P, I, k, m, red);
 }
 
 // Column blk's sum, then step OP in the last of the `cols` workgroups to finish. The step runs also
@@ -937,11 +1018,13 @@ template <int OP>
 __device__ __forceinline__ void reduce_step_body(int blk, int cols, const KPtrs &P, int nb, const int *guard, int k,
                                                  int m) {
     __shared__ double sred[MAX_RESTART + 2];
+    StepIn in;
+    in.load<OP>(P, k, m);
     reduce_cols_body(blk, P.partials, nb, P.red, guard);
     if (!last_workgroup<false>(P.done, cols, blk)) return;
     for (int c = threadIdx.x; c < cols; c += WG) sred[c] = load_agent(P.red + c);
     __syncthreads();
-    step_tail<OP>(P, k, m, sred);
+    step_tail<OP>(P, in, k, m, sred);
 }
 
 __device__ __forceinline__ void zero_body(int blk, int64_t len, double *v) {

@@ -65,19 +65,22 @@ constexpr int FOLD_VE = 4;
 static_assert((int64_t)FOLD_NB * WG * FOLD_VE < VEC_SMALL, "folded systems have the smaller tile");
 
 template <int OP>
-__device__ __forceinline__ void fold_tail(const KPtrs &P, int nb, int cols, const int *guard, int k, int m) {
+__device__ __forceinline__ void fold_tail(const KPtrs &P, const StepIn &in, int nb, int cols, const int *guard, int k,
+                                          int m) {
     __shared__ double sred[MAX_RESTART + 2];
     if (!last_workgroup<true>(P.done, gridDim.x, blockIdx.x)) return;
     if (!skipped(guard)) reduce_cols_fold(P.partials, nb, cols, sred);
-    step_tail<OP>(P, k, m, sred);
+    step_tail<OP>(P, in, k, m, sred);
 }
 
 template <int OP>
 __global__ __launch_bounds__(WG) void k_mdot_step(int64_t len, Basis V, int q,
                                                   const double *__restrict__ w, KPtrs P, int nb, int k, int m) {
     __shared__ WaveSums sh[MAX_RESTART + 2];
+    StepIn in;
+    in.load<OP>(P, k, m);
     mdot_body<FOLD_VE>(blockIdx.x, len, V, q, w, P.partials, nb, sh);
-    fold_tail<OP>(P, nb, q + 1, nullptr, k, m);
+    fold_tail<OP>(P, in, nb, q + 1, nullptr, k, m);
 }
 
 template <int QM>
@@ -85,15 +88,19 @@ __global__ __launch_bounds__(WG) void k_update_dot_step(int64_t len, Basis V, in
                                                         const double *__restrict__ c, double *__restrict__ w, KPtrs P,
                                                         int nb, int k, int m) {
     __shared__ WaveSums sh[MAX_RESTART + 2];
+    StepIn in;
+    in.load<RS_GS2>(P, k, m);
     update_dot_body<QM, FOLD_VE>(gridDim.x - 1 - blockIdx.x, len, V, q, c, w, P.partials, nb, sh);
-    fold_tail<RS_GS2>(P, nb, q + 1, nullptr, k, m);
+    fold_tail<RS_GS2>(P, in, nb, q + 1, nullptr, k, m);
 }
 
 __global__ __launch_bounds__(WG) void k_update_step(int64_t len, Basis V, int q,
                                                     const double *__restrict__ c, double alpha, double *__restrict__ w,
                                                     KPtrs P, int nb, const int *guard, int k, int m) {
+    StepIn in;
+    in.load<RS_GIVENS>(P, k, m);
     update_body<FOLD_VE>(gridDim.x - 1 - blockIdx.x, len, V, q, c, alpha, w, P.partials, guard);
-    fold_tail<RS_GIVENS>(P, nb, 1, guard, k, m);
+    fold_tail<RS_GIVENS>(P, in, nb, 1, guard, k, m);
 }
 
 __global__ __launch_bounds__(WG) void k_zero(int64_t len, double *v) {
