@@ -5,6 +5,7 @@
 
 #include <cstddef>
 #include <cstdint>
+#include <vector>
 
 #include "abilu.h"
 
@@ -35,6 +36,7 @@ struct abilu_pattern {
                                   // (behind lcol in its allocation)
     double *pinned = nullptr;     // host pinned, 64 doubles, for blocking scalar reads
     double *pinned_dev = nullptr; // the same memory as kernels address it
+    std::vector<void *> owned;    // device allocations that hold the arrays above
     int32_t *done = nullptr;      // device [DONE_INTS] completion counts of FGMRES's reductions, zero
                                   // between launches (behind lrow in its allocation)
     bool symmetric = false;       // (i,j) in S_B implies (j,i) in S_B
@@ -210,14 +212,14 @@ inline PatScratch pat_scratch(void *scratch, int32_t n, int64_t Z) {
     return PatScratch{cnt, cnt + len, cnt + 2 * len};
 }
 abilu_status pattern_validate_async(int32_t n, int64_t Z, const int32_t *rowptr, const int32_t *colidx,
-                                    int32_t *diag_pos, void *scratch, unsigned *h_err, hipStream_t s);
+                                    int32_t *diag_pos, int32_t *done, void *scratch, unsigned *h_err, hipStream_t s);
 abilu_status pattern_count_async(int32_t n, int64_t Z, const int32_t *rowptr, const int32_t *colidx,
                                  const int32_t *diag_pos, int32_t *lrow, int32_t *urow, int32_t *pair_ptr,
                                  void *scratch, int64_t *h_sizes, hipStream_t s);
 bool pattern_sizes_ok(int32_t n, int64_t Z, const int64_t *sizes);   // sizes = {ZL, ZU, npairs}
 abilu_status pattern_count(int32_t n, int64_t Z, const int32_t *rowptr, const int32_t *colidx, int32_t *diag_pos,
-                           int32_t *lrow, int32_t *urow, int32_t *pair_ptr, void *scratch, int64_t *h_pinned,
-                           hipStream_t s, int64_t *ZL, int64_t *ZU, int64_t *npairs);
+                           int32_t *lrow, int32_t *urow, int32_t *pair_ptr, int32_t *done, void *scratch,
+                           int64_t *h_pinned, hipStream_t s, int64_t *ZL, int64_t *ZU, int64_t *npairs, int32_t *side);
 abilu_status pattern_fill(int32_t n, int64_t Z, int64_t ZL, int64_t ZU, int64_t npairs, const int32_t *rowptr,
                           const int32_t *colidx, const int32_t *diag_pos, const int32_t *lrow, const int32_t *urow,
                           int32_t *lcol, int32_t *ldiag, int32_t *ucol, int32_t *pik, int32_t *pkj, int32_t *sik, int32_t *skj,

@@ -10,8 +10,14 @@ namespace {
 
 using namespace abilu_setup;
 
+// also clears the words of pat_side_body and the completion counts
 __global__ void k_pat_rows(int n, int64_t Z, const int32_t *__restrict__ rowptr, const int32_t *__restrict__ colidx,
-                           int32_t *__restrict__ diag_pos, unsigned *__restrict__ err) {
+                           int32_t *__restrict__ diag_pos, unsigned *__restrict__ err, unsigned *__restrict__ more,
+                           int32_t *__restrict__ done) {
+    if (blockIdx.x == 0) {
+        if (threadIdx.x < 2) more[threadIdx.x] = 0;
+        for (int t = threadIdx.x; t < DONE_INTS; t += blockDim.x) done[t] = 0;
+    }
     pat_rows_body(blockIdx.x, n, Z, rowptr, colidx, diag_pos, err);
 }
 
@@ -31,8 +37,9 @@ __global__ __launch_bounds__(PAT_ROWS) void k_pat_fill(int n, int ZL, const int3
 }
 
 __global__ void k_pat_tri_counts(int n, const int32_t *__restrict__ rowptr, const int32_t *__restrict__ diag_pos,
-                                 int64_t *__restrict__ nl, int64_t *__restrict__ nu) {
+                                 int64_t *__restrict__ nl, int64_t *__restrict__ nu, unsigned *more) {
     pat_tri_counts_body(blockIdx.x, n, rowptr, diag_pos, nl, nu);
+    pat_side_body(blockIdx.x * blockDim.x + threadIdx.x, n, rowptr, diag_pos, more);
 }
 
 __global__ void k_pat_tri_cols(int n, const int32_t *__restrict__ rowptr, const int32_t *__restrict__ colidx,
@@ -43,8 +50,8 @@ __global__ void k_pat_tri_cols(int n, const int32_t *__restrict__ rowptr, const 
 }
 
 __global__ void k_pat_sym(int n, const int32_t *__restrict__ rowptr, const int32_t *__restrict__ colidx,
-                          const int32_t *__restrict__ diag_pos, unsigned *__restrict__ shape) {
-    pat_sym_body(blockIdx.x, n, rowptr, colidx, diag_pos, shape);
+                          const int32_t *__restrict__ diag_pos, unsigned *__restrict__ unsym) {
+    pat_sym_body(blockIdx.x, n, rowptr, colidx, diag_pos, unsym);
 }
 
 // PairIndex's records of rows of at most two blocks a side: {j0, j1}, {c0, c1} with the counts in the
@@ -87,15 +94,39 @@ __global__ void k_pat_blocks(int n, int ZL, const int32_t *__restrict__ rowptr, 
     }
 }
 
-// a length in ints, up to a 256-byte boundary
-size_t ints(int64_t len) { return (size_t)((len + 63) / 64 * 64); }
+// Device arrays of a pattern. Those of 2 MiB and more, which cost the runtime 12 us each to allocate and
+// 12 to free, share one allocation; smaller ones come from its pool in under 1 us each.
+struct Piece {
+    int32_t **p;
+    size_t ints;
+};
+hipError_t allocate(abilu_pattern *p, std::initializer_list<Piece> pieces) {
+    constexpr size_t LARGE = (size_t)2 << 18;
+    const auto up = [](size_t ints) { return (ints + 63) / 64 * 64; };   // 256-byte boundaries
+    size_t large = 0;
+    for (const Piece &q : pieces) large += q.ints >= LARGE ? up(q.ints) : 0;
+    const auto get = [&](size_t ints, int32_t **out) {
+        const hipError_t e = hipMalloc(out, sizeof(int32_t) * ints);
+        if (e == hipSuccess) p->owned.push_back(*out);
+        return e;
+    };
+    int32_t *next = nullptr;
+    if (large)
+        if (const hipError_t e = get(large, &next); e != hipSuccess) return e;
+    for (const Piece &q : pieces) {
+        if (q.ints >= LARGE) {
+            *q.p = next;
+            next += up(q.ints);
+        } else if (const hipError_t e = get(q.ints, q.p); e != hipSuccess) {
+            return e;
+        }
+    }
+    return hipSuccess;
+}
 
 void free_pattern(abilu_pattern *p) {
     if (!p) return;
-    (void)hipFree(p->rowptr);   // with colidx, diag_pos, pair_ptr, lrow, done, urow
-    (void)hipFree(p->lcol);     // with ldiag, ucol, pik, pkj, sik, skj
-    (void)hipFree(p->lrec);     // with urec
-    (void)hipFree(p->brec);
+    for (void *q : p->owned) (void)hipFree(q);
     abilu::free_chunks(p);
     if (p->pinned) (void)hipHostFree(p->pinned);
     delete p;
@@ -105,28 +136,33 @@ void free_pattern(abilu_pattern *p) {
 
 namespace abilu {
 
+// the two words of pat_side_body, behind the last pair offset
+static unsigned *shape_words(void *scratch, int32_t n, int64_t Z) {
+    return (unsigned *)(pat_scratch(scratch, n, Z).ptr64 + Z + 1);
+}
+
 size_t pattern_scratch_bytes(int32_t n, int64_t Z) {
     const int64_t len = Z + n + 2;
     return 256 + sizeof(int64_t) * (size_t)(2 * len + scan_tiles(Z > n ? Z : n) + 1);
 }
 
 // Non-blocking stage 1a: validation and diagonal positions; the error word (nonzero: invalid
-// pattern) is copied to h_err when the stream reaches it.
+// pattern) is copied to h_err when the stream reaches it. Clears the completion counts `done`.
 abilu_status pattern_validate_async(int32_t n, int64_t Z, const int32_t *rowptr, const int32_t *colidx,
-                                    int32_t *diag_pos, void *scratch, unsigned *h_err, hipStream_t s) {
+                                    int32_t *diag_pos, int32_t *done, void *scratch, unsigned *h_err, hipStream_t s) {
     unsigned *err = (unsigned *)scratch;
     if (!hip_ok(hipMemsetAsync(err, 0, sizeof(unsigned), s), "pattern error clear")) return ABILU_EDEVICE;
-    if (n > 0) {
-        k_pat_rows<<<div_up(n, 256), 256, 0, s>>>(n, Z, rowptr, colidx, diag_pos, err);
-        if (launch_status() != ABILU_OK) return ABILU_EDEVICE;
-    }
+    k_pat_rows<<<max(1, div_up(n, 256)), 256, 0, s>>>(n, Z, rowptr, colidx, diag_pos, err, shape_words(scratch, n, Z),
+                                                      done);
+    if (launch_status() != ABILU_OK) return ABILU_EDEVICE;
     if (!hip_ok(hipMemcpyAsync(h_err, err, sizeof(unsigned), hipMemcpyDeviceToHost, s), "pattern error readback"))
         return ABILU_EDEVICE;
     return ABILU_OK;
 }
 
 // Non-blocking stage 1b (valid patterns only): lower/upper row offsets and the update-set
-// offsets (pair_ptr); h_sizes receives ZL, ZU and the number of pairs. ptr64 in the scratch
+// offsets (pair_ptr); h_sizes receives ZL, ZU, the number of pairs and the two words of
+// pat_side_body. ptr64 in the scratch
 // keeps the int64 pair offsets for pattern_fill.
 abilu_status pattern_count_async(int32_t n, int64_t Z, const int32_t *rowptr, const int32_t *colidx,
                                  const int32_t *diag_pos, int32_t *lrow, int32_t *urow, int32_t *pair_ptr,
@@ -138,7 +174,7 @@ abilu_status pattern_count_async(int32_t n, int64_t Z, const int32_t *rowptr, co
         if (!hip_ok((x), #x)) return ABILU_EDEVICE;        \
     } while (0)
     if (n > 0) {
-        k_pat_tri_counts<<<div_up(n, 256), 256, 0, s>>>(n, rowptr, diag_pos, cnt, cnt + (n + 1));
+        k_pat_tri_counts<<<div_up(n, 256), 256, 0, s>>>(n, rowptr, diag_pos, cnt, cnt + (n + 1), shape_words(scratch, n, Z));
         CK(hipGetLastError());
     }
     for (int part = 0; part < 2; ++part) {
@@ -150,7 +186,7 @@ abilu_status pattern_count_async(int32_t n, int64_t Z, const int32_t *rowptr, co
         CK(hipGetLastError());
     }
     CK(scan_exclusive(Z, cnt, tot, ptr64, pair_ptr, s));
-    CK(hipMemcpyAsync(h_sizes + 2, ptr64 + Z, sizeof(int64_t), hipMemcpyDeviceToHost, s));
+    CK(hipMemcpyAsync(h_sizes + 2, ptr64 + Z, 2 * sizeof(int64_t), hipMemcpyDeviceToHost, s));
     return ABILU_OK;
 #undef CK
 }
@@ -162,9 +198,9 @@ bool pattern_sizes_ok(int32_t n, int64_t Z, const int64_t *sizes) {
 
 // Blocking stage 1 (two stream syncs).
 abilu_status pattern_count(int32_t n, int64_t Z, const int32_t *rowptr, const int32_t *colidx, int32_t *diag_pos,
-                           int32_t *lrow, int32_t *urow, int32_t *pair_ptr, void *scratch, int64_t *h_pinned,
-                           hipStream_t s, int64_t *ZL, int64_t *ZU, int64_t *npairs) {
-    abilu_status st = pattern_validate_async(n, Z, rowptr, colidx, diag_pos, scratch, (unsigned *)h_pinned, s);
+                           int32_t *lrow, int32_t *urow, int32_t *pair_ptr, int32_t *done, void *scratch,
+                           int64_t *h_pinned, hipStream_t s, int64_t *ZL, int64_t *ZU, int64_t *npairs, int32_t *side) {
+    abilu_status st = pattern_validate_async(n, Z, rowptr, colidx, diag_pos, done, scratch, (unsigned *)h_pinned, s);
     if (st != ABILU_OK) return st;
     if (!hip_ok(hipStreamSynchronize(s), "pattern validation sync")) return ABILU_EDEVICE;
     if (*(const unsigned *)h_pinned) return ABILU_EPATTERN;
@@ -174,6 +210,7 @@ abilu_status pattern_count(int32_t n, int64_t Z, const int32_t *rowptr, const in
     *ZL = h_pinned[0];
     *ZU = h_pinned[1];
     *npairs = h_pinned[2];
+    *side = side_class((const unsigned *)(h_pinned + 3));
     return pattern_sizes_ok(n, Z, h_pinned) ? ABILU_OK : ABILU_EPATTERN;
 }
 
@@ -184,8 +221,9 @@ abilu_status pattern_fill(int32_t n, int64_t Z, int64_t ZL, int64_t ZU, int64_t 
                           int32_t *lcol, int32_t *ldiag, int32_t *ucol, int32_t *pik, int32_t *pkj, int32_t *sik,
                           int32_t *skj, const void *scratch, hipStream_t s) {
     const int64_t *ptr64 = pat_scratch(const_cast<void *>(scratch), n, Z).ptr64;
-    // the arrays from lcol to ucol are one allocation
-    if (!hip_ok(hipMemsetAsync(lcol, 0, sizeof(int32_t) * (size_t)(ucol - lcol + ZU + 1), s), "column clear"))
+    // ldiag follows lcol
+    if (!hip_ok(hipMemsetAsync(lcol, 0, sizeof(int32_t) * 2 * (ZL + 1), s), "lcol clear") ||
+        !hip_ok(hipMemsetAsync(ucol, 0, sizeof(int32_t) * (ZU + 1), s), "ucol clear"))
         return ABILU_EDEVICE;
     if (n > 0) {
         k_pat_tri_cols<<<div_up(n, 256), 256, 0, s>>>(n, rowptr, colidx, diag_pos, lrow, urow, lcol, ldiag, ucol);
@@ -212,6 +250,7 @@ extern "C" abilu_status abilu_build_pattern(int32_t nbrows, const int32_t *d_row
     const int n = nbrows;
 
     abilu_pattern *p = new abilu_pattern();
+    p->owned.reserve(16);
     void *scratch = nullptr;
     abilu_status st = ABILU_OK;
     int32_t ends[2] = {0, 0};
@@ -243,61 +282,45 @@ extern "C" abilu_status abilu_build_pattern(int32_t nbrows, const int32_t *d_row
         CKA(hipHostMalloc((void **)&p->pinned, 64 * sizeof(double), hipHostMallocDefault));
         CK(hipHostGetDevicePointer((void **)&p->pinned_dev, p->pinned, 0));
         for (int q = 0; q < 64; ++q) p->pinned[q] = 0.0;
-        {
-            const size_t nr = ints(n + 1), nz = ints(Z + 1), nd = ints(DONE_INTS);
-            CKA(hipMalloc(&p->rowptr, sizeof(int32_t) * (4 * nr + 2 * nz + nd)));
-            p->diag_pos = p->rowptr + nr;
-            p->lrow = p->diag_pos + nr;
-            p->urow = p->lrow + nr;
-            p->done = p->urow + nr;
-            p->colidx = p->done + nd;
-            p->pair_ptr = p->colidx + nz;
-        }
-        CK(hipMemsetAsync(p->done, 0, sizeof(int32_t) * DONE_INTS, s));
+        const size_t lrow_ints = ((size_t)n + 1 + DONE_STRIDE - 1) / DONE_STRIDE * DONE_STRIDE;
+        CKA(allocate(p, {{&p->rowptr, (size_t)n + 1}, {&p->colidx, (size_t)Z + 1}, {&p->diag_pos, (size_t)n + 1},
+                         {&p->pair_ptr, (size_t)Z + 1}, {&p->lrow, lrow_ints + DONE_INTS}, {&p->urow, (size_t)n + 1}}));
+        p->done = p->lrow + lrow_ints;
         CKA(hipMalloc(&scratch, pattern_scratch_bytes(n, Z)));
         CK(hipMemcpyAsync(p->rowptr, d_rowptr, sizeof(int32_t) * (n + 1), hipMemcpyDeviceToDevice, s));
         if (Z > 0) CK(hipMemcpyAsync(p->colidx, d_colidx, sizeof(int32_t) * Z, hipMemcpyDeviceToDevice, s));
-        st = pattern_count(n, Z, p->rowptr, p->colidx, p->diag_pos, p->lrow, p->urow, p->pair_ptr, scratch,
-                           (int64_t *)p->pinned, s, &ZL, &ZU, &npairs);
+        st = pattern_count(n, Z, p->rowptr, p->colidx, p->diag_pos, p->lrow, p->urow, p->pair_ptr, p->done, scratch,
+                           (int64_t *)p->pinned, s, &ZL, &ZU, &npairs, &p->side);
         if (st != ABILU_OK) goto fail;
         p->nnzb_lower = ZL;
         p->nnzb_upper = ZU;
         p->npairs = npairs;
-        {
-            const size_t nl = ints(ZL + 1), nu = ints(ZU + 1), np = ints(npairs + 1);
-            CKA(hipMalloc(&p->lcol, sizeof(int32_t) * (2 * nl + nu + 4 * np)));
-            p->ldiag = p->lcol + nl;
-            p->ucol = p->ldiag + nl;
-            p->pik = p->ucol + nu;
-            p->pkj = p->pik + np;
-            p->sik = p->pkj + np;
-            p->skj = p->sik + np;
-        }
+        const size_t np = (size_t)npairs + 1, recs = p->side <= 2 ? 8 * (size_t)n : 0;
+        CKA(allocate(p, {{&p->lcol, 2 * ((size_t)ZL + 1)}, {&p->ucol, (size_t)ZU + 1}, {&p->pik, np}, {&p->pkj, np},
+                         {&p->sik, np}, {&p->skj, np}, {(int32_t **)&p->lrec, recs + 1},
+                         {(int32_t **)&p->urec, recs + 1}}));
+        p->ldiag = p->lcol + (ZL + 1);
         st = pattern_fill(n, Z, ZL, ZU, npairs, p->rowptr, p->colidx, p->diag_pos, p->lrow, p->urow, p->lcol,
                           p->ldiag, p->ucol, p->pik, p->pkj, p->sik, p->skj, scratch, s);
         if (st != ABILU_OK) goto fail;
-        // structural symmetry and the longest rows (the factor sweeps choose their form by them)
+        // structural symmetry (the factor sweeps choose their form by it)
         {
-            unsigned *shape = (unsigned *)scratch;
-            CK(hipMemsetAsync(shape, 0, 3 * sizeof(unsigned), s));
+            unsigned *unsym = (unsigned *)scratch;
+            CK(hipMemsetAsync(unsym, 0, sizeof(unsigned), s));
             if (n > 0) {
-                k_pat_sym<<<div_up(n, 256), 256, 0, s>>>(n, p->rowptr, p->colidx, p->diag_pos, shape);
+                k_pat_sym<<<div_up(n, 256), 256, 0, s>>>(n, p->rowptr, p->colidx, p->diag_pos, unsym);
                 CK(hipGetLastError());
             }
-            CK(hipMemcpyAsync(p->pinned, shape, 3 * sizeof(unsigned), hipMemcpyDeviceToHost, s));
+            CK(hipMemcpyAsync(p->pinned, unsym, sizeof(unsigned), hipMemcpyDeviceToHost, s));
             CK(hipStreamSynchronize(s));
-            const unsigned *h = (const unsigned *)p->pinned;
-            p->symmetric = h[0] == 0;
-            p->side = side_class(h + 1);
+            p->symmetric = *(const unsigned *)p->pinned == 0;
             if (n > 0 && p->side <= 2) {
-                CKA(hipMalloc(&p->lrec, sizeof(int2) * 8 * (size_t)n));
-                p->urec = p->lrec + 4 * (size_t)n;
                 k_pat_pairs<<<div_up(2 * (int64_t)n, 256), 256, 0, s>>>(n, p->rowptr, p->colidx, p->diag_pos, p->lrow,
                                                                         p->urow, p->lrec, p->urec);
                 CK(hipGetLastError());
             }
             if (n > 0 && !p->fv()) {
-                CKA(hipMalloc(&p->brec, sizeof(int4) * Z));
+                CKA(allocate(p, {{(int32_t **)&p->brec, 4 * (size_t)Z}}));
                 k_pat_blocks<<<div_up(n, 256), 256, 0, s>>>(n, (int)ZL, p->rowptr, p->diag_pos, p->lrow, p->urow,
                                                             p->pair_ptr, p->ldiag, p->brec);
                 CK(hipGetLastError());

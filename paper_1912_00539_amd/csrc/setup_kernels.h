@@ -258,18 +258,16 @@ __device__ __forceinline__ void pat_side_body(int i, int n, const int32_t *__res
 }
 inline int side_class(const unsigned *more) { return more[1] ? 4 : more[0] ? 3 : 2; }
 
-// structural symmetry: one thread per block row; sets shape[0] when some (i,j) in S_B has no (j,i).
-// shape[1], shape[2]: pat_side_body.
+// structural symmetry: one thread per block row; sets *unsym when some (i,j) in S_B has no (j,i)
 __device__ __forceinline__ void pat_sym_body(int blk, int n, const int32_t *__restrict__ rowptr,
                                              const int32_t *__restrict__ colidx, const int32_t *__restrict__ diag_pos,
-                                             unsigned *__restrict__ shape) {
+                                             unsigned *__restrict__ unsym) {
     int i = blk * blockDim.x + threadIdx.x;
-    pat_side_body(i, n, rowptr, diag_pos, shape + 1);
     if (i >= n) return;
     for (int e = rowptr[i]; e < rowptr[i + 1]; ++e) {
         const int j = colidx[e];
         if (j != i && find_col(rowptr, colidx, j, i) < 0) {
-            atomicOr(shape, 1u);
+            atomicOr(unsym, 1u);
             return;
         }
     }
