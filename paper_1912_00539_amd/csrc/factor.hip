@@ -444,6 +444,186 @@ __global__ __launch_bounds__(WG) void k_factor_sweep_chunk_rows_pipe(int n, int 
     if (fl) atomicOr(flags, fl);
 }
 
+// Chunks that are chains, on a pattern of the row-at-once form (update sets of the diagonal blocks
+// only, at most CL blocks a side): a sweep in two launches. All of a row but its link to the row before
+// it in the chunk does not depend on the chain, and is formed here for every row at once:
+// the lower blocks of other chunks, L_ik = A_ik U_kk^{-1}, and their terms of the diagonal block, whose
+// partial sum goes to its place; A_ij, which is U_ij, above the diagonal; and A_{i,i-1} in the place of
+// the link's L. Loads and arithmetic as in factor_sweep_fv_row, the order of the terms as in
+// factor_chunk_row (the link is the last of them). FROM_A: U_ki and the inverses come from A, so no
+// initialisation pass runs before; every row raises the flag of its own initial inverse.
+// Bound by memory (A, read once, and the factor): 95 us for 480 MB on 500,000 line-ordered quads, FP32.
+template <typename T, bool FROM_A, int CL>
+__global__ __launch_bounds__(WG) void k_factor_chunk_far(FvPattern P, int R, const double *__restrict__ A, const T *XO,
+                                                         const T *DO, T *Xn, unsigned *flags) {
+    const int i = blockIdx.x * ROWS_PER_WG + (threadIdx.x >> 2);
+    const int r = threadIdx.x & 3;
+    if (i >= P.n) return;
+    const int b0 = P.rowptr[i], b1 = P.rowptr[i + 1], lb = P.lrow[i], nl = P.lrow[i + 1] - lb, ub = P.urow[i];
+    const int d = b0 + nl, nu = b1 - d - 1, c0 = i / R * R;
+    using LV = typename std::conditional<FROM_A, double, T>::type;
+    int jc[CL], jd[CL], pk[CL];
+    double aL[CL][4], aD[4], aU[CL][4];
+#pragma unroll
+    for (int u = 0; u < CL; ++u) {
+        if (u < nl) {
+            jc[u] = P.lcol[lb + u];
+            jd[u] = FROM_A ? P.ldiag[lb + u] : jc[u];
+            pk[u] = FROM_A ? P.pkj[lb + u] : P.skj[lb + u];
+        }
+    }
+#pragma unroll
+    for (int u = 0; u < CL; ++u)
+        if (u < nl) load_row(A + (int64_t)(b0 + u) * BB, r, aL[u]);
+    load_row(A + (int64_t)d * BB, r, aD);
+#pragma unroll
+    for (int w = 0; w < CL; ++w)
+        if (w < nu) load_row(A + (int64_t)(d + 1 + w) * BB, r, aU[w]);
+    LV dj[CL][4], uk[CL][4];
+#pragma unroll
+    for (int u = 0; u < CL; ++u) {
+        if (u < nl && jc[u] < c0) {
+            if constexpr (FROM_A) {
+                load_row(A + (int64_t)jd[u] * BB, r, dj[u]);
+                load_row(A + (int64_t)pk[u] * BB, r, uk[u]);
+            } else {
+                load_row(DO + (int64_t)jd[u] * BB, r, dj[u]);
+                load_row(XO + (int64_t)pk[u] * BB, r, uk[u]);
+            }
+        }
+    }
+    unsigned fl = 0;
+    T t[4];
+    to_t(aD, t);
+    if (FROM_A && !surely_invertible(t, r)) {
+        T unused[4];
+        if (!inv4_row(t, r, unused)) fl |= ABILU_FLAG_MODIFIED;
+    }
+#pragma unroll
+    for (int u = 0; u < CL; ++u) {
+        if (u < nl) {
+            T a[4], x[4];
+            to_t(aL[u], a);
+            if (jc[u] < c0) {
+                T D[4], v[4];
+#pragma unroll
+                for (int c = 0; c < 4; ++c) {
+                    D[c] = (T)dj[u][c];
+                    v[c] = (T)uk[u][c];
+                }
+                if constexpr (FROM_A) {
+                    T Di[4];
+                    if (!inv4_row(D, r, Di)) fl |= ABILU_FLAG_MODIFIED;
+                    row_times_block(a, Di, x);
+                } else {
+                    row_times_block(a, D, x);
+                }
+                fl |= nonfinite4(x);
+                row_times_block_sub(x, v, t);
+            } else {
+                copy_row(a, x);
+            }
+            store_row(Xn + (int64_t)(lb + u) * BB, r, x);
+        }
+    }
+    store_row(Xn + ((int64_t)P.ZL + i) * BB, r, t);
+#pragma unroll
+    for (int w = 0; w < CL; ++w) {
+        if (w < nu) {
+            T v[4];
+            to_t(aU[w], v);
+            fl |= nonfinite4(v);
+            store_row(Xn + ((int64_t)P.ZL + P.n + ub + w) * BB, r, v);
+        }
+    }
+    if (fl) atomicOr(flags, fl);
+}
+
+// The links: a quad per chunk walks its rows, L = A_{i,i-1} U_{i-1,i-1}^{-1}, the last term of the
+// diagonal block, its inverse. G rows' operands are fetched while the G rows before them are computed.
+// Bound by the chain of inverses, two waves on a SIMD (63 us on 500,000 line-ordered quads, FP32, chunks
+// of 16 rows). The sweep from A, both launches, against one launch that walked whole rows after the
+// initial inverses, us: 16 rows FP32 166 -> 160 and FP64 250 -> 213; 64 rows FP32 239 -> 184 and FP64
+// 418 -> 263; 10,057 quads, 16 rows, FP32 44 -> 24 and FP64 71 -> 33.
+template <typename T, int G>
+__global__ __launch_bounds__(WG) void k_factor_chunk_links(int n, int ZL, int R, int nch,
+                                                           const int32_t *__restrict__ rec, T *Xn, T *Dn,
+                                                           unsigned *flags) {
+    const int c = blockIdx.x * ROWS_PER_WG + (threadIdx.x >> 2);
+    if (c >= nch) return;
+    const int r = threadIdx.x & 3;
+    const int c0 = c * R, m = min(n, c0 + R) - c0;
+    T pD[4] = {};
+    unsigned fl = 0;
+    struct Index {
+        int l, u;   // places of the link's L and U, l < 0 without one
+    };
+    struct Ops {
+        T t[4], a[4], u[4];
+    };
+    // Loads carry no branches and nothing waits for them before the next group: past the chunk's end
+    // the last row is read again, without a link its diagonal block.
+    int4 h[G], sp[G];
+    auto records = [&](int t0) {
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
+            const int t = min(t0 + g, m - 1);
+            h[g] = rec_quad(rec, R, c, nch, t, 0);
+            sp[g] = rec_quad(rec, R, c, nch, t, 3);
+        }
+    };
+    auto fetch = [&](int t0, Index (&x)[G], Ops (&o)[G]) {
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
+            const int dp = ZL + c0 + min(t0 + g, m - 1);
+            const int nl = h[g].w & 15;
+            const bool link = nl > 0 && ((h[g].w >> (12 + 2 * (nl - 1))) & 3) == REC_PREV;
+            x[g].l = link ? h[g].y + nl - 1 : -1;
+            x[g].u = (sp[g].x & -(nl == 1)) | (sp[g].y & -(nl == 2)) | (sp[g].z & -(nl == 3));
+            load_row(Xn + (int64_t)dp * BB, r, o[g].t);
+            load_row(Xn + (int64_t)(link ? x[g].l : dp) * BB, r, o[g].a);
+            load_row(Xn + (int64_t)(link ? x[g].u : dp) * BB, r, o[g].u);
+        }
+    };
+    auto compute = [&](int t0, const Index (&x)[G], Ops (&o)[G]) {
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
+            if (t0 + g < m) {
+                const bool link = x[g].l >= 0;
+                const int64_t dp = (int64_t)ZL + c0 + t0 + g;
+                T L[4], t[4];
+                row_times_block(o[g].a, pD, L);
+                copy_row(o[g].t, t);
+                row_times_block_sub(L, o[g].u, t);
+                if (link) {
+                    fl |= nonfinite4(L);
+                    store_row(Xn + (int64_t)x[g].l * BB, r, L);
+                    store_row(Xn + dp * BB, r, t);
+                }
+#pragma unroll
+                for (int q = 0; q < 4; ++q) t[q] = link ? t[q] : o[g].t[q];
+                fl |= nonfinite4(t);
+                if (!inv4_row_gathered(t, r, pD)) fl |= ABILU_FLAG_MODIFIED;
+                store_row(Dn + (int64_t)(c0 + t0 + g) * BB, r, pD);
+            }
+        }
+    };
+    Index x0[G], x1[G];
+    Ops o0[G], o1[G];
+    records(0);
+    fetch(0, x0, o0);
+    records(G);
+    for (int t0 = 0; t0 < m; t0 += 2 * G) {
+        fetch(t0 + G, x1, o1);
+        records(t0 + 2 * G);
+        compute(t0, x0, o0);
+        fetch(t0 + 2 * G, x0, o0);
+        records(t0 + 3 * G);
+        compute(t0 + G, x1, o1);
+    }
+    if (fl) atomicOr(flags, fl);
+}
+
 // Conversions between the factor layout and CSR order (one quad per block row).
 template <typename T, bool TO_CSR>
 __global__ __launch_bounds__(WG) void k_factor_permute(int n, int ZL, const int32_t *__restrict__ rowptr,
@@ -579,7 +759,32 @@ abilu_status factor_t(const abilu_pattern *p, const double *A, T *LU, T *Dinv, i
         // from A itself (X0) in both modes.
         const bool cs = (mode == ABILU_CHUNK_SYNC);
         const double sched = 4.0 * z.N + 4.0 * (p->nchunks + 1) + 4.0 * (double)(p->total_levels[0] + p->nchunks);
+        // Chains of rows with diagonal update sets: what does not depend on the chain first, then the
+        // chain (no inverses of A's diagonal blocks are needed before the first sweep).
+        const bool chains = p->chunk_runner == ABILU_CHUNK_BY_ROWS && p->chains && p->fv();
+        auto chain_sweep = [&](bool fromA, const T *XO, const T *DO, T *Xn, T *Dn, const char *nm) -> abilu_status {
+            const FvPattern P{n, ZL, p->rowptr, p->lrow, p->urow, p->lcol, p->ldiag, p->pkj, p->skj};
+            // the records read of the links: two of their planes
+            ProfScope ps(NAME("factor_sweep", nm), s,
+                         (fromA ? bytes_sweep_from_a(z, sF, false) : bytes_sweep(z, sF, false, false)) + 32 * z.N);
+            auto far = [&](auto from, auto cap) {
+                k_factor_chunk_far<T, decltype(from)::value, decltype(cap)::value><<<grid, WG, 0, s>>>(
+                    P, p->chunk_rows, A, XO, DO, Xn, flags);
+            };
+            auto form = [&](auto from) {
+                if (p->side <= 2) far(from, std::integral_constant<int, 2>{});
+                else far(from, std::integral_constant<int, FV_CAP>{});
+            };
+            if (fromA) form(std::true_type{});
+            else form(std::false_type{});
+            LAUNCHED();
+            k_factor_chunk_links<T, sizeof(T) == 4 ? 4 : 2><<<div_up(p->nchunks, ROWS_PER_WG), WG, 0, s>>>(
+                n, ZL, p->chunk_rows, p->nchunks, p->rec, Xn, Dn, flags);
+            LAUNCHED();
+            return ABILU_OK;
+        };
         auto chunk_sweep = [&](bool fromA, const T *XO, const T *DO, T *Xn, T *Dn, const char *nm) -> abilu_status {
+            if (chains) return chain_sweep(fromA, XO, DO, Xn, Dn, nm);
             ProfScope ps(NAME("factor_sweep", nm), s, bytes_sweep(z, sF, false, fromA) + sched);
             if (p->chunk_runner == ABILU_CHUNK_BY_ROWS) {
                 const int g = div_up(p->nchunks, ROWS_PER_WG);
@@ -620,7 +825,7 @@ abilu_status factor_t(const abilu_pattern *p, const double *A, T *LU, T *Dinv, i
         if (!cs) {
             int q0 = 0;
             if (init == ABILU_INIT_FROM_A) {
-                if ((st = init_dinv_A(Dinv)) != ABILU_OK) return st;
+                if (!chains && (st = init_dinv_A(Dinv)) != ABILU_OK) return st;
                 if ((st = chunk_sweep(true, (const T *)nullptr, Dinv, LU, Dinv, "_chunk_async_fromA")) != ABILU_OK)
                     return st;
                 q0 = 1;
@@ -634,7 +839,7 @@ abilu_status factor_t(const abilu_pattern *p, const double *A, T *LU, T *Dinv, i
         auto cX = [&](int q) { return ((nsw - q) % 2 == 0) ? LU : X1; };
         auto cD = [&](int q) { return ((nsw - q) % 2 == 0) ? Dinv : D1; };
         if (init == ABILU_INIT_FROM_A) {
-            if ((st = init_dinv_A(cD(0))) != ABILU_OK) return st;
+            if (!chains && (st = init_dinv_A(cD(0))) != ABILU_OK) return st;
             if ((st = chunk_sweep(true, (const T *)nullptr, cD(0), cX(1), cD(1), "_chunk_sync_fromA")) != ABILU_OK)
                 return st;
         } else {
