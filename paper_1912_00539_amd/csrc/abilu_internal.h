@@ -29,8 +29,8 @@ struct abilu_pattern {
     int32_t *urow = nullptr;      // device [n+1]
     int32_t *lcol = nullptr;      // device [ZL+1] columns of the lower part (one padding entry)
     int32_t *ucol = nullptr;      // device [ZU+1] columns of the upper part
-    int2 *lrec = nullptr;         // device [4n], [4n] indices of pairs of sweeps (side <= 2 only; PairIndex)
-    int2 *urec = nullptr;
+    int32_t *lrec = nullptr;      // device [PAIR_REC n] each: indices of pairs of sweeps (side <= 3 only; PairIndex)
+    int32_t *urec = nullptr;
     int4 *brec = nullptr;         // device [Z] by factor layout: CSR position, pair range, ldiag (not if fv())
     int32_t *ldiag = nullptr;     // device [ZL+1] CSR position of the diagonal block of each lower column
                                   // (behind lcol in its allocation)
@@ -41,6 +41,7 @@ struct abilu_pattern {
                                   // between launches (behind lrow in its allocation)
     bool symmetric = false;       // (i,j) in S_B implies (j,i) in S_B
     int32_t side = 4;             // most blocks of a row on one side of the diagonal: 2 (at most), 3, 4 (or more)
+    bool local = false;           // most lower neighbours lie within PAIR_NEAR rows (pairs of sweeps)
     // update sets of the diagonal blocks only, and rows that the factor sweeps' row-at-once form holds
     // (FV_CAP lower and upper blocks): finite-volume meshes of triangles and quads
     bool fv() const { return symmetric && npairs == nnzb_lower && side <= 3; }
@@ -90,6 +91,15 @@ __host__ __device__ inline int vec_tile(int64_t len) { return WG * vec_e(len); }
 
 // diagnostics: rows per workgroup
 constexpr int DIAG_ROWS = 512;
+
+// A pair of sweeps reads its neighbours' rows again, out of the L2 of its XCD (4 MB, of 240 to 450 bytes a
+// row) where they are near: taken if three quarters of the lower blocks are within PAIR_NEAR rows.
+// Triangles in random order, three sweeps, single / pairs, us: 62,486 FP64 23.5 / 24.9; 180,000 FP32 39.6 /
+// 54.5; 800,000 FP64 246 / 321; in Cuthill-McKee order 800,000 FP32 114 / 93, FP64 205 / 156.
+constexpr int PAIR_NEAR = 16384;
+// words of a row's record of a pair of sweeps: S columns, S rows, S * S columns of those, in four lanes
+template <int S>
+constexpr int PAIR_REC = S <= 2 ? 8 : 16;
 
 // completion counts of the reductions (ints, a cache line apart): the root, then one per group of
 // workgroups (last_workgroup)
@@ -219,7 +229,7 @@ abilu_status pattern_count_async(int32_t n, int64_t Z, const int32_t *rowptr, co
 bool pattern_sizes_ok(int32_t n, int64_t Z, const int64_t *sizes);   // sizes = {ZL, ZU, npairs}
 abilu_status pattern_count(int32_t n, int64_t Z, const int32_t *rowptr, const int32_t *colidx, int32_t *diag_pos,
                            int32_t *lrow, int32_t *urow, int32_t *pair_ptr, int32_t *done, void *scratch,
-                           int64_t *h_pinned, hipStream_t s, int64_t *ZL, int64_t *ZU, int64_t *npairs, int32_t *side);
+                           int64_t *h_pinned, hipStream_t s, int64_t *ZL, int64_t *ZU, int64_t *npairs, int32_t *side, bool *local);
 abilu_status pattern_fill(int32_t n, int64_t Z, int64_t ZL, int64_t ZU, int64_t npairs, const int32_t *rowptr,
                           const int32_t *colidx, const int32_t *diag_pos, const int32_t *lrow, const int32_t *urow,
                           int32_t *lcol, int32_t *ldiag, int32_t *ucol, int32_t *pik, int32_t *pkj, int32_t *sik, int32_t *skj,

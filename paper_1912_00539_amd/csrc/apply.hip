@@ -66,25 +66,25 @@ __global__ __launch_bounds__(WG) void k_bwd(int n, const int32_t *__restrict__ u
 // Two sweeps in one launch (see fwd_pair_row, bwd_pair_row).
 template <typename T, typename YI, bool EMIT_Z, int CL, bool SCALED>
 __global__ __launch_bounds__(WG) void k_fwd_pair(int n, const int32_t *__restrict__ lrow,
-                                                 const int32_t *__restrict__ lcol, const int2 *__restrict__ rec,
+                                                 const int32_t *__restrict__ lcol, const int32_t *__restrict__ rec,
                                                  const T *__restrict__ Lb, const double *__restrict__ rhs,
                                                  const YI *__restrict__ yin, T *__restrict__ yout,
                                                  const T *__restrict__ Dinv, T *__restrict__ zout,
                                                  const double *__restrict__ rscale, int first) {
     const double rs = rhs_scale<SCALED>(rscale);
     const int blk = xcd_tile(blockIdx.x, gridDim.x);
-    fwd_pair_row<T, YI, EMIT_Z, CL, CL == 2>(blk * ROWS_PER_WG + (threadIdx.x >> 2), n, lrow, lcol, rec, Lb, rhs, yin, yout,
+    fwd_pair_row<T, YI, EMIT_Z, CL, true>(blk * ROWS_PER_WG + (threadIdx.x >> 2), n, lrow, lcol, rec, Lb, rhs, yin, yout,
                                     Dinv, zout, rs, first ? rs : 1.0);
 }
 
 template <typename T, typename ZO, int CU>
 __global__ __launch_bounds__(WG) void k_bwd_pair(int n, const int32_t *__restrict__ urow,
-                                                 const int32_t *__restrict__ ucol, const int2 *__restrict__ rec,
+                                                 const int32_t *__restrict__ ucol, const int32_t *__restrict__ rec,
                                                  const T *__restrict__ Ub, const T *__restrict__ Dinv,
                                                  const T *__restrict__ y, const T *__restrict__ zin,
                                                  ZO *__restrict__ zout, int desc) {
     const int blk = xcd_tile(desc ? (int)(gridDim.x - 1 - blockIdx.x) : (int)blockIdx.x, gridDim.x);
-    bwd_pair_row<T, ZO, CU, CU == 2>(blk * ROWS_PER_WG + (threadIdx.x >> 2), n, urow, ucol, rec, Ub, Dinv, y, zin,
+    bwd_pair_row<T, ZO, CU, true>(blk * ROWS_PER_WG + (threadIdx.x >> 2), n, urow, ucol, rec, Ub, Dinv, y, zin,
                             zout);
 }
 
@@ -882,8 +882,9 @@ abilu_status apply_t(const abilu_pattern *p, const T *LU, const T *Dinv, const d
     }
     // Sweeps two at a time where there are two and the pattern's rows hold at most three blocks on
     // each side (a row of c blocks reads c^2 more: on the nine-point grid's rows of four that is more
-    // than the sweep saves). Faster at every size measured, 2 thousand to 4 million cells, by 15-40%.
-    const bool pairs = nsw >= 3 && p->side <= FV_CAP;
+    // than the sweep saves) and most neighbours are near (PAIR_NEAR). Faster at every such size
+    // measured, 2 thousand to 4 million cells, by 15-40%.
+    const bool pairs = nsw >= 3 && p->side <= FV_CAP && p->local;
     const bool two = p->side <= 2;
     const int pgrid = xcd_grid(div_up(n, ROWS_PER_WG));
     // forward sweeps 2..nsw (sweep 1: y = r itself); the last also emits za = Dinv y

@@ -288,32 +288,60 @@ __device__ __forceinline__ void bwd_body(int blk, int n, const int32_t *__restri
 __device__ __forceinline__ int xcd_tile(int b, int g) { return (b & 7) * (g >> 3) + (b >> 3); }
 inline int xcd_grid(int tiles) { return (tiles + 7) / 8 * 8; }
 
+// f(integral_constant<int, 0>) ... f(integral_constant<int, N - 1>)
+template <int N, typename F>
+__device__ __forceinline__ void unroll(F f) {
+    if constexpr (N > 0) {
+        unroll<N - 1>(f);
+        f(std::integral_constant<int, N - 1>{});
+    }
+}
+
 // The indices of a row of a pair of sweeps: its first block b0 and its count, the columns j of its
-// blocks, the first block c0 and the count nj of each row j, and their columns. For rows of at most two
-// blocks the pattern keeps all but b0 in a record of 32 bytes, eight per lane of the quad, so that
-// every block and vector is asked for after one load, where the walk is two levels (four with the
+// blocks, the first block c0 and the count nj of each row j, and their columns. A single system's
+// pattern keeps all but b0 in a record of 32 bytes (rows of at most two blocks) or 64 (three), eight or
+// sixteen per lane of the quad: the words j, then c0 with the count in its low two bits, then the columns
+// of each row j, -1 where there is none. Every block and vector is asked for after one load, where the
+// walk is two levels (four with the
 // columns) deeper. The row's own blocks are asked for between first() and second(), so that the walk
 // does not hold them up (server, which keeps no records: 57 us a sweep behind it, 52 so).
 template <int CL, bool REC>
 struct PairIndex {
     int b0, nl, j[CL], c0[CL], nj[CL], kk[CL][CL];
     __device__ __forceinline__ void first(int i, int r, const int32_t *__restrict__ row,
-                                          const int32_t *__restrict__ col, const int2 *__restrict__ rec) {
+                                          const int32_t *__restrict__ col, const int32_t *__restrict__ rec) {
         b0 = row[i];
         if constexpr (REC) {
-            const int2 w = rec[(int64_t)i * 4 + r];
-            const unsigned p0 = (unsigned)qb<1>(w.x), p1 = (unsigned)qb<1>(w.y);
-            j[0] = qb<0>(w.x);
-            j[1] = qb<0>(w.y);
-            nl = (j[0] >= 0) + (j[1] >= 0);
-            c0[0] = (int)(p0 >> 2);
-            nj[0] = (int)(p0 & 3);
-            c0[1] = (int)(p1 >> 2);
-            nj[1] = (int)(p1 & 3);
-            kk[0][0] = qb<2>(w.x);
-            kk[0][1] = qb<2>(w.y);
-            kk[1][0] = qb<3>(w.x);
-            kk[1][1] = qb<3>(w.y);
+            constexpr int P = PAIR_REC<CL> / 4;   // words per lane
+            int w[P];
+            if constexpr (P == 2) {
+                const int2 v = reinterpret_cast<const int2 *>(rec)[(int64_t)i * 4 + r];
+                w[0] = v.x;
+                w[1] = v.y;
+            } else {
+                const int4 v = reinterpret_cast<const int4 *>(rec)[(int64_t)i * 4 + r];
+                w[0] = v.x;
+                w[1] = v.y;
+                w[2] = v.z;
+                w[3] = v.w;
+            }
+            const auto word = [&](auto n) {
+                constexpr int N = decltype(n)::value;
+                return qb<N / P>(w[N % P]);
+            };
+            nl = 0;
+            unroll<CL>([&](auto u) {
+                constexpr int U = decltype(u)::value;
+                j[U] = word(std::integral_constant<int, U>{});
+                nl += j[U] >= 0;
+                const unsigned cn = (unsigned)word(std::integral_constant<int, CL + U>{});
+                c0[U] = (int)(cn >> 2);
+                nj[U] = (int)(cn & 3);
+                unroll<CL>([&](auto v) {
+                    constexpr int V = decltype(v)::value;
+                    kk[U][V] = word(std::integral_constant<int, 2 * CL + U * CL + V>{});
+                });
+            });
         } else {
             nl = row[i + 1] - b0;
 #pragma unroll
@@ -345,10 +373,11 @@ struct PairIndex {
 // for four); 61,952 FP64 21.2 -> 12.8; 180,000 FP32 29.8 -> 22.2; 500,000 line-ordered quads FP32
 // 87.6 -> 73.0 (94.3 without xcd_tile); 4 million triangles FP32 608 -> 477. Of this the records gave,
 // on kernels, 2,000 FP32 4 -> 3.1; 180,000 FP32 13.1 + 12.1 -> 12.1 + 10.1; 4 million 253 + 245 ->
-// 251 + 227. Two rows per quad at once (95 registers) lose: 180,000 14.7 + 11.1, 4 million 272 + 221.
+// 251 + 227, and with three blocks a side 316 + 305 -> 272 + 233. Two rows per quad at once (95 registers) lose: 180,000 14.7 + 11.1, 4 million 272 + 221.
 template <typename T, typename YI, bool EMIT_Z, int CL, bool REC>
 __device__ __forceinline__ void fwd_pair_row(int i, int n, const int32_t *__restrict__ lrow,
-                                             const int32_t *__restrict__ lcol, const int2 *__restrict__ rec, const T *__restrict__ Lb,
+                                             const int32_t *__restrict__ lcol, const int32_t *__restrict__ rec,
+                                             const T *__restrict__ Lb,
                                              const double *__restrict__ rhs, const YI *__restrict__ yin,
                                              T *__restrict__ yout, const T *__restrict__ Dinv, T *__restrict__ zout,
                                              double rs, double ys) {
@@ -413,7 +442,7 @@ __device__ __forceinline__ void fwd_pair_row(int i, int n, const int32_t *__rest
 // z_j = D_j (y_j - sum_k U_jk zin_k) for the upper neighbours j, then z_i from them.
 template <typename T, typename ZO, int CU, bool REC>
 __device__ __forceinline__ void bwd_pair_row(int i, int n, const int32_t *__restrict__ urow,
-                                             const int32_t *__restrict__ ucol, const int2 *__restrict__ rec,
+                                             const int32_t *__restrict__ ucol, const int32_t *__restrict__ rec,
                                              const T *__restrict__ Ub, const T *__restrict__ Dinv,
                                              const T *__restrict__ y, const T *__restrict__ zin,
                                              ZO *__restrict__ zout) {

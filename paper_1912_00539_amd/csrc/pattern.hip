@@ -10,12 +10,12 @@ namespace {
 
 using namespace abilu_setup;
 
-// also clears the words of pat_side_body and the completion counts
+// also clears the words of k_pat_tri_counts and the completion counts
 __global__ void k_pat_rows(int n, int64_t Z, const int32_t *__restrict__ rowptr, const int32_t *__restrict__ colidx,
                            int32_t *__restrict__ diag_pos, unsigned *__restrict__ err, unsigned *__restrict__ more,
                            int32_t *__restrict__ done) {
     if (blockIdx.x == 0) {
-        if (threadIdx.x < 2) more[threadIdx.x] = 0;
+        if (threadIdx.x < 4) more[threadIdx.x] = 0;
         for (int t = threadIdx.x; t < DONE_INTS; t += blockDim.x) done[t] = 0;
     }
     pat_rows_body(blockIdx.x, n, Z, rowptr, colidx, diag_pos, err);
@@ -36,10 +36,30 @@ __global__ __launch_bounds__(PAT_ROWS) void k_pat_fill(int n, int ZL, const int3
     pat_fill_body(blockIdx.x, n, ZL, rowptr, colidx, diag_pos, lrow, urow, ptr, pik, pkj, sik, skj);
 }
 
-__global__ void k_pat_tri_counts(int n, const int32_t *__restrict__ rowptr, const int32_t *__restrict__ diag_pos,
-                                 int64_t *__restrict__ nl, int64_t *__restrict__ nu, unsigned *more) {
+// also pat_side_body, and over a sample of 256 workgroups at most the lower blocks farther than PAIR_NEAR
+// rows and all of them: more[2], more[3] (the sample bounds the additions to one address)
+__global__ void k_pat_tri_counts(int n, const int32_t *__restrict__ rowptr, const int32_t *__restrict__ colidx,
+                                 const int32_t *__restrict__ diag_pos, int64_t *__restrict__ nl,
+                                 int64_t *__restrict__ nu, unsigned *more) {
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
     pat_tri_counts_body(blockIdx.x, n, rowptr, diag_pos, nl, nu);
-    pat_side_body(blockIdx.x * blockDim.x + threadIdx.x, n, rowptr, diag_pos, more);
+    pat_side_body(i, n, rowptr, diag_pos, more);
+    if (n <= PAIR_NEAR || blockIdx.x % (gridDim.x / 256 + 1) != 0) return;
+    int far = 0, all = 0;
+    if (i < n) {
+        for (int e = rowptr[i]; e < diag_pos[i]; ++e) {
+            ++all;
+            far += i - colidx[e] > PAIR_NEAR;
+        }
+    }
+    for (int o = 32; o > 0; o >>= 1) {
+        far += __shfl_xor(far, o, 64);
+        all += __shfl_xor(all, o, 64);
+    }
+    if ((threadIdx.x & 63) == 0 && all) {
+        atomicAdd(more + 2, (unsigned)far);
+        atomicAdd(more + 3, (unsigned)all);
+    }
 }
 
 __global__ void k_pat_tri_cols(int n, const int32_t *__restrict__ rowptr, const int32_t *__restrict__ colidx,
@@ -54,30 +74,34 @@ __global__ void k_pat_sym(int n, const int32_t *__restrict__ rowptr, const int32
     pat_sym_body(blockIdx.x, n, rowptr, colidx, diag_pos, unsym);
 }
 
-// PairIndex's records of rows of at most two blocks a side: {j0, j1}, {c0, c1} with the counts in the
-// low two bits, {k00, k01}, {k10, k11}; -1 where there is none.
+// PairIndex's records of rows of at most S blocks a side
+template <int S>
 __global__ void k_pat_pairs(int n, const int32_t *__restrict__ rowptr, const int32_t *__restrict__ colidx,
                             const int32_t *__restrict__ diag_pos, const int32_t *__restrict__ lrow,
-                            const int32_t *__restrict__ urow, int2 *__restrict__ lrec, int2 *__restrict__ urec) {
+                            const int32_t *__restrict__ urow, int32_t *__restrict__ lrec, int32_t *__restrict__ urec) {
+    constexpr int W = PAIR_REC<S>;
     const int t = blockIdx.x * blockDim.x + threadIdx.x;
     const int i = t >> 1, upper = t & 1;
     if (i >= n) return;
-    int j[2], k[2][2];
-    unsigned c[2];
+    int w[W];
+#pragma unroll
+    for (int q = 0; q < W; ++q) w[q] = q >= S && q < 2 * S ? 0 : -1;
     const int d = diag_pos[i], e0 = upper ? d + 1 : rowptr[i], e1 = upper ? rowptr[i + 1] : d;
-    for (int u = 0; u < 2; ++u) {
-        j[u] = k[u][0] = k[u][1] = -1;
-        c[u] = 0;
+#pragma unroll
+    for (int u = 0; u < S; ++u) {
         if (e0 + u < e1) {
-            j[u] = colidx[e0 + u];
-            const int dj = diag_pos[j[u]], f0 = upper ? dj + 1 : rowptr[j[u]], f1 = upper ? rowptr[j[u] + 1] : dj;
-            c[u] = (unsigned)(upper ? urow[j[u]] : lrow[j[u]]) << 2 | (unsigned)(f1 - f0);
-            for (int v = 0; v < f1 - f0; ++v) k[u][v] = colidx[f0 + v];
+            const int j = colidx[e0 + u];
+            const int dj = diag_pos[j], f0 = upper ? dj + 1 : rowptr[j], f1 = upper ? rowptr[j + 1] : dj;
+            w[u] = j;
+            w[S + u] = (int)((unsigned)(upper ? urow[j] : lrow[j]) << 2 | (unsigned)(f1 - f0));
+#pragma unroll
+            for (int v = 0; v < S; ++v)
+                if (f0 + v < f1) w[2 * S + u * S + v] = colidx[f0 + v];
         }
     }
-    int4 *out = (int4 *)((upper ? urec : lrec) + (int64_t)i * 4);
-    out[0] = make_int4(j[0], j[1], (int)c[0], (int)c[1]);
-    out[1] = make_int4(k[0][0], k[0][1], k[1][0], k[1][1]);
+    int4 *out = (int4 *)((upper ? urec : lrec) + (int64_t)i * W);
+#pragma unroll
+    for (int q = 0; q < W / 4; ++q) out[q] = make_int4(w[4 * q], w[4 * q + 1], w[4 * q + 2], w[4 * q + 3]);
 }
 
 // What a synchronous factor sweep needs of each block, in one load.
@@ -136,7 +160,8 @@ void free_pattern(abilu_pattern *p) {
 
 namespace abilu {
 
-// the two words of pat_side_body, behind the last pair offset
+// the four words of k_pat_tri_counts, behind the last pair offset (without rows, the last two lie in the
+// scans' scratch behind it)
 static unsigned *shape_words(void *scratch, int32_t n, int64_t Z) {
     return (unsigned *)(pat_scratch(scratch, n, Z).ptr64 + Z + 1);
 }
@@ -161,8 +186,8 @@ abilu_status pattern_validate_async(int32_t n, int64_t Z, const int32_t *rowptr,
 }
 
 // Non-blocking stage 1b (valid patterns only): lower/upper row offsets and the update-set
-// offsets (pair_ptr); h_sizes receives ZL, ZU, the number of pairs and the two words of
-// pat_side_body. ptr64 in the scratch
+// offsets (pair_ptr); h_sizes receives ZL, ZU, the number of pairs and the four words of
+// k_pat_tri_counts. ptr64 in the scratch
 // keeps the int64 pair offsets for pattern_fill.
 abilu_status pattern_count_async(int32_t n, int64_t Z, const int32_t *rowptr, const int32_t *colidx,
                                  const int32_t *diag_pos, int32_t *lrow, int32_t *urow, int32_t *pair_ptr,
@@ -174,7 +199,8 @@ abilu_status pattern_count_async(int32_t n, int64_t Z, const int32_t *rowptr, co
         if (!hip_ok((x), #x)) return ABILU_EDEVICE;        \
     } while (0)
     if (n > 0) {
-        k_pat_tri_counts<<<div_up(n, 256), 256, 0, s>>>(n, rowptr, diag_pos, cnt, cnt + (n + 1), shape_words(scratch, n, Z));
+        k_pat_tri_counts<<<div_up(n, 256), 256, 0, s>>>(n, rowptr, colidx, diag_pos, cnt, cnt + (n + 1),
+                                                        shape_words(scratch, n, Z));
         CK(hipGetLastError());
     }
     for (int part = 0; part < 2; ++part) {
@@ -186,7 +212,7 @@ abilu_status pattern_count_async(int32_t n, int64_t Z, const int32_t *rowptr, co
         CK(hipGetLastError());
     }
     CK(scan_exclusive(Z, cnt, tot, ptr64, pair_ptr, s));
-    CK(hipMemcpyAsync(h_sizes + 2, ptr64 + Z, 2 * sizeof(int64_t), hipMemcpyDeviceToHost, s));
+    CK(hipMemcpyAsync(h_sizes + 2, ptr64 + Z, 3 * sizeof(int64_t), hipMemcpyDeviceToHost, s));
     return ABILU_OK;
 #undef CK
 }
@@ -199,7 +225,7 @@ bool pattern_sizes_ok(int32_t n, int64_t Z, const int64_t *sizes) {
 // Blocking stage 1 (two stream syncs).
 abilu_status pattern_count(int32_t n, int64_t Z, const int32_t *rowptr, const int32_t *colidx, int32_t *diag_pos,
                            int32_t *lrow, int32_t *urow, int32_t *pair_ptr, int32_t *done, void *scratch,
-                           int64_t *h_pinned, hipStream_t s, int64_t *ZL, int64_t *ZU, int64_t *npairs, int32_t *side) {
+                           int64_t *h_pinned, hipStream_t s, int64_t *ZL, int64_t *ZU, int64_t *npairs, int32_t *side, bool *local) {
     abilu_status st = pattern_validate_async(n, Z, rowptr, colidx, diag_pos, done, scratch, (unsigned *)h_pinned, s);
     if (st != ABILU_OK) return st;
     if (!hip_ok(hipStreamSynchronize(s), "pattern validation sync")) return ABILU_EDEVICE;
@@ -210,7 +236,9 @@ abilu_status pattern_count(int32_t n, int64_t Z, const int32_t *rowptr, const in
     *ZL = h_pinned[0];
     *ZU = h_pinned[1];
     *npairs = h_pinned[2];
-    *side = side_class((const unsigned *)(h_pinned + 3));
+    const unsigned *words = (const unsigned *)(h_pinned + 3);
+    *side = side_class(words);
+    *local = n <= PAIR_NEAR || 4ull * words[2] <= words[3];
     return pattern_sizes_ok(n, Z, h_pinned) ? ABILU_OK : ABILU_EPATTERN;
 }
 
@@ -290,15 +318,14 @@ extern "C" abilu_status abilu_build_pattern(int32_t nbrows, const int32_t *d_row
         CK(hipMemcpyAsync(p->rowptr, d_rowptr, sizeof(int32_t) * (n + 1), hipMemcpyDeviceToDevice, s));
         if (Z > 0) CK(hipMemcpyAsync(p->colidx, d_colidx, sizeof(int32_t) * Z, hipMemcpyDeviceToDevice, s));
         st = pattern_count(n, Z, p->rowptr, p->colidx, p->diag_pos, p->lrow, p->urow, p->pair_ptr, p->done, scratch,
-                           (int64_t *)p->pinned, s, &ZL, &ZU, &npairs, &p->side);
+                           (int64_t *)p->pinned, s, &ZL, &ZU, &npairs, &p->side, &p->local);
         if (st != ABILU_OK) goto fail;
         p->nnzb_lower = ZL;
         p->nnzb_upper = ZU;
         p->npairs = npairs;
-        const size_t np = (size_t)npairs + 1, recs = p->side <= 2 ? 8 * (size_t)n : 0;
+        const size_t np = (size_t)npairs + 1, recs = !p->local ? 0 : p->side <= 2 ? PAIR_REC<2> * (size_t)n : p->side <= 3 ? PAIR_REC<3> * (size_t)n : 0;
         CKA(allocate(p, {{&p->lcol, 2 * ((size_t)ZL + 1)}, {&p->ucol, (size_t)ZU + 1}, {&p->pik, np}, {&p->pkj, np},
-                         {&p->sik, np}, {&p->skj, np}, {(int32_t **)&p->lrec, recs + 1},
-                         {(int32_t **)&p->urec, recs + 1}}));
+                         {&p->sik, np}, {&p->skj, np}, {&p->lrec, recs + 1}, {&p->urec, recs + 1}}));
         p->ldiag = p->lcol + (ZL + 1);
         st = pattern_fill(n, Z, ZL, ZU, npairs, p->rowptr, p->colidx, p->diag_pos, p->lrow, p->urow, p->lcol,
                           p->ldiag, p->ucol, p->pik, p->pkj, p->sik, p->skj, scratch, s);
@@ -314,9 +341,13 @@ extern "C" abilu_status abilu_build_pattern(int32_t nbrows, const int32_t *d_row
             CK(hipMemcpyAsync(p->pinned, unsym, sizeof(unsigned), hipMemcpyDeviceToHost, s));
             CK(hipStreamSynchronize(s));
             p->symmetric = *(const unsigned *)p->pinned == 0;
-            if (n > 0 && p->side <= 2) {
-                k_pat_pairs<<<div_up(2 * (int64_t)n, 256), 256, 0, s>>>(n, p->rowptr, p->colidx, p->diag_pos, p->lrow,
-                                                                        p->urow, p->lrec, p->urec);
+            if (n > 0 && p->local && p->side <= 3) {
+                auto records = [&](auto size) {
+                    k_pat_pairs<decltype(size)::value><<<div_up(2 * (int64_t)n, 256), 256, 0, s>>>(
+                        n, p->rowptr, p->colidx, p->diag_pos, p->lrow, p->urow, p->lrec, p->urec);
+                };
+                if (p->side <= 2) records(std::integral_constant<int, 2>{});
+                else records(std::integral_constant<int, 3>{});
                 CK(hipGetLastError());
             }
             if (n > 0 && !p->fv()) {
