@@ -471,8 +471,8 @@ ReqLayout req_layout(const abilu_serve_config &c, int32_t n, int64_t Z, size_t g
     L.pair_ptr = take(4 * (size_t)(Z + 1));
     L.lrow = take(4 * (size_t)(n + 1));
     L.urow = take(4 * (size_t)(n + 1));
-    L.lcol = take(4 * (size_t)(L.zcap + 1));
-    L.ldiag = take(4 * (size_t)(L.zcap + 1));
+    L.ldiag = take(4 * (size_t)(2 * L.zcap + 1));   // and lcol behind it, whose padding entry pads both
+    L.lcol = L.ldiag + 4 * (size_t)L.zcap;
     L.ucol = take(4 * (size_t)(L.zcap + 1));
     L.pik = take(4 * (size_t)(L.pcap + 1));
     L.pkj = take(4 * (size_t)(L.pcap + 1));
@@ -491,13 +491,13 @@ ReqLayout req_layout(const abilu_serve_config &c, int32_t n, int64_t Z, size_t g
     L.zb = sync ? take(sF * nv) : NONE;
     L.partials = take(8 * (m + 2) * (size_t)L.nb_vec);
     L.H = take(8 * (m + 1) * m);
-    L.cs = take(8 * (m + 2));
-    L.sn = take(8 * (m + 2));
-    L.g = take(8 * (m + 2));
-    L.coef = take(8 * (m + 2));
-    L.misc = take(8 * 16);
-    L.vscale = take(8 * (m + 2));
-    L.red = take(8 * (m + 4));
+    L.cs = take(8 * (5 * (m + 2) + 16 + (m + 4)));   // the small vectors of the Hessenberg problem
+    L.sn = L.cs + 8 * (m + 2);
+    L.g = L.sn + 8 * (m + 2);
+    L.coef = L.g + 8 * (m + 2);
+    L.vscale = L.coef + 8 * (m + 2);
+    L.misc = L.vscale + 8 * (m + 2);
+    L.red = L.misc + 8 * 16;
     L.V = take(8 * (m + 1) * nv);
     L.Z = take(8 * m * nv);
     // generation and pattern-analysis scratch reuse the Krylov bases (free until the first tick)
