@@ -19,9 +19,10 @@
  *    and from A's CSR order. Dinv[N][4][4] holds U_ii^{-1}. Element type double (ABILU_F64) or
  *    float (ABILU_F32).
  *  - Memory: every pointer named d_* is device memory on the current HIP device, allocated and
- *    owned by the caller. The library owns only the pattern object (device arrays plus a small
- *    pinned host buffer); the compute entry points allocate nothing. Scratch space is a
- *    caller-provided workspace of at least abilu_workspace_bytes() bytes, 256-byte aligned.
+ *    owned by the caller. The library owns only the pattern object (device arrays, among them the
+ *    completion counts of fgmres_solve's reductions, plus a small pinned host buffer); the compute
+ *    entry points allocate nothing. Scratch space is a caller-provided workspace of at least
+ *    abilu_workspace_bytes() bytes, 256-byte aligned.
  *  - Streams: `stream` is a hipStream_t (NULL = the null stream). Every call is ordered on it.
  *    Only abilu_build_pattern, fgmres_solve, abilu_ilu_residual, abilu_read_flags and
  *    abilu_profile_report block, and they wait on `stream` only.
@@ -286,7 +287,9 @@ abilu_status abilu_factor(const abilu_pattern *p, const double *d_A, void *d_LU,
  *   forward  y_i <- r_i - sum_{j<i} L_ij y_j                  (L_ii = I)
  *   backward z_i <- U_ii^{-1} (y_i - sum_{j>i} U_ij z_j)
  * nsweeps forward sweeps then nsweeps backward sweeps (nsweeps = 0: z = r, no preconditioning).
- * SYNC sweeps read the previous sweep's vector; ASYNC sweeps update the vector in place. From the
+ * SYNC sweeps read the previous sweep's vector; ASYNC sweeps update the vector in place, or, on
+ * patterns of at most three blocks a side of a row and from three sweeps on, run two at a time in the
+ * schedule in which no read sees a value written in its sweep. From the
  * zero initial guess the first sweeps are y = r and z = U_ii^{-1} y and are taken in that closed
  * form (not launched) in these two modes. ABILU_ASYNC_SERIAL runs every sweep, forward rows
  * ascending and backward rows descending, from zero vectors. The chunked modes launch every sweep;
@@ -360,7 +363,7 @@ typedef struct {
  *            no SpMV is spent on it)
  *   restart >= 1, maxit >= 0, rtol >= 0; apply_sweeps / mode / prec as for abilu_apply
  *   work_bytes >= abilu_workspace_bytes(p, prec, restart)
- * Blocks (one host read of a few scalars per iteration). Returns ABILU_OK, ABILU_WARN_NOCONV,
+ * Blocks (the host polls a few scalars in the pattern's pinned buffer once per iteration). Returns ABILU_OK, ABILU_WARN_NOCONV,
  * ABILU_WARN_MODIFIED (flag set and converged), ABILU_ENONFINITE, ABILU_EINVAL, ABILU_EDEVICE.
  */
 #define ABILU_FGMRES_ZERO_GUESS 1u
