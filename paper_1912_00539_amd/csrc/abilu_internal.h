@@ -98,8 +98,15 @@ constexpr int DIAG_ROWS = 512;
 // 54.5; 800,000 FP64 246 / 321; in Cuthill-McKee order 800,000 FP32 114 / 93, FP64 205 / 156.
 constexpr int PAIR_NEAR = 16384;
 // words of a row's record of a pair of sweeps: S columns, S rows, S * S columns of those, in four lanes
+// (a row's word is its first block, shifted by two, and its count)
 template <int S>
 constexpr int PAIR_REC = S <= 2 ? 8 : 16;
+// Whether the records hold every offset of the parts (30 bits); rows beyond that take their sweeps one at a
+// time, and the pattern no memory for records.
+inline bool pair_records_hold(int64_t n, int64_t ZL, int64_t ZU) {
+    constexpr int64_t LIMIT = (int64_t)1 << 30;
+    return n < LIMIT && ZL < LIMIT && ZU < LIMIT;
+}
 
 // completion counts of the reductions (ints, a cache line apart): the root, then one per group of
 // workgroups (last_workgroup)

@@ -74,34 +74,11 @@ __global__ void k_pat_sym(int n, const int32_t *__restrict__ rowptr, const int32
     pat_sym_body(blockIdx.x, n, rowptr, colidx, diag_pos, unsym);
 }
 
-// PairIndex's records of rows of at most S blocks a side
 template <int S>
 __global__ void k_pat_pairs(int n, const int32_t *__restrict__ rowptr, const int32_t *__restrict__ colidx,
                             const int32_t *__restrict__ diag_pos, const int32_t *__restrict__ lrow,
                             const int32_t *__restrict__ urow, int32_t *__restrict__ lrec, int32_t *__restrict__ urec) {
-    constexpr int W = PAIR_REC<S>;
-    const int t = blockIdx.x * blockDim.x + threadIdx.x;
-    const int i = t >> 1, upper = t & 1;
-    if (i >= n) return;
-    int w[W];
-#pragma unroll
-    for (int q = 0; q < W; ++q) w[q] = q >= S && q < 2 * S ? 0 : -1;
-    const int d = diag_pos[i], e0 = upper ? d + 1 : rowptr[i], e1 = upper ? rowptr[i + 1] : d;
-#pragma unroll
-    for (int u = 0; u < S; ++u) {
-        if (e0 + u < e1) {
-            const int j = colidx[e0 + u];
-            const int dj = diag_pos[j], f0 = upper ? dj + 1 : rowptr[j], f1 = upper ? rowptr[j + 1] : dj;
-            w[u] = j;
-            w[S + u] = (int)((unsigned)(upper ? urow[j] : lrow[j]) << 2 | (unsigned)(f1 - f0));
-#pragma unroll
-            for (int v = 0; v < S; ++v)
-                if (f0 + v < f1) w[2 * S + u * S + v] = colidx[f0 + v];
-        }
-    }
-    int4 *out = (int4 *)((upper ? urec : lrec) + (int64_t)i * W);
-#pragma unroll
-    for (int q = 0; q < W / 4; ++q) out[q] = make_int4(w[4 * q], w[4 * q + 1], w[4 * q + 2], w[4 * q + 3]);
+    pat_pairs_body<S>(blockIdx.x, blockDim.x, threadIdx.x, n, rowptr, colidx, diag_pos, lrow, urow, lrec, urec);
 }
 
 // What a synchronous factor sweep needs of each block, in one load.
@@ -323,6 +300,7 @@ extern "C" abilu_status abilu_build_pattern(int32_t nbrows, const int32_t *d_row
         p->nnzb_lower = ZL;
         p->nnzb_upper = ZU;
         p->npairs = npairs;
+        p->local = p->local && pair_records_hold(n, ZL, ZU);
         const size_t np = (size_t)npairs + 1, recs = !p->local ? 0 : p->side <= 2 ? PAIR_REC<2> * (size_t)n : p->side <= 3 ? PAIR_REC<3> * (size_t)n : 0;
         CKA(allocate(p, {{&p->lcol, 2 * ((size_t)ZL + 1)}, {&p->ucol, (size_t)ZU + 1}, {&p->pik, np}, {&p->pkj, np},
                          {&p->sik, np}, {&p->skj, np}, {&p->lrec, recs + 1}, {&p->urec, recs + 1}}));

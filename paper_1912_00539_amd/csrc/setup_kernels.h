@@ -102,10 +102,10 @@ __device__ __forceinline__ void scan_finish_body(int blk, int64_t len, const int
 
 // ------------------------------------------------------------------ pattern analysis
 // position of column j in row k, or -1 (binary search over the sorted row)
-__device__ __forceinline__ int find_col(const int32_t *rowptr, const int32_t *colidx, int k, int j) {
+__host__ __device__ __forceinline__ int find_col(const int32_t *rowptr, const int32_t *colidx, int k, int j) {
     int lo = rowptr[k], hi = rowptr[k + 1] - 1;
     while (lo <= hi) {
-        int mid = (lo + hi) >> 1;
+        int mid = lo + ((hi - lo) >> 1);   // lo + hi may pass 2^31
         int c = colidx[mid];
         if (c == j) return mid;
         if (c < j) lo = mid + 1; else hi = mid - 1;
@@ -136,11 +136,11 @@ __device__ __forceinline__ void pat_rows_body(int blk, int n, int64_t Z, const i
 }
 
 // position of column j in the strictly upper part of row k (j > k), or -1 (binary search)
-__device__ __forceinline__ int find_upper(const int32_t *rowptr, const int32_t *colidx, const int32_t *diag_pos,
+__host__ __device__ __forceinline__ int find_upper(const int32_t *rowptr, const int32_t *colidx, const int32_t *diag_pos,
                                           int k, int j) {
     int lo = diag_pos[k] + 1, hi = rowptr[k + 1] - 1;
     while (lo <= hi) {
-        int mid = (lo + hi) >> 1;
+        int mid = lo + ((hi - lo) >> 1);   // lo + hi may pass 2^31
         int c = colidx[mid];
         if (c == j) return mid;
         if (c < j) lo = mid + 1; else hi = mid - 1;
@@ -297,6 +297,41 @@ __device__ __forceinline__ void pat_tri_cols_body(int blk, int n, const int32_t 
         ldiag[lrow[i] + (e - b0)] = diag_pos[j];
     }
     for (int e = d + 1; e < b1; ++e) ucol[urow[i] + (e - d - 1)] = colidx[e];
+}
+
+// PairIndex's records of rows of at most S blocks a side: thread `tid` of workgroup `blk` (of `width`
+// threads) writes one row's record of one direction. 2 n threads: their number may pass 2^31.
+template <int S>
+__host__ __device__ __forceinline__ void pat_pairs_body(unsigned blk, unsigned width, unsigned tid, int n,
+                                                        const int32_t *__restrict__ rowptr,
+                                                        const int32_t *__restrict__ colidx,
+                                                        const int32_t *__restrict__ diag_pos,
+                                                        const int32_t *__restrict__ lrow,
+                                                        const int32_t *__restrict__ urow, int32_t *__restrict__ lrec,
+                                                        int32_t *__restrict__ urec) {
+    constexpr int W = PAIR_REC<S>;
+    const int64_t t = (int64_t)blk * width + tid, i = t >> 1;
+    const bool upper = (t & 1) != 0;
+    if (i >= n) return;
+    int w[W];
+#pragma unroll
+    for (int q = 0; q < W; ++q) w[q] = q >= S && q < 2 * S ? 0 : -1;
+    const int d = diag_pos[i], e0 = upper ? d + 1 : rowptr[i], e1 = upper ? rowptr[i + 1] : d;
+#pragma unroll
+    for (int u = 0; u < S; ++u) {
+        if (e0 + u < e1) {
+            const int j = colidx[e0 + u];
+            const int dj = diag_pos[j], f0 = upper ? dj + 1 : rowptr[j], f1 = upper ? rowptr[j + 1] : dj;
+            w[u] = j;
+            w[S + u] = (int)((unsigned)(upper ? urow[j] : lrow[j]) << 2 | (unsigned)(f1 - f0));
+#pragma unroll
+            for (int v = 0; v < S; ++v)
+                if (f0 + v < f1) w[2 * S + u * S + v] = colidx[f0 + v];
+        }
+    }
+    int4 *out = (int4 *)((upper ? urec : lrec) + i * W);
+#pragma unroll
+    for (int q = 0; q < W / 4; ++q) out[q] = make_int4(w[4 * q], w[4 * q + 1], w[4 * q + 2], w[4 * q + 3]);
 }
 
 
