@@ -523,7 +523,8 @@ __device__ __forceinline__ bool inv4_row_gathered(const T (&row)[4], int r, T (&
 // floats is either a float or at least 2^-49 (relative) away from the midpoint of two floats, so
 // rounding the product to float gives the correctly rounded quotient, in 3 instructions (and 6 per
 // divisor) where a float division takes about 12. (Quotients in the subnormal range may differ in
-// the last place from the division's; a zero or non-finite divisor gives a non-finite quotient.)
+// the last place from the division's; a zero or infinite divisor gives NaN where the division gives an
+// infinity or zero.)
 template <typename T>
 struct Divisor {
     double b;
@@ -546,8 +547,8 @@ struct Divisor {
 // forms its own multiplier and updates its own row, the pivot row coming by DPP, then lane c solves
 // for column c of the inverse and the quad transposes: the operations of inv4_row_pivoted on each
 // element, in its order (the same bits), with 7 divisions per lane instead of 10, 18 product
-// subtractions instead of 42 and no row exchanges. A quad that finds a larger multiplier takes
-// inv4_row_pivoted.
+// subtractions instead of 42 and no row exchanges. A quad that finds a larger multiplier, or in float a
+// last pivot that Divisor does not take, takes inv4_row_pivoted.
 template <typename T>
 __device__ __forceinline__ bool inv4_row(const T (&row)[4], int r, T (&out)[4]) {
     T m1 = row[1], m2 = row[2], m3 = row[3];
@@ -568,7 +569,9 @@ __device__ __forceinline__ bool inv4_row(const T (&row)[4], int r, T (&out)[4]) 
     const T f2 = d2.under(m2);
     m3 = sub_prod(m3, f2, u23);
     const T u33 = qb<3>(m3);
-    const bool natural = (r < 1 || fabs(f0) <= T(1)) && (r < 2 || fabs(f1) <= T(1)) && (r < 3 || fabs(f2) <= T(1));
+    bool natural = (r < 1 || fabs(f0) <= T(1)) && (r < 2 || fabs(f1) <= T(1)) && (r < 3 || fabs(f2) <= T(1));
+    // an infinite pivot among the first three shows in a multiplier (NaN); the last has none
+    if constexpr (sizeof(T) == 4) natural = natural && isfinite(u33);
     T x[4];
 #pragma unroll
     for (int q = 0; q < 4; ++q) x[q] = q == r ? T(1) : T(0);
