@@ -5,7 +5,6 @@
 
 #include <cstddef>
 #include <cstdint>
-#include <vector>
 
 #include "abilu.h"
 
@@ -36,7 +35,8 @@ struct abilu_pattern {
                                   // (behind lcol in its allocation)
     double *pinned = nullptr;     // host pinned, 64 doubles, for blocking scalar reads
     double *pinned_dev = nullptr; // the same memory as kernels address it
-    std::vector<void *> owned;    // device allocations that hold the arrays above
+    void *owned[20] = {};         // device allocations that hold the arrays above
+    int32_t nowned = 0;
     int32_t *done = nullptr;      // device [DONE_INTS] completion counts of FGMRES's reductions, zero
                                   // between launches (behind lrow in its allocation)
     bool symmetric = false;       // (i,j) in S_B implies (j,i) in S_B

@@ -11,7 +11,6 @@
 #include <chrono>
 #include <cmath>
 #include <cstring>
-#include <functional>
 
 #include "kernels.h"
 
@@ -335,6 +334,37 @@ abilu_status read_status(Ctx &c, const unsigned long long *slot, Status *out) {
     return ABILU_OK;
 }
 
+// The status asked for last, until it is read: `decide` takes it in and says whether the solve, or the
+// cycle, stops. Asked as the gate of an application begun before it, it lets at most `limit` launches pass.
+enum { START, CYCLE, STEP };
+template <typename Decide>
+struct Pending : Gate {
+    Ctx &c;
+    const Decide &decide;
+    Status now{};
+    const unsigned long long *slot = nullptr;
+    bool open = false, stop = false;
+    int kind = START, launched = 0, limit = 0;
+    abilu_status st = ABILU_OK;
+    Pending(Ctx &ctx, const Decide &d) : c(ctx), decide(d) {}
+    void expect(int k) {
+        open = true;
+        kind = k;
+        slot = c.slot;
+        launched = 0;
+    }
+    void read() {
+        if (!open) return;
+        open = false;
+        st = read_status(c, slot, &now);
+        stop = st != ABILU_OK || decide(kind, now);
+    }
+    bool go() override {
+        if (open && (status_here(slot) || ++launched >= limit)) read();
+        return !stop;
+    }
+};
+
 // r = b - A x into V_0, beta = ||r|| into g[0] and status[ST_BETA], 1 / beta into vscale[0]. The SpMV runs
 // its workgroups descending (measured slightly faster than ascending after either predecessor).
 abilu_status true_residual(Ctx &c, const double *A, const double *b, const double *x) {
@@ -413,50 +443,21 @@ extern "C" abilu_status fgmres_solve(const abilu_pattern *p, const double *d_A, 
     // nothing reads). Ahead of the status at most `limit` kernels are launched: enough to cover the
     // 6-8 us between the status being written and the next launch arriving, and none where a needless
     // sweep costs more.
-    enum { START, CYCLE, STEP };
-    struct Pending : Gate {
-        Ctx &c;
-        Status now{};
-        const unsigned long long *slot = nullptr;
-        bool open = false, stop = false;
-        int kind = START, launched = 0, limit = 0;
-        abilu_status st = ABILU_OK;
-        std::function<bool(int)> decide;   // takes the status in; true: stop
-        explicit Pending(Ctx &ctx) : c(ctx) {}
-        void expect(int k) {
-            open = true;
-            kind = k;
-            slot = c.slot;
-            launched = 0;
-        }
-        void read() {
-            if (!open) return;
-            open = false;
-            st = read_status(c, slot, &now);
-            stop = st != ABILU_OK || decide(kind);
-        }
-        bool go() override {
-            if (open && (status_here(slot) || ++launched >= limit)) read();
-            return !stop;
-        }
-    } pending(c);
-    const bool gated = (mode == ABILU_SYNC || mode == ABILU_ASYNC) && apply_sweeps >= 2;   // modes that ask the gate
-    pending.limit = !gated ? 0 : p->n <= 60000 ? 2 : p->n <= 400000 ? 1 : 0;
     int pass2_begin = 0, pass2_end = 0;
-    pending.decide = [&](int kind) {
+    const auto decide = [&](int kind, const Status &now) {   // takes the status in; true: stop
         if (kind == STEP) {
-            if (pending.now.guard)
+            if (now.guard)
                 ++reorth;
             else
                 prof_cancel_bytes(pass2_begin, pass2_end);   // the second pass exited at once
             ++iters;
-            est = pending.now.v0;
-            nonfinite = !std::isfinite(est) || !std::isfinite(pending.now.v1);
-            return nonfinite || est <= tol || pending.now.v1 == 0.0;
+            est = now.v0;
+            nonfinite = !std::isfinite(est) || !std::isfinite(now.v1);
+            return nonfinite || est <= tol || now.v1 == 0.0;
         }
-        beta = pending.now.v0;
+        beta = now.v0;
         if (kind == START) {
-            const double bnorm = pending.now.v1;
+            const double bnorm = now.v1;
             bn = bnorm > 0 ? bnorm : 1.0;
             tol = rtol * bn;
             est = beta;
@@ -468,6 +469,9 @@ extern "C" abilu_status fgmres_solve(const abilu_pattern *p, const double *d_A, 
         converged = beta <= tol;
         return converged || nonfinite || iters >= maxit || !(beta > 0.0);
     };
+    Pending<decltype(decide)> pending(c, decide);
+    const bool gated = (mode == ABILU_SYNC || mode == ABILU_ASYNC) && apply_sweeps >= 2;   // modes that ask the gate
+    pending.limit = !gated ? 0 : p->n <= 60000 ? 2 : p->n <= 400000 ? 1 : 0;
     pending.expect(START);
     if (pending.limit == 0 || maxit == 0) pending.read();
 

@@ -3,6 +3,7 @@
 // equation bilu), stored as CSR lists of block-position pairs ascending in k.
 #include <climits>
 #include <cstring>
+#include <new>
 
 #include "setup_kernels.h"
 
@@ -107,8 +108,9 @@ hipError_t allocate(abilu_pattern *p, std::initializer_list<Piece> pieces) {
     size_t large = 0;
     for (const Piece &q : pieces) large += q.ints >= LARGE ? up(q.ints) : 0;
     const auto get = [&](size_t ints, int32_t **out) {
+        if (p->nowned >= (int)(sizeof(p->owned) / sizeof(p->owned[0]))) return hipErrorOutOfMemory;
         const hipError_t e = hipMalloc(out, sizeof(int32_t) * ints);
-        if (e == hipSuccess) p->owned.push_back(*out);
+        if (e == hipSuccess) p->owned[p->nowned++] = *out;
         return e;
     };
     int32_t *next = nullptr;
@@ -127,7 +129,7 @@ hipError_t allocate(abilu_pattern *p, std::initializer_list<Piece> pieces) {
 
 void free_pattern(abilu_pattern *p) {
     if (!p) return;
-    for (void *q : p->owned) (void)hipFree(q);
+    for (int q = 0; q < p->nowned; ++q) (void)hipFree(p->owned[q]);
     abilu::free_chunks(p);
     if (p->pinned) (void)hipHostFree(p->pinned);
     delete p;
@@ -254,8 +256,8 @@ extern "C" abilu_status abilu_build_pattern(int32_t nbrows, const int32_t *d_row
     hipStream_t s = (hipStream_t)stream;
     const int n = nbrows;
 
-    abilu_pattern *p = new abilu_pattern();
-    p->owned.reserve(16);
+    abilu_pattern *p = new (std::nothrow) abilu_pattern();
+    if (!p) return ABILU_ENOMEM;
     void *scratch = nullptr;
     abilu_status st = ABILU_OK;
     int32_t ends[2] = {0, 0};
