@@ -1,6 +1,7 @@
 // Pattern analysis on the device: validation, diagonal positions and the update sets
 // K(i,j) = { k < min(i,j) : (i,k), (k,j) in S_B } of the block ILU(0) equations (Section 4.2,
 // equation bilu), stored as CSR lists of block-position pairs ascending in k.
+#include <algorithm>
 #include <climits>
 #include <cstring>
 #include <new>
@@ -11,12 +12,13 @@ namespace {
 
 using namespace abilu_setup;
 
-// also clears the words of k_pat_tri_counts and the completion counts
+// also clears the words of k_pat_tri_counts, the one of k_pat_sym and the completion counts
 __global__ void k_pat_rows(int n, int64_t Z, const int32_t *__restrict__ rowptr, const int32_t *__restrict__ colidx,
                            int32_t *__restrict__ diag_pos, unsigned *__restrict__ err, unsigned *__restrict__ more,
-                           int32_t *__restrict__ done) {
+                           unsigned *__restrict__ unsym, int32_t *__restrict__ done) {
     if (blockIdx.x == 0) {
         if (threadIdx.x < 4) more[threadIdx.x] = 0;
+        if (threadIdx.x == 0) *unsym = 0;
         for (int t = threadIdx.x; t < DONE_INTS; t += blockDim.x) done[t] = 0;
     }
     pat_rows_body(blockIdx.x, n, Z, rowptr, colidx, diag_pos, err);
@@ -66,8 +68,13 @@ __global__ void k_pat_tri_counts(int n, const int32_t *__restrict__ rowptr, cons
 __global__ void k_pat_tri_cols(int n, const int32_t *__restrict__ rowptr, const int32_t *__restrict__ colidx,
                                const int32_t *__restrict__ diag_pos, const int32_t *__restrict__ lrow,
                                const int32_t *__restrict__ urow, int32_t *__restrict__ lcol,
-                               int32_t *__restrict__ ldiag, int32_t *__restrict__ ucol) {
+                               int32_t *__restrict__ ldiag, int32_t *__restrict__ ucol, int ZL, int ZU) {
     pat_tri_cols_body(blockIdx.x, n, rowptr, colidx, diag_pos, lrow, urow, lcol, ldiag, ucol);
+    if (blockIdx.x == 0 && threadIdx.x == 0) {   // the padding entry behind each
+        lcol[ZL] = 0;
+        ldiag[ZL] = 0;
+        ucol[ZU] = 0;
+    }
 }
 
 __global__ void k_pat_sym(int n, const int32_t *__restrict__ rowptr, const int32_t *__restrict__ colidx,
@@ -95,6 +102,10 @@ __global__ void k_pat_blocks(int n, int ZL, const int32_t *__restrict__ rowptr, 
         brec[g] = make_int4(e, pair_ptr[e], pair_ptr[e + 1], e < d ? ldiag[g] : 0);
     }
 }
+
+// abilu_build_pattern's scratch kept as storage of records: where they start, and up to which size (beyond,
+// an allocation of the records' own size holds a fifth to a third less memory).
+constexpr size_t REC_AT = 256, KEEP_SCRATCH = (size_t)64 << 20;
 
 // Device arrays of a pattern. Those of 2 MiB and more, which cost the runtime 12 us each to allocate and
 // 12 to free, share one allocation; smaller ones come from its pool in under 1 us each.
@@ -145,6 +156,9 @@ static unsigned *shape_words(void *scratch, int32_t n, int64_t Z) {
     return (unsigned *)(pat_scratch(scratch, n, Z).ptr64 + Z + 1);
 }
 
+// the word of k_pat_sym, beside the error word in the scratch's header
+static unsigned *unsym_word(void *scratch) { return (unsigned *)scratch + 1; }
+
 size_t pattern_scratch_bytes(int32_t n, int64_t Z) {
     const int64_t len = Z + n + 2;
     return 256 + sizeof(int64_t) * (size_t)(2 * len + scan_tiles(Z > n ? Z : n) + 1);
@@ -157,7 +171,7 @@ abilu_status pattern_validate_async(int32_t n, int64_t Z, const int32_t *rowptr,
     unsigned *err = (unsigned *)scratch;
     if (!hip_ok(hipMemsetAsync(err, 0, sizeof(unsigned), s), "pattern error clear")) return ABILU_EDEVICE;
     k_pat_rows<<<max(1, div_up(n, 256)), 256, 0, s>>>(n, Z, rowptr, colidx, diag_pos, err, shape_words(scratch, n, Z),
-                                                      done);
+                                                      unsym_word(scratch), done);
     if (launch_status() != ABILU_OK) return ABILU_EDEVICE;
     if (!hip_ok(hipMemcpyAsync(h_err, err, sizeof(unsigned), hipMemcpyDeviceToHost, s), "pattern error readback"))
         return ABILU_EDEVICE;
@@ -228,14 +242,9 @@ abilu_status pattern_fill(int32_t n, int64_t Z, int64_t ZL, int64_t ZU, int64_t 
                           int32_t *lcol, int32_t *ldiag, int32_t *ucol, int32_t *pik, int32_t *pkj, int32_t *sik,
                           int32_t *skj, const void *scratch, hipStream_t s) {
     const int64_t *ptr64 = pat_scratch(const_cast<void *>(scratch), n, Z).ptr64;
-    // ldiag follows lcol
-    if (!hip_ok(hipMemsetAsync(lcol, 0, sizeof(int32_t) * 2 * (ZL + 1), s), "lcol clear") ||
-        !hip_ok(hipMemsetAsync(ucol, 0, sizeof(int32_t) * (ZU + 1), s), "ucol clear"))
-        return ABILU_EDEVICE;
-    if (n > 0) {
-        k_pat_tri_cols<<<div_up(n, 256), 256, 0, s>>>(n, rowptr, colidx, diag_pos, lrow, urow, lcol, ldiag, ucol);
-        if (launch_status() != ABILU_OK) return ABILU_EDEVICE;
-    }
+    k_pat_tri_cols<<<max(1, div_up(n, 256)), 256, 0, s>>>(n, rowptr, colidx, diag_pos, lrow, urow, lcol, ldiag, ucol,
+                                                          (int)ZL, (int)ZU);
+    if (launch_status() != ABILU_OK) return ABILU_EDEVICE;
     if (n > 0 && npairs > 0) {
         k_pat_fill<<<div_up(n, PAT_ROWS), PAT_ROWS, 0, s>>>(n, (int)ZL, rowptr, colidx, diag_pos, lrow, urow, ptr64, pik, pkj,
                                                    sik, skj);
@@ -258,7 +267,17 @@ extern "C" abilu_status abilu_build_pattern(int32_t nbrows, const int32_t *d_row
 
     abilu_pattern *p = new (std::nothrow) abilu_pattern();
     if (!p) return ABILU_ENOMEM;
-    void *scratch = nullptr;
+    void *scratch = nullptr;   // until the pattern keeps it
+    size_t scratch_bytes = 0;
+    // The scratch has served when the records are written: up to KEEP_SCRATCH the first of them that fit
+    // take its place behind the header, instead of an allocation more (12 us, and 12 to free) and a free.
+    auto keep_scratch = [&](size_t bytes) -> void * {
+        if (!scratch || scratch_bytes > KEEP_SCRATCH || REC_AT + bytes > scratch_bytes) return nullptr;
+        void *at = (char *)scratch + REC_AT;
+        p->owned[p->nowned++] = scratch;
+        scratch = nullptr;
+        return at;
+    };
     abilu_status st = ABILU_OK;
     int32_t ends[2] = {0, 0};
     int64_t ZL = 0, ZU = 0, npairs = 0;
@@ -293,7 +312,13 @@ extern "C" abilu_status abilu_build_pattern(int32_t nbrows, const int32_t *d_row
         CKA(allocate(p, {{&p->rowptr, (size_t)n + 1}, {&p->colidx, (size_t)Z + 1}, {&p->diag_pos, (size_t)n + 1},
                          {&p->pair_ptr, (size_t)Z + 1}, {&p->lrow, lrow_ints + DONE_INTS}, {&p->urow, (size_t)n + 1}}));
         p->done = p->lrow + lrow_ints;
-        CKA(hipMalloc(&scratch, pattern_scratch_bytes(n, Z)));
+        scratch_bytes = pattern_scratch_bytes(n, Z);
+        // room for the records of pairs of rows of two blocks a side, or of three where there are that many
+        const size_t rec_room = REC_AT + (Z > 5 * (int64_t)n ? 128 : 64) * (size_t)n;
+        if (rec_room <= KEEP_SCRATCH) scratch_bytes = std::max(scratch_bytes, rec_room);
+        CKA(hipMalloc(&scratch, scratch_bytes));
+        void *const work = scratch;
+        unsigned *const unsym = unsym_word(scratch);
         CK(hipMemcpyAsync(p->rowptr, d_rowptr, sizeof(int32_t) * (n + 1), hipMemcpyDeviceToDevice, s));
         if (Z > 0) CK(hipMemcpyAsync(p->colidx, d_colidx, sizeof(int32_t) * Z, hipMemcpyDeviceToDevice, s));
         st = pattern_count(n, Z, p->rowptr, p->colidx, p->diag_pos, p->lrow, p->urow, p->pair_ptr, p->done, scratch,
@@ -303,25 +328,40 @@ extern "C" abilu_status abilu_build_pattern(int32_t nbrows, const int32_t *d_row
         p->nnzb_upper = ZU;
         p->npairs = npairs;
         p->local = p->local && pair_records_hold(n, ZL, ZU);
-        const size_t np = (size_t)npairs + 1, recs = !p->local ? 0 : p->side <= 2 ? PAIR_REC<2> * (size_t)n : p->side <= 3 ? PAIR_REC<3> * (size_t)n : 0;
+        const size_t np = (size_t)npairs + 1;
+        const size_t recs = (!p->local || p->side > 3 ? 0 : p->side <= 2 ? PAIR_REC<2> : PAIR_REC<3>) * (size_t)n;
         CKA(allocate(p, {{&p->lcol, 2 * ((size_t)ZL + 1)}, {&p->ucol, (size_t)ZU + 1}, {&p->pik, np}, {&p->pkj, np},
-                         {&p->sik, np}, {&p->skj, np}, {&p->lrec, recs + 1}, {&p->urec, recs + 1}}));
+                         {&p->sik, np}, {&p->skj, np}}));
+        if (recs) {
+            if (int32_t *at = (int32_t *)keep_scratch(8 * recs)) {
+                p->lrec = at;
+                p->urec = at + recs;
+            } else {
+                CKA(allocate(p, {{&p->lrec, recs}, {&p->urec, recs}}));
+            }
+        }
         p->ldiag = p->lcol + (ZL + 1);
         st = pattern_fill(n, Z, ZL, ZU, npairs, p->rowptr, p->colidx, p->diag_pos, p->lrow, p->urow, p->lcol,
-                          p->ldiag, p->ucol, p->pik, p->pkj, p->sik, p->skj, scratch, s);
+                          p->ldiag, p->ucol, p->pik, p->pkj, p->sik, p->skj, work, s);
         if (st != ABILU_OK) goto fail;
-        // structural symmetry (the factor sweeps choose their form by it)
+        // structural symmetry (the factor sweeps choose their form by it); the records of pairs and of
+        // blocks, which need not wait for it, in the same wait of the host
         {
-            unsigned *unsym = (unsigned *)scratch;
-            CK(hipMemsetAsync(unsym, 0, sizeof(unsigned), s));
+            auto blocks = [&]() -> abilu_status {
+                p->brec = (int4 *)keep_scratch(16 * (size_t)Z);
+                if (!p->brec && !hip_ok(allocate(p, {{(int32_t **)&p->brec, 4 * (size_t)Z}}), "block records"))
+                    return ABILU_ENOMEM;
+                k_pat_blocks<<<div_up(n, 256), 256, 0, s>>>(n, (int)ZL, p->rowptr, p->diag_pos, p->lrow, p->urow,
+                                                            p->pair_ptr, p->ldiag, p->brec);
+                return launch_status();
+            };
             if (n > 0) {
                 k_pat_sym<<<div_up(n, 256), 256, 0, s>>>(n, p->rowptr, p->colidx, p->diag_pos, unsym);
                 CK(hipGetLastError());
             }
             CK(hipMemcpyAsync(p->pinned, unsym, sizeof(unsigned), hipMemcpyDeviceToHost, s));
-            CK(hipStreamSynchronize(s));
-            p->symmetric = *(const unsigned *)p->pinned == 0;
-            if (n > 0 && p->local && p->side <= 3) {
+            p->symmetric = true;   // until the host knows
+            if (recs) {
                 auto records = [&](auto size) {
                     k_pat_pairs<decltype(size)::value><<<div_up(2 * (int64_t)n, 256), 256, 0, s>>>(
                         n, p->rowptr, p->colidx, p->diag_pos, p->lrow, p->urow, p->lrec, p->urec);
@@ -330,13 +370,13 @@ extern "C" abilu_status abilu_build_pattern(int32_t nbrows, const int32_t *d_row
                 else records(std::integral_constant<int, 3>{});
                 CK(hipGetLastError());
             }
-            if (n > 0 && !p->fv()) {
-                CKA(allocate(p, {{(int32_t **)&p->brec, 4 * (size_t)Z}}));
-                k_pat_blocks<<<div_up(n, 256), 256, 0, s>>>(n, (int)ZL, p->rowptr, p->diag_pos, p->lrow, p->urow,
-                                                            p->pair_ptr, p->ldiag, p->brec);
-                CK(hipGetLastError());
-            }
+            if (n > 0 && !p->fv() && (st = blocks()) != ABILU_OK) goto fail;
             CK(hipStreamSynchronize(s));
+            p->symmetric = *(const unsigned *)p->pinned == 0;
+            if (n > 0 && !p->fv() && !p->brec) {
+                if ((st = blocks()) != ABILU_OK) goto fail;
+                CK(hipStreamSynchronize(s));
+            }
         }
     }
     (void)hipFree(scratch);
