@@ -20,6 +20,7 @@
 #include <type_traits>
 
 #include "kernels.h"
+#include "rules.h"
 
 using namespace abilu;
 using namespace abilu_dev;
@@ -802,7 +803,7 @@ abilu_status apply_t(const abilu_pattern *p, const T *LU, const T *Dinv, const d
         const bool short_fwd = by_rows && R <= SHORT_CHUNK && p->rec_max[0] <= REC_CAP;
         const bool short_bwd = by_rows && R <= SHORT_CHUNK && p->rec_max[1] <= REC_CAP;
         // chains of short rows: sixteen lanes per chunk
-        const bool chain = by_rows && p->chains && p->side <= FV_CAP;
+        const bool chain = by_rows && p->chains && p->side <= FV_CAP && abilu_rules::chain_apply(R, nch, p->side, sF == 8);
         const int cg = div_up(nch, WG / CHAIN_LANES);
         auto fwd = [&](const T *yo, T *yn) {
             if (chain) {

@@ -1,0 +1,15 @@
+// The dispatch rules at shapes measured on either side of their lines: "rule arguments -> 0 or 1" lines,
+// compared with the measured choice by tests/test_rules.py.
+#include <cstdio>
+#include <cstdlib>
+#include <cstring>
+
+#include "rules.h"
+
+using namespace abilu_rules;
+
+int main(int argc, char **argv) {
+    auto a = [&](int q) { return q < argc ? std::atoll(argv[q]) : 0; };
+    if (argc > 1 && !std::strcmp(argv[1], "chain_apply")) return chain_apply((int)a(2), a(3), (int)a(4), a(5) != 0);
+    return 2;
+}

@@ -1,0 +1,37 @@
+"""The rules that choose between forms of a kernel (csrc/rules.h), at shapes where both forms were timed:
+the faster one has to be chosen wherever they differ by more than 5%."""
+import os
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+
+@pytest.fixture(scope="module")
+def rules(tmp_path_factory):
+    exe = str(tmp_path_factory.mktemp("rules") / "rules")
+    subprocess.check_call(["g++", "-std=c++17", "-I", os.path.join(ROOT, "paper_1912_00539_amd", "csrc"),
+                           os.path.join(ROOT, "tests", "host", "rules.cpp"), "-o", exe])
+
+    def ask(rule, *args):
+        rc = subprocess.run([exe, rule] + [str(int(a)) for a in args]).returncode
+        assert rc in (0, 1), (rule, rc)
+        return rc == 1
+    return ask
+
+
+# cells, rows per chunk, blocks a side, FP64, time of three sweeps each way: a quad, sixteen lanes per chunk
+CHAIN_APPLY = [(500000, 1, 2, 0, 177, 563), (500000, 2, 2, 0, 167, 287), (500000, 3, 2, 0, 158, 205),
+               (500000, 5, 2, 0, 177, 146), (500000, 16, 2, 0, 156, 112), (500000, 1, 2, 1, 279, 1153),
+               (500000, 4, 2, 1, 270, 338), (500000, 10, 2, 1, 285, 228), (500000, 64, 2, 1, 598, 223),
+               (500000, 4, 3, 0, 200, 240), (500000, 6, 3, 0, 221, 194), (500000, 8, 3, 1, 345, 408),
+               (500000, 12, 3, 1, 394, 345), (120000, 4, 2, 0, 47, 56), (120000, 6, 2, 0, 54, 45),
+               (120000, 6, 2, 1, 77, 82), (120000, 8, 2, 1, 84, 75), (10057, 1, 2, 0, 25, 32), (10057, 3, 2, 0, 30, 26),
+               (10057, 2, 2, 1, 30, 35), (10057, 3, 2, 1, 33, 27), (64000, 3, 3, 0, 42, 55), (64000, 5, 3, 0, 48, 44),
+               (64000, 5, 3, 1, 68, 86), (64000, 8, 3, 1, 84, 56)]
+
+
+@pytest.mark.parametrize("n,R,side,f64,quad,sixteen", CHAIN_APPLY)
+def test_chain_apply(rules, n, R, side, f64, quad, sixteen):
+    assert rules("chain_apply", R, -(-n // R), side, f64) == (sixteen < quad)
