@@ -30,7 +30,11 @@ namespace {
 
 
 // The factor on the right-hand side (1 without one). The sweeps have it as a compile-time choice: an
-// application outside FGMRES is 1-1.5% faster without the multiplication.
+// application outside FGMRES is 1-1.5% faster without the multiplication, and a forward sweep of the
+// chunked runners, where the product ends up behind the wait for the next row's record, up to a third (one
+// sweep each way, FP32, 30,523 uneven rows in chunks of 256 by rows: 584 us with it, 508 without; FP64,
+// 200,000 quads in chunks of 2,048 by levels: 1,112 and 1,050). Reading the right-hand side a row ahead, or
+// multiplying behind the first loads, is no faster than the product at the load.
 template <bool SCALED = true>
 __device__ __forceinline__ double rhs_scale(const double *rscale) {
     if constexpr (!SCALED) return 1.0;
@@ -204,14 +208,14 @@ __device__ __forceinline__ void bwd_chunk_row(int i, int c1, const int32_t *__re
     zn[(int64_t)i * 4 + r] = (ZN)dot4(dr[0], a[0], dr[1], a[1], dr[2], a[2], dr[3], a[3]);
 }
 
-template <typename T, bool ZERO_OUT>
+template <typename T, bool ZERO_OUT, bool SCALED>
 __global__ __launch_bounds__(WG) void k_fwd_chunk(int n, int R, const int32_t *__restrict__ order,
                                                   const int32_t *__restrict__ lvptr,
                                                   const int32_t *__restrict__ lvstart,
                                                   const int32_t *__restrict__ lrow, const int32_t *__restrict__ lcol,
                                                   const T *__restrict__ Lb, const double *__restrict__ rhs,
                                                   const double *__restrict__ rscale, const T *yo, T *yn) {
-    const double rs = rhs_scale(rscale);
+    const double rs = rhs_scale<SCALED>(rscale);
     const int c = blockIdx.x, c0 = c * R;
     const int b = lvptr[c], nl = lvptr[c + 1] - b - 1;
     const int quad = threadIdx.x >> 2;
@@ -246,13 +250,13 @@ __global__ __launch_bounds__(WG) void k_bwd_chunk(int n, int R, const int32_t *_
 // computed just before from a register. Each row's operands are located by its record (read one
 // row ahead) and fetched together; rows with more than REC_CAP blocks in the part take the general
 // row code. The arithmetic and its order are those of fwd_chunk_row / bwd_chunk_row.
-template <typename T, bool ZERO_OUT>
+template <typename T, bool ZERO_OUT, bool SCALED>
 __global__ __launch_bounds__(WG) void k_fwd_chunk_rows(int n, int R, int nch, const int32_t *__restrict__ rec,
                                                        const int32_t *__restrict__ lrow,
                                                        const int32_t *__restrict__ lcol, const T *__restrict__ Lb,
                                                        const double *__restrict__ rhs,
                                                        const double *__restrict__ rscale, const T *yo, T *yn) {
-    const double rs = rhs_scale(rscale);
+    const double rs = rhs_scale<SCALED>(rscale);
     const int c = blockIdx.x * ROWS_PER_WG + (threadIdx.x >> 2);
     if (c >= nch) return;
     const int r = threadIdx.x & 3;
@@ -407,11 +411,11 @@ __device__ __forceinline__ void load_chunk_records(const int32_t *__restrict__ r
     }
 }
 
-template <typename T, bool ZERO_OUT>
+template <typename T, bool ZERO_OUT, bool SCALED>
 __global__ __launch_bounds__(WG) void k_fwd_chunk_short(int n, int R, int nch, const int32_t *__restrict__ rec,
                                                         const T *__restrict__ Lb, const double *__restrict__ rhs,
                                                         const double *__restrict__ rscale, const T *yo, T *yn) {
-    const double rs = rhs_scale(rscale);
+    const double rs = rhs_scale<SCALED>(rscale);
     const int c = blockIdx.x * ROWS_PER_WG + (threadIdx.x >> 2);
     if (c >= nch) return;
     const int r = threadIdx.x & 3;
@@ -561,14 +565,14 @@ __device__ __forceinline__ T from_quad_before(T v) {   // lane l of a DPP row of
 
 constexpr int CHAIN_LANES = 16, CHAIN_STEP = 16;   // lanes per chunk, rows taken at once
 
-template <typename T, bool ZERO_OUT, int CL>
+template <typename T, bool ZERO_OUT, bool SCALED, int CL>
 __global__ __launch_bounds__(WG) void k_fwd_chain(int n, int R, int nch, const int32_t *__restrict__ lrow,
                                                   const int32_t *__restrict__ lcol, const T *__restrict__ Lb,
                                                   const double *__restrict__ rhs, const double *__restrict__ rscale,
                                                   const T *yo, T *yn) {
     const int c = blockIdx.x * (WG / CHAIN_LANES) + threadIdx.x / CHAIN_LANES;
     if (c >= nch) return;
-    const double rs = rhs_scale(rscale);
+    const double rs = rhs_scale<SCALED>(rscale);
     const int r = threadIdx.x & 3, quad = (threadIdx.x >> 2) & 3;
     const int c0 = c * R, m = min(n, c0 + R) - c0;
     constexpr int G = CHAIN_STEP / 4;
@@ -805,25 +809,26 @@ abilu_status apply_t(const abilu_pattern *p, const T *LU, const T *Dinv, const d
         // chains of short rows: sixteen lanes per chunk
         const bool chain = by_rows && p->chains && p->side <= FV_CAP && abilu_rules::chain_apply(R, nch, p->side, sF == 8);
         const int cg = div_up(nch, WG / CHAIN_LANES);
+        auto fwd_as = [&](const T *yo, T *yn, auto zero, auto scaled) {
+            constexpr bool Z = decltype(zero)::value, SC = decltype(scaled)::value;
+            if (chain && p->side <= 2)
+                k_fwd_chain<T, Z, SC, 2><<<cg, WG, 0, s>>>(n, R, nch, lrow, lcol, Lb, r, rs, yo, yn);
+            else if (chain)
+                k_fwd_chain<T, Z, SC, FV_CAP><<<cg, WG, 0, s>>>(n, R, nch, lrow, lcol, Lb, r, rs, yo, yn);
+            else if (short_fwd)
+                k_fwd_chunk_short<T, Z, SC><<<g, WG, 0, s>>>(n, R, nch, p->rec, Lb, r, rs, yo, yn);
+            else if (by_rows)
+                k_fwd_chunk_rows<T, Z, SC><<<g, WG, 0, s>>>(n, R, nch, p->rec, lrow, lcol, Lb, r, rs, yo, yn);
+            else
+                k_fwd_chunk<T, Z, SC><<<g, WG, 0, s>>>(n, R, O[0], LP[0], LS[0], lrow, lcol, Lb, r, rs, yo, yn);
+        };
         auto fwd = [&](const T *yo, T *yn) {
-            if (chain) {
-                auto go = [&](auto cl) {
-                    constexpr int CL = decltype(cl)::value;
-                    if (!yo) k_fwd_chain<T, true, CL><<<cg, WG, 0, s>>>(n, R, nch, lrow, lcol, Lb, r, rs, yo, yn);
-                    else k_fwd_chain<T, false, CL><<<cg, WG, 0, s>>>(n, R, nch, lrow, lcol, Lb, r, rs, yo, yn);
-                };
-                if (p->side <= 2) go(std::integral_constant<int, 2>{});
-                else go(std::integral_constant<int, FV_CAP>{});
-            } else if (short_fwd) {
-                if (!yo) k_fwd_chunk_short<T, true><<<g, WG, 0, s>>>(n, R, nch, p->rec, Lb, r, rs, yo, yn);
-                else k_fwd_chunk_short<T, false><<<g, WG, 0, s>>>(n, R, nch, p->rec, Lb, r, rs, yo, yn);
-            } else if (by_rows) {
-                if (!yo) k_fwd_chunk_rows<T, true><<<g, WG, 0, s>>>(n, R, nch, p->rec, lrow, lcol, Lb, r, rs, yo, yn);
-                else k_fwd_chunk_rows<T, false><<<g, WG, 0, s>>>(n, R, nch, p->rec, lrow, lcol, Lb, r, rs, yo, yn);
-            } else {
-                if (!yo) k_fwd_chunk<T, true><<<g, WG, 0, s>>>(n, R, O[0], LP[0], LS[0], lrow, lcol, Lb, r, rs, yo, yn);
-                else k_fwd_chunk<T, false><<<g, WG, 0, s>>>(n, R, O[0], LP[0], LS[0], lrow, lcol, Lb, r, rs, yo, yn);
-            }
+            auto by_scale = [&](auto zero) {
+                if (rs) fwd_as(yo, yn, zero, std::true_type{});
+                else fwd_as(yo, yn, zero, std::false_type{});
+            };
+            if (!yo) by_scale(std::true_type{});
+            else by_scale(std::false_type{});
         };
         auto bwd = [&](const T *y, const T *zo, auto *zn) {
             using ZN = std::remove_pointer_t<decltype(zn)>;
