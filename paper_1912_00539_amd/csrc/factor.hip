@@ -28,6 +28,7 @@
 //        other chunks from the previous sweep, or as in memory), run a chunk per workgroup level
 //        by level or a chunk per quad row by row. ASYNC_SERIAL: every row in order by one quad.
 #include "kernels.h"
+#include "rules.h"
 
 using namespace abilu;
 using namespace abilu_dev;
@@ -542,9 +543,9 @@ __global__ __launch_bounds__(WG) void k_factor_chunk_far(FvPattern P, int R, con
 // The links: a quad per chunk walks its rows, L = A_{i,i-1} U_{i-1,i-1}^{-1}, the last term of the
 // diagonal block, its inverse. G rows' operands are fetched while the G rows before them are computed.
 // Bound by the chain of inverses, two waves on a SIMD (63 us on 500,000 line-ordered quads, FP32, chunks
-// of 16 rows). The sweep from A, both launches, against one launch that walked whole rows after the
-// initial inverses, us: 16 rows FP32 166 -> 160 and FP64 250 -> 213; 64 rows FP32 239 -> 184 and FP64
-// 418 -> 263; 10,057 quads, 16 rows, FP32 44 -> 24 and FP64 71 -> 33.
+// of 16 rows). The sweep from A, both launches, against one launch that walks whole rows after the
+// initial inverses, us: 16 rows FP32 166 -> 159 and FP64 250 -> 211; 64 rows FP32 239 -> 183 and FP64
+// 418 -> 262; 10,057 quads, 16 rows, FP32 44 -> 24 and FP64 72 -> 33 (chain_factor says where it does not pay).
 template <typename T, int G>
 __global__ __launch_bounds__(WG) void k_factor_chunk_links(int n, int ZL, int R, int nch,
                                                            const int32_t *__restrict__ rec, T *Xn, T *Dn,
@@ -762,6 +763,9 @@ abilu_status factor_t(const abilu_pattern *p, const double *A, T *LU, T *Dinv, i
         // Chains of rows with diagonal update sets: what does not depend on the chain first, then the
         // chain (no inverses of A's diagonal blocks are needed before the first sweep).
         const bool chains = p->chunk_runner == ABILU_CHUNK_BY_ROWS && p->chains && p->fv();
+        const auto links = [&](bool fromA) {
+            return chains && abilu_rules::chain_factor(p->chunk_rows, p->nchunks, p->side, sF == 8, fromA);
+        };
         auto chain_sweep = [&](bool fromA, const T *XO, const T *DO, T *Xn, T *Dn, const char *nm) -> abilu_status {
             const FvPattern P{n, ZL, p->rowptr, p->lrow, p->urow, p->lcol, p->ldiag, p->pkj, p->skj};
             // the records read of the links: two of their planes
@@ -784,7 +788,7 @@ abilu_status factor_t(const abilu_pattern *p, const double *A, T *LU, T *Dinv, i
             return ABILU_OK;
         };
         auto chunk_sweep = [&](bool fromA, const T *XO, const T *DO, T *Xn, T *Dn, const char *nm) -> abilu_status {
-            if (chains) return chain_sweep(fromA, XO, DO, Xn, Dn, nm);
+            if (links(fromA)) return chain_sweep(fromA, XO, DO, Xn, Dn, nm);
             ProfScope ps(NAME("factor_sweep", nm), s, bytes_sweep(z, sF, false, fromA) + sched);
             if (p->chunk_runner == ABILU_CHUNK_BY_ROWS) {
                 const int g = div_up(p->nchunks, ROWS_PER_WG);
@@ -825,7 +829,7 @@ abilu_status factor_t(const abilu_pattern *p, const double *A, T *LU, T *Dinv, i
         if (!cs) {
             int q0 = 0;
             if (init == ABILU_INIT_FROM_A) {
-                if (!chains && (st = init_dinv_A(Dinv)) != ABILU_OK) return st;
+                if (!links(true) && (st = init_dinv_A(Dinv)) != ABILU_OK) return st;
                 if ((st = chunk_sweep(true, (const T *)nullptr, Dinv, LU, Dinv, "_chunk_async_fromA")) != ABILU_OK)
                     return st;
                 q0 = 1;
@@ -839,7 +843,7 @@ abilu_status factor_t(const abilu_pattern *p, const double *A, T *LU, T *Dinv, i
         auto cX = [&](int q) { return ((nsw - q) % 2 == 0) ? LU : X1; };
         auto cD = [&](int q) { return ((nsw - q) % 2 == 0) ? Dinv : D1; };
         if (init == ABILU_INIT_FROM_A) {
-            if (!chains && (st = init_dinv_A(cD(0))) != ABILU_OK) return st;
+            if (!links(true) && (st = init_dinv_A(cD(0))) != ABILU_OK) return st;
             if ((st = chunk_sweep(true, (const T *)nullptr, cD(0), cX(1), cD(1), "_chunk_sync_fromA")) != ABILU_OK)
                 return st;
         } else {

@@ -22,4 +22,28 @@ inline bool chain_apply(int rows_per_chunk, int64_t nchunks, int side, bool f64)
     return rows_per_chunk >= rows || (rows_per_chunk >= 3 && nchunks <= 8192);
 }
 
+// Chunked factor sweep on chains of rows with diagonal update sets: all rows at once and then the links
+// (k_factor_chunk_far, k_factor_chunk_links) or whole rows, one after the other. The two launches write the
+// diagonal blocks and the links' L twice and read them back, but no chain of loads runs through the rows.
+// In double precision, and with three blocks a side, that pays almost always; in single precision with
+// two where the chunks are long or few. One sweep, whole rows / two launches:
+//   FP32, from A (with the initial inverses that whole rows need)
+//     500,000 line-ordered quads   1 row 124 / 173, 2 rows 152 / 160, 4 rows 154 / 155,
+//                                  5 rows 164 / 157, 6 rows 167 / 157, 8 rows 164 / 158, 64 rows 239 / 183
+//     120,000 quads   1 row 34 / 47, 4 rows 37 / 39, 6 rows 41 / 42, 8 rows 42 / 40, 16 rows 57 / 46
+//      10,057 quads   1 row 12 / 11, 4 rows 15 / 13
+//   FP32, from the previous iterate
+//     500,000 quads   1 row 195 / 261, 4 rows 231 / 254, 16 rows 241 / 259, 24 rows 272 / 264, 48 rows 254 / 260, 64 rows 293 / 275
+//     120,000 quads   4 rows 47 / 54, 8 rows 51 / 54, 10 rows (12,000 chunks) 56 / 56, 12 rows 59 / 58, 16 rows 67 / 60
+//      10,057 quads   1 row 14 / 18, 3 rows 16 / 18, 4 rows 18 / 18, 8 rows 28 / 21
+//     500,000 hexahedra (three a side)   1 row 313 / 329, 2 rows 330 / 323, 16 rows 348 / 322
+//   FP64, 500,000 quads   from A 1 row 233 / 208; from the previous iterate 1 row 365 / 376, 3 rows 374 / 369
+inline bool chain_factor(int rows_per_chunk, int64_t nchunks, int side, bool f64, bool from_a) {
+    const bool few = nchunks <= 12000;
+    if (side > 2) return rows_per_chunk >= 2 || (f64 && from_a);
+    if (f64) return from_a || rows_per_chunk >= 3;
+    if (from_a) return rows_per_chunk >= 8 || few || (rows_per_chunk >= 5 && nchunks > 50000);
+    return rows_per_chunk >= 24 || (rows_per_chunk >= 4 && few);
+}
+
 }  // namespace abilu_rules

@@ -11,5 +11,6 @@ using namespace abilu_rules;
 int main(int argc, char **argv) {
     auto a = [&](int q) { return q < argc ? std::atoll(argv[q]) : 0; };
     if (argc > 1 && !std::strcmp(argv[1], "chain_apply")) return chain_apply((int)a(2), a(3), (int)a(4), a(5) != 0);
+    if (argc > 1 && !std::strcmp(argv[1], "chain_factor")) return chain_factor((int)a(2), a(3), (int)a(4), a(5) != 0, a(6) != 0);
     return 2;
 }

@@ -1,6 +1,6 @@
-"""Chunked application on short chains, where the number of rows and of chunks decides between sixteen
-lanes and a quad per chunk: against the workgroup-per-chunk runner, bit for bit, on either side of each
-line."""
+"""Chunked sweeps on short chains, where the number of rows and of chunks decides between forms: in the
+application sixteen lanes or a quad per chunk, in the factor two launches or whole rows, sweep by sweep.
+Against the workgroup-per-chunk runner, bit for bit, on either side of each line."""
 import numpy as np
 import pytest
 
@@ -36,3 +36,27 @@ def test_short_chains(kind, prec):
                 s.work.fill_(255)
                 s.apply(s.b, v, nsw, "chunk_sync")
             assert torch.equal(*z), (R, nsw)
+
+
+@pytest.mark.parametrize("prec", ["f64", "f32"])
+@pytest.mark.parametrize("kind", ["aniso", "lines3"])
+def test_short_chains_factor(kind, prec):
+    import torch
+    from paper_1912_00539_amd.runtime import DeviceSystem
+    c = lines(kind)
+    rows = np.repeat(np.arange(c.n), np.diff(c.rowptr))
+    c.vals = c.vals.copy()
+    c.vals[np.flatnonzero(rows == c.colidx)[[5, c.n // 2]]] = 0.0   # singular blocks raise their flag once
+    a, b = DeviceSystem(c, prec=prec), DeviceSystem(c, prec=prec)
+    for R in (1, 2, 3, 4, 8, 24):
+        assert a.set_chunks(R, "rows")["runner"] == "rows" and b.set_chunks(R, "levels")["runner"] == "levels"
+        for nsw, init in ((1, "A"), (2, "A"), (3, "A"), (1, "LU"), (2, "LU")):
+            for s in (a, b):
+                if init == "A":
+                    s.LU.fill_(float("nan"))
+                    s.Dinv.fill_(float("nan"))
+                s.work.fill_(0)
+                s.factor(nsw, "chunk_sync", init=init)
+            assert torch.equal(a.LU.nan_to_num(), b.LU.nan_to_num()), (R, nsw, init)
+            assert torch.equal(a.Dinv.nan_to_num(), b.Dinv.nan_to_num()), (R, nsw, init)
+            assert a.flags(clear=True) == b.flags(clear=True), (R, nsw, init)

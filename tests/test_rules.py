@@ -35,3 +35,21 @@ CHAIN_APPLY = [(500000, 1, 2, 0, 177, 563), (500000, 2, 2, 0, 167, 287), (500000
 @pytest.mark.parametrize("n,R,side,f64,quad,sixteen", CHAIN_APPLY)
 def test_chain_apply(rules, n, R, side, f64, quad, sixteen):
     assert rules("chain_apply", R, -(-n // R), side, f64) == (sixteen < quad)
+
+
+# cells, rows per chunk, blocks a side, FP64, from A, time of a sweep: whole rows, two launches
+CHAIN_FACTOR = [(500000, 1, 2, 0, 1, 124, 173), (500000, 2, 2, 0, 1, 152, 160), (500000, 8, 2, 0, 1, 164, 158),
+                (500000, 6, 2, 0, 1, 167, 157), (120000, 6, 2, 0, 1, 39, 42),
+                (500000, 64, 2, 0, 1, 239, 183), (120000, 1, 2, 0, 1, 34, 47), (120000, 16, 2, 0, 1, 57, 46),
+                (10057, 4, 2, 0, 1, 15, 13), (10057, 16, 2, 0, 1, 44, 24), (500000, 1, 2, 0, 0, 195, 261),
+                (500000, 4, 2, 0, 0, 231, 254), (500000, 16, 2, 0, 0, 241, 259), (500000, 64, 2, 0, 0, 293, 275),
+                (500000, 128, 2, 0, 0, 461, 327), (120000, 4, 2, 0, 0, 47, 54), (120000, 16, 2, 0, 0, 67, 60),
+                (10057, 1, 2, 0, 0, 14, 18), (10057, 3, 2, 0, 0, 16, 18), (10057, 8, 2, 0, 0, 28, 21),
+                (500000, 1, 2, 1, 1, 233, 208), (500000, 16, 2, 1, 1, 250, 211), (10057, 1, 2, 1, 0, 17, 19),
+                (10057, 4, 2, 1, 0, 28, 23), (500000, 64, 2, 1, 0, 547, 420), (500000, 1, 3, 0, 0, 313, 329),
+                (500000, 5, 3, 0, 0, 370, 324), (64000, 1, 3, 1, 1, 44, 38), (64000, 3, 3, 0, 1, 34, 30)]
+
+
+@pytest.mark.parametrize("n,R,side,f64,from_a,whole,two", CHAIN_FACTOR)
+def test_chain_factor(rules, n, R, side, f64, from_a, whole, two):
+    assert rules("chain_factor", R, -(-n // R), side, f64, from_a) == (two < whole)
