@@ -42,6 +42,7 @@ struct abilu_pattern {
     bool symmetric = false;       // (i,j) in S_B implies (j,i) in S_B
     int32_t side = 4;             // most blocks of a row on one side of the diagonal: 2 (at most), 3, 4 (or more)
     bool local = false;           // most lower neighbours lie within PAIR_NEAR rows (pairs of sweeps)
+    bool near = false;            // within PAIR_NEAR3 rows
     // update sets of the diagonal blocks only, and rows that the factor sweeps' row-at-once form holds
     // (FV_CAP lower and upper blocks): finite-volume meshes of triangles and quads
     bool fv() const { return symmetric && npairs == nnzb_lower && side <= 3; }
@@ -97,6 +98,7 @@ constexpr int DIAG_ROWS = 512;
 // Triangles in random order, three sweeps, single / pairs, us: 62,486 FP64 23.5 / 24.9; 180,000 FP32 39.6 /
 // 54.5; 800,000 FP64 246 / 321; in Cuthill-McKee order 800,000 FP32 114 / 93, FP64 205 / 156.
 constexpr int PAIR_NEAR = 16384;
+constexpr int PAIR_NEAR3 = 2048;   // the distance for single precision and three blocks a side (rules.h)
 // words of a row's record of a pair of sweeps: S columns, S rows, S * S columns of those, in four lanes
 // (a row's word is its first block, shifted by two, and its count)
 template <int S>
@@ -236,7 +238,8 @@ abilu_status pattern_count_async(int32_t n, int64_t Z, const int32_t *rowptr, co
 bool pattern_sizes_ok(int32_t n, int64_t Z, const int64_t *sizes);   // sizes = {ZL, ZU, npairs}
 abilu_status pattern_count(int32_t n, int64_t Z, const int32_t *rowptr, const int32_t *colidx, int32_t *diag_pos,
                            int32_t *lrow, int32_t *urow, int32_t *pair_ptr, int32_t *done, void *scratch,
-                           int64_t *h_pinned, hipStream_t s, int64_t *ZL, int64_t *ZU, int64_t *npairs, int32_t *side, bool *local);
+                           int64_t *h_pinned, hipStream_t s, int64_t *ZL, int64_t *ZU, int64_t *npairs, int32_t *side, bool *local,
+                           bool *near);
 abilu_status pattern_fill(int32_t n, int64_t Z, int64_t ZL, int64_t ZU, int64_t npairs, const int32_t *rowptr,
                           const int32_t *colidx, const int32_t *diag_pos, const int32_t *lrow, const int32_t *urow,
                           int32_t *lcol, int32_t *ldiag, int32_t *ucol, int32_t *pik, int32_t *pkj, int32_t *sik, int32_t *skj,

@@ -39,30 +39,34 @@ __global__ __launch_bounds__(PAT_ROWS) void k_pat_fill(int n, int ZL, const int3
     pat_fill_body(blockIdx.x, n, ZL, rowptr, colidx, diag_pos, lrow, urow, ptr, pik, pkj, sik, skj);
 }
 
-// also pat_side_body, and over a sample of 256 workgroups at most the lower blocks farther than PAIR_NEAR
-// rows and all of them: more[2], more[3] (the sample bounds the additions to one address)
-__global__ void k_pat_tri_counts(int n, const int32_t *__restrict__ rowptr, const int32_t *__restrict__ colidx,
-                                 const int32_t *__restrict__ diag_pos, int64_t *__restrict__ nl,
-                                 int64_t *__restrict__ nu, unsigned *more) {
+// also pat_side_body, and over a sample of 64 workgroups at most a tally of lower blocks: all of them, those
+// farther than PAIR_NEAR rows and those farther than PAIR_NEAR3, in 21 bits each (TALLY_*; at most 64 of a
+// row) of the 64-bit word at more + 2. One addition a workgroup: additions to one address follow each other
+// at 15 ns, and three of every wave of 256 workgroups took 45 us.
+constexpr int TALLY_FAR = 21, TALLY_FAR3 = 42, TALLY_ROW = 64;
+constexpr unsigned long long TALLY_MASK = (1ull << 21) - 1;
+__global__ __launch_bounds__(256) void k_pat_tri_counts(int n, const int32_t *__restrict__ rowptr,
+                                                        const int32_t *__restrict__ colidx,
+                                                        const int32_t *__restrict__ diag_pos, int64_t *__restrict__ nl,
+                                                        int64_t *__restrict__ nu, unsigned *more) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     pat_tri_counts_body(blockIdx.x, n, rowptr, diag_pos, nl, nu);
     pat_side_body(i, n, rowptr, diag_pos, more);
-    if (n <= PAIR_NEAR || blockIdx.x % (gridDim.x / 256 + 1) != 0) return;
-    int far = 0, all = 0;
+    if (n <= PAIR_NEAR3 || blockIdx.x % (gridDim.x / 64 + 1) != 0) return;
+    __shared__ unsigned long long sh[4];
+    unsigned long long tally = 0;
     if (i < n) {
-        for (int e = rowptr[i]; e < diag_pos[i]; ++e) {
-            ++all;
-            far += i - colidx[e] > PAIR_NEAR;
+        const int b0 = rowptr[i], b1 = min(diag_pos[i], b0 + TALLY_ROW);
+        for (int e = b0; e < b1; ++e) {
+            const int away = i - colidx[e];
+            tally += 1ull + ((unsigned long long)(away > PAIR_NEAR) << TALLY_FAR) +
+                     ((unsigned long long)(away > PAIR_NEAR3) << TALLY_FAR3);
         }
     }
-    for (int o = 32; o > 0; o >>= 1) {
-        far += __shfl_xor(far, o, 64);
-        all += __shfl_xor(all, o, 64);
-    }
-    if ((threadIdx.x & 63) == 0 && all) {
-        atomicAdd(more + 2, (unsigned)far);
-        atomicAdd(more + 3, (unsigned)all);
-    }
+    for (int o = 32; o > 0; o >>= 1) tally += __shfl_xor(tally, o, 64);
+    if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = tally;
+    __syncthreads();
+    if (threadIdx.x == 0) atomicAdd((unsigned long long *)(more + 2), (sh[0] + sh[1]) + (sh[2] + sh[3]));
 }
 
 __global__ void k_pat_tri_cols(int n, const int32_t *__restrict__ rowptr, const int32_t *__restrict__ colidx,
@@ -218,7 +222,8 @@ bool pattern_sizes_ok(int32_t n, int64_t Z, const int64_t *sizes) {
 // Blocking stage 1 (two stream syncs).
 abilu_status pattern_count(int32_t n, int64_t Z, const int32_t *rowptr, const int32_t *colidx, int32_t *diag_pos,
                            int32_t *lrow, int32_t *urow, int32_t *pair_ptr, int32_t *done, void *scratch,
-                           int64_t *h_pinned, hipStream_t s, int64_t *ZL, int64_t *ZU, int64_t *npairs, int32_t *side, bool *local) {
+                           int64_t *h_pinned, hipStream_t s, int64_t *ZL, int64_t *ZU, int64_t *npairs, int32_t *side, bool *local,
+                           bool *near) {
     abilu_status st = pattern_validate_async(n, Z, rowptr, colidx, diag_pos, done, scratch, (unsigned *)h_pinned, s);
     if (st != ABILU_OK) return st;
     if (!hip_ok(hipStreamSynchronize(s), "pattern validation sync")) return ABILU_EDEVICE;
@@ -231,7 +236,9 @@ abilu_status pattern_count(int32_t n, int64_t Z, const int32_t *rowptr, const in
     *npairs = h_pinned[2];
     const unsigned *words = (const unsigned *)(h_pinned + 3);
     *side = side_class(words);
-    *local = n <= PAIR_NEAR || 4ull * words[2] <= words[3];
+    const unsigned long long tally = (unsigned long long)h_pinned[4], all = tally & TALLY_MASK;
+    *local = n <= PAIR_NEAR || 4 * ((tally >> TALLY_FAR) & TALLY_MASK) <= all;
+    *near = n <= PAIR_NEAR3 || 4 * (tally >> TALLY_FAR3) <= all;
     return pattern_sizes_ok(n, Z, h_pinned) ? ABILU_OK : ABILU_EPATTERN;
 }
 
@@ -322,7 +329,7 @@ extern "C" abilu_status abilu_build_pattern(int32_t nbrows, const int32_t *d_row
         CK(hipMemcpyAsync(p->rowptr, d_rowptr, sizeof(int32_t) * (n + 1), hipMemcpyDeviceToDevice, s));
         if (Z > 0) CK(hipMemcpyAsync(p->colidx, d_colidx, sizeof(int32_t) * Z, hipMemcpyDeviceToDevice, s));
         st = pattern_count(n, Z, p->rowptr, p->colidx, p->diag_pos, p->lrow, p->urow, p->pair_ptr, p->done, scratch,
-                           (int64_t *)p->pinned, s, &ZL, &ZU, &npairs, &p->side, &p->local);
+                           (int64_t *)p->pinned, s, &ZL, &ZU, &npairs, &p->side, &p->local, &p->near);
         if (st != ABILU_OK) goto fail;
         p->nnzb_lower = ZL;
         p->nnzb_upper = ZU;

@@ -6,6 +6,25 @@
 
 namespace abilu_rules {
 
+// Application sweeps two at a time: rows of at most three blocks a side (a row of c blocks reads c^2 more:
+// on the nine-point grid's rows of four that is more than the sweep saves), from three sweeps on, where
+// most neighbours are near enough to be read again out of an L2 (`local`; `near` is the narrower distance).
+// In single precision, where nearly every row has three blocks a side, the second reading and the longer
+// records weigh as much as the sweep saved once the rows of an XCD and their neighbours' pass its L2.
+// Three sweeps each way, single / pairs, hexahedra in planes of k x k cells:
+//   FP32   64,000 cells k = 40 21.7 / 16.4, k = 120 (72,000) 22.7 / 21.3; 200,000 cells k = 100 48.8 / 49.0;
+//          700,000 cells k = 20 156 / 149, k = 40 158 / 156, k = 50 157 / 157, k = 70 158 / 166, k = 100 160 / 177,
+//          k = 120 161 / 186
+//   FP64   700,000 cells k = 20 284 / 230, k = 70 290 / 257, k = 120 298 / 276
+//   600,000 triangles in random order within 2,000 and 16,000 cells (up to three a side, 1.5 on average)
+//          FP32 108 / 80 and 114 / 80, FP64 173 / 125 and 175 / 127
+// `local` ends where quads lose (neighbours d rows away, 700,000 cells, FP32): d = 4,000 113 / 95,
+// 12,000 114 / 107, 16,000 111 / 110 (150,000 cells 26.6 / 27.9); in FP64 there 207 / 175.
+inline bool sweep_pairs(int nsweeps, int side, bool local, bool near, int64_t n, int64_t lower_blocks, bool f64) {
+    if (nsweeps < 3 || side > 3 || !local) return false;
+    return f64 || near || n <= 131072 || 2 * lower_blocks <= 5 * n;
+}
+
 // Chunked application on chunks that are chains: sixteen lanes per chunk (k_fwd_chain, k_bwd_chain) or a
 // quad per chunk. The sixteen lanes hold sixteen rows at a time, so on shorter chunks most of them repeat
 // the last row: below five rows (FP64: seven, and ten with three blocks a side) the quad is faster, unless

@@ -53,3 +53,20 @@ CHAIN_FACTOR = [(500000, 1, 2, 0, 1, 124, 173), (500000, 2, 2, 0, 1, 152, 160), 
 @pytest.mark.parametrize("n,R,side,f64,from_a,whole,two", CHAIN_FACTOR)
 def test_chain_factor(rules, n, R, side, f64, from_a, whole, two):
     assert rules("chain_factor", R, -(-n // R), side, f64, from_a) == (two < whole)
+
+
+# cells, lower blocks, blocks a side, farthest neighbour, FP64, time of three sweeps each way: single, pairs
+SWEEP_PAIRS = [(64000, 187200, 3, 1600, 0, 21.7, 16.4), (72000, 200000, 3, 14400, 0, 22.7, 21.3),
+               (700000, 2062000, 3, 400, 0, 156, 149), (700700, 2085000, 3, 4900, 0, 158, 166),
+               (700000, 2079000, 3, 10000, 0, 160, 177), (720000, 2140000, 3, 14400, 0, 161, 186),
+               (700000, 2062000, 3, 400, 1, 284, 230), (720000, 2140000, 3, 14400, 1, 298, 276),
+               (600000, 900000, 3, 3000, 0, 108, 80), (700000, 1400000, 2, 4000, 0, 113, 95),
+               (700000, 1400000, 2, 12000, 0, 114, 107), (700000, 1400000, 2, 12000, 1, 208, 175),
+               (180000, 270000, 3, 180000, 0, 39.6, 54.5), (800000, 1200000, 3, 800000, 1, 246, 321)]
+
+
+@pytest.mark.parametrize("n,ZL,side,far,f64,single,pairs", SWEEP_PAIRS)
+def test_sweep_pairs(rules, n, ZL, side, far, f64, single, pairs):
+    args = side, far <= 16384, far <= 2048, n, ZL, f64
+    assert rules("sweep_pairs", 3, *args) == (pairs < single)
+    assert not rules("sweep_pairs", 2, *args) and not rules("sweep_pairs", 3, 4, *args[1:])
