@@ -684,7 +684,7 @@ void launch_sweep(const abilu_pattern *p, int grid, hipStream_t s, const double 
         }
     }
     if constexpr (!LA)
-        k_factor_sweep<T, LA, UA, DA><<<grid, WG, 0, s>>>(
+        k_factor_sweep<T, LA, UA, DA><<<grid, WG, DA && abilu_rules::crowded_sweep(p->n, p->nnzb) ? abilu_rules::CROWDED_LDS : 0, s>>>(
             p->n, (int)p->nnzb_lower, p->rowptr, p->colidx, p->diag_pos, p->lrow, p->urow, p->pair_ptr, p->pik, p->pkj,
             p->sik, p->skj, A, XL, XU, Dp, Xn, Dn, flags, p->symmetric ? 1 : 0);
 }

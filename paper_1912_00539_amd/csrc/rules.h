@@ -65,4 +65,14 @@ inline bool chain_factor(int rows_per_chunk, int64_t nchunks, int side, bool f64
     return rows_per_chunk >= 24 || (rows_per_chunk >= 4 && few);
 }
 
+// Workgroups of the asynchronous first sweep from A that a compute unit takes at once, bounded (by LDS
+// that the launch asks for and nobody uses) where rows are long and A is larger than the 256 MB cache that
+// all XCDs share: each row in flight brings some 27 blocks and as many rows of others, and with four or more
+// of these workgroups on every unit the rows push each other's blocks out. One sweep, as many as fit / three:
+//   27-point rows   100,000 cells (333 MB) FP64 642 / 558, FP32 699 / 480; 294,000 FP64 1,885 / 1,602, FP32 2,064 / 1,376
+//                    57,600 cells (186 MB) FP64 346 / 418, FP32 294 / 369
+//   rows of 7       560,000 cells FP64 385 / 432, FP32 295 / 365
+constexpr int CROWDED_LDS = 53000;   // bytes of 160 KB: three workgroups
+inline bool crowded_sweep(int64_t n, int64_t blocks) { return blocks >= 18 * n && 128 * blocks > ((int64_t)256 << 20); }
+
 }  // namespace abilu_rules

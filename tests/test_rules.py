@@ -70,3 +70,13 @@ def test_sweep_pairs(rules, n, ZL, side, far, f64, single, pairs):
     args = side, far <= 16384, far <= 2048, n, ZL, f64
     assert rules("sweep_pairs", 3, *args) == (pairs < single)
     assert not rules("sweep_pairs", 2, *args) and not rules("sweep_pairs", 3, 4, *args[1:])
+
+
+# cells, blocks, time of an asynchronous FP64 sweep from A: as many workgroups as fit, three a compute unit
+CROWDED_SWEEP = [(57600, 1460000, 346, 418), (100000, 2600000, 642, 558), (180000, 4700000, 1133, 997),
+                 (294000, 7700000, 1885, 1602), (560000, 3900000, 385, 432), (700000, 4800000, 400, 442)]
+
+
+@pytest.mark.parametrize("n,Z,fit,three", CROWDED_SWEEP)
+def test_crowded_sweep(rules, n, Z, fit, three):
+    assert rules("crowded_sweep", n, Z) == (three < fit)
