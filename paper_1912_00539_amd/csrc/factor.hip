@@ -669,10 +669,10 @@ void launch_sweep(const abilu_pattern *p, int grid, hipStream_t s, const double 
         else if constexpr (!UA) go(std::integral_constant<int, L_FROM_PREV>{});
         return;
     }
-    // Elsewhere, between two buffers: a quad per block; in place: a quad per row, since the asynchronous
+    // Elsewhere, between two buffers: mostly a quad per block; in place: a quad per row, since the asynchronous
     // sweep takes its row's own lower blocks as this sweep has just made them.
     if constexpr (LA == UA) {
-        if (XL != Xn) {
+        if (XL != Xn && abilu_rules::sweep_by_blocks(p->n, p->nnzb, p->nnzb_lower, p->npairs, p->near, sizeof(T) == 8, UA)) {
             const auto eighth = [](int64_t blocks) { return div_up(div_up(blocks, ROWS_PER_WG), 8); };
             const int64_t ZU = p->nnzb - p->nnzb_lower - p->n;
             const int slabs = max(1, eighth(p->n) / 16);
@@ -683,8 +683,8 @@ void launch_sweep(const abilu_pattern *p, int grid, hipStream_t s, const double 
             return;
         }
     }
-    if constexpr (!LA)
-        k_factor_sweep<T, LA, UA, DA><<<grid, WG, DA && abilu_rules::crowded_sweep(p->n, p->nnzb) ? abilu_rules::CROWDED_LDS : 0, s>>>(
+    if constexpr (!LA || sizeof(T) == 4)   // from A in double precision always by blocks
+        k_factor_sweep<T, LA, UA, DA><<<grid, WG, DA && !LA && abilu_rules::crowded_sweep(p->n, p->nnzb) ? abilu_rules::CROWDED_LDS : 0, s>>>(
             p->n, (int)p->nnzb_lower, p->rowptr, p->colidx, p->diag_pos, p->lrow, p->urow, p->pair_ptr, p->pik, p->pkj,
             p->sik, p->skj, A, XL, XU, Dp, Xn, Dn, flags, p->symmetric ? 1 : 0);
 }

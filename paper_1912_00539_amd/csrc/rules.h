@@ -65,6 +65,24 @@ inline bool chain_factor(int rows_per_chunk, int64_t nchunks, int side, bool f64
     return rows_per_chunk >= 24 || (rows_per_chunk >= 4 && few);
 }
 
+// Synchronous factor sweep with a quad per block, or with a quad per row, on patterns whose rows do not fit
+// the row-at-once form. With update sets off the diagonal the blocks win by up to half. With the diagonal
+// ones alone only the diagonal blocks have pairs, and on large patterns with far neighbours a row's blocks,
+// read together, pay for a row's serial chain. One sweep, rows / blocks:
+//   from A, FP32   hexahedra in random order 396,800 cells (2.7 million blocks) 175 / 176, 550,000 (3.8) 240 / 254,
+//                  700,000 306 / 335, shuffled within ten cells 400,000 152 / 141, 700,000 256 / 283;
+//                  quads in random order 550,000 (2.7) 174 / 172, 800,000 (4.0) 251 / 265;
+//                  shuffled within eight cells (near) 800,000 228 / 162
+//   from A, FP64   700,000 hexahedra in random order 474 / 428, 800,000 quads 409 / 349
+//   from the previous iterate, FP64   hexahedra in random order 150,000 157 / 158, 249,900 253 / 260,
+//                  700,000 679 / 722; quads 250,000 189 / 191, 800,000 571 / 604; near 800,000 554 / 548
+//   from the previous iterate, FP32   700,000 hexahedra 450 / 460, 550,000 359 / 362, shuffled within ten 426 / 414
+inline bool sweep_by_blocks(int64_t n, int64_t blocks, int64_t lower_blocks, int64_t pairs, bool near, bool f64,
+                            bool from_a) {
+    if (pairs > lower_blocks || near || f64 == from_a) return true;
+    return f64 ? n < 200000 : blocks < 3600000;
+}
+
 // Workgroups of the asynchronous first sweep from A that a compute unit takes at once, bounded (by LDS
 // that the launch asks for and nobody uses) where rows are long and A is larger than the 256 MB cache that
 // all XCDs share: each row in flight brings some 27 blocks and as many rows of others, and with four or more

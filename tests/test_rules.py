@@ -80,3 +80,20 @@ CROWDED_SWEEP = [(57600, 1460000, 346, 418), (100000, 2600000, 642, 558), (18000
 @pytest.mark.parametrize("n,Z,fit,three", CROWDED_SWEEP)
 def test_crowded_sweep(rules, n, Z, fit, three):
     assert rules("crowded_sweep", n, Z) == (three < fit)
+
+
+# cells, blocks, neighbours near, FP64, from A, time of a synchronous sweep: a quad per row, per block
+SWEEP_BY_BLOCKS = [(400000, 2760000, 0, 0, 1, 152, 141), (550000, 3810000, 0, 0, 1, 240, 254),
+                   (700000, 4840000, 0, 0, 1, 306, 335), (800000, 3996000, 0, 0, 1, 251, 265),
+                   (800000, 3996000, 1, 0, 1, 228, 162), (700000, 4840000, 0, 1, 1, 474, 428),
+                   (150000, 1030000, 0, 1, 1, 90, 78), (249900, 1720000, 0, 1, 0, 253, 260),
+                   (700000, 4840000, 0, 1, 0, 679, 722), (800000, 3996000, 0, 1, 0, 571, 604),
+                   (90000, 448800, 0, 1, 0, 60, 58), (800000, 3996000, 1, 1, 0, 554, 548),
+                   (249900, 1720000, 0, 0, 0, 165, 160)]
+
+
+@pytest.mark.parametrize("n,Z,near,f64,from_a,row,block", SWEEP_BY_BLOCKS)
+def test_sweep_by_blocks(rules, n, Z, near, f64, from_a, row, block):
+    ZL = (Z - n) // 2
+    assert rules("sweep_by_blocks", n, Z, ZL, ZL, near, f64, from_a) == (block < row)
+    assert rules("sweep_by_blocks", n, Z, ZL, ZL + 1, near, f64, from_a)   # update sets off the diagonal
