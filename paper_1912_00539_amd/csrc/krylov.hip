@@ -13,6 +13,7 @@
 #include <cstring>
 
 #include "kernels.h"
+#include "rules.h"
 
 using namespace abilu;
 using namespace abilu_dev;
@@ -59,7 +60,9 @@ __global__ __launch_bounds__(WG) void k_reduce_step(KPtrs P, int nb, const int *
 // ---- systems of at most FOLD_NB vector workgroups (all of the smaller tile): the dot and update
 // kernels reduce their own partials in their last workgroup and run the step there, one launch
 // instead of two, with the sums of the two-launch form bit for bit. Beyond FOLD_NB one workgroup
-// would add more than four entries per lane and column (at 4 million cells, 31).
+// would add more than four entries per lane and column (at 4 million cells, 31). Solves of triangles to
+// 1e-10, FP32, two launches / folded, us: 319 workgroups 433 / 428, 400 534 / 527, 512 576 / 579; with a limit
+// of 1,024 instead, 600 638 / 651, 704 (180,000 cells) 684 / 703, 1,024 913 / 922.
 constexpr int FOLD_VE = 4;
 static_assert((int64_t)FOLD_NB * WG * FOLD_VE < VEC_SMALL, "folded systems have the smaller tile");
 
@@ -440,9 +443,7 @@ extern "C" abilu_status fgmres_solve(const abilu_pattern *p, const double *d_A, 
     // The status of the launches so far (the start's, a cycle's or an Arnoldi step's), not yet read.
     // An Arnoldi step's application may begin before: it stops at the first launch after which the
     // status says that it is not needed, and has then written scratch vectors only (or a z_k that
-    // nothing reads). Ahead of the status at most `limit` kernels are launched: enough to cover the
-    // 6-8 us between the status being written and the next launch arriving, and none where a needless
-    // sweep costs more.
+    // nothing reads). Ahead of the status at most `limit` kernels are launched.
     int pass2_begin = 0, pass2_end = 0;
     const auto decide = [&](int kind, const Status &now) {   // takes the status in; true: stop
         if (kind == STEP) {
@@ -471,7 +472,7 @@ extern "C" abilu_status fgmres_solve(const abilu_pattern *p, const double *d_A, 
     };
     Pending<decltype(decide)> pending(c, decide);
     const bool gated = (mode == ABILU_SYNC || mode == ABILU_ASYNC) && apply_sweeps >= 2;   // modes that ask the gate
-    pending.limit = !gated ? 0 : p->n <= 60000 ? 2 : p->n <= 400000 ? 1 : 0;
+    pending.limit = gated ? abilu_rules::launches_ahead(p->nnzb) : 0;
     pending.expect(START);
     if (pending.limit == 0 || maxit == 0) pending.read();
 

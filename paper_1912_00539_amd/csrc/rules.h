@@ -93,4 +93,18 @@ inline bool sweep_by_blocks(int64_t n, int64_t blocks, int64_t lower_blocks, int
 constexpr int CROWDED_LDS = 53000;   // bytes of 160 KB: three workgroups
 inline bool crowded_sweep(int64_t n, int64_t blocks) { return blocks >= 18 * n && 128 * blocks > ((int64_t)256 << 20); }
 
+// Launches of an application that FGMRES makes ahead of the status which decides on it. They cover the 6-8 us
+// between the status being written and the next launch arriving; where the solve stops they were for
+// nothing, which costs the more the more blocks a sweep reads. A solve to 1e-10 (1e-2, two iterations or
+// one), us, with none / one / two ahead:
+//     39,478 blocks (9,940 triangles, FP32)   298 / 295 / 286
+//    119,110 blocks (29,900 triangles)   382 / 379 / 378; FP64 451 / 459 / 448
+//    191,380 blocks (48,000 triangles)   392 / 368 / 371 (150 / 148 / 152)
+//  1,198,450 blocks (300,000 triangles)   1,070 / 1,041 / 1,063 (305 / 305 / 325)
+//  1,475,944 blocks (57,600 27-point rows)   560 / 546 / 555 (208 / 207 / 219)
+//  1,598,200 blocks (400,000 triangles)   1,365 / 1,349 / 1,379 (379 / 391 / 419)
+//  2,797,600 blocks (700,000 triangles)   2,170 / 2,168 / 2,217 (591 / 621 / 666)
+//  4,689,232 blocks (180,000 27-point rows)   1,454 / 1,468 / 1,509 (499 / 529 / 570)
+inline int launches_ahead(int64_t blocks) { return blocks <= 150000 ? 2 : blocks <= 1600000 ? 1 : 0; }
+
 }  // namespace abilu_rules

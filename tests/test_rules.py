@@ -97,3 +97,15 @@ def test_sweep_by_blocks(rules, n, Z, near, f64, from_a, row, block):
     ZL = (Z - n) // 2
     assert rules("sweep_by_blocks", n, Z, ZL, ZL, near, f64, from_a) == (block < row)
     assert rules("sweep_by_blocks", n, Z, ZL, ZL + 1, near, f64, from_a)   # update sets off the diagonal
+
+
+# blocks, times of a solve to 1e-10 and of one of two iterations or one: none, one, two launches ahead
+AHEAD = [(39478, 298, 295, 286), (191380, 392, 368, 371), (191380, 150, 148, 152), (718800, 716, 678, 689),
+         (850353, 616, 590, 595), (1248000, 923, 896, 920), (2797600, 591, 621, 666), (4689232, 1454, 1468, 1509),
+         (4689232, 499, 529, 570)]
+
+
+@pytest.mark.parametrize("blocks,none,one,two", AHEAD)
+def test_launches_ahead(rules, blocks, none, one, two):
+    best = min((none, 0), (one, 1), (two, 2))[1]
+    assert rules("launches_ahead", blocks, best)
