@@ -289,8 +289,8 @@ struct Gate {
 abilu_status apply_impl(const abilu_pattern *p, const void *LU, const void *Dinv, abilu_prec prec,
                         const double *r, const double *rscale, double *z, int nsweeps, abilu_mode mode, char *work,
                         const Workspace &W, hipStream_t s, Gate *gate = nullptr);
-// Whether the last kernel of apply_impl(nsweeps, mode) ran its workgroups in descending row order.
-bool apply_ends_descending(int nsweeps, abilu_mode mode);
+// Whether the last kernel of apply_impl runs its workgroups in descending row order.
+bool apply_ends_descending(const abilu_pattern *p, abilu_prec prec, int nsweeps, abilu_mode mode);
 // desc: run the workgroups in descending row order (the result does not depend on it; a kernel
 // that starts on the rows its predecessor touched last finds them in the Infinity Cache).
 abilu_status spmv_impl(const abilu_pattern *p, const double *A, const double *x, double *y,

@@ -741,6 +741,10 @@ const char *tname<float>() { return "f32"; }
 template <>
 const char *tname<double>() { return "f64"; }
 
+bool in_pairs(const abilu_pattern *p, int nsweeps, bool f64) {
+    return abilu_rules::sweep_pairs(nsweeps, p->side, p->local, p->near, p->n, p->nnzb_lower, f64);
+}
+
 template <typename T>
 abilu_status apply_t(const abilu_pattern *p, const T *LU, const T *Dinv, const double *r, const double *rs, double *z, int nsw,
                      abilu_mode mode, char *work, const Workspace &W, hipStream_t s, Gate *gate) {
@@ -887,7 +891,7 @@ abilu_status apply_t(const abilu_pattern *p, const T *LU, const T *Dinv, const d
         return ABILU_OK;
     }
     // Sweeps two at a time: faster by 15-40% from 2 thousand to 4 million cells where the rule says so.
-    const bool pairs = abilu_rules::sweep_pairs(nsw, p->side, p->local, p->near, n, p->nnzb_lower, sF == 8);
+    const bool pairs = in_pairs(p, nsw, sF == 8);
     const bool two = p->side <= 2;
     const int pgrid = xcd_grid(div_up(n, ROWS_PER_WG));
     // forward sweeps 2..nsw (sweep 1: y = r itself); the last also emits za = Dinv y
@@ -931,9 +935,9 @@ abilu_status apply_t(const abilu_pattern *p, const T *LU, const T *Dinv, const d
     // synchronous sweep's result does not depend on the order; an asynchronous one reads values of
     // the same sweep in either order, and descending is the order of back substitution.
     T *zprev = za;
-    for (int q = 2; q <= nsw; ++q) {
+    for (int q = 2, launch = 0; q <= nsw; ++q, ++launch) {
         const bool pair = pairs && q + 1 <= nsw;
-        const int desc = (q % 2 == 0) ? 1 : 0;
+        const int desc = abilu_rules::backward_descends(launch) ? 1 : 0;
         if (pair) ++q;
         const bool last = (q == nsw);
         // ASYNC, last sweep descending: an in-place FP32 copy of z lets the rows updated later in
@@ -991,9 +995,9 @@ abilu_status apply_impl(const abilu_pattern *p, const void *LU, const void *Dinv
     return apply_t<double>(p, (const double *)LU, (const double *)Dinv, r, rscale, z, nsweeps, mode, work, W, s, gate);
 }
 
-bool apply_ends_descending(int nsweeps, abilu_mode mode) {
-    // the last backward sweep q = nsweeps >= 2 of the sweep modes runs descending for even q
-    return (mode == ABILU_SYNC || mode == ABILU_ASYNC) && nsweeps >= 2 && nsweeps % 2 == 0;
+bool apply_ends_descending(const abilu_pattern *p, abilu_prec prec, int nsweeps, abilu_mode mode) {
+    return (mode == ABILU_SYNC || mode == ABILU_ASYNC) &&
+           abilu_rules::apply_ends_descending(nsweeps, in_pairs(p, nsweeps, prec == ABILU_F64));
 }
 
 abilu_status spmv_impl(const abilu_pattern *p, const double *A, const double *x, double *y, const double *b,

@@ -492,7 +492,7 @@ extern "C" abilu_status fgmres_solve(const abilu_pattern *p, const double *d_A, 
                 prof_cancel_bytes(apply_begin, prof_mark());   // begun for nothing
                 break;
             }
-            if ((st = spmv_impl(p, d_A, zk, w, nullptr, !apply_ends_descending(apply_sweeps, mode), c.s)) !=
+            if ((st = spmv_impl(p, d_A, zk, w, nullptr, !apply_ends_descending(p, prec, apply_sweeps, mode), c.s)) !=
                 ABILU_OK)
                 return st;
             // Gram-Schmidt pass 1: dots, H(0:k,k); the update, with the second pass's dots and the

@@ -25,6 +25,16 @@ inline bool sweep_pairs(int nsweeps, int side, bool local, bool near, int64_t n,
     return f64 || near || n <= 131072 || 2 * lower_blocks <= 5 * n;
 }
 
+// Launches of the backward sweeps 2 .. nsweeps, alone or two at a time. The first runs descending, behind the
+// ascending forward sweeps, and each then opposite to the one before, so that it starts on the rows touched
+// last; the Arnoldi SpMV behind an application runs opposite to its last launch.
+inline int backward_launches(int nsweeps, bool pairs) { return nsweeps < 2 ? 0 : pairs ? nsweeps / 2 : nsweeps - 1; }
+inline bool backward_descends(int launch) { return launch % 2 == 0; }
+inline bool apply_ends_descending(int nsweeps, bool pairs) {
+    const int launches = backward_launches(nsweeps, pairs);
+    return launches > 0 && backward_descends(launches - 1);
+}
+
 // Chunked application on chunks that are chains: sixteen lanes per chunk (k_fwd_chain, k_bwd_chain) or a
 // quad per chunk. The sixteen lanes hold sixteen rows at a time, so on shorter chunks most of them repeat
 // the last row: below five rows (FP64: seven, and ten with three blocks a side) the quad is faster, unless

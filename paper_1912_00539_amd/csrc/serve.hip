@@ -27,6 +27,7 @@
 #include "abilu_gen.h"
 #include "abilu_serve.h"
 #include "kernels.h"
+#include "rules.h"
 #include "setup_kernels.h"
 
 using namespace abilu;
@@ -964,9 +965,11 @@ abilu_status run_group(abilu_server *s, Group &G, hipStream_t st) {
         CKL();
         return ABILU_OK;
     };
-    // the Arnoldi SpMV runs opposite to the last backward sweep (descending for even q), the
-    // residual SpMV descending
-    const bool spmv_desc = !(nsw >= 2 && nsw % 2 == 0);
+    // Three sweeps are one pair each way, which needs no second vector; with more, asynchronous
+    // requests, which have none, take their sweeps one at a time.
+    const bool pairs = fv && nsw >= 3 && (sync || nsw == 3);
+    // the Arnoldi SpMV runs opposite to the last backward launch, the residual SpMV descending
+    const bool spmv_desc = !abilu_rules::apply_ends_descending(nsw, pairs);
     auto spmv = [&](bool resid, int xin, int yout) -> abilu_status {
         ProfScope ps(resid ? "serve_spmv_resid" : "serve_spmv", st,
                      B([&](const Sizes &z, const Req &) { return bytes_spmv(z, resid); }));
@@ -1048,9 +1051,6 @@ abilu_status run_group(abilu_server *s, Group &G, hipStream_t st) {
         } else {
             // sweep 1 forward is y = v_k and sweep 1 backward z = Dinv y (emitted by the last forward
             // sweep); ASYNC sweeps 2.. update in place, SYNC sweeps and pairs of sweeps ping-pong.
-            // Three sweeps are one pair each way, which needs no second vector; with more, asynchronous
-            // requests, which have none, take their sweeps one at a time
-            const bool pairs = fv && nsw >= 3 && (sync || nsw == 3);
             int yprev = R_VK, ycur = R_YA;
             for (int q = 2; q <= nsw; ++q) {
                 const bool from_r = q == 2, pair = pairs && q + 1 <= nsw;
@@ -1062,9 +1062,9 @@ abilu_status run_group(abilu_server *s, Group &G, hipStream_t st) {
                 yprev = ycur;
             }
             int zprev = R_ZA;
-            for (int q = 2; q <= nsw; ++q) {
+            for (int q = 2, launch = 0; q <= nsw; ++q, ++launch) {
                 const bool pair = pairs && q + 1 <= nsw;
-                const int desc = q % 2 == 0;
+                const int desc = abilu_rules::backward_descends(launch);
                 if (pair) ++q;
                 const bool last = q == nsw;
                 const bool dual = last && !sync && desc && !pairs;   // the in-place copy serves only a descending sweep

@@ -109,3 +109,15 @@ AHEAD = [(39478, 298, 295, 286), (191380, 392, 368, 371), (191380, 150, 148, 152
 def test_launches_ahead(rules, blocks, none, one, two):
     best = min((none, 0), (one, 1), (two, 2))[1]
     assert rules("launches_ahead", blocks, best)
+
+
+@pytest.mark.parametrize("pairs", [False, True])
+@pytest.mark.parametrize("nsw", [0, 1, 2, 3, 4, 5, 6, 7, 8])
+def test_direction_of_the_last_backward_launch(rules, nsw, pairs):
+    """The launches as the application makes them: the first descending, then in turn."""
+    q, desc = 2, []
+    while q <= nsw:
+        desc.append(len(desc) % 2 == 0)
+        assert rules("backward_descends", len(desc) - 1) == desc[-1]
+        q += 2 if pairs and q + 1 <= nsw else 1
+    assert rules("apply_ends_descending", nsw, pairs) == (bool(desc) and desc[-1])
