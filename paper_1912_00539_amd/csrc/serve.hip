@@ -38,6 +38,7 @@ namespace {
 
 constexpr int HDR = 128;        // per-slot status header: flags word at 0, status doubles at 64
 constexpr int MAX_SLOTS = 4096;
+constexpr int SERVED_SIDE = 2;  // most blocks of a row on one side of the diagonal
 constexpr int ONE_WG = 64;      // threads per workgroup of the back substitution
 constexpr int64_t ADMIT_MIN_CELLS = 1 << 20;   // admission budget per step when few cells are active
 
@@ -124,22 +125,14 @@ __global__ __launch_bounds__(WG) void kb_factor_init(const Slot *slots, const Me
                                             COPY ? (T *)S.LU : (T *)nullptr, fbuf_d<T>(S, sel & 8), S.flags);
 }
 
-template <typename T, bool LA, bool UA, bool DA = false>
-__global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(sweep_waves<T>()))) void kb_factor_sweep(const Slot *slots, const Member *mem, int nmem, int sel) {
-    MEMBER();
-    const T *Xin = (LA && UA) ? (const T *)nullptr : fbuf_x<T>(S, sel & 1);
-    factor_sweep_body<T, LA, UA, DA>(blk, S.n, S.ZL, S.rowptr, S.colidx, S.diag_pos, S.lrow, S.urow, S.pair_ptr, S.pik,
-                                 S.pkj, S.sik, S.skj, S.A, Xin, UA ? (const T *)nullptr : Xin,
-                                 fbuf_d<T>(S, sel & 2), fbuf_x<T>(S, sel & 4), fbuf_d<T>(S, sel & 8), S.flags);
-}
-
-// The row-at-once form, where every member of the group has diagonal update sets only (the generated
-// meshes are structurally symmetric) and at most CL blocks a side of a row.
-template <typename T, int LSRC, bool FROM_A, int CL>
+// The row-at-once form: served patterns are the generated meshes', structurally symmetric, with diagonal
+// update sets only and at most SERVED_SIDE blocks a side of a row (kbs_pat_rows and the sizes at admission
+// see to it).
+template <typename T, int LSRC, bool FROM_A>
 __global__ __launch_bounds__(WG) void kb_factor_sweep_fv(const Slot *slots, const Member *mem, int nmem, int sel) {
     MEMBER();
     const FvPattern P{S.n, S.ZL, S.rowptr, S.lrow, S.urow, S.lcol, S.ldiag, S.pkj, S.skj};
-    factor_sweep_fv_row<T, LSRC, FROM_A, CL, CL>(
+    factor_sweep_fv_row<T, LSRC, FROM_A, SERVED_SIDE, SERVED_SIDE>(
         blk * ROWS_PER_WG + (threadIdx.x >> 2), P, S.A, FROM_A ? (const T *)nullptr : fbuf_x<T>(S, sel & 1),
         fbuf_d<T>(S, sel & 2), fbuf_x<T>(S, sel & 4), fbuf_d<T>(S, sel & 8), S.flags);
 }
@@ -157,7 +150,7 @@ __global__ __launch_bounds__(WG) void kb_fwd(const Slot *slots, const Member *me
 // pattern keeps for them: 64 bytes a cell more of a request's footprint for about 2% of its time. The
 // launch's tiles are dealt to the XCDs in contiguous eighths; its grid is a multiple of 8, and the
 // workgroups past the last of `tiles` end at once.
-template <typename T, typename YI, bool EMIT_Z, int CL>
+template <typename T, typename YI, bool EMIT_Z>
 __global__ __launch_bounds__(WG) void kb_fwd_pair(const Slot *slots, const Member *mem, int nmem, int tiles, int yin,
                                                   int yout) {
     const int b = xcd_tile(blockIdx.x, gridDim.x);
@@ -165,13 +158,13 @@ __global__ __launch_bounds__(WG) void kb_fwd_pair(const Slot *slots, const Membe
     const Member M = mem[find_member(mem, nmem, b)];
     const Slot &S = slots[M.slot];
     const double rs = S.vscale[M.k];
-    fwd_pair_row<T, YI, EMIT_Z, CL, false>((b - M.tile0) * ROWS_PER_WG + (threadIdx.x >> 2), S.n, S.lrow, S.lcol, nullptr,
+    fwd_pair_row<T, YI, EMIT_Z, SERVED_SIDE, false>((b - M.tile0) * ROWS_PER_WG + (threadIdx.x >> 2), S.n, S.lrow, S.lcol, nullptr,
                                         (const T *)S.LU, (const double *)role(S, M, R_VK),
                                         (const YI *)role(S, M, yin), (T *)role(S, M, yout), (const T *)S.Dinv,
                                         (T *)S.za, rs, yin == R_VK ? rs : 1.0);
 }
 
-template <typename T, typename ZO, int CL>
+template <typename T, typename ZO>
 __global__ __launch_bounds__(WG) void kb_bwd_pair(const Slot *slots, const Member *mem, int nmem, int tiles, int y,
                                                   int zin, int zout, int desc) {
     const int b = xcd_tile(desc ? (int)(gridDim.x - 1 - blockIdx.x) : (int)blockIdx.x, gridDim.x);
@@ -179,7 +172,7 @@ __global__ __launch_bounds__(WG) void kb_bwd_pair(const Slot *slots, const Membe
     const Member M = mem[find_member(mem, nmem, b)];
     const Slot &S = slots[M.slot];
     const T *Ub = (const T *)S.LU + ((int64_t)S.ZL + S.n) * BB;
-    bwd_pair_row<T, ZO, CL, false>((b - M.tile0) * ROWS_PER_WG + (threadIdx.x >> 2), S.n, S.urow, S.ucol, nullptr, Ub,
+    bwd_pair_row<T, ZO, SERVED_SIDE, false>((b - M.tile0) * ROWS_PER_WG + (threadIdx.x >> 2), S.n, S.urow, S.ucol, nullptr, Ub,
                                 (const T *)S.Dinv, (const T *)role(S, M, y), (const T *)role(S, M, zin),
                                 (ZO *)role(S, M, zout));
 }
@@ -341,14 +334,16 @@ __global__ __launch_bounds__(abilu_setup::SCAN_T) void kbs_scan_finish(const Set
 
 __global__ void kbs_pat_rows(const SetupDesc *sd, const Member *mem, int nmem, int64_t *adm) {
     SMEMBER();
-    abilu_setup::pat_rows_body(blk, D.n, D.Z, D.rowptr, D.colidx, D.diag_pos, (unsigned *)(adm + 4 * m_));
+    unsigned *err = (unsigned *)(adm + 4 * m_);
+    abilu_setup::pat_rows_body(blk, D.n, D.Z, D.rowptr, D.colidx, D.diag_pos, err);
+    // the sweeps hold SERVED_SIDE blocks a side
+    const int i = blk * blockDim.x + threadIdx.x;
+    if (i < D.n && max(D.diag_pos[i] - D.rowptr[i], D.rowptr[i + 1] - D.diag_pos[i] - 1) > SERVED_SIDE) atomicOr(err, 1u);
 }
 
-// also the length of the rows, into pshape (two words a member)
-__global__ void kbs_pat_tri_counts(const SetupDesc *sd, const Member *mem, int nmem, unsigned *pshape) {
+__global__ void kbs_pat_tri_counts(const SetupDesc *sd, const Member *mem, int nmem) {
     SMEMBER();
     abilu_setup::pat_tri_counts_body(blk, D.n, D.rowptr, D.diag_pos, D.cnt, D.cnt + (D.n + 1));
-    abilu_setup::pat_side_body(blk * blockDim.x + threadIdx.x, D.n, D.rowptr, D.diag_pos, pshape + 2 * m_);
 }
 
 __global__ void kbs_pat_count(const SetupDesc *sd, const Member *mem, int nmem) {
@@ -521,7 +516,6 @@ struct Req {
     ReqLayout L{};
     int32_t n = 0;
     int64_t Z = 0, ZL = 0, ZU = 0, P = 0;   // pattern sizes (after admission)
-    int side = 0;                           // most strictly lower or strictly upper blocks of a row
     int k = 0, iters = 0, restarts = 0, reorth = 0;
     double bnorm = 0, tol = 0, beta = 0, est = 0;
     uint32_t flags = 0;
@@ -545,7 +539,7 @@ struct abilu_server {
     SetupDesc *d_sdesc = nullptr, *h_sdesc = nullptr;
     Slot *d_sslot = nullptr;
     Member *d_stab = nullptr, *h_stab = nullptr;
-    int64_t *d_adm = nullptr, *h_adm = nullptr;    // per member: error word, ZL, ZU, npairs; then two words of row shape each
+    int64_t *d_adm = nullptr, *h_adm = nullptr;    // per member: error word, ZL, ZU, npairs
     std::vector<hipEvent_t> ev;                    // per slot: setup finished
     std::vector<Req> reqs;
     std::deque<int64_t> queue;                     // released, not yet admitted (FIFO)
@@ -752,7 +746,7 @@ abilu_status admit_queued(abilu_server *s, int64_t cell_budget) {
     } while (0)
     CKS(hipMemcpyAsync(s->d_sdesc, s->h_sdesc, sizeof(SetupDesc) * B, hipMemcpyHostToDevice, st));
     CKS(hipMemcpyAsync(s->d_sslot, s->h_slots, sizeof(Slot) * B, hipMemcpyHostToDevice, st));
-    CKS(hipMemsetAsync(s->d_adm, 0, sizeof(int64_t) * 5 * B, st));
+    CKS(hipMemsetAsync(s->d_adm, 0, sizeof(int64_t) * 4 * B, st));
     if (upload_setup_tables(s, ids, members, T) != ABILU_OK) return ABILU_EDEVICE;
     // pass 1: generation (row lengths, row pointers, blocks and right-hand side) and validation
     kbs_gen_rowlen<<<T.tiles[SS_ROW256], 256, 0, st>>>(s->d_sdesc, T.d[SS_ROW256], T.count);
@@ -780,19 +774,18 @@ abilu_status admit_queued(abilu_server *s, int64_t cell_budget) {
         if (upload_setup_tables(s, ids, members, T) != ABILU_OK) return ABILU_EDEVICE;
     }
     // pass 2: lower / upper part offsets and update-set offsets, with their totals
-    kbs_pat_tri_counts<<<T.tiles[SS_ROW256], 256, 0, st>>>(s->d_sdesc, T.d[SS_ROW256], T.count,
-                                                                (unsigned *)(s->d_adm + 4 * B));
+    kbs_pat_tri_counts<<<T.tiles[SS_ROW256], 256, 0, st>>>(s->d_sdesc, T.d[SS_ROW256], T.count);
     CKL();
     if (launch_scan(s, T, SC_LROW) != ABILU_OK || launch_scan(s, T, SC_UROW) != ABILU_OK) return ABILU_EDEVICE;
     kbs_pat_count<<<T.tiles[SS_ROW128], abilu_setup::PAT_ROWS, 0, st>>>(s->d_sdesc, T.d[SS_ROW128], T.count);
     CKL();
     if (launch_scan(s, T, SC_PAIR) != ABILU_OK) return ABILU_EDEVICE;
-    CKS(hipMemcpyAsync(s->h_adm, s->d_adm, sizeof(int64_t) * 5 * B, hipMemcpyDeviceToHost, st));
+    CKS(hipMemcpyAsync(s->h_adm, s->d_adm, sizeof(int64_t) * 4 * B, hipMemcpyDeviceToHost, st));
     CKS(hipStreamSynchronize(st));
     if (keep(
             [&](int m, const Req &r) {
                 const int64_t *sz = s->h_adm + 4 * m + 1;
-                return !pattern_sizes_ok(r.n, r.Z, sz) || sz[0] > r.L.zcap || sz[1] > r.L.zcap || sz[2] > r.L.pcap;
+                return !pattern_sizes_ok(r.n, r.Z, sz) || sz[0] > r.L.zcap || sz[1] > r.L.zcap || sz[2] != sz[0];
             },
             ABILU_EPATTERN)) {
         if (members.empty()) return ABILU_OK;
@@ -811,7 +804,6 @@ abilu_status admit_queued(abilu_server *s, int64_t cell_budget) {
     for (int m : members) {
         Req &r = s->reqs[ids[m]];
         const int64_t *sz = s->h_adm + 4 * m + 1;
-        r.side = abilu_setup::side_class((const unsigned *)(s->h_adm + 4 * B + m));
         r.ZL = sz[0];
         r.ZU = sz[1];
         r.P = sz[2];
@@ -931,30 +923,15 @@ abilu_status run_group(abilu_server *s, Group &G, hipStream_t st) {
         CKL();
         return ABILU_OK;
     };
-    // the forms for short rows (and diagonal update sets only), by the group's longest row
-    int side = 0;
-    bool fv = true;
-    for (int64_t id : G.ids) {
-        fv = fv && s->reqs[id].P == s->reqs[id].ZL;
-        side = std::max(side, s->reqs[id].side);
-    }
-    fv = fv && side <= FV_CAP;
-    auto with_cap = [&](auto f) {   // f(CL) with the smallest form that holds the rows
-        if (side <= 2) f(std::integral_constant<int, 2>{});
-        else f(std::integral_constant<int, FV_CAP>{});
-    };
 #define P_() dim3(xcd_grid(G.t[SH_ROW64].tiles)), dim3(WG), 0, st
     auto fwd = [&](const char *name, bool pair, bool yin_f64, bool emit, int yin, int yout) -> abilu_status {
         ProfScope ps(name, st, B([&](const Sizes &z, const Req &) { return bytes_fwd(z, sF, yin_f64 ? 8 : sF, emit); }));
         const int tiles = G.t[SH_ROW64].tiles;
         if (pair) {
-            with_cap([&](auto cl) {
-                constexpr int CL = decltype(cl)::value;
-                if (yin_f64 && emit) kb_fwd_pair<T, double, true, CL><<<P_()>>>(A_(SH_ROW64), tiles, yin, yout);
-                else if (yin_f64) kb_fwd_pair<T, double, false, CL><<<P_()>>>(A_(SH_ROW64), tiles, yin, yout);
-                else if (emit) kb_fwd_pair<T, T, true, CL><<<P_()>>>(A_(SH_ROW64), tiles, yin, yout);
-                else kb_fwd_pair<T, T, false, CL><<<P_()>>>(A_(SH_ROW64), tiles, yin, yout);
-            });
+            if (yin_f64 && emit) kb_fwd_pair<T, double, true><<<P_()>>>(A_(SH_ROW64), tiles, yin, yout);
+            else if (yin_f64) kb_fwd_pair<T, double, false><<<P_()>>>(A_(SH_ROW64), tiles, yin, yout);
+            else if (emit) kb_fwd_pair<T, T, true><<<P_()>>>(A_(SH_ROW64), tiles, yin, yout);
+            else kb_fwd_pair<T, T, false><<<P_()>>>(A_(SH_ROW64), tiles, yin, yout);
         } else if (yin_f64) {
             if (emit) kb_fwd<T, double, true><<<L_(SH_APPLY)>>>(A_(SH_APPLY), yin, yout);
             else kb_fwd<T, double, false><<<L_(SH_APPLY)>>>(A_(SH_APPLY), yin, yout);
@@ -967,7 +944,7 @@ abilu_status run_group(abilu_server *s, Group &G, hipStream_t st) {
     };
     // Three sweeps are one pair each way, which needs no second vector; with more, asynchronous
     // requests, which have none, take their sweeps one at a time.
-    const bool pairs = fv && nsw >= 3 && (sync || nsw == 3);
+    const bool pairs = nsw >= 3 && (sync || nsw == 3);
     // the Arnoldi SpMV runs opposite to the last backward launch, the residual SpMV descending
     const bool spmv_desc = !abilu_rules::apply_ends_descending(nsw, pairs);
     auto spmv = [&](bool resid, int xin, int yout) -> abilu_status {
@@ -985,13 +962,8 @@ abilu_status run_group(abilu_server *s, Group &G, hipStream_t st) {
         auto sweep = [&](auto la, auto ua, int sel) {
             constexpr bool LA = decltype(la)::value, UA = decltype(ua)::value;
             constexpr int LSRC = LA ? L_FROM_A0 : L_FROM_NEW;
-            if (!fv) kb_factor_sweep<T, LA, UA, UA><<<L_(SH_ROW64)>>>(A_(SH_ROW64), sel);
-            else
-                with_cap([&](auto cl) {
-                    constexpr int CL = decltype(cl)::value;
-                    if (LA || !sync) kb_factor_sweep_fv<T, LSRC, UA, CL><<<L_(SH_ROW64)>>>(A_(SH_ROW64), sel);
-                    else if constexpr (!UA) kb_factor_sweep_fv<T, L_FROM_PREV, UA, CL><<<L_(SH_ROW64)>>>(A_(SH_ROW64), sel);
-                });
+            if (LA || !sync) kb_factor_sweep_fv<T, LSRC, UA><<<L_(SH_ROW64)>>>(A_(SH_ROW64), sel);
+            else if constexpr (!UA) kb_factor_sweep_fv<T, L_FROM_PREV, UA><<<L_(SH_ROW64)>>>(A_(SH_ROW64), sel);
         };
         if (fsw == 0) {
             if ((e = init(true, 0)) != ABILU_OK) return e;
@@ -1071,12 +1043,10 @@ abilu_status run_group(abilu_server *s, Group &G, hipStream_t st) {
                 ProfScope ps(last ? "serve_apply_bwd_last" : "serve_apply_bwd", st,
                              B([&](const Sizes &z, const Req &) { return bytes_bwd(z, sF, last ? 8 : sF, dual); }));
                 const int zcur = (sync || pairs) ? ((zprev == R_ZA) ? R_ZB : R_ZA) : R_ZA, tiles = G.t[SH_ROW64].tiles;
-                if (pair)
-                    with_cap([&](auto cl) {
-                        constexpr int CL = decltype(cl)::value;
-                        if (last) kb_bwd_pair<T, double, CL><<<P_()>>>(A_(SH_ROW64), tiles, ycur, zprev, R_ZK, desc);
-                        else kb_bwd_pair<T, T, CL><<<P_()>>>(A_(SH_ROW64), tiles, ycur, zprev, zcur, desc);
-                    });
+                if (pair && last)
+                    kb_bwd_pair<T, double><<<P_()>>>(A_(SH_ROW64), tiles, ycur, zprev, R_ZK, desc);
+                else if (pair)
+                    kb_bwd_pair<T, T><<<P_()>>>(A_(SH_ROW64), tiles, ycur, zprev, zcur, desc);
                 else if (last && dual)
                     kb_bwd<T, T, double, true, true><<<L_(SH_APPLY)>>>(A_(SH_APPLY), ycur, zprev, R_ZK, desc);
                 else if (last)
@@ -1377,11 +1347,11 @@ extern "C" abilu_status abilu_serve_create(const abilu_serve_config *cfg, void *
               hip_ok(hipMalloc(&s->d_sdesc, sizeof(SetupDesc) * S), "serve setup descriptors") &&
               hip_ok(hipMalloc(&s->d_sslot, sizeof(Slot) * S), "serve staged slots") &&
               hip_ok(hipMalloc(&s->d_stab, sizeof(Member) * SS_COUNT * S), "serve setup tables") &&
-              hip_ok(hipMalloc(&s->d_adm, sizeof(int64_t) * 5 * S), "serve admission words") &&
+              hip_ok(hipMalloc(&s->d_adm, sizeof(int64_t) * 4 * S), "serve admission words") &&
               hip_ok(hipHostMalloc((void **)&s->h_sdesc, sizeof(SetupDesc) * S, hipHostMallocDefault), "serve pinned") &&
               hip_ok(hipHostMalloc((void **)&s->h_stab, sizeof(Member) * SS_COUNT * S, hipHostMallocDefault),
                      "serve pinned") &&
-              hip_ok(hipHostMalloc((void **)&s->h_adm, sizeof(int64_t) * 5 * S, hipHostMallocDefault), "serve pinned");
+              hip_ok(hipHostMalloc((void **)&s->h_adm, sizeof(int64_t) * 4 * S, hipHostMallocDefault), "serve pinned");
     for (int q = 0; ok && q < S; ++q)
         ok = hip_ok(hipEventCreateWithFlags(&s->ev[q], hipEventDisableTiming), "serve events");
     if (ok) ok = hip_ok(hipMemset(s->d_hdr, 0, (size_t)HDR * S), "serve header init");
