@@ -49,7 +49,7 @@ typedef enum {
     ABILU_WARN_NOCONV = 2,     /* FGMRES stopped at maxit without reaching rtol */
     ABILU_EINVAL = -1,         /* bad argument (null pointer, size, enum, workspace too small) */
     ABILU_EPATTERN = -2,       /* unsorted columns, missing diagonal, index out of range */
-    ABILU_ENOMEM = -3,         /* device or pinned allocation failed (pattern build only) */
+    ABILU_ENOMEM = -3,         /* device, pinned or host allocation failed (pattern build only) */
     ABILU_EDEVICE = -4,        /* a HIP runtime call or kernel launch failed */
     ABILU_ENONFINITE = -5      /* a non-finite value appeared (FGMRES result) */
 } abilu_status;
@@ -287,9 +287,12 @@ abilu_status abilu_factor(const abilu_pattern *p, const double *d_A, void *d_LU,
  *   forward  y_i <- r_i - sum_{j<i} L_ij y_j                  (L_ii = I)
  *   backward z_i <- U_ii^{-1} (y_i - sum_{j>i} U_ij z_j)
  * nsweeps forward sweeps then nsweeps backward sweeps (nsweeps = 0: z = r, no preconditioning).
- * SYNC sweeps read the previous sweep's vector; ASYNC sweeps update the vector in place, or, on
- * patterns of at most three blocks a side of a row and from three sweeps on, run two at a time in the
- * schedule in which no read sees a value written in its sweep. From the
+ * SYNC sweeps read the previous sweep's vector; ASYNC sweeps update the vector in place. From three
+ * sweeps on, patterns with at most three blocks a side of a row and three quarters of the lower
+ * neighbours within 16,384 rows take two sweeps in a launch, in both modes (not in ABILU_F32 with more
+ * than 131,072 rows of mostly three blocks a side and neighbours farther than 2,048 rows). ASYNC then
+ * runs every sweep, a last single one too, in the schedule in which no read sees a value written in its
+ * sweep, and its result is that of SYNC, bit for bit. From the
  * zero initial guess the first sweeps are y = r and z = U_ii^{-1} y and are taken in that closed
  * form (not launched) in these two modes. ABILU_ASYNC_SERIAL runs every sweep, forward rows
  * ascending and backward rows descending, from zero vectors. The chunked modes launch every sweep;

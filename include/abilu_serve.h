@@ -17,8 +17,11 @@
  * Admission (device generation and pattern analysis) runs on a second stream and overlaps the
  * ticks. A request's arithmetic never depends on the other requests: its tiles, reductions and
  * stopping decisions are those it would have alone (in ABILU_SYNC mode the result is bitwise the
- * same alone, in any mix, and as from abilu_factor + fgmres_solve; ABILU_ASYNC sweeps update in
- * place, so their rounding depends on scheduling as in the single-system path).
+ * same alone, in any mix, and as from abilu_factor + fgmres_solve; ABILU_ASYNC factor sweeps update
+ * in place, so their rounding depends on scheduling as in the single-system path. ABILU_ASYNC
+ * applications of three sweeps are the SYNC ones, as abilu_apply's of such patterns are; of two, and,
+ * unlike abilu_apply's, of four and more they update in place: a request of this mode has one vector
+ * for each triangle).
  *
  * Errors: entry points return abilu_status; a failed request records its status in its result
  * (ABILU_ENOMEM: larger than the whole pool, ABILU_EPATTERN: invalid generated pattern,
