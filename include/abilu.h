@@ -71,7 +71,9 @@ typedef enum {
  * order. Needs the pattern's chunk schedule (abilu_pattern_set_chunks). The iteration is exact after as many sweeps as there are chunks
  * (Section 4.2).
  *   ABILU_CHUNK_SYNC : rows of other chunks are read from the previous sweep (deterministic).
- *   ABILU_CHUNK_ASYNC: in place; rows of other chunks are read as they are in memory.
+ *   ABILU_CHUNK_ASYNC: in place; rows of other chunks are read as they are in memory. The first
+ *                      factor sweep from A takes their blocks from A, and, on 1,024 chunks or fewer
+ *                      that are chains, their inverses too.
  * Every apply sweep is launched (no closed-form first sweep). Not accepted by the server. */
 typedef enum {
     ABILU_SYNC = 0,

@@ -812,8 +812,12 @@ abilu_status apply_t(const abilu_pattern *p, const T *LU, const T *Dinv, const d
         // chunks of at most SHORT_CHUNK rows whose rows all fit a record: the unrolled runner
         const bool short_fwd = by_rows && R <= SHORT_CHUNK && p->rec_max[0] <= REC_CAP;
         const bool short_bwd = by_rows && R <= SHORT_CHUNK && p->rec_max[1] <= REC_CAP;
-        // chains of short rows: sixteen lanes per chunk
-        const bool chain = by_rows && p->chains && p->side <= FV_CAP && abilu_rules::chain_apply(R, nch, p->side, sF == 8);
+        // chains of short rows: sixteen lanes per chunk, CHUNK_SYNC only. They read sixteen rows' values of
+        // other chunks at once; row after row a quad sees those that other chunks have made meanwhile, and
+        // CHUNK_ASYNC lives by that: distance from the triangular solves after three and six sweeps, 500,000
+        // line-ordered quads, 16 rows, 1.2e-4 and 5.4e-9 by quads, 3.2e-4 and 4.5e-7 by sixteen lanes.
+        const bool chain = cs && by_rows && p->chains && p->side <= FV_CAP &&
+                           abilu_rules::chain_apply(R, nch, p->side, sF == 8);
         const int cg = div_up(nch, WG / CHAIN_LANES);
         auto fwd_as = [&](const T *yo, T *yn, auto zero, auto scaled) {
             constexpr bool Z = decltype(zero)::value, SC = decltype(scaled)::value;

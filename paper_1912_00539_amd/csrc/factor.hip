@@ -763,8 +763,14 @@ abilu_status factor_t(const abilu_pattern *p, const double *A, T *LU, T *Dinv, i
         // Chains of rows with diagonal update sets: what does not depend on the chain first, then the
         // chain (no inverses of A's diagonal blocks are needed before the first sweep).
         const bool chains = p->chunk_runner == ABILU_CHUNK_BY_ROWS && p->chains && p->fv();
+        // In place (CHUNK_ASYNC) only the sweep from A on few chunks: the two launches take other chunks'
+        // inverses from before the sweep, row after row they are taken as they are in memory. ILU residual
+        // after the second sweep, FP64: 500,000 line-ordered quads, 16 rows, 1e-9 and less by rows, 3.9e-7
+        // by two launches (as CHUNK_SYNC), 4.6e-8 with the first sweep alone in two launches; 150,000
+        // hexahedra 4e-7, 1.1e-5.
         const auto links = [&](bool fromA) {
-            return chains && abilu_rules::chain_factor(p->chunk_rows, p->nchunks, p->side, sF == 8, fromA);
+            return chains && (cs ? abilu_rules::chain_factor(p->chunk_rows, p->nchunks, p->side, sF == 8, fromA)
+                                 : fromA && abilu_rules::chain_factor_in_place(p->nchunks));
         };
         auto chain_sweep = [&](bool fromA, const T *XO, const T *DO, T *Xn, T *Dn, const char *nm) -> abilu_status {
             const FvPattern P{n, ZL, p->rowptr, p->lrow, p->urow, p->lcol, p->ldiag, p->pkj, p->skj};

@@ -75,6 +75,11 @@ inline bool chain_factor(int rows_per_chunk, int64_t nchunks, int side, bool f64
     return rows_per_chunk >= 24 || (rows_per_chunk >= 4 && few);
 }
 
+// The same in place, from A: few chunks all run side by side, and one sees little of the same sweep of
+// another (ILU residual after it, by rows / by two launches: 629 chunks of line-ordered quads 3.44e-3 both,
+// 1,000 chunks of hexahedra 1.0e-3 / 1.25e-3), while whole rows are bound by latency (629 chunks, FP32 44 / 24 us).
+inline bool chain_factor_in_place(int64_t nchunks) { return nchunks <= 1024; }
+
 // Synchronous factor sweep with a quad per block, or with a quad per row, on patterns whose rows do not fit
 // the row-at-once form. With update sets off the diagonal the blocks win by up to half. With the diagonal
 // ones alone only the diagonal blocks have pairs, and on large patterns with far neighbours a row's blocks,
