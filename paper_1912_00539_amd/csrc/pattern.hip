@@ -113,15 +113,15 @@ constexpr size_t REC_AT = 256, KEEP_SCRATCH = (size_t)64 << 20;
 
 // Device arrays of a pattern. Those of 2 MiB and more, which cost the runtime 12 us each to allocate and
 // 12 to free, share one allocation; smaller ones come from its pool in under 1 us each.
+constexpr size_t LARGE_INTS = (size_t)2 << 18;
 struct Piece {
     int32_t **p;
     size_t ints;
 };
 hipError_t allocate(abilu_pattern *p, std::initializer_list<Piece> pieces) {
-    constexpr size_t LARGE = (size_t)2 << 18;
     const auto up = [](size_t ints) { return (ints + 63) / 64 * 64; };   // 256-byte boundaries
     size_t large = 0;
-    for (const Piece &q : pieces) large += q.ints >= LARGE ? up(q.ints) : 0;
+    for (const Piece &q : pieces) large += q.ints >= LARGE_INTS ? up(q.ints) : 0;
     const auto get = [&](size_t ints, int32_t **out) {
         if (p->nowned >= (int)(sizeof(p->owned) / sizeof(p->owned[0]))) return hipErrorOutOfMemory;
         const hipError_t e = hipMalloc(out, sizeof(int32_t) * ints);
@@ -132,11 +132,11 @@ hipError_t allocate(abilu_pattern *p, std::initializer_list<Piece> pieces) {
     if (large)
         if (const hipError_t e = get(large, &next); e != hipSuccess) return e;
     for (const Piece &q : pieces) {
-        if (q.ints >= LARGE) {
+        if (q.ints >= LARGE_INTS) {
             *q.p = next;
             next += up(q.ints);
-        } else if (const hipError_t e = get(q.ints, q.p); e != hipSuccess) {
-            return e;
+        } else if (q.ints) {
+            if (const hipError_t e = get(q.ints, q.p); e != hipSuccess) return e;
         }
     }
     return hipSuccess;
@@ -337,8 +337,11 @@ extern "C" abilu_status abilu_build_pattern(int32_t nbrows, const int32_t *d_row
         p->local = p->local && pair_records_hold(n, ZL, ZU);
         const size_t np = (size_t)npairs + 1;
         const size_t recs = (!p->local || p->side > 3 ? 0 : p->side <= 2 ? PAIR_REC<2> : PAIR_REC<3>) * (size_t)n;
+        // where both kinds of records are needed, the block form's in the allocation of the large arrays, if
+        // there is one (else by itself while kernels run)
+        const size_t both = recs && (npairs != ZL || p->side > 3) && np >= LARGE_INTS ? 4 * (size_t)Z : 0;
         CKA(allocate(p, {{&p->lcol, 2 * ((size_t)ZL + 1)}, {&p->ucol, (size_t)ZU + 1}, {&p->pik, np}, {&p->pkj, np},
-                         {&p->sik, np}, {&p->skj, np}}));
+                         {&p->sik, np}, {&p->skj, np}, {(int32_t **)&p->brec, both}}));
         if (recs) {
             if (int32_t *at = (int32_t *)keep_scratch(8 * recs)) {
                 p->lrec = at;
@@ -355,7 +358,7 @@ extern "C" abilu_status abilu_build_pattern(int32_t nbrows, const int32_t *d_row
         // blocks, which need not wait for it, in the same wait of the host
         {
             auto blocks = [&]() -> abilu_status {
-                p->brec = (int4 *)keep_scratch(16 * (size_t)Z);
+                if (!p->brec) p->brec = (int4 *)keep_scratch(16 * (size_t)Z);
                 if (!p->brec && !hip_ok(allocate(p, {{(int32_t **)&p->brec, 4 * (size_t)Z}}), "block records"))
                     return ABILU_ENOMEM;
                 k_pat_blocks<<<div_up(n, 256), 256, 0, s>>>(n, (int)ZL, p->rowptr, p->diag_pos, p->lrow, p->urow,
@@ -380,7 +383,7 @@ extern "C" abilu_status abilu_build_pattern(int32_t nbrows, const int32_t *d_row
             if (n > 0 && !p->fv() && (st = blocks()) != ABILU_OK) goto fail;
             CK(hipStreamSynchronize(s));
             p->symmetric = *(const unsigned *)p->pinned == 0;
-            if (n > 0 && !p->fv() && !p->brec) {
+            if (n > 0 && !p->fv() && !p->brec) {   // as many pairs as lower blocks, and not symmetric
                 if ((st = blocks()) != ABILU_OK) goto fail;
                 CK(hipStreamSynchronize(s));
             }
