@@ -472,7 +472,7 @@ extern "C" abilu_status fgmres_solve(const abilu_pattern *p, const double *d_A, 
     };
     Pending<decltype(decide)> pending(c, decide);
     const bool gated = (mode == ABILU_SYNC || mode == ABILU_ASYNC) && apply_sweeps >= 2;   // modes that ask the gate
-    pending.limit = gated ? abilu_rules::launches_ahead(p->nnzb) : 0;
+    pending.limit = gated ? abilu_rules::launches_ahead(p->n, p->nnzb) : 0;
     pending.expect(START);
     if (pending.limit == 0 || maxit == 0) pending.read();
 

@@ -110,16 +110,25 @@ inline bool crowded_sweep(int64_t n, int64_t blocks) { return blocks >= 18 * n &
 
 // Launches of an application that FGMRES makes ahead of the status which decides on it. They cover the 6-8 us
 // between the status being written and the next launch arriving; where the solve stops they were for
-// nothing, which costs the more the more blocks a sweep reads. A solve to 1e-10 (1e-2, two iterations or
-// one), us, with none / one / two ahead:
-//     39,478 blocks (9,940 triangles, FP32)   298 / 295 / 286
-//    119,110 blocks (29,900 triangles)   382 / 379 / 378; FP64 451 / 459 / 448
-//    191,380 blocks (48,000 triangles)   392 / 368 / 371 (150 / 148 / 152)
-//  1,198,450 blocks (300,000 triangles)   1,070 / 1,041 / 1,063 (305 / 305 / 325)
-//  1,475,944 blocks (57,600 27-point rows)   560 / 546 / 555 (208 / 207 / 219)
-//  1,598,200 blocks (400,000 triangles)   1,365 / 1,349 / 1,379 (379 / 391 / 419)
-//  2,797,600 blocks (700,000 triangles)   2,170 / 2,168 / 2,217 (591 / 621 / 666)
-//  4,689,232 blocks (180,000 27-point rows)   1,454 / 1,468 / 1,509 (499 / 529 / 570)
-inline int launches_ahead(int64_t blocks) { return blocks <= 150000 ? 2 : blocks <= 1600000 ? 1 : 0; }
+// nothing, which costs the more the longer a sweep takes. So two while a launch is shorter than that wait
+// (60,000 rows of about eight blocks), one while it costs little beside an iteration, none beyond. A solve
+// to 1e-10 (1e-2, two iterations or one), us, with none / one / two ahead:
+//     48,000 rows, 191,380 blocks (triangles)   406 / 404 / 373 (165 / 157 / 152); FP64 432 / 417 / 399
+//     24,000 rows, 168,000 blocks (nine-point)   572 / 537 / 526 (182 / 177 / 176)
+//     40,000 rows, 199,000 blocks (quads, two sweeps)   438 / 428 / 419 (165 / 155 / 156)
+//     60,000 rows, 299,000 blocks (quads, two sweeps)   493 / 477 / 465 (180 / 167 / 170)
+//     80,000 rows, 399,000 blocks (quads)   490 / 473 / 462 (197 / 183 / 195)
+//      8,000 rows, 195,112 blocks (27-point)   395 / 377 / 379 (217 / 213 / 220)
+//     15,625 rows, 389,017 blocks (27-point)   443 / 427 / 421 (238 / 239 / 244)
+//     57,600 rows, 1,475,944 blocks (27-point)   849 / 839 / 849 (497 / 505 / 516)
+//    400,000 rows, 1,598,200 blocks (triangles)   1,365 / 1,349 / 1,379 (379 / 391 / 419)
+//    230,000 rows, 1,600,000 blocks (nine-point)   1,876 / 1,829 / 1,839 (577 / 579 / 598)
+//    400,000 rows, 2,800,000 blocks (nine-point)   2,971 / 2,907 / 2,944 (922 / 931 / 959)
+//    700,000 rows, 2,797,600 blocks (triangles)   2,170 / 2,168 / 2,217 (591 / 621 / 666)
+//    180,000 rows, 4,689,232 blocks (27-point)   2,294 / 2,316 / 2,355 (1,353 / 1,388 / 1,426)
+inline int launches_ahead(int64_t n, int64_t blocks) {
+    if (n <= 60000 && (blocks <= 150000 || blocks <= 8 * n)) return 2;
+    return n <= 400000 && blocks <= 3000000 ? 1 : 0;
+}
 
 }  // namespace abilu_rules
